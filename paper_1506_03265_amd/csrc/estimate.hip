@@ -17,6 +17,11 @@ namespace {
 constexpr int kT = 256;
 constexpr int kLdsMaxK = 3072;  // 20 bytes per node -> 60 KB
 
+// Bytes of one workgroup's distances, stamps and queues in global memory: a
+// multiple of 8, so that every workgroup's 64-bit distances are aligned (a
+// 64-bit atomic on an address that is not faults).
+__host__ __device__ inline size_t slice_bytes(int32_t k) { return ((size_t)k * 20 + 7) & ~(size_t)7; }
+
 struct ECtl {
   unsigned long long phi;
   uint32_t bad;   // the quotient CSR is malformed: nothing is indexed with it
@@ -93,8 +98,7 @@ __global__ void __launch_bounds__(kT) k_apsp_global(int32_t k, const int64_t *rp
                                                     const uint64_t *w, uint64_t *phi, char *slices,
                                                     const uint32_t *bad) {
   if (*bad) return;
-  const size_t per = (size_t)k * 20;
-  char *base = slices + per * blockIdx.x;
+  char *base = slices + slice_bytes(k) * blockIdx.x;
   uint64_t *dist = (uint64_t *)base;
   uint32_t *stamp = (uint32_t *)(dist + k);
   int32_t *q0 = (int32_t *)(stamp + k);
@@ -173,7 +177,7 @@ extern "C" size_t cldiam_estimate_workspace_size(int32_t k, int64_t qm) {
   (void)qm;
   if (k < 1) return 0;
   size_t s = 256;
-  if (k > kLdsMaxK) s += (size_t)k * 20 * grid_for(k) + 256;
+  if (k > kLdsMaxK) s += slice_bytes(k) * grid_for(k) + 256;
   return s;
 }
 
@@ -188,7 +192,7 @@ extern "C" int cldiam_estimate_diameter(int32_t k, int64_t qm, const int64_t *d_
   cld::Arena a(ws, ws_bytes);
   ECtl *ctl = a.take<ECtl>(1);
   char *slices = nullptr;
-  if (k > kLdsMaxK) slices = a.take<char>((size_t)k * 20 * grid_for(k));
+  if (k > kLdsMaxK) slices = a.take<char>(slice_bytes(k) * grid_for(k));
   if (!ctl || (k > kLdsMaxK && !slices)) {
     cld::set_error("estimate_diameter: workspace of %zu bytes, %zu needed", ws_bytes,
                    cldiam_estimate_workspace_size(k, qm));
@@ -217,7 +221,7 @@ extern "C" int cldiam_estimate_diameter_noalloc(int32_t k, int64_t qm, const int
   // as many workgroups as the slices that fit (at least 1 for every k up to the maximum)
   int grid = grid_for(k);
   if (k > kLdsMaxK) {
-    const size_t fit = (kStaticBytes - kStaticCtl) / ((size_t)k * 20);
+    const size_t fit = (kStaticBytes - kStaticCtl) / slice_bytes(k);
     if ((size_t)grid > fit) grid = (int)fit;
   }
   return estimate_run(k, qm, d_qrow_ptr, d_qcol, d_qw, radius, h_phi_gc, h_phi_approx, (ECtl *)base,
