@@ -184,9 +184,8 @@ typedef struct {
 /* Schedule knobs of a decomposition job.  They change only how the work is
  * scheduled on the device, never the results. */
 typedef struct {
-  int32_t local_rounds; /* workgroup-local relaxation rounds per sweep (at least 16 while a frontier has
-                           at most 32768 nodes); < 0 = default: 16 on graphs with at most 16 arcs per
-                           node, on denser ones 2 above 2^21 nodes and 0 below */
+  int32_t local_rounds; /* workgroup-local relaxation rounds per sweep; < 0 = default: 16 on graphs with at
+                           most 16 arcs per node, on denser ones 2 above 2^21 nodes and 0 below */
   int32_t grid_blocks;  /* workgroups per sweep; 0 = one per compute unit */
   float bucket_width;   /* distance bucket of a relaxation sweep, in mean arc weights: a sweep relaxes
                            only frontier nodes whose tentative distance is below (smallest distance on
@@ -212,7 +211,7 @@ typedef struct {
   int32_t local_cutoff; /* a workgroup ends its local rounds once this percentage of the sweep's
                            workgroups have finished the sweep (their work then waits for the next sweep,
                            which spreads it over the whole grid); 1 .. 100 (100: never), 0 = default
-                           (75) */
+                           (100) */
   int32_t pull_mode;    /* CLDIAM_PULL_*: offers over arcs that became light when Delta grew, and from the
                            sources of a new stage, can only reach unreached nodes.  In pull mode those
                            nodes take their best offer from their neighbours, reading keys written

@@ -5,22 +5,21 @@
 // One device job decomposes a batch of graphs (a single graph is a batch of
 // one).  Every graph runs its own state machine
 //
-//   SELECT -> RELAX* -> [NEXT -> RELAX*]* -> ASSIGN -> RMAX -> COMPACT -> SELECT ...
+//   SELECT -> RELAX* -> NEXT -> [RELAX* -> NEXT]* -> ASSIGN [-> RMAX] -> SELECT ...
 //                                                              -> SINGLE -> DONE
 //
-// and all graphs advance in lock step through "sweeps": in one sweep every
-// graph contributes the items of the list its phase works on (uncovered
-// nodes, frontier, blocked nodes or newly covered nodes), each graph's items
-// are cut into chunks (one per workgroup, or a few per workgroup on large
-// dense graphs), workgroup b takes chunk b and further chunks go to whichever
-// workgroup asks next.  Between sweeps one workgroup runs the per-graph
-// control step (one thread per graph), which applies Algorithm 1's decisions:
-// coverage test, Delta doubling, stage end, termination.
+// and all graphs advance in lock step through "sweeps", one kernel launch
+// each.  Between sweeps every graph's control step applies Algorithm 1's
+// decisions: coverage test, Delta doubling, stage end, termination.
 //
-// A relaxation sweep takes only frontier nodes whose tentative distance lies
-// in the current distance bucket (a narrower one for nodes with long rows)
-// and keeps the others on the frontier, which orders the label-correcting
-// growth like Delta-stepping without changing its fixpoint.
+// Node sets are bitmaps: the uncovered nodes, the frontier (current and next)
+// and the blocked nodes, one 64-bit word per 64 nodes.  Each graph's words are
+// cut into chunks (one per workgroup, or a few per workgroup on large dense
+// graphs); workgroup b takes chunk b and further chunks go to whichever
+// workgroup asks next.  A workgroup owns the words of its chunk, so it walks its
+// nodes in ascending order (neighbouring nodes share cache lines: frontiers
+// kept as unordered lists moved several times the lines) and changes the sets
+// that it walks without atomics.
 //
 // Node state is one u64 key per node: (growth distance << 32) | center id,
 // ~0 when unset.  An offer (d_u + w, c_u) is applied with a 64-bit atomicMin,
@@ -30,33 +29,37 @@
 // stages keep key (0, cluster) and are sources of later stages (the effect of
 // Procedure Contract); no contracted graph is built.
 //
-// Lists (per graph, each of the graph's node count; all are node ids local to
-// the graph):
-//   U[2]          uncovered nodes (current / compacted)
-//   pool[3]       frontier (current, next) and blocked list, roles rotate
-//   C             nodes covered in the current stage
-// A node is pushed on the next frontier when its key improves (once per sweep,
-// deduplicated by a sweep stamp), on C when its key first becomes finite, and
-// on the blocked list when its scan stopped at an arc heavier than
-// Delta - d_u (once per level, level stamp).  At a level's fixpoint every arc
-// from a reached node into an unreached one is such a blocked arc, so:
-//   - the smallest distance at which a new node becomes reachable is the
-//     minimum over blocked arcs into unreached nodes of d_u + w (NEXT), and
-//     Delta doublings below it cannot change anything, so they are applied
-//     without growth;
-//   - the blocked list is exactly the set of nodes to rescan after Delta grows,
-//     and after the stage it is the set of assigned nodes adjacent to the
-//     remaining uncovered nodes, i.e. the sources of the next stage.
+// A relaxation sweep takes only frontier nodes whose tentative distance lies
+// in the current distance bucket (a narrower one for nodes with long rows)
+// and keeps the others on the frontier, which orders the label-correcting
+// growth like Delta-stepping without changing its fixpoint.  It goes on from
+// the nodes that it improves in local rounds over a queue in LDS.  Every
+// improvement of a key is the responsibility of the thread that made it: it
+// goes into the workgroup's queue, or, when it lies beyond the bucket, finds
+// the queue full or is left over when the rounds end, on the next frontier.  A
+// queued improvement is dropped only when the key has become smaller since,
+// which is another thread's responsibility.  So after a sweep every node whose
+// key has not been relaxed is on the next frontier, nothing is relaxed twice
+// with the same key, and neither the atomicMin on the key nor the atomicOr on
+// a bitmap has to return a value (a wave goes on without waiting for them).
 //
-// Pushes are staged in LDS per workgroup and written out with one global
-// reservation per list and flush; every list counter sits in its own 128-byte
-// line, so the serialisation of same-address atomics stays off the critical
-// path.
+// A node is blocked when its scan stopped at an arc heavier than Delta - d_u.
+// At a level's fixpoint every arc from a reached node into an unreached node
+// is such a blocked arc, so NEXT, which looks at the blocked nodes' heavy arcs,
+//   - finds the smallest distance at which a new node becomes reachable (Delta
+//     doublings below it cannot change anything and are applied without growth);
+//   - keeps exactly the blocked nodes with an unreached neighbour as the
+//     frontier of the next level, or, when the stage ends, as the sources of
+//     the next stage: the other nodes' offers cannot be accepted any more.
+// The same sweep counts the covered nodes, so that growth itself keeps no count.
 //
-// Drivers: a persistent cooperative kernel that alternates sweep and control
-// with grid barriers (one launch per job), or host-driven launches of a sweep
-// kernel and a control kernel (the host polls a done flag).  Both run the
-// same device code.
+// Drivers: host-driven launches of one kernel per sweep (the host polls a done
+// flag), or a persistent cooperative kernel with grid barriers.  In a job of
+// one graph every workgroup runs the control step by itself at the start of a
+// sweep, from the state and the counters that the sweep before left (state in
+// a ring of two, counters in a ring of three: last, current, being cleared); it
+// costs 1 to 2 us, where a launch of its own cost 6.  Jobs of several graphs
+// take a control launch (one thread per graph) before every sweep.
 
 #include <math.h>
 #include <stdio.h>
@@ -76,21 +79,20 @@ enum Phase : uint32_t {
   PH_START = 0,
   PH_SELECT = 1,
   PH_RELAX = 2,
-  PH_NEXT = 3,
-  PH_ASSIGN = 4,
-  PH_RMAX = 5,
-  PH_COMPACT = 6,
+  PH_COUNT = 3,    // covered nodes only (pull mode, or before a switch to it)
+  PH_NEXT = 4,
+  PH_ASSIGN = 5,
+  PH_RMAX = 6,
   PH_SINGLE = 7,
   PH_DONE = 8,
-  PH_IDLE = 9,   // empty slot of a server job
+  PH_IDLE = 9,     // empty slot of a server job
   PH_COMMIT = 10,  // synchronous steps: publish the step's updates
-  PH_MERGE = 11,   // synchronous steps: add the blocked list to the active list
-  PH_C2_INIT = 12,      // CLUSTER2: fresh state for every node
-  PH_C2_SELECT = 13,    // CLUSTER2: centers of iteration i with probability 2^i / n
-  PH_C2_BOUNDARY = 14,  // CLUSTER2: Contract2's rescaled edges out of last iteration's clusters
-  PH_C2_ASSIGN = 15,    // CLUSTER2: assignment, D = d + Delta2 (i - birth iteration)
-  PH_PULL = 16,         // pull mode: unreached nodes take their best offer from reached neighbours
-  PH_NEXT_PULL = 17,    // pull mode: NEXT computed from the unreached nodes' side
+  PH_C2_INIT = 11,      // CLUSTER2: fresh state for every node
+  PH_C2_SELECT = 12,    // CLUSTER2: centers of iteration i with probability 2^i / n, and Contract2's
+                        // rescaled edges out of last iteration's clusters
+  PH_C2_ASSIGN = 13,    // CLUSTER2: assignment, D = d + Delta2 (i - birth iteration)
+  PH_PULL = 14,         // pull mode: unreached nodes take their best offer from reached neighbours
+  PH_NEXT_PULL = 15,    // pull mode: NEXT computed from the unreached nodes' side
 };
 
 struct GDesc {
@@ -98,10 +100,11 @@ struct GDesc {
   const uint64_t *arcs;
   int32_t *cluster;
   uint64_t *D;
-  int64_t off;       // offset of this graph in node-indexed workspace arrays
+  int64_t off;       // offset of this graph in node-indexed workspace arrays (a multiple of 64)
   double K;          // (gamma * tau) * log2(n)
   uint64_t seed;
   int32_t n;
+  uint32_t words;    // bitmap words: ceil(n / 64)
   uint32_t stop;     // ceil(8 tau log2 n)
   uint32_t delta0;
   uint32_t bucket;   // distance bucket width of RELAX sweeps; 0 = unbounded
@@ -110,7 +113,7 @@ struct GDesc {
   uint32_t c2_iters; // CLUSTER2: ceil(log2 n) iterations
   int32_t local_rounds;  // workgroup-local relaxation rounds per RELAX run
   int32_t row_shift;     // long rows use a bucket of width Delta >> row_shift; < 0 = none
-  int32_t chunk_factor;  // RELAX / NEXT chunks per workgroup and sweep
+  int32_t chunk_factor;  // growth chunks per workgroup and sweep
   int32_t mid_deg;       // rows of more arcs are relaxed by one wave ("long rows")
   int32_t big_deg;       // rows of more arcs are relaxed by the whole workgroup
   uint32_t lq_cap;       // slots of the local relaxation queue used (at most kLocalCap)
@@ -121,113 +124,119 @@ struct GDesc {
 
 // Control-owned state of one graph.
 struct GState {
-  uint32_t phase, stage, delta, level_id;
   uint64_t T;
-  uint32_t nU, ucur;
-  uint32_t fcur, fnxt, blk;
+  uint64_t rounds, updates, msgs;   // synchronous steps
+  uint64_t radius;      // max D
+  uint64_t radius1;     // CLUSTER2: R_CL of the preliminary CLUSTER run
+  uint64_t blk_arcs;    // heavy arcs left on the rows marked blocked in this level (what a push rescan reads)
+  uint64_t arcs;        // arcs read by relaxation (diagnostic)
+  uint32_t phase, stage, delta;
+  uint32_t nU;          // uncovered nodes at the start of the stage
+  uint32_t cov;         // covered in this stage, at the last count
+  uint32_t centers;     // centers drawn in this stage
+  uint32_t cur, nxt, blk, alt;   // roles of the four bitmaps: frontier, next frontier, blocked, spare (empty)
   int32_t status;
   uint32_t levels, sweeps, centers_total, singletons;
-  uint32_t theta;    // RELAX sweeps relax frontier nodes with tentative distance below theta
-  uint32_t row_base; // ... and nodes of long rows only below row_limit(row_base)
-  // synchronous steps
-  uint32_t steps_call;  // steps of the current PartialGrowth call
-  uint32_t fid;         // sweep id that stamped the current active list
-  uint32_t after;       // phase after a MERGE sweep
+  uint32_t theta;       // RELAX sweeps relax frontier nodes with tentative distance below theta
+  uint32_t row_base;    // ... and nodes of long rows only below row_limit(row_base)
+  uint32_t steps_call;  // synchronous steps of the current PartialGrowth call
+  uint32_t merge;       // synchronous steps: the blocked nodes join the frontier of the next RELAX
   uint32_t c2;          // 1 while in CLUSTER2's iterations
-  uint64_t rounds, updates;
-  uint64_t radius1;     // CLUSTER2: R_CL of the preliminary CLUSTER run
   uint32_t pull;        // 1 once the graph grows new levels and stages by pulling (see PH_PULL)
   uint32_t pull_base;   // distance at which the current pulled level starts (its first bucket)
+  uint32_t src_blk;     // the next stage's sources are the blocked set (no NEXT has filtered it)
+  uint32_t records;     // some long row has a scan record
+  uint32_t pad;
+};
+static_assert(sizeof(GState) % 4 == 0, "copied word by word");
+
+// What a sweep of one graph reports to its next control step.
+struct alignas(128) GCount {
+  uint32_t fmin;        // RELAX: smallest tentative distance on the next frontier (~0: it is empty)
+  uint32_t cov;         // covered nodes (COUNT, NEXT, COMMIT: newly covered, C2_ASSIGN)
+  uint32_t centers;     // centers drawn
+  uint32_t upd;         // synchronous steps: nodes updated
+  uint32_t records;
+  uint32_t pad;
+  unsigned long long next;      // NEXT: smallest reach distance
+  unsigned long long radius;    // max D of the nodes assigned
+  unsigned long long msgs;      // synchronous steps: offers sent
+  unsigned long long blk_arcs;
+  unsigned long long hub_arcs;  // first SELECT (auto pull mode): arcs in hub rows
+  unsigned long long arcs;
 };
 
-struct alignas(128) PadU32 {
-  uint32_t v;
-  uint32_t pad_[31];
-};
-struct alignas(128) PadU64 {
-  unsigned long long v;
-  uint32_t pad_[30];
-};
-
-// Counters written by sweeps, one 128-byte line each.
-struct GCount {
-  PadU32 cnt[3];   // pool lists
-  PadU32 cntU[2];  // uncovered lists
-  PadU32 cntC;     // covered list
-  PadU32 centers;  // centers drawn in this stage
-  PadU64 next;     // NEXT: smallest reach distance
-  PadU64 radius;   // max D
-  PadU32 fmin;     // RELAX: smallest tentative distance pushed on the next frontier
-  PadU64 msgs;     // synchronous steps: offers sent
-  PadU64 blk_arcs; // heavy arcs left on the rows of the blocked list (what a push rescan would read)
-  PadU64 hub_arcs; // first SELECT (auto pull mode): arcs in hub rows
+// Job-wide counters of one sweep.
+struct alignas(128) SweepCount {
+  uint32_t cursor;   // chunks taken beyond the first nblocks
+  uint32_t pad0[31];
+  uint32_t idle;     // workgroups that have finished the sweep
+  uint32_t pad1[31];
 };
 
 struct Ctl {
-  uint32_t sweep_id;  // stamp of the current sweep (>= 1)
   uint32_t done;      // 1 when every graph is DONE
-  uint32_t total;     // items of the current sweep
+  uint32_t total;     // chunks of the current sweep (several graphs)
   uint32_t error;     // first error status (as positive code) or 0
   uint32_t iterations;
   uint32_t timeout;   // barrier wait gave up
+  uint32_t pad;
   unsigned long long t_start;   // wall clock at the first control step
   unsigned long long t_limit;   // ticks after which the job stops with a timeout
-  PadU64 arcs;                  // arcs read by relaxation (diagnostic)
-  PadU32 cursor;                // chunks of the current sweep taken beyond the first nblocks
-  PadU32 idle;                  // workgroups that have finished the current sweep
+  SweepCount sc[3];
   CldBarrier bar;
 };
 
 struct Job {
   const GDesc *desc;
-  GState *st;
-  GCount *cn;
+  GState *st;        // one per graph (one graph: its final state)
+  GState *ring;      // one graph: the state after the last sweep and the current one
+  GCount *cn;        // one per graph (one graph: a ring of three)
   Ctl *ctl;
-  uint32_t *seg;     // [0, G]: exclusive prefix of per-graph work chunks; [G+1, 2G]: items per chunk;
-                     // [2G+1, 3G]: items of the graph in this sweep
+  uint32_t *seg;     // [0, G]: exclusive prefix of per-graph chunks; [G+1, 2G]: words per chunk
   int32_t *log;      // G x CLDIAM_STAGE_LOG x 4
   uint64_t *key;
   uint64_t *keyn;    // synchronous steps: state after the current step (key holds the state before it);
-                     // otherwise, for long rows, the key of the row's last scan
+                     // CLUSTER2's iterations: growth distance of the assigned nodes; otherwise, for long rows,
+                     // the key of the row's last scan
   uint32_t *slim;    // with keyn: the light limit (Delta - d) of that scan; arcs up to it have been offered
-  uint64_t *R;
-  uint32_t *fstamp;
-  uint32_t *bstamp;
-  int32_t *pool[3];
-  int32_t *U[2];
-  int32_t *C;
+  uint64_t *R;       // by center: largest D of its cluster after the last stage; CLUSTER2: birth iteration
+  uint64_t *U;       // bitmap: uncovered nodes
+  uint64_t *F[4];    // bitmaps in the roles of GState
   int32_t G;
   int32_t nblocks;        // workgroups of a sweep launch
   uint32_t *hmirror = nullptr;   // host-driven job: mapped pinned words {control steps done, done flag} that
                                  // the host polls while it queues steps (nullptr: not mirrored)
   uint32_t cutoff;        // a workgroup ends its local rounds once this many workgroups have finished the
-                          // sweep (the rounds are optional: every improved node is on the next frontier)
+                          // sweep (what it leaves is on the next frontier)
 };
 
-constexpr int kThreads = 1024;        // control workgroup
+constexpr int kThreads = 1024;        // control workgroup of many graphs
 constexpr int kSweepThreads = 1024;   // sweep workgroup
-constexpr int kCuThreads = 1024;      // sweep threads resident per CU (16 waves at the sweep's register use)
-constexpr int kStageCap = 4 * kSweepThreads;   // LDS staging slots per output list
+constexpr int kCuThreads = 1024;      // sweep threads resident per CU
+constexpr int kWaves = kSweepThreads / 64;
+constexpr int kList = 8 * kSweepThreads;       // nodes of one expansion of a bitmap window
 constexpr int kLocalCap = 4 * kSweepThreads;   // LDS local-round queue slots
 constexpr int kMidDeg = 32;       // default: rows above this degree are relaxed by one wave
 constexpr int kBigDeg = 8192;     // default: rows above this degree are relaxed by the whole workgroup
-constexpr int kMidCap = 2 * kSweepThreads;   // deferred wave rows per round
-constexpr int kBigCap = kSweepThreads / 8;   // deferred workgroup rows per round
+constexpr int kMidCap = 2 * kSweepThreads;   // deferred wave rows per pass
+constexpr int kBigCap = kSweepThreads / 8;   // deferred workgroup rows per pass
 constexpr int kLocalRounds = 16;  // default local relaxation rounds per RELAX run
-constexpr int kLocalCutoffPct = 75;    // default: local rounds end once this % of workgroups finished the sweep
+// Default: local rounds do not wait for the other workgroups.  Ended once 75%
+// of the workgroups have finished the sweep, the rest of the growth waits for
+// the next launch (64 x 64 mesh 0.69 instead of 0.43 ms, 1153 x 1021 mesh 3.05
+// instead of 2.36, road-like 4096 x 4096 mesh 9.5 instead of 8.7).
+constexpr int kLocalCutoffPct = 100;
 constexpr int kDenseWaveRow = 128;     // default wave_row_min on graphs of more than kDenseDegree arcs per node
 constexpr int kLocalRoundsDense = 2;   // ... on graphs with more than kDenseDegree arcs per node and
 constexpr int kDenseDegree = 16;       // more than kDenseLarge nodes (none on smaller dense graphs)
 constexpr int32_t kDenseLarge = 1 << 21;
-constexpr int32_t kDenseChunks = 3;     // RELAX / NEXT chunks per workgroup on dense graphs
+constexpr int32_t kDenseChunks = 3;     // growth chunks per workgroup on dense graphs
 constexpr int32_t kRowShiftMin = 5;     // default long-row bucket: Delta >> shift, shift from the arc count
 constexpr int32_t kRowShiftMax = 8;
-constexpr uint32_t kSmallFrontier = 1u << 15;   // frontiers up to this size get kSmallRounds local rounds
-constexpr int kSmallRounds = 16;
 constexpr int kJobSeconds = 60;   // device-side limit of one decomposition job
-constexpr uint32_t kPassChunk = kSweepThreads;   // smallest chunk of a node pass (SELECT, ASSIGN, ...)
-constexpr uint32_t kBatchGrowChunk = kSweepThreads;        // jobs of several graphs: smallest growth chunk
-constexpr uint32_t kBatchPassChunk = 16 * kSweepThreads;   // ... and smallest node-pass chunk (items)
+constexpr uint32_t kGrowWords = 8;      // fewest bitmap words of a growth chunk ...
+constexpr uint32_t kPassWords = 16;     // ... and of a node pass's
 constexpr uint32_t kRmaxSlots = 1024;   // RMAX: LDS table of cluster maxima (direct-mapped by center id)
 constexpr uint32_t kRmaxFree = 0xffffffffu;
 static_assert(kRmaxSlots == 1024, "RMAX slots are the top 10 bits of a 32-bit hash");
@@ -237,49 +246,28 @@ constexpr int64_t kHubShare = 8;    // ... holding more than 1/kHubShare of the 
 
 // ------------------------------------------------------------- control --
 
-// Which counter holds the items of a phase's sweep, 3 bits per phase.  A
-// table and two selects rather than a switch: the switch form (cases sharing
-// a counter) compiled, for one phase, into divergent branches that never set
-// the counter's address.
-enum : uint32_t { IT_NONE = 0, IT_U = 1, IT_FCUR = 2, IT_BLK = 3, IT_FNXT = 4 };
-constexpr uint64_t item_kind(uint32_t phase, uint32_t kind) { return (uint64_t)kind << (3 * phase); }
-constexpr uint64_t kItemTable =
-    item_kind(PH_SELECT, IT_U) | item_kind(PH_COMPACT, IT_U) | item_kind(PH_SINGLE, IT_U) |
-    item_kind(PH_ASSIGN, IT_U) | item_kind(PH_RMAX, IT_U) | item_kind(PH_RELAX, IT_FCUR) |
-    item_kind(PH_NEXT, IT_BLK) | item_kind(PH_MERGE, IT_BLK) | item_kind(PH_COMMIT, IT_FNXT) |
-    item_kind(PH_C2_SELECT, IT_U) | item_kind(PH_C2_ASSIGN, IT_U) | item_kind(PH_C2_BOUNDARY, IT_BLK) |
-    item_kind(PH_PULL, IT_U) | item_kind(PH_NEXT_PULL, IT_U);
-static_assert(3 * PH_NEXT_PULL + 3 <= 64, "item table holds every phase");
-
-__device__ uint32_t items_of(const GState &s, const GCount &c) {
-  const uint32_t p = s.phase;
-  const uint32_t kind = p <= PH_NEXT_PULL ? (uint32_t)(kItemTable >> (3 * p)) & 7u : IT_NONE;
-  if (kind == IT_NONE) return 0;
-  const uint32_t idx = kind == IT_FCUR ? s.fcur : (kind == IT_BLK ? s.blk : (kind == IT_FNXT ? s.fnxt : s.ucur));
-  const PadU32 *list = kind == IT_U ? c.cntU : c.cnt;
-  return list[idx].v;
-}
-
 // A failing graph stops alone; the other graphs of the job go on.
-__device__ void fail(GState &s, Ctl *ctl, int status) {
-  (void)ctl;
+__device__ void fail(GState &s, int status) {
   s.status = status;
   s.phase = PH_DONE;
 }
 
-__device__ void begin_stage(const GDesc &d, GState &s, GCount &c, Ctl *ctl) {
+__device__ void finish(const GDesc &d, GState &s);
+
+__device__ void begin_stage(const GDesc &d, GState &s) {
+  s.centers = 0;
+  s.cov = 0;
   if (s.nU == 0 || s.nU < d.stop || d.n < 2) {
     s.phase = PH_SINGLE;
+    if (s.nU == 0) finish(d, s);   // nobody is left to be a singleton
     return;
   }
   if (s.stage >= CLDIAM_MAX_STAGES) {
-    fail(s, ctl, CLDIAM_ESTAGES);
+    fail(s, CLDIAM_ESTAGES);
     return;
   }
   double p = d.K / (double)s.nU;
   s.T = p >= 1.0 ? ((uint64_t)1 << 32) : (uint64_t)floor(p * 4294967296.0);
-  c.centers.v = 0;
-  c.cntC.v = 0;
   s.phase = PH_SELECT;
 }
 
@@ -301,359 +289,363 @@ __device__ __forceinline__ uint32_t row_limit(const GDesc &d, uint32_t delta, ui
   return t < 0xffffffffull ? (uint32_t)t : 0xffffffffu;
 }
 
+__device__ __forceinline__ void swap_roles(uint32_t &a, uint32_t &b) {
+  const uint32_t t = a;
+  a = b;
+  b = t;
+}
+
+// A growth starts at distance lo on the frontier.
+__device__ __forceinline__ void begin_growth(const GDesc &d, GState &s, uint32_t lo) {
+  s.theta = bucket_limit(d, lo);
+  s.row_base = lo;
+  s.phase = PH_RELAX;
+}
+
 // CLUSTER2: iteration s.stage + 1 draws centers with probability 2^i / n.
-__device__ void c2_begin_iteration(const GDesc &d, GState &s, GCount &c) {
+__device__ void c2_begin_iteration(const GDesc &d, GState &s) {
   const int i = (int)s.stage + 1;
   const double p = ldexp(1.0, i) / (double)d.n;
   s.T = p >= 1.0 ? ((uint64_t)1 << 32) : (uint64_t)floor(p * 4294967296.0);
-  c.centers.v = 0;
-  c.cntC.v = 0;
+  s.centers = 0;
+  s.cov = 0;
   s.phase = PH_C2_SELECT;
 }
 
 // Synchronous steps: a new PartialGrowth call at the current Delta.
-__device__ __forceinline__ void begin_call(GState &s, uint32_t sweep_id) {
+__device__ __forceinline__ void begin_call(GState &s) {
   s.levels++;
-  s.level_id = sweep_id;
   s.steps_call = 0;
   s.theta = 0xffffffffu;
   s.row_base = 0xffffffffu;
   s.phase = PH_RELAX;
 }
 
-// Synchronous steps: add the blocked list to the active list, then `after`.
-__device__ __forceinline__ void merge_then(GState &s, uint32_t after) {
-  s.after = after;
-  s.phase = PH_MERGE;
-}
-
 // Pull mode pays once the heavy arcs of the blocked rows, which a push rescan
 // and a push NEXT read, outweigh kPullArcs arcs per unreached node (about
 // what pulling reads per node: its rows are sorted by weight and it stops at
 // its first reached neighbour).
-__device__ __forceinline__ bool pull_pays(const GCount &c, uint32_t unreached) {
-  return c.blk_arcs.v > (unsigned long long)kPullArcs * unreached;
+__device__ __forceinline__ bool pull_pays(const GState &s, uint32_t unreached) {
+  return s.blk_arcs > (uint64_t)kPullArcs * unreached;
 }
 
-__device__ __forceinline__ bool double_delta(GState &s, Ctl *ctl) {
+__device__ __forceinline__ bool double_delta(GState &s) {
   if (2ull * s.delta > CLD_DELTA_MAX) {
-    fail(s, ctl, CLDIAM_EOVERFLOW);
+    fail(s, CLDIAM_EOVERFLOW);
     return false;
   }
   s.delta *= 2;
   return true;
 }
 
-// Per-graph transition after a sweep of its current phase.
-__device__ void control_graph(const Job &job, int g, uint32_t sweep_id) {
-  const GDesc &d = job.desc[g];
-  GState &s = job.st[g];
-  GCount &c = job.cn[g];
+// Doubles Delta to the first value at which a node at distance `reach` is
+// reached, one level per doubling.
+__device__ __forceinline__ bool raise_delta(GState &s, uint64_t reach) {
+  uint64_t dl = s.delta;
+  do {
+    if (2 * dl > CLD_DELTA_MAX) {
+      fail(s, CLDIAM_EOVERFLOW);
+      return false;
+    }
+    dl *= 2;
+    s.levels++;
+  } while (dl < reach);
+  s.delta = (uint32_t)dl;
+  s.blk_arcs = 0;
+  return true;
+}
+
+__device__ __forceinline__ void log_stage(const GState &s, int32_t *log) {
+  if (!log || s.stage >= CLDIAM_STAGE_LOG) return;
+  int32_t *lg = log + (size_t)s.stage * 4;
+  lg[0] = (int32_t)s.nU; lg[1] = (int32_t)s.centers; lg[2] = (int32_t)s.cov; lg[3] = (int32_t)s.delta;
+}
+
+// CLUSTER is complete (singletons included): the end, or CLUSTER2's start.
+__device__ void finish(const GDesc &d, GState &s) {
+  s.singletons = s.nU;
+  s.phase = PH_DONE;
+  if (d.variant != CLDIAM_VARIANT_CLUSTER2) return;
+  const uint64_t r1 = s.radius;
+  if (2 * r1 > CLD_DELTA_MAX) { fail(s, CLDIAM_EOVERFLOW); return; }
+  s.radius1 = r1;
+  s.delta = (uint32_t)(2 * r1);
+  if (d.c2_iters == 0) return;   // one node: its own cluster
+  s.c2 = 1;
+  s.pull = 0;
+  s.stage = 0;
+  s.levels = 0;
+  s.centers_total = 0;
+  s.singletons = 0;
+  s.radius = 0;
+  s.phase = PH_C2_INIT;
+}
+
+// The stage's covered nodes are assigned and off the uncovered set.
+__device__ void end_stage(const GDesc &d, GState &s, int32_t *log) {
+  log_stage(s, log);
+  s.nU -= s.cov;
+  s.stage++;
+  if (s.c2) {
+    // the blocked set stays: next iteration's Contract2 boundary
+    if (s.nU == 0) {
+      // iterations without an uncovered node change nothing
+      s.centers = 0;
+      s.cov = 0;
+      for (; s.stage < d.c2_iters; s.stage++) {
+        s.levels++;
+        log_stage(s, log);
+      }
+    }
+    if (s.stage >= d.c2_iters) s.phase = PH_DONE;
+    else c2_begin_iteration(d, s);
+    return;
+  }
+  if (d.variant != CLDIAM_VARIANT_STEPS) {
+    // sources of the next stage: the nodes that NEXT kept (already the
+    // frontier), or the blocked set; in pull mode none (SELECT and PULL
+    // empty both): the uncovered nodes pull from their assigned neighbours
+    if (!s.pull && d.pull_mode == CLDIAM_PULL_AUTO && pull_pays(s, s.nU)) s.pull = 1;
+    if (s.src_blk) swap_roles(s.cur, s.blk);
+    s.src_blk = 0;
+    s.blk_arcs = 0;
+  }
+  // (synchronous steps: the active set and, with s.merge, the blocked set)
+  begin_stage(d, s);
+}
+
+// Transition of one graph after a sweep of its current phase, whose counters
+// are c.  log: its stage log (nullptr: another workgroup writes it).
+__device__ void control_graph(const GDesc &d, GState &s, const GCount &c, int32_t *log) {
+  s.arcs += c.arcs;
+  s.records |= c.records;
   switch (s.phase) {
     case PH_START:
       s.delta = d.delta0;
       s.stage = 0;
       s.nU = (uint32_t)d.n;
-      c.cntU[0].v = (uint32_t)d.n;
-      s.ucur = 0;
-      s.fcur = 0; s.fnxt = 1; s.blk = 2;
-      c.cnt[0].v = c.cnt[1].v = c.cnt[2].v = 0;
-      c.blk_arcs.v = 0;
-      c.hub_arcs.v = 0;
-      c.radius.v = 0;
-      if ((uint64_t)s.delta > CLD_DELTA_MAX) { fail(s, job.ctl, CLDIAM_EOVERFLOW); break; }
+      s.cur = 0; s.nxt = 1; s.blk = 2; s.alt = 3;
+      if ((uint64_t)s.delta > CLD_DELTA_MAX) { fail(s, CLDIAM_EOVERFLOW); break; }
       s.pull = d.pull_mode == CLDIAM_PULL_ALWAYS ? 1u : 0u;
-      begin_stage(d, s, c, job.ctl);
+      begin_stage(d, s);
       break;
     case PH_SELECT:
       // frontier = sources from the previous stage + the new centers, all at
       // distance 0
-      s.centers_total += c.centers.v;
+      s.centers = c.centers;
+      s.cov = c.centers;
+      s.centers_total += c.centers;
       if (d.variant == CLDIAM_VARIANT_STEPS) {
         // the outer loop's test comes first: enough new centers end the stage
-        if (2ull * c.cntC.v >= (uint64_t)s.nU) { s.phase = PH_ASSIGN; break; }
-        begin_call(s, sweep_id);
+        if (2ull * s.cov >= (uint64_t)s.nU) { s.phase = PH_ASSIGN; break; }
+        begin_call(s);
         break;
       }
       s.levels++;
       // a skewed degree distribution (hub rows holding a large share of the
       // arcs) goes with a low diameter: the growth then reaches most nodes
       // within a few hops, which a pull pass does for less than pushing
-      if (!s.pull && s.stage == 0 && d.pull_mode == CLDIAM_PULL_AUTO && c.hub_arcs.v > d.hub_min) s.pull = 1;
+      if (!s.pull && s.stage == 0 && d.pull_mode == CLDIAM_PULL_AUTO && c.hub_arcs > d.hub_min) s.pull = 1;
       if (s.pull) {
         // the uncovered nodes pull from the assigned nodes and the new centers
         s.pull_base = 0;
         s.phase = PH_PULL;
         break;
       }
-      s.level_id = sweep_id;
-      s.theta = bucket_limit(d, 0);
-      s.row_base = 0;
-      c.fmin.v = 0xffffffffu;
-      s.phase = PH_RELAX;
+      begin_growth(d, s, 0);
       break;
     case PH_PULL:
       // the pulled nodes are the frontier of the level
-      s.level_id = sweep_id;
-      s.theta = bucket_limit(d, s.pull_base);
-      s.row_base = s.pull_base;
-      c.fmin.v = 0xffffffffu;
-      s.phase = PH_RELAX;
+      begin_growth(d, s, s.pull_base);
       break;
     case PH_RELAX:
       s.sweeps++;
       if (d.variant == CLDIAM_VARIANT_STEPS) {
         s.rounds++;
         s.steps_call++;
-        s.fid = sweep_id - 1;   // the stamp of the step's updated nodes
+        s.msgs += c.msgs;
+        if (s.merge) { swap_roles(s.blk, s.alt); s.merge = 0; }   // the old blocked set is used up
         s.phase = PH_COMMIT;
         break;
       }
-      if (c.cnt[s.fnxt].v > 0) {
-        uint32_t t = s.fcur; s.fcur = s.fnxt; s.fnxt = t;
-        c.cnt[s.fnxt].v = 0;
+      s.blk_arcs += c.blk_arcs;
+      if (c.fmin != 0xffffffffu) {
+        swap_roles(s.cur, s.nxt);
         // the next bucket starts at the smallest distance on the frontier
-        const uint32_t th = c.fmin.v == 0xffffffffu ? 0xffffffffu : bucket_limit(d, c.fmin.v);
+        const uint32_t th = bucket_limit(d, c.fmin);
         if (th > s.theta) s.theta = th;
-        if (c.fmin.v > s.row_base) s.row_base = c.fmin.v;
-        c.fmin.v = 0xffffffffu;
+        if (c.fmin > s.row_base) s.row_base = c.fmin;
+      } else if (s.c2) {
+        s.phase = PH_C2_ASSIGN;
       } else {
-        c.cnt[s.fcur].v = 0;
-        if (s.c2) s.phase = PH_C2_ASSIGN;
-        else if (2ull * c.cntC.v >= (uint64_t)s.nU) s.phase = PH_ASSIGN;
-        else {
-          // pull from the unreached side once the heavy arcs of the blocked
-          // rows (what a push rescan reads) outweigh the unreached nodes
-          if (!s.pull && d.pull_mode == CLDIAM_PULL_AUTO && pull_pays(c, s.nU - c.cntC.v)) s.pull = 1;
-          c.next.v = CLD_INF64;
-          s.phase = s.pull ? PH_NEXT_PULL : PH_NEXT;
-        }
+        // fixpoint.  In pull mode, and when a switch to it may pay (blocked
+        // heavy arcs for more than 1/16 of the nodes), count before choosing
+        // the side that NEXT looks from.
+        s.phase = s.pull || (d.pull_mode == CLDIAM_PULL_AUTO && pull_pays(s, s.nU >> 4)) ? PH_COUNT : PH_NEXT;
       }
       break;
+    case PH_COUNT:
+      s.cov = c.cov;
+      if (2ull * s.cov >= (uint64_t)s.nU) {
+        s.src_blk = s.pull ? 0u : 1u;
+        s.phase = PH_ASSIGN;
+        break;
+      }
+      if (!s.pull && pull_pays(s, s.nU - s.cov)) s.pull = 1;
+      s.phase = s.pull ? PH_NEXT_PULL : PH_NEXT;
+      break;
     case PH_COMMIT: {
-      const uint32_t nn = c.cnt[s.fnxt].v;
+      const uint32_t nn = c.upd;
       s.updates += nn;
-      uint32_t t = s.fcur; s.fcur = s.fnxt; s.fnxt = t;   // the updated nodes are the next active set
-      c.cnt[s.fnxt].v = 0;
-      if (nn > 0 && 2ull * c.cntC.v >= (uint64_t)s.nU) {
-        merge_then(s, PH_ASSIGN);
+      s.cov += c.cov;
+      swap_roles(s.cur, s.nxt);   // the updated nodes are the next active set
+      if (nn > 0 && 2ull * s.cov >= (uint64_t)s.nU) {
+        s.merge = 1;
+        s.phase = PH_ASSIGN;
       } else if (nn > 0 && d.step_cap && s.steps_call >= d.step_cap) {
-        if (!double_delta(s, job.ctl)) break;
-        merge_then(s, PH_RELAX);
+        if (!double_delta(s)) break;
+        s.merge = 1;
+        begin_call(s);
       } else if (nn > 0) {
         s.phase = PH_RELAX;
       } else {
-        c.next.v = CLD_INF64;   // fixpoint: is any uncovered node reachable?
-        s.phase = PH_NEXT;
+        s.phase = PH_NEXT;      // fixpoint: is any uncovered node reachable?
       }
       break;
     }
-    case PH_MERGE:
-      c.cnt[s.blk].v = 0;
-      if (s.after == PH_RELAX) begin_call(s, sweep_id);
-      else s.phase = s.after;
-      break;
     case PH_NEXT:
       if (d.variant == CLDIAM_VARIANT_STEPS) {
-        if (c.next.v == CLD_INF64) {
-          merge_then(s, PH_ASSIGN);
-        } else if (double_delta(s, job.ctl)) {
-          merge_then(s, PH_RELAX);
-        }
+        s.merge = 1;
+        if (c.next == CLD_INF64) s.phase = PH_ASSIGN;
+        else if (double_delta(s)) begin_call(s);
         break;
       }
-      if (c.next.v == CLD_INF64) {
-        s.phase = PH_ASSIGN;
-      } else {
-        uint64_t dl = s.delta;
-        do {
-          if (2 * dl > CLD_DELTA_MAX) { fail(s, job.ctl, CLDIAM_EOVERFLOW); return; }
-          dl *= 2;
-          s.levels++;
-        } while (dl < c.next.v);
-        s.delta = (uint32_t)dl;
-        // rescan the blocked nodes at the new Delta; fresh blocked list
-        uint32_t t = s.fcur; s.fcur = s.blk; s.blk = t;
-        c.cnt[s.blk].v = 0;
-        c.blk_arcs.v = 0;
-        s.level_id = sweep_id;
-        s.theta = bucket_limit(d, (uint32_t)c.next.v);
-        s.row_base = (uint32_t)c.next.v;
-        c.fmin.v = 0xffffffffu;
-        s.phase = PH_RELAX;
-      }
+      s.cov = c.cov;
+      if (2ull * s.cov >= (uint64_t)s.nU || c.next == CLD_INF64) s.phase = PH_ASSIGN;
+      else if (raise_delta(s, c.next)) begin_growth(d, s, (uint32_t)c.next);
       break;
     case PH_NEXT_PULL:
-      if (c.next.v == CLD_INF64) {
+      if (c.next == CLD_INF64) {
         s.phase = PH_ASSIGN;
-      } else {
-        uint64_t dl = s.delta;
-        do {
-          if (2 * dl > CLD_DELTA_MAX) { fail(s, job.ctl, CLDIAM_EOVERFLOW); return; }
-          dl *= 2;
-          s.levels++;
-        } while (dl < c.next.v);
-        s.delta = (uint32_t)dl;
-        c.cnt[s.blk].v = 0;
-        c.blk_arcs.v = 0;
-        s.pull_base = (uint32_t)c.next.v;
+      } else if (raise_delta(s, c.next)) {
+        s.pull_base = (uint32_t)c.next;
         s.phase = PH_PULL;
       }
       break;
     case PH_ASSIGN:
-      s.phase = PH_RMAX;
+      if (c.radius > s.radius) s.radius = c.radius;
+      if (s.stage > 0) s.phase = PH_RMAX;
+      else end_stage(d, s, log);
       break;
     case PH_RMAX:
-      c.cntU[s.ucur ^ 1].v = 0;
-      s.phase = PH_COMPACT;
+      end_stage(d, s, log);
       break;
-    case PH_COMPACT: {
-      if (s.stage < CLDIAM_STAGE_LOG) {
-        int32_t *lg = job.log + ((size_t)g * CLDIAM_STAGE_LOG + s.stage) * 4;
-        lg[0] = (int32_t)s.nU; lg[1] = (int32_t)c.centers.v; lg[2] = (int32_t)c.cntC.v; lg[3] = (int32_t)s.delta;
-      }
-      s.ucur ^= 1;
-      s.nU = c.cntU[s.ucur].v;
-      s.stage++;
-      if (s.c2) {
-        // the blocked list stays: next iteration's Contract2 boundary
-        c.cnt[s.fcur].v = 0;
-        c.cnt[s.fnxt].v = 0;
-        if (s.stage >= d.c2_iters) s.phase = PH_DONE;
-        else c2_begin_iteration(d, s, c);
-        break;
-      }
-      if (d.variant != CLDIAM_VARIANT_STEPS) {
-        // sources of the next stage: the blocked list of the last level, or,
-        // when it outnumbers the remaining uncovered nodes, none: those
-        // nodes pull from their assigned neighbours instead
-        if (!s.pull && d.pull_mode == CLDIAM_PULL_AUTO && pull_pays(c, c.cntU[s.ucur].v)) s.pull = 1;
-        if (!s.pull) { uint32_t t = s.fcur; s.fcur = s.blk; s.blk = t; }
-        else c.cnt[s.fcur].v = 0;
-      }
-      // (synchronous steps: the active list, merged with the blocked list,
-      // already holds them)
-      c.cnt[s.blk].v = 0;
-      c.blk_arcs.v = 0;
-      c.cnt[s.fnxt].v = 0;
-      begin_stage(d, s, c, job.ctl);
-      break;
-    }
     case PH_SINGLE:
-      s.singletons = s.nU;
-      s.phase = PH_DONE;
-      if (d.variant == CLDIAM_VARIANT_CLUSTER2) {
-        // CLUSTER2 on top of the finished CLUSTER run
-        const uint64_t r1 = c.radius.v;
-        if (2 * r1 > CLD_DELTA_MAX) { fail(s, job.ctl, CLDIAM_EOVERFLOW); break; }
-        s.radius1 = r1;
-        s.delta = (uint32_t)(2 * r1);
-        if (d.c2_iters == 0) break;   // one node: its own cluster
-        s.c2 = 1;
-        s.pull = 0;
-        s.stage = 0;
-        s.levels = 0;
-        s.centers_total = 0;
-        s.singletons = 0;
-        c.radius.v = 0;
-        s.phase = PH_C2_INIT;
-      }
+      finish(d, s);
       break;
     case PH_C2_INIT:
       s.nU = (uint32_t)d.n;
-      s.ucur = 0;
-      c.cntU[0].v = (uint32_t)d.n;
-      c.cnt[0].v = c.cnt[1].v = c.cnt[2].v = 0;
-      c2_begin_iteration(d, s, c);
+      s.cur = 0; s.nxt = 1; s.blk = 2; s.alt = 3;
+      c2_begin_iteration(d, s);
       break;
     case PH_C2_SELECT:
-      s.centers_total += c.centers.v;
+      s.centers = c.centers;
+      s.centers_total += c.centers;
       s.levels++;
-      s.phase = PH_C2_BOUNDARY;
-      break;
-    case PH_C2_BOUNDARY:
-      // the boundary list is consumed; growth marks a fresh one
-      c.cnt[s.blk].v = 0;
-      s.level_id = sweep_id;
-      s.theta = bucket_limit(d, 0);
-      s.row_base = 0;
-      c.fmin.v = 0xffffffffu;
-      s.phase = PH_RELAX;
+      begin_growth(d, s, 0);
       break;
     case PH_C2_ASSIGN:
-      c.cntU[s.ucur ^ 1].v = 0;
-      s.phase = PH_COMPACT;
+      if (c.radius > s.radius) s.radius = c.radius;
+      s.cov = c.cov;
+      end_stage(d, s, log);
       break;
     default:
       break;
   }
 }
 
-// One workgroup of T threads: control of every graph, then the next sweep's
-// index space.
+__device__ __forceinline__ void clear_count(GCount &c) {
+  c.fmin = 0xffffffffu;
+  c.cov = c.centers = c.upd = c.records = 0;
+  c.next = CLD_INF64;
+  c.radius = c.msgs = c.blk_arcs = c.hub_arcs = c.arcs = 0;
+}
+
+__device__ __forceinline__ bool is_growth(uint32_t phase) {
+  return phase == PH_RELAX || phase == PH_NEXT || phase == PH_PULL || phase == PH_NEXT_PULL;
+}
+
+// Bitmap words per chunk of a graph's sweep: chunk_factor chunks per workgroup
+// in growth, one in node passes, none smaller than a wave or two of nodes.
+__device__ __forceinline__ uint32_t chunk_words(const GDesc &d, uint32_t phase, int32_t nblocks) {
+  const bool grow = is_growth(phase);
+  const uint32_t nch = (uint32_t)nblocks * (grow ? (uint32_t)d.chunk_factor : 1u);
+  const uint32_t per = (d.words + nch - 1) / nch, least = grow ? kGrowWords : kPassWords;
+  return per > least ? per : least;
+}
+
+// Device time limit of a job, checked once per control step.
+__device__ __forceinline__ void check_time(Ctl *ctl) {
+  const unsigned long long now = wall_clock64();
+  if (ctl->iterations == 0) ctl->t_start = now;
+  else if (now - ctl->t_start > ctl->t_limit && ctl->error == 0) atomicCAS(&ctl->error, 0u, (uint32_t)(-CLDIAM_ETIMEOUT));
+}
+
+__device__ __forceinline__ void report(const Job &job, uint32_t iterations, uint32_t done) {
+  if (!job.hmirror) return;
+  __hip_atomic_store(&job.hmirror[0], iterations, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  __hip_atomic_store(&job.hmirror[1], done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+// One workgroup of T threads: control of every graph of a job of several,
+// then the next sweep's chunks.
 template <int T>
 __device__ void control_block(const Job &job) {
   __shared__ uint32_t scan[T];
   __shared__ uint32_t carry, alldone;
   __shared__ unsigned long long work;
   Ctl *ctl = job.ctl;
-  uint32_t sweep_id = ctl->sweep_id + 1;
   if (threadIdx.x == 0) {
     carry = 0;
     alldone = 1;
     work = 0;
-    const unsigned long long now = wall_clock64();
-    if (ctl->iterations == 0) ctl->t_start = now;
-    else if (now - ctl->t_start > ctl->t_limit && ctl->error == 0) atomicCAS(&ctl->error, 0u, (uint32_t)(-CLDIAM_ETIMEOUT));
+    check_time(ctl);
   }
   __syncthreads();
-  // every graph's transition and the items of its next sweep
   for (int base = 0; base < job.G; base += T) {
     const int g = base + (int)threadIdx.x;
     if (g < job.G) {
-      if (ctl->error == 0 || job.st[g].phase == PH_DONE) control_graph(job, g, sweep_id);
-      if (ctl->error != 0 && job.st[g].phase != PH_DONE) job.st[g].phase = PH_DONE;
-      const uint32_t phase = job.st[g].phase;
-      const uint32_t n_items =
-          job.st[g].phase == PH_C2_INIT ? (uint32_t)job.desc[g].n : items_of(job.st[g], job.cn[g]);
-      job.seg[2 * job.G + 1 + g] = n_items;
-      if (n_items) atomicAdd(&work, (unsigned long long)n_items);
-      if (phase != PH_DONE && phase != PH_IDLE) atomicAnd(&alldone, 0u);
+      GState &s = job.st[g];
+      if (s.phase != PH_DONE && s.phase != PH_IDLE) {
+        if (ctl->error == 0) control_graph(job.desc[g], s, job.cn[g], job.log + (size_t)g * CLDIAM_STAGE_LOG * 4);
+        else s.phase = PH_DONE;
+        clear_count(job.cn[g]);
+        if (s.phase != PH_DONE) {
+          atomicAdd(&work, (unsigned long long)job.desc[g].words);
+          atomicAnd(&alldone, 0u);
+        }
+      }
     }
   }
   __syncthreads();
-  // In a job of several graphs no chunk is smaller than the sweep's average
-  // items per workgroup (up to kBatchGrowChunk / kBatchPassChunk): a small
-  // frontier or node list then takes a few larger chunks instead of one per
-  // workgroup, each of which would pay a chunk's fixed cost (setup,
-  // barriers, local rounds) for a handful of items.
-  const unsigned long long avg = work / (unsigned long long)job.nblocks;
+  // A chunk is no smaller than half the sweep's average words per workgroup:
+  // many small graphs then take a few chunks each, instead of one per
+  // workgroup that would pay a chunk's fixed cost for a handful of nodes.
+  const unsigned long long avg = work / (2ull * (unsigned long long)job.nblocks);
   for (int base = 0; base < job.G; base += T) {
     const int g = base + (int)threadIdx.x;
-    uint32_t items = 0;
+    uint32_t chunks = 0;
     if (g < job.G) {
       const uint32_t phase = job.st[g].phase;
-      const uint32_t n_items = job.seg[2 * job.G + 1 + g];
-      // Otherwise every graph is cut into its own chunks, at most chunk_factor
-      // per workgroup, so that the frontier of each graph is spread over the
-      // whole grid whatever the other graphs of the job are doing (a node pass
-      // of millions of cheap items beside a small frontier of costly rows).
       uint32_t per = 0;
-      if (n_items) {
-        const bool grow = phase == PH_RELAX || phase == PH_NEXT || phase == PH_PULL || phase == PH_NEXT_PULL;
-        const uint32_t nch = (uint32_t)job.nblocks * (grow ? (uint32_t)job.desc[g].chunk_factor : 1u);
-        per = (n_items + nch - 1) / nch;
-        if (!grow && per < kPassChunk) per = kPassChunk;
-        if (job.G > 1) {
-          const unsigned long long cap = grow ? kBatchGrowChunk : kBatchPassChunk;
-          const uint32_t least = (uint32_t)(avg < cap ? avg : cap);
-          if (per < least) per = least;
-        }
-        items = (n_items + per - 1) / per;
+      if (phase != PH_DONE && phase != PH_IDLE) {
+        per = chunk_words(job.desc[g], phase, job.nblocks);
+        if (per < avg) per = (uint32_t)avg;
+        chunks = (job.desc[g].words + per - 1) / per;
       }
       job.seg[job.G + 1 + g] = per;
     }
-    scan[threadIdx.x] = items;
+    scan[threadIdx.x] = chunks;
     __syncthreads();
     for (int o = 1; o < T; o <<= 1) {
       uint32_t x = threadIdx.x >= (unsigned)o ? scan[threadIdx.x - o] : 0;
@@ -661,7 +653,7 @@ __device__ void control_block(const Job &job) {
       scan[threadIdx.x] += x;
       __syncthreads();
     }
-    if (g < job.G) job.seg[g] = carry + scan[threadIdx.x] - items;
+    if (g < job.G) job.seg[g] = carry + scan[threadIdx.x] - chunks;
     __syncthreads();
     if (threadIdx.x == T - 1) carry += scan[T - 1];
     __syncthreads();
@@ -669,312 +661,246 @@ __device__ void control_block(const Job &job) {
   if (threadIdx.x == 0) {
     job.seg[job.G] = carry;
     ctl->total = carry;
-    ctl->cursor.v = 0;
-    ctl->idle.v = 0;
-    ctl->sweep_id = sweep_id;
+    ctl->sc[0].cursor = 0;
+    ctl->sc[0].idle = 0;
     ctl->iterations++;
     ctl->done = alldone;
-    if (job.hmirror) {
-      __hip_atomic_store(&job.hmirror[0], ctl->iterations, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-      __hip_atomic_store(&job.hmirror[1], alldone, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-    }
+    report(job, ctl->iterations, alldone);
   }
   __syncthreads();
 }
 
 // --------------------------------------------------------------- sweeps --
 
-struct Out {
-  int32_t *list;     // list base for this graph (offset applied)
-  uint32_t *count;   // its global counter
-};
-
-// LDS staging of up to three output lists of one graph run.
+// LDS of a sweep workgroup.
 struct Stage {
-  int32_t buf[3][kStageCap];
   union {
-    int32_t lq[2][kLocalCap];  // RELAX: local relaxation queues
-    struct {                   // RMAX: per-cluster maxima of this workgroup's nodes
+    struct {                     // growth
+      int32_t list[kList];       // nodes of the window being walked
+      uint64_t qk[2][kLocalCap]; // local relaxation queues: key to relax with ...
+      int32_t qv[2][kLocalCap];  // ... and node
+      int32_t mid[kMidCap];      // rows deferred to one wave each
+      int32_t big[kBigCap];      // rows deferred to the whole workgroup
+    };
+    struct {                     // RMAX: per-cluster maxima of this workgroup's nodes
       uint32_t tag[kRmaxSlots];
       unsigned long long mx[kRmaxSlots];
     } rmax;
   };
-  uint32_t lq_cnt[2];
-  int32_t mid[kMidCap];      // rows deferred to one wave each
-  int32_t big[kBigCap];      // rows deferred to the whole workgroup
-  uint32_t mid_cnt, big_cnt;
-  unsigned long long blk_min;  // workgroup minimum for the NEXT scan of a big row
+  uint32_t qn[2];
+  uint32_t mid_cnt[2], big_cnt[2];   // of the even and the odd passes (see coop_rows)
+  unsigned long long blk_min;  // workgroup minimum over a big row (NEXT, PULL)
   unsigned long long row_key;  // key of the big row being scanned
   int32_t row_lo;              // end of its light prefix (index within the row)
   int32_t row_start;           // first arc of its scan (index within the row)
   uint32_t blk_hit;
-  uint32_t cnt[3];
-  uint32_t base[3];
-  unsigned long long acc;   // min (NEXT) or max (ASSIGN) accumulator
-  unsigned long long blk_arcs;   // RELAX: heavy arcs of the rows this workgroup put on the blocked list
-  uint32_t acc32;           // centers drawn (SELECT)
-  uint32_t flush;           // a list passed the flush threshold
-  uint32_t fmin;            // RELAX: smallest distance pushed on the next frontier
-  uint32_t chunk;           // next chunk of this workgroup
-  uint32_t stop;            // local rounds end early: most of the grid has finished the sweep
-  Out out[3];               // output lists of the current run (in LDS: the flush indexes them by list number)
+  uint32_t wsum[kWaves];
+  uint32_t chunk;              // next chunk of this workgroup
+  uint32_t stop;               // local rounds end early: most of the grid has finished the sweep
+  GCount sum;                  // this workgroup's part of the sweep's counters
+  GCount last;                 // one graph: the counters of the sweep before ...
+  GState st;                   // ... and the state that the control step made of it
 };
 
-// Stage v on output list k; falls back to a direct global slot when the LDS
-// buffer is full (only possible for rows with thousands of improved arcs).
-__device__ __forceinline__ void stage_push(Stage &S, const Out *out, int k, int32_t v) {
-  const uint32_t slot = atomicAdd(&S.cnt[k], 1u);
-  if (slot < kStageCap) {
-    S.buf[k][slot] = v;
+// One graph's sweep as a workgroup sees it.
+struct Run {
+  const Job &job;
+  const GDesc &d;
+  const GState &s;
+  Stage &S;
+  uint64_t *key;         // this graph's part of the node arrays and bitmaps
+  uint64_t *keyn;
+  uint32_t *slim;
+  uint64_t *cur, *nxt;
+  uint64_t *mark;        // where blocked nodes are marked (nullptr: nowhere)
+  uint32_t delta, theta, theta_row;
+  bool resume;           // long rows resume their last scan
+  uint32_t pass = 0;     // list passes so far
+  // per-thread sums
+  uint32_t scanned = 0, heavy = 0;
+  unsigned long long acc = 0;   // NEXT: min; ASSIGN: max; SELECT: hub arcs
+};
+
+__device__ __forceinline__ void set_bit(uint64_t *bits, int32_t v) {
+  atomicOr((unsigned long long *)&bits[v >> 6], 1ull << (v & 63));
+}
+
+// v stays for the next sweep, at tentative distance dist.
+__device__ __forceinline__ void leave(Run &r, int32_t v, uint32_t dist) {
+  set_bit(r.nxt, v);
+  if (dist < r.S.sum.fmin) atomicMin(&r.S.sum.fmin, dist);
+}
+
+// u's scan stopped at a heavy arc; `heavy` arcs are left on its row.  word is
+// u's word of the blocked set as read before.
+__device__ __forceinline__ void mark_blocked(Run &r, int32_t u, uint64_t word, int32_t heavy) {
+  if (word >> (u & 63) & 1) return;
+  set_bit(r.mark, u);
+  r.heavy += (uint32_t)heavy;
+}
+
+__device__ __forceinline__ uint64_t marks_of(const Run &r, int32_t u) { return r.mark ? r.mark[u >> 6] : ~0ull; }
+
+// Applies a thread's K offers cand[i] to v[i] that beat the keys read
+// (better[i]) and queues them in queue q: one reservation per wave.
+template <int K>
+__device__ __forceinline__ void improve(Run &r, int q, const bool (&better)[K], const int32_t (&v)[K],
+                                        const uint64_t (&cand)[K]) {
+  const uint64_t below = (1ull << (threadIdx.x & 63)) - 1ull;
+  uint32_t at[K], total = 0;
+  bool near[K];
+#pragma unroll
+  for (int i = 0; i < K; ++i) {
+    if (better[i]) atomicMin((unsigned long long *)&r.key[v[i]], (unsigned long long)cand[i]);
+    near[i] = better[i] && (uint32_t)(cand[i] >> 32) < r.theta;
+    const uint64_t m = __ballot(near[i]);
+    at[i] = total + (uint32_t)__popcll(m & below);
+    total += (uint32_t)__popcll(m);
+  }
+  if (total) {
+    uint32_t base = 0;
+    const int first = __ffsll((long long)__ballot(true)) - 1;
+    if ((int)(threadIdx.x & 63) == first) base = atomicAdd(&r.S.qn[q], total);
+    base = __shfl(base, first);
+#pragma unroll
+    for (int i = 0; i < K; ++i) {
+      if (!near[i]) continue;
+      const uint32_t slot = base + at[i];
+      if (slot < r.d.lq_cap) {
+        r.S.qv[q][slot] = v[i];
+        r.S.qk[q][slot] = cand[i];
+      } else {
+        leave(r, v[i], (uint32_t)(cand[i] >> 32));
+      }
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < K; ++i)
+    if (better[i] && !near[i]) leave(r, v[i], (uint32_t)(cand[i] >> 32));
+}
+
+constexpr int kArcBatch = 4;   // arcs of a row in flight per thread
+
+// The same for synchronous steps: offers were judged against the state before
+// the step (key) and go to the state after it (keyn), the lexicographic
+// minimum over the step's offers wins.
+template <int K>
+__device__ __forceinline__ void improve_sync(Run &r, const bool (&better)[K], const int32_t (&v)[K],
+                                             const uint64_t (&cand)[K]) {
+#pragma unroll
+  for (int i = 0; i < K; ++i) {
+    if (!better[i]) continue;
+    atomicMin((unsigned long long *)&r.keyn[v[i]], (unsigned long long)cand[i]);
+    set_bit(r.nxt, v[i]);
+  }
+}
+
+// K arcs of u's row (key ku; in[i]: part of the row): the light ones
+// (w <= lim) are offered, the first heavy one ends the scan.  Returns the
+// number of light arcs; *blocked is set if a heavy one is among them.
+template <bool kSync, int K>
+__device__ __forceinline__ uint32_t offer(Run &r, int q, uint64_t ku, uint32_t lim, const bool (&in)[K],
+                                          const uint64_t (&arc)[K], bool *blocked) {
+  bool better[K];
+  int32_t v[K];
+  uint64_t cand[K];
+  uint32_t light = 0;
+#pragma unroll
+  for (int i = 0; i < K; ++i) {
+    const bool ok = in[i] && (uint32_t)(arc[i] >> 32) <= lim;
+    if (in[i] && !ok) *blocked = true;
+    light += ok;
+    v[i] = (int32_t)(uint32_t)arc[i];
+    cand[i] = ku + (arc[i] & 0xffffffff00000000ull);
+    better[i] = ok;
+  }
+#pragma unroll
+  for (int i = 0; i < K; ++i) {
+    const uint64_t k = better[i] ? r.key[v[i]] : 0ull;
+    better[i] = kSync ? (cand[i] >> 32) < (k >> 32) && better[i] : cand[i] < k;   // no offer is below 0
+  }
+  if (kSync) improve_sync<K>(r, better, v, cand);
+  else improve<K>(r, q, better, v, cand);
+  return light;
+}
+
+// Queues a long row for the cooperative passes that end this pass; false when
+// the queue is full (the caller then handles the row itself).
+__device__ __forceinline__ bool defer_row(Run &r, int32_t u, int32_t deg) {
+  if (deg > r.d.big_deg) {
+    const uint32_t slot = atomicAdd(&r.S.big_cnt[r.pass & 1], 1u);
+    if (slot < kBigCap) { r.S.big[slot] = u; return true; }
   } else {
-    out[k].list[atomicAdd(out[k].count, 1u)] = v;
-  }
-}
-
-// Writes the staged entries out: one global reservation per list.
-__device__ void stage_flush(Stage &S, const Out *out, int nout) {
-  __syncthreads();
-  if (threadIdx.x < (unsigned)nout) {
-    const int k = threadIdx.x;
-    const uint32_t n = S.cnt[k] < kStageCap ? S.cnt[k] : kStageCap;
-    uint32_t *count = k == 0 ? out[0].count : (k == 1 ? out[1].count : out[2].count);
-    S.base[k] = n ? atomicAdd(count, n) : 0;
-    S.cnt[k] = n;
-  }
-  __syncthreads();
-  {
-    const uint32_t n = S.cnt[0], b = S.base[0];
-    for (uint32_t i = threadIdx.x; i < n; i += blockDim.x) out[0].list[b + i] = S.buf[0][i];
-  }
-  if (nout > 1) {
-    const uint32_t n = S.cnt[1], b = S.base[1];
-    for (uint32_t i = threadIdx.x; i < n; i += blockDim.x) out[1].list[b + i] = S.buf[1][i];
-  }
-  if (nout > 2) {
-    const uint32_t n = S.cnt[2], b = S.base[2];
-    for (uint32_t i = threadIdx.x; i < n; i += blockDim.x) out[2].list[b + i] = S.buf[2][i];
-  }
-  __syncthreads();
-  if (threadIdx.x < 3) S.cnt[threadIdx.x] = 0;
-  if (threadIdx.x == 0) S.flush = 0;
-  __syncthreads();
-}
-
-// Synchronous step for one active node u (see relax_one_sync).  Returns the
-// number of offers sent (arcs with d_u + w <= Delta).
-__device__ __forceinline__ uint32_t relax_sync(const Job &job, const GDesc &d, int64_t off, uint32_t delta,
-                                               uint32_t it, uint32_t level_id, int32_t u, Stage &S,
-                                               const Out *out);
-
-// Smallest tentative distance pushed on the next frontier by this workgroup.
-__device__ __forceinline__ void note_fmin(Stage &S, uint32_t dist) {
-  if (dist < S.fmin) atomicMin(&S.fmin, dist);
-}
-
-// RELAX: scan the light prefix of u's row (w <= Delta - d_u) and offer
-// (d_u + w, c_u) to every neighbour.  Outputs: 0 next frontier, 1 covered,
-// 2 blocked.  Arcs are handled four at a time so that their key loads and
-// atomics are in flight together.  Improved neighbours are also appended to
-// the workgroup's local queue `lq` (when it has room) for the local rounds.
-constexpr int kArcBatch = 4;
-
-// Queues a long row for the cooperative passes of this round; false when the
-// queue is full (the caller then handles the row itself).
-__device__ __forceinline__ bool defer_row(Stage &S, int32_t u, int32_t deg, int32_t big_deg) {
-  if (deg > big_deg) {
-    const uint32_t slot = atomicAdd(&S.big_cnt, 1u);
-    if (slot < kBigCap) { S.big[slot] = u; return true; }
-  } else {
-    const uint32_t slot = atomicAdd(&S.mid_cnt, 1u);
-    if (slot < kMidCap) { S.mid[slot] = u; return true; }
+    const uint32_t slot = atomicAdd(&r.S.mid_cnt[r.pass & 1], 1u);
+    if (slot < kMidCap) { r.S.mid[slot] = u; return true; }
   }
   return false;
 }
 
-__device__ __forceinline__ void lq_push(uint32_t *lq_cnt, int32_t *lq, int32_t v, uint32_t cap) {
-  const uint32_t slot = atomicAdd(lq_cnt, 1u);
-  if (slot < cap) lq[slot] = v;
-}
-
-__device__ __forceinline__ uint32_t relax_item(const Job &job, const GDesc &d, int64_t off, uint32_t delta,
-                                               uint32_t theta, uint32_t theta_row, uint32_t it,
-                                               uint32_t level_id, int32_t u,
-                                               Stage &S, const Out *out, uint32_t *lq_cnt, int32_t *lq) {
-  const uint64_t ku = job.key[off + u];
-  int64_t a0 = 0;
-  int32_t deg = 0;   // a row has fewer than 2^31 arcs: indices within it are 32-bit
-  bool later = (uint32_t)(ku >> 32) >= theta;
-  if (!later) {
-    a0 = d.row_ptr[u];
-    deg = (int32_t)(d.row_ptr[u + 1] - a0);
-    later = deg > d.mid_deg && (uint32_t)(ku >> 32) >= theta_row;
-  }
-  if (later) {
-    // beyond the current distance bucket: stays on the frontier for a later
-    // sweep (it may already be there if it improved in this sweep)
-    if (atomicExch(&job.fstamp[off + u], it) != it) {
-      stage_push(S, out, 0, u);
-      note_fmin(S, (uint32_t)(ku >> 32));
-    }
-    return 0;
-  }
-  if (deg > d.mid_deg && defer_row(S, u, deg, d.big_deg)) return 0;
-  const uint64_t *row = d.arcs + a0;
-  const uint32_t lim = delta - (uint32_t)(ku >> 32);
+// Relaxes u with key ku, four arcs of its row at a time so that their loads
+// overlap; long rows are deferred.
+template <bool kSync>
+__device__ __forceinline__ void relax_row(Run &r, int q, int32_t u, uint64_t ku, int64_t a0, int32_t deg) {
+  if (deg > r.d.mid_deg && defer_row(r, u, deg)) return;
+  const uint64_t word = marks_of(r, u);
+  const uint64_t *row = r.d.arcs + a0;
+  const uint32_t lim = r.delta - (uint32_t)(ku >> 32);
   bool blocked = false;
-  uint32_t scanned = 0;
+  uint32_t light = 0;
   for (int32_t base = 0; base < deg && !blocked; base += kArcBatch) {
-    uint64_t arc[kArcBatch], cur[kArcBatch];
-    bool ok[kArcBatch];
+    uint64_t arc[kArcBatch];
+    bool in[kArcBatch];
 #pragma unroll
-    for (int j = 0; j < kArcBatch; ++j) arc[j] = base + j < deg ? row[base + j] : ~0ull;
-#pragma unroll
-    for (int j = 0; j < kArcBatch; ++j) {
-      const bool in = base + j < deg;
-      ok[j] = in && (uint32_t)(arc[j] >> 32) <= lim;
-      if (in && !ok[j]) blocked = true;
-      scanned += ok[j];
+    for (int i = 0; i < kArcBatch; ++i) {
+      in[i] = base + i < deg;
+      arc[i] = in[i] ? row[base + i] : ~0ull;
     }
-#pragma unroll
-    for (int j = 0; j < kArcBatch; ++j) cur[j] = ok[j] ? job.key[off + (int32_t)(uint32_t)arc[j]] : 0ull;
-    // An offer that beats the key it read is applied with atomicMin and, in
-    // the same round trip, stamps the target for the next frontier.  The
-    // stamp may be taken by an offer that then loses to a concurrent better
-    // one; the node is then still on the frontier (harmless), and an improver
-    // never finds the node missing from it.  The returned stamp also keeps each
-    // node to one entry per list and sweep, which the lists' capacity (n) needs.
-    bool front[kArcBatch];
-#pragma unroll
-    for (int j = 0; j < kArcBatch; ++j) {
-      const uint64_t cand = ku + (arc[j] & 0xffffffff00000000ull);
-      ok[j] = ok[j] && cand < cur[j];
-      const int64_t gv = off + (int32_t)(uint32_t)arc[j];
-      cur[j] = ok[j] ? atomicMin((unsigned long long *)&job.key[gv], (unsigned long long)cand) : 0ull;
-      front[j] = ok[j] && atomicExch(&job.fstamp[gv], it) != it;
-      ok[j] = ok[j] && cand < cur[j];
-    }
-#pragma unroll
-    for (int j = 0; j < kArcBatch; ++j) {
-      const int32_t v = (int32_t)(uint32_t)arc[j];
-      if (front[j]) {
-        stage_push(S, out, 0, v);
-        note_fmin(S, (uint32_t)(ku >> 32) + (uint32_t)(arc[j] >> 32));
-      }
-      if (!ok[j]) continue;
-      if (cur[j] == CLD_INF64) stage_push(S, out, 1, v);
-      if (lq) lq_push(lq_cnt, lq, v, d.lq_cap);
-    }
+    light += offer<kSync, kArcBatch>(r, q, ku, lim, in, arc, &blocked);
   }
-  if (blocked && job.bstamp[off + u] != level_id && atomicExch(&job.bstamp[off + u], level_id) != level_id) {
-    stage_push(S, out, 2, u);
-    atomicAdd(&S.blk_arcs, (unsigned long long)(deg - (int32_t)scanned));   // the light arcs come first
-  }
-  return scanned;
+  r.scanned += light;
+  if (blocked) mark_blocked(r, u, word, deg - (int32_t)light);
 }
 
-__device__ __forceinline__ uint32_t relax_sync(const Job &job, const GDesc &d, int64_t off, uint32_t delta,
-                                               uint32_t it, uint32_t level_id, int32_t u, Stage &S,
-                                               const Out *out) {
-  const int64_t a0 = d.row_ptr[u];
-  const int32_t deg = (int32_t)(d.row_ptr[u + 1] - a0);
-  if (deg > d.mid_deg && defer_row(S, u, deg, d.big_deg)) return 0;
-  const uint64_t *row = d.arcs + a0;
-  const uint64_t ku = job.key[off + u];
-  const uint32_t lim = delta - (uint32_t)(ku >> 32);
-  bool blocked = false;
-  uint32_t scanned = 0;
-  for (int32_t base = 0; base < deg && !blocked; base += kArcBatch) {
-    uint64_t arc[kArcBatch], cur[kArcBatch], old[kArcBatch];
-    bool ok[kArcBatch], front[kArcBatch];
-#pragma unroll
-    for (int j = 0; j < kArcBatch; ++j) arc[j] = base + j < deg ? row[base + j] : ~0ull;
-#pragma unroll
-    for (int j = 0; j < kArcBatch; ++j) {
-      const bool in = base + j < deg;
-      ok[j] = in && (uint32_t)(arc[j] >> 32) <= lim;
-      if (in && !ok[j]) blocked = true;
-      scanned += ok[j];
-    }
-#pragma unroll
-    for (int j = 0; j < kArcBatch; ++j) cur[j] = ok[j] ? job.key[off + (int32_t)(uint32_t)arc[j]] : 0ull;
-#pragma unroll
-    for (int j = 0; j < kArcBatch; ++j) {
-      const uint64_t cand = ku + (arc[j] & 0xffffffff00000000ull);
-      ok[j] = ok[j] && (cand >> 32) < (cur[j] >> 32);
-      const int64_t gv = off + (int32_t)(uint32_t)arc[j];
-      old[j] = ok[j] ? atomicMin((unsigned long long *)&job.keyn[gv], (unsigned long long)cand) : 0ull;
-      front[j] = ok[j] && atomicExch(&job.fstamp[gv], it) != it;
-    }
-#pragma unroll
-    for (int j = 0; j < kArcBatch; ++j) {
-      const int32_t v = (int32_t)(uint32_t)arc[j];
-      if (front[j]) stage_push(S, out, 0, v);
-      if (ok[j] && old[j] == CLD_INF64) stage_push(S, out, 1, v);
-    }
-  }
-  if (blocked && job.bstamp[off + u] != level_id && atomicExch(&job.bstamp[off + u], level_id) != level_id)
-    stage_push(S, out, 2, u);
-  return scanned;
+// A frontier node.
+template <bool kSync>
+__device__ __forceinline__ void relax_item(Run &r, int32_t u) {
+  const uint64_t ku = r.key[u];
+  const int64_t a0 = r.d.row_ptr[u];
+  const int32_t deg = (int32_t)(r.d.row_ptr[u + 1] - a0);   // indices within a row are 32-bit
+  const uint32_t dist = (uint32_t)(ku >> 32);
+  // beyond the current distance bucket: stays for a later sweep
+  if (!kSync && (dist >= r.theta || (deg > r.d.mid_deg && dist >= r.theta_row))) leave(r, u, dist);
+  else relax_row<kSync>(r, 0, u, ku, a0, deg);
 }
 
-// One arc of a cooperative row: the same offer as in relax_item.
-__device__ __forceinline__ void relax_one(const Job &job, int64_t off, uint64_t ku, uint64_t arc, uint32_t it,
-                                          Stage &S, const Out *out, uint32_t *lq_cnt, int32_t *lq, uint32_t lq_cap) {
-  const int32_t v = (int32_t)(uint32_t)arc;
-  const int64_t gv = off + v;
-  const uint64_t cand = ku + (arc & 0xffffffff00000000ull);
-  if (cand < job.key[gv]) {
-    const uint64_t old = atomicMin((unsigned long long *)&job.key[gv], (unsigned long long)cand);
-    if (atomicExch(&job.fstamp[gv], it) != it) {
-      stage_push(S, out, 0, v);
-      note_fmin(S, (uint32_t)(cand >> 32));
-    }
-    if (cand < old) {
-      if (old == CLD_INF64) stage_push(S, out, 1, v);
-      if (lq) lq_push(lq_cnt, lq, v, lq_cap);
-    }
-  }
-}
-
-// Synchronous steps: an offer is judged against the state before the step
-// (key) and applied to the state after it (keyn); only a strictly smaller
-// distance is accepted, the lexicographic minimum over the step's offers wins.
-__device__ __forceinline__ void relax_one_sync(const Job &job, int64_t off, uint64_t ku, uint64_t arc, uint32_t it,
-                                               Stage &S, const Out *out) {
-  const int32_t v = (int32_t)(uint32_t)arc;
-  const int64_t gv = off + v;
-  const uint64_t cand = ku + (arc & 0xffffffff00000000ull);
-  if ((cand >> 32) < (job.key[gv] >> 32)) {
-    const uint64_t old = atomicMin((unsigned long long *)&job.keyn[gv], (unsigned long long)cand);
-    if (atomicExch(&job.fstamp[gv], it) != it) stage_push(S, out, 0, v);
-    if (old == CLD_INF64) stage_push(S, out, 1, v);
-  }
-}
-
-__device__ __forceinline__ void mark_blocked(const Job &job, int64_t off, int32_t u, uint32_t level_id, int32_t heavy,
-                                             Stage &S, const Out *out) {
-  if (job.bstamp[off + u] != level_id && atomicExch(&job.bstamp[off + u], level_id) != level_id) {
-    stage_push(S, out, 2, u);
-    atomicAdd(&S.blk_arcs, (unsigned long long)heavy);
-  }
+// A queued improvement.
+__device__ __forceinline__ void relax_queued(Run &r, int q, int32_t u, uint64_t ku) {
+  const uint64_t now = r.key[u];
+  const int64_t a0 = r.d.row_ptr[u];
+  const int32_t deg = (int32_t)(r.d.row_ptr[u + 1] - a0);
+  if (now < ku) return;   // improved again since: another entry's business
+  const uint32_t dist = (uint32_t)(ku >> 32);
+  if (deg > r.d.mid_deg && dist >= r.theta_row) leave(r, u, dist);
+  else relax_row<false>(r, q, u, ku, a0, deg);
 }
 
 // NEXT for a short row: smallest d_u + w over its heavy arcs (w > Delta - d_u)
 // into unreached nodes.  Rows are sorted by weight, so the first such arc in
 // ascending order gives the minimum.
-__device__ __forceinline__ uint64_t next_small(const Job &job, const GDesc &d, int64_t off, uint32_t delta,
-                                               int32_t u) {
-  const uint64_t ku = job.key[off + u];
-  const uint32_t du = (uint32_t)(ku >> 32);
-  const uint32_t lim = delta - du;
-  const int64_t a0 = d.row_ptr[u];
-  const uint64_t *row = d.arcs + a0;
-  const int32_t deg = (int32_t)(d.row_ptr[u + 1] - a0);
-  for (int32_t a = 0; a < deg; ++a) {
-    const uint64_t arc = row[a];
-    const uint32_t w = (uint32_t)(arc >> 32);
-    if (w <= lim) continue;
-    if (job.key[off + (int32_t)(uint32_t)arc] == CLD_INF64) return (uint64_t)du + w;
+__device__ __forceinline__ uint64_t next_small(const Run &r, uint64_t ku, int64_t a0, int32_t deg) {
+  const uint32_t du = (uint32_t)(ku >> 32), lim = r.delta - du;
+  const uint64_t *row = r.d.arcs + a0;
+  for (int32_t base = 0; base < deg; base += kArcBatch) {
+    uint64_t arc[kArcBatch];
+    bool hit[kArcBatch];
+#pragma unroll
+    for (int i = 0; i < kArcBatch; ++i) arc[i] = base + i < deg ? row[base + i] : 0ull;   // 0: light
+#pragma unroll
+    for (int i = 0; i < kArcBatch; ++i)
+      hit[i] = (uint32_t)(arc[i] >> 32) > lim && r.key[(int32_t)(uint32_t)arc[i]] == CLD_INF64;
+#pragma unroll
+    for (int i = 0; i < kArcBatch; ++i)
+      if (hit[i]) return (uint64_t)du + (arc[i] >> 32);
   }
   return CLD_INF64;
 }
@@ -1017,137 +943,161 @@ __device__ __forceinline__ int32_t wave_first_above(const uint64_t *arcs, int32_
 }
 
 // Resume index within the row [0, end) of u (arcs at row).
-__device__ __forceinline__ int32_t resume_at_wave(const Job &job, int64_t off, int32_t u, uint64_t ku,
-                                                  const uint64_t *row, int32_t end) {
-  if (job.keyn[off + u] != ku) return 0;
-  return wave_first_above(row, 0, end, job.slim[off + u]);
+__device__ __forceinline__ int32_t resume_at_wave(const Run &r, int32_t u, uint64_t ku, const uint64_t *row,
+                                                  int32_t end) {
+  if (r.keyn[u] != ku) return 0;
+  return wave_first_above(row, 0, end, r.slim[u]);
 }
 
-__device__ __forceinline__ void note_scan(const Job &job, int64_t off, int32_t u, uint64_t ku, uint32_t lim) {
-  job.slim[off + u] = lim;
-  job.keyn[off + u] = ku;
+__device__ __forceinline__ void note_scan(Run &r, int32_t u, uint64_t ku, uint32_t lim) {
+  r.slim[u] = lim;
+  r.keyn[u] = ku;
+  r.S.sum.records = 1;
 }
 
-// Cooperative passes over the rows deferred in this round: each wave takes
-// whole mid-size rows (64 arcs per step), then the whole workgroup takes each
-// big row (blockDim arcs per step).  mode 0 relaxes the light prefix; mode 2
-// does the same as a synchronous step; mode 1 (NEXT) finds the first heavy arc
-// into an unreached node and folds d_u + w into S.acc.
-__device__ uint32_t coop_rows(const Job &job, const GDesc &d, int64_t off, uint32_t delta, uint32_t it,
-                              uint32_t level_id, Stage &S, const Out *out, uint32_t *lq_cnt, int32_t *lq, int mode,
-                              bool resume) {
+// Ends a pass: the rows that it deferred, each wave taking whole mid-size
+// rows (64 lanes x kArcBatch arcs per step), then the whole workgroup each big
+// row.  The deferral counters alternate between passes, so a wave that is late
+// to read this pass's sees none of the next pass's rows and every wave takes
+// the same branch after the one barrier.  `mid` handles a row in a wave, `big`
+// one in the workgroup (called by every thread, with a barrier behind it).
+template <class Mid, class Big>
+__device__ __forceinline__ void coop_rows(Run &r, Mid mid, Big big) {
   __syncthreads();
-  const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nwaves = blockDim.x >> 6;
-  const uint32_t nm = S.mid_cnt < kMidCap ? S.mid_cnt : kMidCap;
-  const uint32_t nb = S.big_cnt < kBigCap ? S.big_cnt : kBigCap;
-  uint32_t scanned = 0;
-  for (uint32_t r = wave; r < nm; r += nwaves) {
-    const int32_t u = S.mid[r];
-    const int64_t a0 = d.row_ptr[u];
-    const int32_t a1 = (int32_t)(d.row_ptr[u + 1] - a0);   // row-relative from here on
-    const uint64_t *row = d.arcs + a0;
-    const uint64_t ku = job.key[off + u];
-    const uint32_t lim = delta - (uint32_t)(ku >> 32);
-    if (mode != 1) {
-      const int32_t start = resume ? resume_at_wave(job, off, u, ku, row, a1) : 0;
-      int32_t light_end = start;   // the light arcs are a prefix of the row
-      for (int32_t base = start; base < a1; base += 64) {
-        const int32_t a = base + (int32_t)lane;
-        const uint64_t arc = a < a1 ? row[a] : ~0ull;
-        const bool light = a < a1 && (uint32_t)(arc >> 32) <= lim;
-        const int nl = __popcll(__ballot(light));
-        light_end = base + nl;
-        if (nl == 0) break;
-        if (light) {
-          ++scanned;
-          if (mode == 2) relax_one_sync(job, off, ku, arc, it, S, out);
-          else relax_one(job, off, ku, arc, it, S, out, lq_cnt, lq, d.lq_cap);
-        }
-        if (nl < 64) break;
-      }
-      if (lane == 0 && (uint32_t)(row[a1 - 1] >> 32) > lim)
-        mark_blocked(job, off, u, level_id, a1 - light_end, S, out);
-      if (resume && lane == 0) note_scan(job, off, u, ku, lim);
-    } else {
-      // the heavy arcs start after the light prefix
-      for (int32_t base = wave_first_above(row, 0, a1, lim); base < a1; base += 64) {
-        const int32_t a = base + (int32_t)lane;
-        const uint64_t arc = a < a1 ? row[a] : 0ull;
-        const uint32_t w = (uint32_t)(arc >> 32);
-        const bool hit = a < a1 && w > lim && job.key[off + (int32_t)(uint32_t)arc] == CLD_INF64;
-        const unsigned long long m = __ballot(hit);
-        if (m) {
-          // first hit in ascending order has the smallest weight
-          const int src = __ffsll((long long)m) - 1;
-          const uint64_t c = (uint64_t)(uint32_t)(ku >> 32) + (uint32_t)(__shfl(arc, src) >> 32);
-          if (lane == 0 && c < S.acc) atomicMin(&S.acc, (unsigned long long)c);
-          break;
-        }
-      }
-    }
+  Stage &S = r.S;
+  const uint32_t p = r.pass++ & 1;
+  const uint32_t nm = S.mid_cnt[p] < kMidCap ? S.mid_cnt[p] : kMidCap;
+  const uint32_t nb = S.big_cnt[p] < kBigCap ? S.big_cnt[p] : kBigCap;
+  if (nm == 0 && nb == 0) return;
+  for (uint32_t i = threadIdx.x >> 6; i < nm; i += kWaves) {
+    const int32_t u = S.mid[i];
+    const int64_t a0 = r.d.row_ptr[u];
+    mid(u, r.d.arcs + a0, (int32_t)(r.d.row_ptr[u + 1] - a0));
   }
   for (uint32_t h = 0; h < nb; ++h) {
     const int32_t u = S.big[h];
-    const int64_t a0 = d.row_ptr[u];
-    const int32_t a1 = (int32_t)(d.row_ptr[u + 1] - a0);   // row-relative from here on
-    const uint64_t *row = d.arcs + a0;
+    const int64_t a0 = r.d.row_ptr[u];
+    big(u, r.d.arcs + a0, (int32_t)(r.d.row_ptr[u + 1] - a0));
+    __syncthreads();
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) { S.mid_cnt[p] = 0; S.big_cnt[p] = 0; }
+  __syncthreads();
+}
+
+template <bool kSync>
+__device__ __forceinline__ void relax_long(Run &r, int q) {
+  const int32_t lane = (int32_t)(threadIdx.x & 63), tid = (int32_t)threadIdx.x;
+  auto mid = [&](int32_t u, const uint64_t *row, int32_t deg) {
+    const uint64_t word = marks_of(r, u), ku = r.key[u];
+    const uint32_t lim = r.delta - (uint32_t)(ku >> 32);
+    const int32_t start = r.resume ? resume_at_wave(r, u, ku, row, deg) : 0;
+    int32_t end = start;   // of the light prefix
+    bool any = false;
+    for (int32_t base = start; base < deg && !any; base += 64 * kArcBatch) {
+      uint64_t arc[kArcBatch];
+      bool in[kArcBatch], blocked = false;
+#pragma unroll
+      for (int i = 0; i < kArcBatch; ++i) {
+        const int32_t a = base + 64 * i + lane;
+        in[i] = a < deg;
+        arc[i] = in[i] ? row[a] : ~0ull;
+      }
+      uint32_t light = offer<kSync, kArcBatch>(r, q, ku, lim, in, arc, &blocked);
+      r.scanned += light;
+      any = __any(blocked);
+      for (int o = 32; o >= 1; o >>= 1) light += __shfl_xor(light, o);
+      end += (int32_t)light;
+    }
+    if (lane == 0) {
+      if (any) mark_blocked(r, u, word, deg - end);
+      if (r.resume) note_scan(r, u, ku, lim);
+    }
+  };
+  auto big = [&](int32_t u, const uint64_t *row, int32_t deg) {
     // wave 0 reads u's key once for the whole workgroup (so every thread scans
     // with the same key and the scan record describes all of them) and finds
     // the end of the light prefix and the resume point
     if (threadIdx.x < 64) {
-      const uint64_t k = job.key[off + u];
-      const int32_t light_end = wave_first_above(row, 0, a1, delta - (uint32_t)(k >> 32));
-      const int32_t from = (mode != 1 && resume) ? resume_at_wave(job, off, u, k, row, light_end) : 0;
+      const uint64_t k = r.key[u];
+      const int32_t light_end = wave_first_above(row, 0, deg, r.delta - (uint32_t)(k >> 32));
+      const int32_t from = r.resume ? resume_at_wave(r, u, k, row, light_end) : 0;
       if (threadIdx.x == 0) {
-        S.row_key = k;
-        S.row_lo = light_end;
-        S.row_start = from;
+        r.S.row_key = k;
+        r.S.row_lo = light_end;
+        r.S.row_start = from;
       }
     }
     __syncthreads();
-    const uint64_t ku = S.row_key;
-    const uint32_t lim = delta - (uint32_t)(ku >> 32);
-    const int32_t lo = S.row_lo;   // first index with w > lim
-    if (mode != 1) {
-      const int32_t start = S.row_start;
-      for (int32_t a = start + (int32_t)threadIdx.x; a < lo; a += (int32_t)blockDim.x) {
-        ++scanned;
-        if (mode == 2) relax_one_sync(job, off, ku, row[a], it, S, out);
-        else relax_one(job, off, ku, row[a], it, S, out, lq_cnt, lq, d.lq_cap);
+    const uint64_t ku = r.S.row_key;
+    const uint32_t lim = r.delta - (uint32_t)(ku >> 32);
+    const int32_t lo = r.S.row_lo;
+    for (int32_t base = r.S.row_start; base < lo; base += kSweepThreads * kArcBatch) {
+      uint64_t arc[kArcBatch];
+      bool in[kArcBatch], blocked = false;
+#pragma unroll
+      for (int i = 0; i < kArcBatch; ++i) {
+        const int32_t a = base + kSweepThreads * i + tid;
+        in[i] = a < lo;
+        arc[i] = in[i] ? row[a] : ~0ull;
       }
-      if (threadIdx.x == 0 && lo < a1) mark_blocked(job, off, u, level_id, a1 - lo, S, out);
-      // keep LDS staging within bounds between rows
-      __syncthreads();
-      // every thread's part of the row is done: record the scan
-      if (resume && threadIdx.x == 0) note_scan(job, off, u, ku, lim);
-      if (threadIdx.x < 3 && S.cnt[threadIdx.x] > kStageCap - kSweepThreads) S.flush = 1;
-      __syncthreads();
-      if (S.flush) stage_flush(S, out, 3);
-    } else {
-      for (int32_t base = lo; base < a1; base += (int32_t)blockDim.x) {
-        if (threadIdx.x == 0) { S.blk_min = CLD_INF64; S.blk_hit = 0; }
-        __syncthreads();
-        const int32_t a = base + (int32_t)threadIdx.x;
-        if (a < a1) {
-          const uint64_t arc = row[a];
-          if (job.key[off + (int32_t)(uint32_t)arc] == CLD_INF64) {
-            const uint64_t c = (uint64_t)(uint32_t)(ku >> 32) + (uint32_t)(arc >> 32);
-            atomicMin(&S.blk_min, (unsigned long long)c);
-            S.blk_hit = 1;
-          }
-        }
-        __syncthreads();
-        const bool found = S.blk_hit != 0;
-        if (found && threadIdx.x == 0 && S.blk_min < S.acc) atomicMin(&S.acc, S.blk_min);
-        __syncthreads();
-        if (found) break;
+      r.scanned += offer<kSync, kArcBatch>(r, q, ku, lim, in, arc, &blocked);
+    }
+    if (threadIdx.x == 0 && lo < deg) mark_blocked(r, u, marks_of(r, u), deg - lo);
+    __syncthreads();
+    // every thread's part of the row is done: record the scan
+    if (r.resume && threadIdx.x == 0) note_scan(r, u, ku, lim);
+  };
+  coop_rows(r, mid, big);
+}
+
+// NEXT: u keeps its place on the frontier (unless the steps are synchronous,
+// whose blocked set stays whole) and its reach counts.
+__device__ __forceinline__ void next_hit(Run &r, int32_t u, uint64_t reach) {
+  if (reach < r.acc) r.acc = reach;
+  if (r.d.variant != CLDIAM_VARIANT_STEPS) set_bit(r.cur, u);
+}
+
+__device__ __forceinline__ void next_long(Run &r) {
+  const int32_t lane = (int32_t)(threadIdx.x & 63);
+  auto mid = [&](int32_t u, const uint64_t *row, int32_t deg) {
+    const uint32_t du = (uint32_t)(r.key[u] >> 32), lim = r.delta - du;
+    // the heavy arcs start after the light prefix
+    for (int32_t base = wave_first_above(row, 0, deg, lim); base < deg; base += 64) {
+      const int32_t a = base + lane;
+      const uint64_t arc = a < deg ? row[a] : 0ull;
+      const bool hit = a < deg && (uint32_t)(arc >> 32) > lim && r.key[(int32_t)(uint32_t)arc] == CLD_INF64;
+      const unsigned long long m = __ballot(hit);
+      if (m) {
+        // first hit in ascending order has the smallest weight
+        if (lane == __ffsll((long long)m) - 1) next_hit(r, u, (uint64_t)du + (arc >> 32));
+        break;
       }
     }
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) { S.mid_cnt = 0; S.big_cnt = 0; }
-  __syncthreads();
-  return scanned;
+  };
+  auto big = [&](int32_t u, const uint64_t *row, int32_t deg) {
+    Stage &S = r.S;
+    const uint32_t du = (uint32_t)(r.key[u] >> 32);
+    if (threadIdx.x < 64) {
+      const int32_t lo = wave_first_above(row, 0, deg, r.delta - du);
+      if (threadIdx.x == 0) { S.row_lo = lo; S.blk_min = CLD_INF64; }
+    }
+    __syncthreads();
+    for (int32_t base = S.row_lo; base < deg; base += kSweepThreads) {
+      const int32_t a = base + (int32_t)threadIdx.x;
+      if (a < deg) {
+        const uint64_t arc = row[a];
+        if (r.key[(int32_t)(uint32_t)arc] == CLD_INF64)
+          atomicMin(&S.blk_min, (unsigned long long)((uint64_t)du + (arc >> 32)));
+      }
+      __syncthreads();
+      const bool found = S.blk_min != CLD_INF64;
+      __syncthreads();
+      if (found) break;
+    }
+    if (threadIdx.x == 0 && S.blk_min != CLD_INF64) next_hit(r, u, S.blk_min);
+  };
+  coop_rows(r, mid, big);
 }
 
 // Pull mode.  Offers over arcs that were heavy at the previous Delta, or
@@ -1157,8 +1107,8 @@ __device__ uint32_t coop_rows(const Job &job, const GDesc &d, int64_t off, uint3
 // instead: PULL gives an unreached node v the lexicographic minimum over its
 // neighbours u with a key of (d_u + w, c_u), d_u + w <= Delta (only v's own
 // thread writes v's key, so no atomic is needed); NEXT_PULL folds the smallest
-// d_u + w over the same arcs into S.acc.  Rows are sorted by weight, so both
-// stop early (pull_more).
+// d_u + w over the same arcs.  Rows are sorted by weight, so both stop early
+// (pull_more).
 // A key read while its node is being pulled in the same pass is a real path
 // too, so taking it only moves the fixpoint closer.
 
@@ -1171,34 +1121,30 @@ __device__ __forceinline__ bool pull_more(uint64_t w, uint64_t best, uint32_t de
 }
 
 // Value of one arc (pull) or distance (next) offered to an unreached node.
-__device__ __forceinline__ uint64_t pull_offer(const Job &job, int64_t off, uint64_t arc, uint32_t delta, bool next) {
-  const uint64_t k = job.key[off + (int32_t)(uint32_t)arc];
+__device__ __forceinline__ uint64_t pull_offer(const Run &r, uint64_t arc, bool next) {
+  const uint64_t k = r.key[(int32_t)(uint32_t)arc];
   if (k == CLD_INF64) return CLD_INF64;
   const uint64_t du = k >> 32, w = arc >> 32;
   if (next) return du + w;
-  return du + w <= delta ? k + (w << 32) : CLD_INF64;
+  return du + w <= r.delta ? k + (w << 32) : CLD_INF64;
 }
 
-__device__ __forceinline__ void pull_apply(const Job &job, int64_t off, int32_t v, uint64_t best, bool next, Stage &S,
-                                           const Out *out) {
+__device__ __forceinline__ void pull_apply(Run &r, int32_t v, uint64_t best, bool next) {
   if (next) {
-    if (best < S.acc) atomicMin(&S.acc, (unsigned long long)best);
+    if (best < r.acc) r.acc = best;
   } else if (best != CLD_INF64) {
-    job.key[off + v] = best;
-    stage_push(S, out, 0, v);
-    stage_push(S, out, 1, v);
+    r.key[v] = best;
+    set_bit(r.cur, v);
   }
 }
 
-// One node of the uncovered list, its row scanned by this thread (long rows
-// are deferred to a wave or to the workgroup).
-__device__ __forceinline__ void pull_item(const Job &job, const GDesc &d, int64_t off, uint32_t delta, int32_t v,
-                                          bool next, Stage &S, const Out *out) {
-  if (job.key[off + v] != CLD_INF64) return;
-  const int64_t a0 = d.row_ptr[v];
-  const int32_t deg = (int32_t)(d.row_ptr[v + 1] - a0);
-  if (deg > d.mid_deg && defer_row(S, v, deg, d.big_deg)) return;
-  const uint64_t *row = d.arcs + a0;
+// One uncovered node, its row scanned by this thread (long rows are deferred).
+__device__ __forceinline__ void pull_item(Run &r, int32_t v, bool next) {
+  if (r.key[v] != CLD_INF64) return;
+  const int64_t a0 = r.d.row_ptr[v];
+  const int32_t deg = (int32_t)(r.d.row_ptr[v + 1] - a0);
+  if (deg > r.d.mid_deg && defer_row(r, v, deg)) return;
+  const uint64_t *row = r.d.arcs + a0;
   uint64_t best = CLD_INF64;
   for (int32_t base = 0; base < deg; base += kArcBatch) {
     uint64_t arc[kArcBatch];
@@ -1209,17 +1155,17 @@ __device__ __forceinline__ void pull_item(const Job &job, const GDesc &d, int64_
 #pragma unroll
     for (int j = 0; j < kArcBatch; ++j) {
       const uint64_t w = arc[j] >> 32;
-      ok[j] = base + j < deg && pull_more(w, best, delta, next);
+      ok[j] = base + j < deg && pull_more(w, best, r.delta, next);
       if (base + j < deg && !ok[j]) stop = true;
     }
     uint64_t c[kArcBatch];
 #pragma unroll
-    for (int j = 0; j < kArcBatch; ++j) c[j] = ok[j] ? pull_offer(job, off, arc[j], delta, next) : CLD_INF64;
+    for (int j = 0; j < kArcBatch; ++j) c[j] = ok[j] ? pull_offer(r, arc[j], next) : CLD_INF64;
 #pragma unroll
     for (int j = 0; j < kArcBatch; ++j) best = c[j] < best ? c[j] : best;
     if (stop) break;
   }
-  pull_apply(job, off, v, best, next, S, out);
+  pull_apply(r, v, best, next);
 }
 
 __device__ __forceinline__ uint64_t wave_min_all(uint64_t x) {
@@ -1232,366 +1178,433 @@ __device__ __forceinline__ uint64_t wave_min_all(uint64_t x) {
 
 // The long rows deferred by pull_item: a wave per row, then the whole
 // workgroup per hub row.
-__device__ void pull_rows(const Job &job, const GDesc &d, int64_t off, uint32_t delta, bool next, Stage &S,
-                          const Out *out) {
-  __syncthreads();
-  const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nwaves = blockDim.x >> 6;
-  const uint32_t nm = S.mid_cnt < kMidCap ? S.mid_cnt : kMidCap;
-  const uint32_t nb = S.big_cnt < kBigCap ? S.big_cnt : kBigCap;
-  for (uint32_t r = wave; r < nm; r += nwaves) {
-    const int32_t v = S.mid[r];
-    const int64_t a0 = d.row_ptr[v];
-    const int32_t a1 = (int32_t)(d.row_ptr[v + 1] - a0);
-    const uint64_t *row = d.arcs + a0;
+__device__ __forceinline__ void pull_long(Run &r, bool next) {
+  const int32_t lane = (int32_t)(threadIdx.x & 63);
+  auto mid = [&](int32_t v, const uint64_t *row, int32_t deg) {
     uint64_t best = CLD_INF64;
-    for (int32_t base = 0; base < a1; base += 64) {
-      const int32_t a = base + (int32_t)lane;
-      const uint64_t arc = a < a1 ? row[a] : ~0ull;
-      const uint64_t w = arc >> 32;
-      const bool in = a < a1 && pull_more(w, best, delta, next);
+    for (int32_t base = 0; base < deg; base += 64) {
+      const int32_t a = base + lane;
+      const uint64_t arc = a < deg ? row[a] : ~0ull;
+      const bool in = a < deg && pull_more(arc >> 32, best, r.delta, next);
       if (!__any(in)) break;
-      const uint64_t m = wave_min_all(in ? pull_offer(job, off, arc, delta, next) : CLD_INF64);
+      const uint64_t m = wave_min_all(in ? pull_offer(r, arc, next) : CLD_INF64);
       best = m < best ? m : best;
     }
-    if (lane == 0) pull_apply(job, off, v, best, next, S, out);
-  }
-  for (uint32_t h = 0; h < nb; ++h) {
-    const int32_t v = S.big[h];
-    const int64_t a0 = d.row_ptr[v];
-    const int32_t a1 = (int32_t)(d.row_ptr[v + 1] - a0);
-    const uint64_t *row = d.arcs + a0;
+    if (lane == 0) pull_apply(r, v, best, next);
+  };
+  auto big = [&](int32_t v, const uint64_t *row, int32_t deg) {
+    Stage &S = r.S;
     if (threadIdx.x == 0) S.blk_min = CLD_INF64;
     __syncthreads();
-    for (int32_t base = 0; base < a1; base += (int32_t)blockDim.x) {
+    for (int32_t base = 0; base < deg; base += kSweepThreads) {
       const uint64_t cur = S.blk_min;   // the same for every thread: nothing changes it between the barriers
       const int32_t a = base + (int32_t)threadIdx.x;
-      if (a < a1) {
+      __syncthreads();
+      if (a < deg) {
         const uint64_t arc = row[a];
-        const uint64_t w = arc >> 32;
-        if (pull_more(w, cur, delta, next)) {
-          const uint64_t c = pull_offer(job, off, arc, delta, next);
+        if (pull_more(arc >> 32, cur, r.delta, next)) {
+          const uint64_t c = pull_offer(r, arc, next);
           if (c < cur) atomicMin(&S.blk_min, (unsigned long long)c);
         }
       }
       __syncthreads();
-      const int32_t nxt = base + (int32_t)blockDim.x;
-      const uint64_t cur2 = S.blk_min;
-      const bool stop = nxt >= a1 || !pull_more(row[nxt] >> 32, cur2, delta, next);
-      __syncthreads();   // every thread has read S.blk_min before the next chunk changes it
+      const int32_t nxt = base + kSweepThreads;
+      const bool stop = nxt >= deg || !pull_more(row[nxt] >> 32, S.blk_min, r.delta, next);
       if (stop) break;
     }
-    if (threadIdx.x == 0) pull_apply(job, off, v, S.blk_min, next, S, out);
-    __syncthreads();
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) { S.mid_cnt = 0; S.big_cnt = 0; }
-  __syncthreads();
+    if (threadIdx.x == 0) pull_apply(r, v, S.blk_min, next);
+  };
+  coop_rows(r, mid, big);
 }
 
 // CLUSTER2, Contract2: u was assigned last iteration at growth distance dl
 // (kept in keyn) with label c; every edge with Delta2 - dl < w <= Delta2 is
 // the rescaled edge (c, v) of weight dl + w - Delta2.  Rows are sorted by
 // weight, so those arcs are one contiguous range.
-__device__ uint32_t c2_boundary(const Job &job, const GDesc &d, int64_t off, uint32_t delta2, uint32_t it, int32_t u,
-                                Stage &S, const Out *out) {
-  const uint32_t dl = (uint32_t)job.keyn[off + u];
-  const uint64_t label = job.key[off + u] & 0xffffffffull;
-  const int64_t a0 = d.row_ptr[u];
-  const int32_t a1 = (int32_t)(d.row_ptr[u + 1] - a0);
-  const uint64_t *row = d.arcs + a0;
+__device__ __forceinline__ void c2_boundary(Run &r, int32_t u) {
+  const uint32_t delta2 = r.delta;
+  const uint32_t dl = (uint32_t)r.keyn[u];
+  const uint64_t label = r.key[u] & 0xffffffffull;
+  const int64_t a0 = r.d.row_ptr[u];
+  const int32_t a1 = (int32_t)(r.d.row_ptr[u + 1] - a0);
+  const uint64_t *row = r.d.arcs + a0;
   int32_t lo = 0, hi = a1;
   while (lo < hi) {   // first arc with w > delta2 - dl
     const int32_t mid = lo + ((hi - lo) >> 1);
     if ((uint32_t)(row[mid] >> 32) <= delta2 - dl) lo = mid + 1; else hi = mid;
   }
-  uint32_t scanned = 0;
   for (int32_t a = lo; a < a1; ++a) {
     const uint64_t arc = row[a];
     const uint32_t w = (uint32_t)(arc >> 32);
     if (w > delta2) break;
-    ++scanned;
+    ++r.scanned;
     const int32_t v = (int32_t)(uint32_t)arc;
-    const int64_t gv = off + v;
     const uint64_t cand = ((uint64_t)(dl + w - delta2) << 32) | label;
-    if (cand < job.key[gv]) {
-      const uint64_t old = atomicMin((unsigned long long *)&job.key[gv], (unsigned long long)cand);
-      if (atomicExch(&job.fstamp[gv], it) != it) stage_push(S, out, 0, v);
-      if (old == CLD_INF64) stage_push(S, out, 1, v);
+    if (cand < r.key[v]) {
+      atomicMin((unsigned long long *)&r.key[v], (unsigned long long)cand);
+      set_bit(r.cur, v);
     }
   }
-  return scanned;
 }
 
-// Items [a, b) of the index space, all of graph g.
-__device__ uint32_t process_run(const Job &job, int g, uint32_t a, uint32_t b, uint32_t it, Stage &S) {
-  const GDesc &d = job.desc[g];
-  const GState &s = job.st[g];
-  GCount &cn = job.cn[g];
-  const int64_t off = d.off;
-  const uint32_t phase = s.phase;
-  const uint32_t delta = s.delta, level_id = s.level_id, stage = s.stage, ucur = s.ucur, theta = s.theta;
-  const uint32_t row_lim = row_limit(d, delta, s.row_base);
-  const uint32_t theta_row = row_lim < theta ? row_lim : theta;
-  const uint32_t fcur = s.fcur, fnxt = s.fnxt, blk = s.blk;
-  const uint64_t T = s.T;
-  Out o[3] = {};
-  int nout = 0;
-  switch (phase) {
-    case PH_SELECT:
-      o[0] = {job.pool[fcur] + off, &cn.cnt[fcur].v};
-      o[1] = {job.C + off, &cn.cntC.v};
-      nout = 2;
-      break;
-    case PH_RELAX:
-      o[0] = {job.pool[fnxt] + off, &cn.cnt[fnxt].v};
-      o[1] = {job.C + off, &cn.cntC.v};
-      o[2] = {job.pool[blk] + off, &cn.cnt[blk].v};
-      nout = 3;
-      break;
-    case PH_COMPACT:
-      o[0] = {job.U[ucur ^ 1] + off, &cn.cntU[ucur ^ 1].v};
-      nout = 1;
-      break;
-    case PH_MERGE:
-      o[0] = {job.pool[fcur] + off, &cn.cnt[fcur].v};
-      nout = 1;
-      break;
-    case PH_PULL:
-    case PH_C2_SELECT:
-    case PH_C2_BOUNDARY:
-      o[0] = {job.pool[fcur] + off, &cn.cnt[fcur].v};
-      o[1] = {job.C + off, &cn.cntC.v};
-      nout = 2;
-      break;
-    default:
-      break;
+// Walks the nodes of a set in words [lo, hi), kSweepThreads nodes per pass in
+// ascending order.  word(w) gives word w (and may clear it: it is called once
+// per word, by the workgroup that owns it); item(v) handles a node and end()
+// the pass's end (every thread, with a barrier inside).  Dense words are
+// spread by their wave together, sparse ones each by its own thread.
+template <class Word, class Item, class End>
+__device__ __forceinline__ void list_pass(Run &r, uint32_t lo, uint32_t hi, Word word, Item item, End end) {
+  Stage &S = r.S;
+  const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  uint64_t ahead = lo + tid < hi ? word(lo + tid) : 0ull;
+  for (uint32_t w0 = lo; w0 < hi; w0 += kSweepThreads) {
+    const uint64_t mine = ahead;
+    const uint32_t w = w0 + tid;
+    ahead = w + kSweepThreads < hi ? word(w + kSweepThreads) : 0ull;
+    const uint32_t count = (uint32_t)__popcll(mine);
+    uint32_t incl = count;
+    for (int o = 1; o < 64; o <<= 1) {
+      const uint32_t y = __shfl_up(incl, o);
+      if (lane >= (uint32_t)o) incl += y;
+    }
+    __syncthreads();
+    if (lane == 63) S.wsum[wave] = incl;
+    __syncthreads();
+    uint32_t at = incl - count, total = 0;
+    for (uint32_t k = 0; k < (uint32_t)kWaves; ++k) {
+      if (k < wave) at += S.wsum[k];
+      total += S.wsum[k];
+    }
+    const bool dense = __any(count > 8);
+    for (uint32_t r0 = 0; r0 < total; r0 += kList) {
+      if (dense) {
+        for (uint64_t left = __ballot(count != 0 && at + count > r0 && at < r0 + kList); left; left &= left - 1) {
+          const int k = __ffsll((long long)left) - 1;
+          const uint64_t x = __shfl(mine, k);
+          const uint32_t p = __shfl(at, k) + (uint32_t)__popcll(x & ((1ull << lane) - 1ull)) - r0;
+          if ((x >> lane & 1) && p < kList) S.list[p] = (int32_t)(((w0 + wave * 64 + k) << 6) + lane);
+        }
+      } else {
+        uint32_t p = at - r0;
+        for (uint64_t x = mine; x; x &= x - 1, ++p)
+          if (p < kList) S.list[p] = (int32_t)((w << 6) + (uint32_t)__ffsll((long long)x) - 1);
+      }
+      __syncthreads();
+      const uint32_t n = total - r0 < kList ? total - r0 : kList;
+      for (uint32_t i = tid; i - tid < n; i += kSweepThreads) {
+        if (i < n) item(S.list[i]);
+        end();
+      }
+      __syncthreads();
+    }
   }
+}
+
+// Walks the nodes of a set in words [lo, hi) wave by wave, kNodeWords words of
+// 64 nodes at a time: load(v) for every node (their loads overlap), then, word
+// by word, use(w, v, in, x) by the whole wave (in: v is in the set, x: its
+// load).  The wave owns the words.
+constexpr int kNodeWords = 8;
+
+template <class Load, class Use>
+__device__ __forceinline__ void node_pass(const uint64_t *bits, uint32_t lo, uint32_t hi, Load load, Use use) {
+  const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  for (uint32_t base = lo + wave * kNodeWords; base < hi; base += kWaves * kNodeWords) {
+    const uint64_t mine = lane < (uint32_t)kNodeWords && base + lane < hi ? bits[base + lane] : 0ull;
+    if (__ballot(mine != 0) == 0) continue;
+    uint64_t word[kNodeWords], x[kNodeWords];
+#pragma unroll
+    for (int j = 0; j < kNodeWords; ++j) {
+      word[j] = __shfl(mine, j);
+      const bool in = word[j] >> lane & 1;
+      x[j] = in ? load((int32_t)(((base + j) << 6) + lane)) : 0ull;
+    }
+#pragma unroll
+    for (int j = 0; j < kNodeWords; ++j)
+      if (word[j]) use(base + j, (int32_t)(((base + j) << 6) + lane), (bool)(word[j] >> lane & 1), x[j]);
+  }
+}
+
+// A covered node's D, for the workgroup's table of cluster maxima: a stage has
+// few clusters, so fold in LDS first (the slot of c, once claimed by c), in
+// global memory when another center holds the slot.
+__device__ __forceinline__ void fold_rmax(Run &r, uint64_t *R, uint32_t c, uint64_t Dv) {
+  Stage &S = r.S;
+  const uint32_t slot = (c * 2654435761u) >> 22;   // 10 bits: kRmaxSlots
+  uint32_t t = S.rmax.tag[slot];
+  if (t == kRmaxFree) {
+    t = atomicCAS(&S.rmax.tag[slot], kRmaxFree, c);
+    if (t == kRmaxFree) t = c;
+  }
+  if (t == c) {
+    if (Dv > S.rmax.mx[slot]) atomicMax(&S.rmax.mx[slot], (unsigned long long)Dv);
+  } else if (Dv > R[c]) {
+    atomicMax((unsigned long long *)&R[c], (unsigned long long)Dv);
+  }
+}
+
+// Bitmap words [lo, hi) of graph g.
+__device__ __forceinline__ void process_run(const Job &job, const GDesc &d, const GState &s, GCount &cn, uint32_t *idle, uint32_t lo,
+                            uint32_t hi, Stage &S) {
+  const uint32_t phase = s.phase, stage = s.stage, lane = threadIdx.x & 63;
+  const uint32_t woff = (uint32_t)(d.off >> 6);
   const bool steps = d.variant == CLDIAM_VARIANT_STEPS;
-  const bool resume = !steps && !s.c2;   // long rows resume their last scan (keyn/slim hold scan records)
+  uint64_t *U = job.U + woff, *R = job.R + d.off;
+  uint64_t *blk = job.F[s.blk] + woff, *alt = job.F[s.alt] + woff;
+  const uint32_t row_lim = row_limit(d, s.delta, s.row_base);
+  Run r{job, d, s, S, job.key + d.off, job.keyn + d.off, job.slim + d.off, job.F[s.cur] + woff, job.F[s.nxt] + woff,
+        s.pull ? nullptr : (s.merge ? alt : blk), s.delta, s.theta, row_lim < s.theta ? row_lim : s.theta,
+        !steps && !s.c2};
   if (threadIdx.x == 0) {
-    S.out[0] = o[0];
-    S.out[1] = o[1];
-    S.out[2] = o[2];
-    S.acc = (phase == PH_NEXT || phase == PH_NEXT_PULL) ? CLD_INF64 : 0ull;
-    S.blk_arcs = 0;
-    S.acc32 = 0;
-    S.fmin = 0xffffffffu;
-    S.lq_cnt[0] = 0;
-    S.lq_cnt[1] = 0;
-    S.mid_cnt = 0;
-    S.big_cnt = 0;
+    clear_count(S.sum);
+    S.qn[0] = S.qn[1] = 0;
+    S.mid_cnt[0] = S.mid_cnt[1] = S.big_cnt[0] = S.big_cnt[1] = 0;
+    S.stop = 0;
   }
-  if (phase == PH_RMAX) {
-    for (uint32_t t = threadIdx.x; t < kRmaxSlots; t += blockDim.x) {
+  const bool table = phase == PH_RMAX || (phase == PH_ASSIGN && stage == 0);
+  if (table) {
+    for (uint32_t t = threadIdx.x; t < kRmaxSlots; t += kSweepThreads) {
       S.rmax.tag[t] = kRmaxFree;
       S.rmax.mx[t] = 0;
     }
   }
   __syncthreads();
-  const Out *out = S.out;
-  uint32_t scanned = 0;
-  for (uint32_t r = a; r < b; r += blockDim.x) {
-    const uint32_t i = r + threadIdx.x;
-    if (i < b) {
-      const uint32_t idx = i;
-      switch (phase) {
-        case PH_SELECT: {
-          const int32_t v = job.U[ucur][off + idx];
-          if (stage == 0 && d.pull_mode == CLDIAM_PULL_AUTO) {
-            const uint32_t deg = (uint32_t)(d.row_ptr[v + 1] - d.row_ptr[v]);
-            if (deg > d.hub_deg) atomicAdd(&S.acc, (unsigned long long)deg);
+  uint32_t cov = 0;   // per wave: nodes counted
+  const auto no_load = [](int32_t) { return 0ull; };
+  const auto key_of = [&](int32_t v) { return r.key[v]; };
+  const auto no_end = [] {};
+  switch (phase) {
+    case PH_SELECT:
+    case PH_C2_SELECT: {
+      const bool c2 = phase == PH_C2_SELECT;
+      if (s.pull && stage > 0) {   // pull mode has no pushing sources
+        for (uint32_t w = lo + threadIdx.x; w < hi; w += kSweepThreads)
+          if (r.cur[w]) r.cur[w] = 0;
+        __syncthreads();
+      }
+      const bool hubs = !c2 && stage == 0 && d.pull_mode == CLDIAM_PULL_AUTO;
+      node_pass(U, lo, hi,
+                [&](int32_t v) { return hubs ? (uint64_t)(d.row_ptr[v + 1] - d.row_ptr[v]) : 0ull; },
+                [&](uint32_t w, int32_t v, bool in, uint64_t deg) {
+        if (deg > d.hub_deg) r.acc += deg;
+        const uint32_t x0 = cld_philox_word0((uint32_t)v, c2 ? stage + 1 : stage, 0u, c2 ? 1u : 0u, (uint32_t)d.seed,
+                                             (uint32_t)(d.seed >> 32));
+        const bool sel = in && (uint64_t)x0 < s.T;
+        if (sel) {
+          r.key[v] = (uint64_t)(uint32_t)v;
+          R[v] = c2 ? stage + 1 : 0;
+          if (steps) r.keyn[v] = (uint64_t)(uint32_t)v;
+        }
+        const uint64_t m = __ballot(sel);
+        if (m && lane == 0) atomicOr((unsigned long long *)&r.cur[w], (unsigned long long)m);
+        cov += (uint32_t)__popcll(m);
+      });
+      if (c2)
+        list_pass(r, lo, hi,
+                  [&](uint32_t w) { const uint64_t x = blk[w]; if (x) blk[w] = 0; return x; },
+                  [&](int32_t u) { c2_boundary(r, u); }, no_end);
+      break;
+    }
+    case PH_RELAX:
+      if (steps) {
+        const bool merge = s.merge != 0;
+        list_pass(r, lo, hi,
+                  [&](uint32_t w) {
+                    uint64_t x = r.cur[w];
+                    if (x) r.cur[w] = 0;
+                    if (merge) {
+                      const uint64_t y = blk[w];
+                      if (y) blk[w] = 0;
+                      x |= y;
+                    }
+                    return x;
+                  },
+                  [&](int32_t u) { relax_item<true>(r, u); }, [&] { relax_long<true>(r, 0); });
+      } else {
+        list_pass(r, lo, hi, [&](uint32_t w) { const uint64_t x = r.cur[w]; if (x) r.cur[w] = 0; return x; },
+                  [&](int32_t u) { relax_item<false>(r, u); }, [&] { relax_long<false>(r, 0); });
+      }
+      break;
+    case PH_COMMIT: {
+      uint32_t upd = 0;
+      node_pass(r.nxt, lo, hi, key_of, [&](uint32_t, int32_t v, bool in, uint64_t old) {
+        if (in) r.key[v] = r.keyn[v];
+        upd += (uint32_t)__popcll(__ballot(in));
+        cov += (uint32_t)__popcll(__ballot(in && old == CLD_INF64));
+      });
+      if (lane == 0 && upd) atomicAdd(&S.sum.upd, upd);
+      break;
+    }
+    case PH_COUNT:
+      node_pass(U, lo, hi, key_of, [&](uint32_t, int32_t, bool in, uint64_t k) {
+        cov += (uint32_t)__popcll(__ballot(in && k != CLD_INF64));
+      });
+      break;
+    case PH_NEXT:
+      r.acc = CLD_INF64;
+      if (!steps)
+        node_pass(U, lo, hi, key_of, [&](uint32_t, int32_t, bool in, uint64_t k) {
+          cov += (uint32_t)__popcll(__ballot(in && k != CLD_INF64));
+        });
+      list_pass(r, lo, hi,
+                [&](uint32_t w) { const uint64_t x = blk[w]; if (x && !steps) blk[w] = 0; return x; },
+                [&](int32_t u) {
+                  const uint64_t ku = r.key[u];
+                  const int64_t a0 = d.row_ptr[u];
+                  const int32_t deg = (int32_t)(d.row_ptr[u + 1] - a0);
+                  if (deg > d.mid_deg && defer_row(r, u, deg)) return;
+                  const uint64_t reach = next_small(r, ku, a0, deg);
+                  if (reach != CLD_INF64) next_hit(r, u, reach);
+                },
+                [&] { next_long(r); });
+      break;
+    case PH_PULL:
+    case PH_NEXT_PULL: {
+      const bool next = phase == PH_NEXT_PULL;
+      if (next) r.acc = CLD_INF64;
+      for (uint32_t w = lo + threadIdx.x; w < hi; w += kSweepThreads)
+        if (blk[w]) blk[w] = 0;   // left from before the switch to pull mode
+      list_pass(r, lo, hi, [&](uint32_t w) { return U[w]; }, [&](int32_t v) { pull_item(r, v, next); },
+                [&] { pull_long(r, next); });
+      break;
+    }
+    case PH_ASSIGN:
+      // D = growth distance + the cluster's radius before this stage (0 in the
+      // first, whose pass therefore folds the new radii and takes the covered
+      // nodes off the uncovered set as well)
+      node_pass(U, lo, hi, key_of, [&](uint32_t w, int32_t v, bool in, uint64_t k) {
+        const bool got = in && k != CLD_INF64;
+        if (got) {
+          const uint32_t c = (uint32_t)k;
+          const uint64_t Dv = (k >> 32) + (stage > 0 ? R[c] : 0ull);
+          d.cluster[v] = (int32_t)c;
+          d.D[v] = Dv;
+          if (Dv > r.acc) r.acc = Dv;
+          if (stage == 0) {
+            fold_rmax(r, R, c, Dv);
+            r.key[v] = (uint64_t)c;
+            if (s.records || steps) r.keyn[v] = (uint64_t)c;
           }
-          const uint32_t x0 = cld_philox_word0((uint32_t)v, stage, 0u, 0u, (uint32_t)d.seed, (uint32_t)(d.seed >> 32));
-          if ((uint64_t)x0 < T) {
-            job.key[off + v] = (uint64_t)(uint32_t)v;
-            if (steps) job.keyn[off + v] = (uint64_t)(uint32_t)v;
-            stage_push(S, out, 0, v);
-            stage_push(S, out, 1, v);
-            atomicAdd(&S.acc32, 1u);
-          }
-          break;
         }
-        case PH_RELAX:
-          if (steps)
-            scanned += relax_sync(job, d, off, delta, it, level_id, job.pool[fcur][off + idx], S, out);
-          else
-            scanned += relax_item(job, d, off, delta, theta, theta_row, it, level_id, job.pool[fcur][off + idx], S,
-                                  out, &S.lq_cnt[0], S.lq[0]);
-          break;
-        case PH_COMMIT: {
-          const int32_t v = job.pool[fnxt][off + idx];
-          job.key[off + v] = job.keyn[off + v];
-          break;
+        if (stage == 0) {
+          const uint64_t m = __ballot(got);
+          if (m && lane == 0) U[w] &= ~m;
         }
-        case PH_MERGE: {
-          const int32_t u = job.pool[blk][off + idx];
-          if (atomicExch(&job.fstamp[off + u], s.fid) != s.fid) stage_push(S, out, 0, u);
-          break;
+      });
+      break;
+    case PH_RMAX:
+      node_pass(U, lo, hi, key_of, [&](uint32_t w, int32_t v, bool in, uint64_t k) {
+        const bool got = in && k != CLD_INF64;
+        if (got) {
+          const uint32_t c = (uint32_t)k;
+          fold_rmax(r, R, c, d.D[v]);
+          r.key[v] = (uint64_t)c;
+          if (s.records || steps) r.keyn[v] = (uint64_t)c;
         }
-        case PH_C2_INIT:
-          job.key[off + idx] = CLD_INF64;
-          job.U[0][off + idx] = (int32_t)idx;
-          break;
-        case PH_C2_SELECT: {
-          const int32_t v = job.U[ucur][off + idx];
-          const uint32_t x0 =
-              cld_philox_word0((uint32_t)v, stage + 1, 0u, 1u, (uint32_t)d.seed, (uint32_t)(d.seed >> 32));
-          if ((uint64_t)x0 < T) {
-            job.key[off + v] = (uint64_t)(uint32_t)v;
-            job.R[off + v] = stage + 1;   // birth iteration of the center
-            stage_push(S, out, 0, v);
-            stage_push(S, out, 1, v);
-            atomicAdd(&S.acc32, 1u);
-          }
-          break;
-        }
-        case PH_C2_BOUNDARY:
-          scanned += c2_boundary(job, d, off, delta, it, job.pool[blk][off + idx], S, out);
-          break;
-        case PH_C2_ASSIGN: {
-          const int32_t v = job.U[ucur][off + idx];
-          const uint64_t k = job.key[off + v];
-          if (k == CLD_INF64) break;
+        const uint64_t m = __ballot(got);
+        if (m && lane == 0) U[w] &= ~m;
+      });
+      break;
+    case PH_SINGLE:
+      node_pass(U, lo, hi, no_load, [&](uint32_t, int32_t v, bool in, uint64_t) {
+        if (!in) return;
+        d.cluster[v] = v;
+        d.D[v] = 0;
+      });
+      break;
+    case PH_C2_INIT:
+      for (uint32_t w = lo + threadIdx.x; w < hi; w += kSweepThreads) {
+        const int64_t left = (int64_t)d.n - ((int64_t)w << 6);
+        U[w] = left >= 64 ? ~0ull : (1ull << left) - 1ull;
+        for (int i = 0; i < 4; ++i) job.F[i][woff + w] = 0;
+      }
+      for (int64_t v = ((int64_t)lo << 6) + threadIdx.x; v < ((int64_t)hi << 6) && v < d.n; v += kSweepThreads)
+        r.key[v] = CLD_INF64;
+      break;
+    case PH_C2_ASSIGN:
+      node_pass(U, lo, hi, key_of, [&](uint32_t w, int32_t v, bool in, uint64_t k) {
+        const bool got = in && k != CLD_INF64;
+        if (got) {
           const uint32_t c = (uint32_t)k;
           const uint64_t local = k >> 32;
-          const uint64_t Dv = local + (uint64_t)delta * (uint64_t)(stage + 1 - job.R[off + c]);
+          const uint64_t Dv = local + (uint64_t)r.delta * (uint64_t)(stage + 1 - R[c]);
           d.cluster[v] = (int32_t)c;
           d.D[v] = Dv;
-          job.keyn[off + v] = local;   // kept for next iteration's rescaled edges
-          job.key[off + v] = (uint64_t)c;
-          if (Dv > S.acc) atomicMax(&S.acc, (unsigned long long)Dv);
-          break;
+          r.keyn[v] = local;   // kept for next iteration's rescaled edges
+          r.key[v] = (uint64_t)c;
+          if (Dv > r.acc) r.acc = Dv;
         }
-        case PH_NEXT: {
-          const int32_t u = job.pool[blk][off + idx];
-          const int32_t deg = (int32_t)(d.row_ptr[u + 1] - d.row_ptr[u]);
-          if (deg > d.mid_deg && defer_row(S, u, deg, d.big_deg)) break;
-          const uint64_t best = next_small(job, d, off, delta, u);
-          if (best < S.acc) atomicMin(&S.acc, (unsigned long long)best);
-          break;
-        }
-        case PH_PULL:
-        case PH_NEXT_PULL:
-          pull_item(job, d, off, delta, job.U[ucur][off + idx], phase == PH_NEXT_PULL, S, out);
-          break;
-        case PH_ASSIGN: {
-          // over the stage's uncovered list (in node order at the first
-          // stage, so these reads and writes are coalesced); covered nodes
-          // are the ones with a finite key
-          const int32_t v = job.U[ucur][off + idx];
-          const uint64_t k = job.key[off + v];
-          if (k == CLD_INF64) break;
-          const uint32_t c = (uint32_t)k;
-          const uint64_t Dv = (k >> 32) + job.R[off + c];
-          d.cluster[v] = (int32_t)c;
-          d.D[v] = Dv;
-          if (Dv > S.acc) atomicMax(&S.acc, (unsigned long long)Dv);
-          break;
-        }
-        case PH_RMAX: {
-          const int32_t v = job.U[ucur][off + idx];
-          const uint64_t k = job.key[off + v];
-          if (k == CLD_INF64) break;
-          const uint32_t c = (uint32_t)k;
-          const uint64_t Dv = d.D[v];
-          // a stage has few clusters: fold the maxima in LDS first (the slot
-          // of c, once claimed by c), in global memory when another center
-          // holds the slot
-          const uint32_t slot = (c * 2654435761u) >> 22;   // 10 bits: kRmaxSlots
-          uint32_t t = S.rmax.tag[slot];
-          if (t == kRmaxFree) {
-            t = atomicCAS(&S.rmax.tag[slot], kRmaxFree, c);
-            if (t == kRmaxFree) t = c;
-          }
-          if (t == c) {
-            if (Dv > S.rmax.mx[slot]) atomicMax(&S.rmax.mx[slot], (unsigned long long)Dv);
-          } else {
-            uint64_t *rr = &job.R[off + c];
-            if (Dv > *rr) atomicMax((unsigned long long *)rr, (unsigned long long)Dv);
-          }
-          job.key[off + v] = (uint64_t)c;
-          job.keyn[off + v] = (uint64_t)c;
-          break;
-        }
-        case PH_COMPACT: {
-          const int32_t v = job.U[ucur][off + idx];
-          if (job.key[off + v] == CLD_INF64) stage_push(S, out, 0, v);
-          break;
-        }
-        case PH_SINGLE: {
-          const int32_t v = job.U[ucur][off + idx];
-          d.cluster[v] = v;
-          d.D[v] = 0;
-          break;
-        }
-        default:
-          break;
-      }
-    }
-    if (phase == PH_PULL || phase == PH_NEXT_PULL) pull_rows(job, d, off, delta, phase == PH_NEXT_PULL, S, out);
-    if (phase == PH_RELAX || phase == PH_NEXT)
-      scanned += coop_rows(job, d, off, delta, it, level_id, S, out, steps ? nullptr : &S.lq_cnt[0],
-                           steps ? nullptr : S.lq[0], phase == PH_NEXT ? 1 : (steps ? 2 : 0), resume);
-    if (nout) {
-      __syncthreads();
-      if (threadIdx.x < (unsigned)nout && S.cnt[threadIdx.x] > kStageCap - kSweepThreads) S.flush = 1;
-      __syncthreads();
-      if (S.flush) stage_flush(S, out, nout);
-    }
+        const uint64_t m = __ballot(got);
+        if (m && lane == 0) U[w] &= ~m;
+        cov += (uint32_t)__popcll(m);
+      });
+      break;
+    default:
+      break;
   }
-  if (phase == PH_RELAX && steps && scanned) atomicAdd(&S.acc, (unsigned long long)scanned);
   if (phase == PH_RELAX && !steps) {
-    // Local rounds: keep relaxing the neighbours this workgroup improved.
-    // Every improved node is also on the global next frontier, so these
-    // rounds only move the fixpoint closer; dropped overflow loses nothing.
+    // Local rounds: relax the nodes that this workgroup improved.  What is
+    // left when they end stays for the next sweep.
     int q = 0;
-    // a small frontier leaves the grid idle between sweeps: let each
-    // workgroup carry its part of the growth further before the next one
-    const uint32_t graph_items = job.seg[2 * job.G + 1 + g];
-    const int rounds = (d.local_rounds > 0 && graph_items <= kSmallFrontier && d.local_rounds < kSmallRounds)
-                           ? kSmallRounds : d.local_rounds;
-    for (int round = 0; round < rounds; ++round) {
-      if (threadIdx.x == 0)
+    uint32_t n = 0;
+    for (int round = 0;; ++round) {
+      __syncthreads();
+      n = S.qn[q] < d.lq_cap ? S.qn[q] : d.lq_cap;
+      if (n == 0 || S.stop || round >= d.local_rounds) break;
+      __syncthreads();
+      if (threadIdx.x == 0) {
+        S.qn[q ^ 1] = 0;
         S.stop = job.cutoff < (uint32_t)job.nblocks &&
-                 __hip_atomic_load(&job.ctl->idle.v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= job.cutoff;
+                 __hip_atomic_load(idle, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= job.cutoff;
+      }
       __syncthreads();
-      const uint32_t n = S.lq_cnt[q] < d.lq_cap ? S.lq_cnt[q] : d.lq_cap;
-      if (n == 0 || S.stop) break;
-      if (threadIdx.x == 0) S.lq_cnt[q ^ 1] = 0;
-      __syncthreads();
-      for (uint32_t t = threadIdx.x; t < n; t += blockDim.x)
-        scanned += relax_item(job, d, off, delta, theta, theta_row, it, level_id, S.lq[q][t], S, out,
-                              &S.lq_cnt[q ^ 1], S.lq[q ^ 1]);
-      scanned += coop_rows(job, d, off, delta, it, level_id, S, out, &S.lq_cnt[q ^ 1], S.lq[q ^ 1], 0, resume);
-      __syncthreads();
-      if (threadIdx.x < (unsigned)nout && S.cnt[threadIdx.x] > kStageCap - kSweepThreads) S.flush = 1;
-      __syncthreads();
-      if (S.flush) stage_flush(S, out, nout);
+      for (uint32_t i = threadIdx.x; i - threadIdx.x < n; i += kSweepThreads) {
+        if (i < n) relax_queued(r, q ^ 1, S.qv[q][i], S.qk[q][i]);
+        relax_long<false>(r, q ^ 1);
+      }
       q ^= 1;
     }
+    for (uint32_t i = threadIdx.x; i < n; i += kSweepThreads) leave(r, S.qv[q][i], (uint32_t)(S.qk[q][i] >> 32));
   }
-  if (nout) stage_flush(S, out, nout);
+  // fold the threads' and waves' sums
+  const bool is_min = phase == PH_NEXT || phase == PH_NEXT_PULL;
+  for (int o = 32; o >= 1; o >>= 1) {
+    r.scanned += __shfl_xor(r.scanned, o);
+    r.heavy += __shfl_xor(r.heavy, o);
+    const unsigned long long y = __shfl_xor(r.acc, o);
+    r.acc = is_min ? (y < r.acc ? y : r.acc) : (phase == PH_SELECT ? r.acc + y : (y > r.acc ? y : r.acc));
+  }
+  if (lane == 0) {
+    if (r.scanned) atomicAdd(&S.sum.arcs, (unsigned long long)r.scanned);
+    if (r.heavy) atomicAdd(&S.sum.blk_arcs, (unsigned long long)r.heavy);
+    if (cov) atomicAdd(&S.sum.cov, cov);
+    if (is_min) atomicMin(&S.sum.next, r.acc);
+    else if (phase == PH_SELECT) atomicAdd(&S.sum.hub_arcs, r.acc);
+    else if (r.acc) atomicMax(&S.sum.radius, r.acc);
+  }
   __syncthreads();
-  if (phase == PH_RMAX) {
-    for (uint32_t t = threadIdx.x; t < kRmaxSlots; t += blockDim.x) {
+  if (table) {
+    for (uint32_t t = threadIdx.x; t < kRmaxSlots; t += kSweepThreads) {
       const uint32_t c = S.rmax.tag[t];
       if (c == kRmaxFree) continue;
-      uint64_t *rr = &job.R[off + c];
       const unsigned long long m = S.rmax.mx[t];
-      if (m > *rr) atomicMax((unsigned long long *)rr, m);
+      if (m > R[c]) atomicMax((unsigned long long *)&R[c], m);
     }
   }
   if (threadIdx.x == 0) {
-    if ((phase == PH_NEXT || phase == PH_NEXT_PULL) && S.acc != CLD_INF64) atomicMin(&cn.next.v, S.acc);
-    if ((phase == PH_ASSIGN || phase == PH_C2_ASSIGN) && S.acc) atomicMax(&cn.radius.v, S.acc);
-    if ((phase == PH_SELECT || phase == PH_C2_SELECT) && S.acc32) atomicAdd(&cn.centers.v, S.acc32);
-    if (phase == PH_SELECT && S.acc) atomicAdd(&cn.hub_arcs.v, S.acc);
-    if (phase == PH_RELAX && S.fmin != 0xffffffffu) atomicMin(&cn.fmin.v, S.fmin);
-    if (phase == PH_RELAX && steps && S.acc) atomicAdd(&cn.msgs.v, S.acc);
-    if (phase == PH_RELAX && S.blk_arcs) atomicAdd(&cn.blk_arcs.v, S.blk_arcs);
+    const GCount &x = S.sum;
+    if (x.fmin != 0xffffffffu) atomicMin(&cn.fmin, x.fmin);
+    if (x.cov) atomicAdd(phase == PH_SELECT || phase == PH_C2_SELECT ? &cn.centers : &cn.cov, x.cov);
+    if (x.upd) atomicAdd(&cn.upd, x.upd);
+    if (x.records) cn.records = 1;
+    if (x.next != CLD_INF64) atomicMin(&cn.next, x.next);
+    if (x.radius) atomicMax(&cn.radius, x.radius);
+    if (steps && phase == PH_RELAX && x.arcs) atomicAdd(&cn.msgs, x.arcs);
+    if (x.blk_arcs) atomicAdd(&cn.blk_arcs, x.blk_arcs);
+    if (x.hub_arcs) atomicAdd(&cn.hub_arcs, x.hub_arcs);
+    if (x.arcs) atomicAdd(&cn.arcs, x.arcs);
   }
   __syncthreads();
-  return scanned;
 }
 
 // Chunk index -> graph (largest g with seg[g] <= i).
@@ -1604,68 +1617,115 @@ __device__ __forceinline__ int graph_of(const Job &job, uint32_t i) {
   return lo;
 }
 
-// The sweep's work is a list of chunks, each a range of one graph's items
-// (at most one chunk of a graph per workgroup); workgroup b takes chunks b,
-// b + nblocks, ...
-__device__ void sweep(const Job &job, uint32_t block, uint32_t nblocks, Stage &S) {
-  const uint32_t total = job.ctl->total;
-  const uint32_t it = job.ctl->sweep_id;
-  if (threadIdx.x < 3) S.cnt[threadIdx.x] = 0;
-  if (threadIdx.x == 0) S.flush = 0;
-  __syncthreads();
-  uint32_t scanned = 0;
-  // chunk b first; chunks past the first nblocks go to whichever workgroup
-  // asks next, so that costly chunks (hub rows) do not hold up a sweep
-  for (uint32_t v = block; v < total;) {
-    const int g = graph_of(job, v);
-    const uint32_t per = job.seg[job.G + 1 + g];
-    const uint32_t n_items = job.seg[2 * job.G + 1 + g];
-    const uint32_t lo = (v - job.seg[g]) * per;
-    const uint32_t hi = lo + per < n_items ? lo + per : n_items;
-    scanned += process_run(job, g, lo, hi, it, S);
+// First chunk of a workgroup: workgroups go to the XCDs in turn, so each XCD
+// takes one eighth of the first chunks and neighbouring ranges share an L2.
+__device__ __forceinline__ uint32_t first_chunk(uint32_t block, uint32_t nblocks, uint32_t total) {
+  if (nblocks & 7) return block;
+  const uint32_t all = total < nblocks ? total : nblocks, per = (all + 7) >> 3;
+  const uint32_t i = block >> 3, c = (block & 7) * per + i;
+  return i < per && c < all ? c : 0xffffffffu;
+}
+
+// Chunks of a sweep; the first of each workgroup, then whichever is next, so
+// that costly chunks (hub rows) do not hold up a sweep.
+template <class Chunk>
+__device__ __forceinline__ void take_chunks(const Job &job, SweepCount &sc, uint32_t total, uint32_t block,
+                                            uint32_t nblocks, Stage &S, Chunk chunk) {
+  for (uint32_t v = first_chunk(block, nblocks, total); v < total;) {
+    chunk(v);
     if (total <= nblocks) break;
-    if (threadIdx.x == 0) S.chunk = nblocks + atomicAdd(&job.ctl->cursor.v, 1u);
+    if (threadIdx.x == 0) S.chunk = nblocks + atomicAdd(&sc.cursor, 1u);
     __syncthreads();
     v = S.chunk;
     __syncthreads();
   }
-  if (threadIdx.x == 0) atomicAdd(&job.ctl->idle.v, 1u);
-  for (int o = 32; o >= 1; o >>= 1) scanned += __shfl_xor(scanned, o);
-  if (cld_lane() == 0 && scanned) atomicAdd(&job.ctl->arcs.v, (unsigned long long)scanned);
+  if (threadIdx.x == 0 && job.cutoff < (uint32_t)job.nblocks) atomicAdd(&sc.idle, 1u);
+}
+
+// A sweep of a job of several graphs, after its control launch.
+__device__ __forceinline__ void sweep_many(const Job &job, uint32_t block, uint32_t nblocks, Stage &S) {
+  const uint32_t total = job.ctl->total;
+  SweepCount &sc = job.ctl->sc[0];
+  take_chunks(job, sc, total, block, nblocks, S, [&](uint32_t v) {
+    const int g = graph_of(job, v);
+    const GDesc &d = job.desc[g];
+    const uint32_t per = job.seg[job.G + 1 + g];
+    const uint32_t lo = (v - job.seg[g]) * per;
+    const uint32_t hi = lo + per < d.words ? lo + per : d.words;
+    process_run(job, d, job.st[g], job.cn[g], &sc.idle, lo, hi, S);
+  });
+}
+
+// Sweep t (from 1) of a job of one graph, its control step included; false
+// when the graph is done.
+__device__ __forceinline__ bool sweep_one(const Job &job, uint32_t t, uint32_t block, uint32_t nblocks, Stage &S) {
+  Ctl *ctl = job.ctl;
+  const GDesc &d = job.desc[0];
+  const uint32_t tid = threadIdx.x;
+  const uint32_t *st = (const uint32_t *)&job.ring[(t - 1) & 1], *cn = (const uint32_t *)&job.cn[(t + 2) % 3];
+  for (uint32_t i = tid; i < sizeof(GState) / 4; i += kSweepThreads) ((uint32_t *)&S.st)[i] = st[i];
+  for (uint32_t i = tid; i < sizeof(GCount) / 4; i += kSweepThreads) ((uint32_t *)&S.last)[i] = cn[i];
+  __syncthreads();
+  if (tid == 0) control_graph(d, S.st, S.last, block == 0 ? job.log : nullptr);
+  __syncthreads();
+  const bool done = S.st.phase == PH_DONE;
+  if (block == 0) {
+    uint32_t *to = (uint32_t *)&job.ring[t & 1], *fin = (uint32_t *)&job.st[0];
+    for (uint32_t i = tid; i < sizeof(GState) / 4; i += kSweepThreads) {
+      const uint32_t x = ((const uint32_t *)&S.st)[i];
+      to[i] = x;
+      if (done) fin[i] = x;
+    }
+    __syncthreads();
+    if (tid == 0) {
+      // past the time limit the next sweep finds the graph done (this one goes
+      // on, so that every workgroup ends at the same sweep)
+      check_time(ctl);
+      if (ctl->error) job.ring[t & 1].phase = PH_DONE;
+      clear_count(job.cn[(t + 1) % 3]);
+      ctl->sc[(t + 1) % 3].cursor = 0;
+      ctl->sc[(t + 1) % 3].idle = 0;
+      ctl->iterations = t;
+      if (done) ctl->done = 1;
+      report(job, t, done ? 1u : 0u);
+    }
+  }
+  if (done) return false;
+  SweepCount &sc = ctl->sc[t % 3];
+  const uint32_t per = chunk_words(d, S.st.phase, (int32_t)nblocks);
+  const uint32_t total = (d.words + per - 1) / per;
+  take_chunks(job, sc, total, block, nblocks, S, [&](uint32_t v) {
+    const uint32_t lo = v * per, hi = lo + per < d.words ? lo + per : d.words;
+    process_run(job, d, S.st, job.cn[t % 3], &sc.idle, lo, hi, S);
+  });
+  return true;
 }
 
 // ---------------------------------------------------------------- kernels --
 
-__global__ void __launch_bounds__(256) k_init(Job job, int64_t total_n) {
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < total_n; i += stride) {
-    job.key[i] = CLD_INF64;
-    job.keyn[i] = CLD_INF64;
-    job.slim[i] = 0;
-    job.R[i] = 0;
-    job.fstamp[i] = 0;
-    job.bstamp[i] = 0;
-  }
-  // U[0] of each graph = 0..n-1
-  for (int g = 0; g < job.G; ++g) {
-    const GDesc &d = job.desc[g];
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < d.n; i += stride)
-      job.U[0][d.off + i] = (int32_t)i;
-  }
+// The descriptor of a job of one graph, and the job's time limit.
+__global__ void k_describe(Job job, GDesc d, unsigned long long t_limit) {
+  *const_cast<GDesc *>(job.desc) = d;
+  job.ctl->t_limit = t_limit;
 }
 
-// Fresh state for one graph of a server job (node range [off, off + n)).
-__global__ void __launch_bounds__(256) k_init_range(Job job, int64_t off, int32_t n) {
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
-    job.key[off + i] = CLD_INF64;
-    job.keyn[off + i] = CLD_INF64;
-    job.slim[off + i] = 0;
-    job.R[off + i] = 0;
-    job.fstamp[off + i] = 0;
-    job.bstamp[off + i] = 0;
-    job.U[0][off + i] = (int32_t)i;
+// Fresh state of the nodes, sets and counters of graph first + blockIdx.y
+// (a job of one graph has three sets of counters).
+__global__ void __launch_bounds__(256) k_init(Job job, int32_t first) {
+  const int32_t g = first + (int32_t)blockIdx.y;
+  const GDesc &d = job.desc[g];
+  if (blockIdx.x == 0 && threadIdx.x < (job.G == 1 ? 3u : 1u)) clear_count(job.cn[g + threadIdx.x]);
+  const int64_t at = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, stride = (int64_t)gridDim.x * blockDim.x;
+  for (int64_t i = at; i < d.n; i += stride) {
+    job.key[d.off + i] = CLD_INF64;
+    job.keyn[d.off + i] = CLD_INF64;
+    job.slim[d.off + i] = 0;
+  }
+  const int64_t woff = d.off >> 6;
+  for (int64_t w = at; w < d.words; w += stride) {
+    const int64_t left = (int64_t)d.n - (w << 6);
+    job.U[woff + w] = left >= 64 ? ~0ull : (1ull << left) - 1ull;
+    for (int i = 0; i < 4; ++i) job.F[i][woff + w] = 0;
   }
 }
 
@@ -1676,25 +1736,42 @@ __global__ void __launch_bounds__(T) k_control(Job job) { control_block<T>(job);
 
 constexpr int kSmallControl = 64;
 
-void launch_control(const Job &job, hipStream_t stream) {
-  if (job.G <= kSmallControl) k_control<kSmallControl><<<1, kSmallControl, 0, stream>>>(job);
-  else k_control<kThreads><<<1, kThreads, 0, stream>>>(job);
-}
-
-__global__ void __launch_bounds__(kSweepThreads) k_sweep(Job job) {
+// One step: for several graphs the control launch, then the sweep.
+__global__ void __launch_bounds__(kSweepThreads, kCuThreads / kSweepThreads) k_sweep_many(Job job) {
   __shared__ Stage S;
   if (job.ctl->done) return;
-  sweep(job, blockIdx.x, gridDim.x, S);
+  sweep_many(job, blockIdx.x, gridDim.x, S);
 }
 
-__global__ void __launch_bounds__(kSweepThreads) k_persistent(Job job) {
+__global__ void __launch_bounds__(kSweepThreads, kCuThreads / kSweepThreads) k_sweep(Job job, uint32_t t) {
+  __shared__ Stage S;
+  if (job.ctl->done) return;
+  sweep_one(job, t, blockIdx.x, gridDim.x, S);
+}
+
+void launch_step(const Job &job, bool one, uint32_t t, hipStream_t stream) {
+  if (one) {
+    k_sweep<<<job.nblocks, kSweepThreads, 0, stream>>>(job, t);
+    return;
+  }
+  if (job.G <= kSmallControl) k_control<kSmallControl><<<1, kSmallControl, 0, stream>>>(job);
+  else k_control<kThreads><<<1, kThreads, 0, stream>>>(job);
+  k_sweep_many<<<job.nblocks, kSweepThreads, 0, stream>>>(job);
+}
+
+__global__ void __launch_bounds__(kSweepThreads, kCuThreads / kSweepThreads) k_persistent(Job job) {
   __shared__ Stage S;
   const uint32_t nb = gridDim.x;
+  if (job.G == 1) {
+    for (uint32_t t = 1; sweep_one(job, t, blockIdx.x, nb, S); ++t)
+      if (!cld_grid_barrier(&job.ctl->bar, &job.ctl->timeout, nb)) return;
+    return;
+  }
   for (;;) {
     if (blockIdx.x == 0) control_block<kSweepThreads>(job);
     if (!cld_grid_barrier(&job.ctl->bar, &job.ctl->timeout, nb)) return;
     if (job.ctl->done || job.ctl->timeout) return;
-    sweep(job, blockIdx.x, nb, S);
+    sweep_many(job, blockIdx.x, nb, S);
     if (!cld_grid_barrier(&job.ctl->bar, &job.ctl->timeout, nb)) return;
   }
 }
@@ -1703,45 +1780,60 @@ __global__ void __launch_bounds__(kSweepThreads) k_persistent(Job job) {
 
 struct Layout {
   GDesc *desc;
-  GState *st;
+  char *zero;         // st, ring, ctl and log lie together: cleared at the start, read back at the end
+  size_t zero_bytes;
+  GState *st, *ring;
   GCount *cn;
   Ctl *ctl;
   uint32_t *seg;
   int32_t *log;
   uint64_t *key, *keyn, *R;
-  uint32_t *slim, *fstamp, *bstamp;
-  int32_t *pool[3], *U[2], *C;
+  uint32_t *slim;
+  uint64_t *U, *F[4];
 };
 
+// Every graph's nodes start at a multiple of 64, so that its bitmap words are
+// its own.
+constexpr int64_t kNodeAlign = 64;
+int64_t aligned_nodes(int64_t n) { return (n + kNodeAlign - 1) / kNodeAlign * kNodeAlign; }
+
+// N: node slots, a multiple of kNodeAlign.
 template <class A>
 bool carve(A &a, int64_t N, int32_t G, Layout *L) {
   auto p_desc = a.template take<GDesc>(G);
   auto p_st = a.template take<GState>(G);
-  auto p_cn = a.template take<GCount>(G);
+  auto p_ring = a.template take<GState>(2);
   auto p_ctl = a.template take<Ctl>(1);
-  auto p_seg = a.template take<uint32_t>(3 * (size_t)G + 1);
   auto p_log = a.template take<int32_t>((size_t)G * CLDIAM_STAGE_LOG * 4);
+  auto p_cn = a.template take<GCount>(G < 3 ? 3 : G);
+  auto p_seg = a.template take<uint32_t>(2 * (size_t)G + 1);
   auto p_key = a.template take<uint64_t>(N);
   auto p_keyn = a.template take<uint64_t>(N);
   auto p_R = a.template take<uint64_t>(N);
   auto p_slim = a.template take<uint32_t>(N);
-  auto p_fs = a.template take<uint32_t>(N);
-  auto p_bs = a.template take<uint32_t>(N);
-  auto p0 = a.template take<int32_t>(N);
-  auto p1 = a.template take<int32_t>(N);
-  auto p2 = a.template take<int32_t>(N);
-  auto u0 = a.template take<int32_t>(N);
-  auto u1 = a.template take<int32_t>(N);
-  auto c = a.template take<int32_t>(N);
+  void *b[5];
+  for (auto &x : b) x = a.template take<uint64_t>(N / 64);
   if (L) {
-    *L = Layout{(GDesc *)p_desc, (GState *)p_st, (GCount *)p_cn, (Ctl *)p_ctl, (uint32_t *)p_seg, (int32_t *)p_log,
-                (uint64_t *)p_key, (uint64_t *)p_keyn, (uint64_t *)p_R, (uint32_t *)p_slim, (uint32_t *)p_fs,
-                (uint32_t *)p_bs,
-                {(int32_t *)p0, (int32_t *)p1, (int32_t *)p2}, {(int32_t *)u0, (int32_t *)u1}, (int32_t *)c};
-    return p_desc && c;
+    *L = Layout{(GDesc *)p_desc, (char *)p_st, (size_t)((char *)p_cn - (char *)p_st), (GState *)p_st,
+                (GState *)p_ring, (GCount *)p_cn, (Ctl *)p_ctl, (uint32_t *)p_seg, (int32_t *)p_log,
+                (uint64_t *)p_key, (uint64_t *)p_keyn, (uint64_t *)p_R, (uint32_t *)p_slim, (uint64_t *)b[0],
+                {(uint64_t *)b[1], (uint64_t *)b[2], (uint64_t *)b[3], (uint64_t *)b[4]}};
+    return p_desc && b[4];
   }
   return true;
 }
+
+Job make_job(const Layout &L, int32_t G) {
+  Job job{};
+  job.desc = L.desc; job.st = L.st; job.ring = L.ring; job.cn = L.cn; job.ctl = L.ctl; job.seg = L.seg;
+  job.log = L.log; job.key = L.key; job.keyn = L.keyn; job.R = L.R; job.slim = L.slim; job.U = L.U;
+  for (int i = 0; i < 4; ++i) job.F[i] = L.F[i];
+  job.G = G;
+  return job;
+}
+
+// Blocks of k_init for the graphs of a job of N node slots.
+dim3 init_grid(int64_t N, int32_t G) { return dim3((unsigned)cld::blocks_for(N / G, 256, G > 1 ? 1024 : 8192), (unsigned)G); }
 
 struct SizeArena {
   cld::Sizer s;
@@ -1757,8 +1849,12 @@ struct PtrArena {
 };
 
 constexpr size_t kMirrorOffset = cld::kPinnedBytes - 128;   // host-loop mirror words in the readback buffer
-constexpr uint32_t kLeadSteps = 16;   // control + sweep steps the host queues ahead of the device
-static_assert(sizeof(Ctl) <= kMirrorOffset, "control block and mirror words must fit a pooled pinned buffer");
+constexpr uint32_t kLeadSteps = 16;   // steps the host queues ahead of the device
+constexpr size_t up256(size_t x) { return (x + 255) & ~(size_t)255; }
+constexpr size_t kReadback = up256(sizeof(GState)) + up256(2 * sizeof(GState)) + up256(sizeof(Ctl)) +
+                             up256(CLDIAM_STAGE_LOG * 16);   // Layout's zero region of one graph
+static_assert(kReadback <= kMirrorOffset, "readback and mirror words must fit a pooled pinned buffer");
+static_assert(sizeof(Stage) <= 160 * 1024, "a workgroup's LDS");
 
 // Workgroups of the sweep grid: one per CU unless requested (bounded by the
 // co-resident maximum for the persistent kernel).
@@ -1805,6 +1901,7 @@ int make_desc(const cldiam_graph &x, int g, const cldiam_tuning *tuning, GDesc *
   d.cluster = x.d_cluster;
   d.D = x.d_D;
   d.n = x.n;
+  d.words = (uint32_t)(((int64_t)x.n + 63) >> 6);
   const double gamma = 4.0 * M_LN2;
   const double L = log2((double)x.n);
   d.K = gamma * x.params.tau * L;
@@ -1877,7 +1974,7 @@ int make_desc(const cldiam_graph &x, int g, const cldiam_tuning *tuning, GDesc *
   return CLDIAM_OK;
 }
 
-void fill_stats(const GDesc &d, const GState &st, const GCount &cn, const int32_t *log, cldiam_stats *o) {
+void fill_stats(const GDesc &d, const GState &st, const int32_t *log, cldiam_stats *o) {
   memset(o, 0, sizeof *o);
   o->stages = (int32_t)st.stage;
   o->levels = (int32_t)st.levels;
@@ -1887,12 +1984,12 @@ void fill_stats(const GDesc &d, const GState &st, const GCount &cn, const int32_
   o->num_clusters = (int32_t)(st.centers_total + st.singletons);
   o->singletons = (int32_t)st.singletons;
   o->sweeps = (int32_t)st.sweeps;
-  o->radius = cn.radius.v;
+  o->radius = st.radius;
   o->status = st.status;
   o->rounds = st.rounds;
   o->radius1 = st.radius1;
   o->updates = st.updates;
-  o->messages = cn.msgs.v;
+  o->messages = st.msgs;
   for (int s = 0; s < CLDIAM_STAGE_LOG && s < o->stages; ++s) {
     const int32_t *l = log + (size_t)s * 4;
     o->stage_uncovered[s] = l[0];
@@ -1916,7 +2013,7 @@ int read_wall_limit(unsigned long long *limit) {
 extern "C" size_t cldiam_decompose_workspace_size(int64_t total_n, int32_t num_graphs) {
   if (total_n < 1 || num_graphs < 1) return 0;
   SizeArena s;
-  carve(s, total_n, num_graphs, nullptr);
+  carve(s, aligned_nodes(total_n + (int64_t)(num_graphs - 1) * (kNodeAlign - 1)), num_graphs, nullptr);
   return s.s.used;
 }
 
@@ -1924,64 +2021,62 @@ extern "C" int cldiam_decompose_batch(int32_t G, const cldiam_graph *gs, cldiam_
                                       const cldiam_tuning *tuning, void *ws, size_t ws_bytes, void *stream_) {
   hipStream_t stream = (hipStream_t)stream_;
   if (G < 1 || !gs) { cld::set_error("decompose: num_graphs < 1 or no graphs"); return CLDIAM_EINVAL; }
-  int64_t N = 0;
+  int64_t total = 0, N = 0;   // nodes, node slots
   std::vector<GDesc> desc(G);
   for (int g = 0; g < G; ++g) {
     int rc = make_desc(gs[g], g, tuning, &desc[g]);
     if (rc) return rc;
     desc[g].off = N;
-    N += gs[g].n;
+    total += gs[g].n;
+    N += aligned_nodes(gs[g].n);
   }
-  if (N >= ((int64_t)1 << 31)) { cld::set_error("decompose: more than 2^31 nodes in one job"); return CLDIAM_EINVAL; }
+  if (total >= ((int64_t)1 << 31)) { cld::set_error("decompose: more than 2^31 nodes in one job"); return CLDIAM_EINVAL; }
   Layout L;
   PtrArena pa(ws, ws_bytes);
   if (!carve(pa, N, G, &L) || pa.a.used > ws_bytes) {
-    cld::set_error("decompose: workspace of %zu bytes, %zu needed", ws_bytes, cldiam_decompose_workspace_size(N, G));
+    cld::set_error("decompose: workspace of %zu bytes, %zu needed", ws_bytes,
+                   cldiam_decompose_workspace_size(total, G));
     return CLDIAM_ENOMEM;
   }
-  Job job{};
-  job.desc = L.desc; job.st = L.st; job.cn = L.cn; job.ctl = L.ctl; job.seg = L.seg; job.log = L.log;
-  job.key = L.key; job.keyn = L.keyn; job.R = L.R; job.slim = L.slim; job.fstamp = L.fstamp;
-  job.bstamp = L.bstamp;
-  for (int i = 0; i < 3; ++i) job.pool[i] = L.pool[i];
-  job.U[0] = L.U[0]; job.U[1] = L.U[1]; job.C = L.C; job.G = G;
-
-  CLD_HIP(hipMemcpyAsync(L.desc, desc.data(), sizeof(GDesc) * G, hipMemcpyHostToDevice, stream));
-  CLD_HIP(hipMemsetAsync(L.st, 0, sizeof(GState) * G, stream));
-  CLD_HIP(hipMemsetAsync(L.cn, 0, sizeof(GCount) * G, stream));
-  CLD_HIP(hipMemsetAsync(L.ctl, 0, sizeof(Ctl), stream));
-  {
-    int dev = 0, khz = 0;
-    CLD_HIP(hipGetDevice(&dev));
-    CLD_HIP(hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, dev));
-    if (khz <= 0) khz = 100000;
-    const unsigned long long limit = (unsigned long long)khz * 1000ull * kJobSeconds;
+  Job job = make_job(L, G);
+  const bool one = G == 1;
+  unsigned long long limit = 0;
+  int rc = read_wall_limit(&limit);
+  if (rc) return rc;
+  CLD_HIP(hipMemsetAsync(L.zero, 0, L.zero_bytes, stream));
+  if (one) {
+    k_describe<<<1, 1, 0, stream>>>(job, desc[0], limit);
+  } else {
+    CLD_HIP(hipMemcpyAsync(L.desc, desc.data(), sizeof(GDesc) * G, hipMemcpyHostToDevice, stream));
     CLD_HIP(hipMemcpyAsync(&L.ctl->t_limit, &limit, sizeof limit, hipMemcpyHostToDevice, stream));
   }
-  CLD_HIP(hipMemsetAsync(L.log, 0, sizeof(int32_t) * G * CLDIAM_STAGE_LOG * 4, stream));
-  k_init<<<cld::blocks_for(N, 256, 8192), 256, 0, stream>>>(job, N);
+  for (int32_t g = 0; g < G; g += 65535) {
+    const int32_t part = G - g < 65535 ? G - g : 65535;
+    k_init<<<init_grid(N, part), 256, 0, stream>>>(job, g);
+  }
   CLD_LAUNCH_CHECK("k_init");
 
   int blocks = 0;
-  {
-    int rc = grid_blocks(driver == CLDIAM_DRIVER_PERSISTENT ? driver : CLDIAM_DRIVER_HOST,
-                         tuning ? tuning->grid_blocks : 0, &blocks);
-    if (rc) return rc;
-    if (blocks == 0 && driver == CLDIAM_DRIVER_PERSISTENT) {
-      cld::set_error("decompose: device has no cooperative launch");
-      return CLDIAM_EINVAL;
-    }
+  rc = grid_blocks(driver == CLDIAM_DRIVER_PERSISTENT ? driver : CLDIAM_DRIVER_HOST, tuning ? tuning->grid_blocks : 0,
+                   &blocks);
+  if (rc) return rc;
+  if (blocks == 0 && driver == CLDIAM_DRIVER_PERSISTENT) {
+    cld::set_error("decompose: device has no cooperative launch");
+    return CLDIAM_EINVAL;
   }
   const bool persistent = driver == CLDIAM_DRIVER_PERSISTENT && blocks > 0;
   if (!persistent && blocks <= 0) blocks = 256;
   if (blocks > 65535) blocks = 65535;
   job.nblocks = blocks;
   job.cutoff = local_cutoff(tuning, blocks);
-  cld::Pinned<Ctl> pinned;   // readback buffer, back to the pool when the call returns
-  Ctl *hc = pinned.p;
-  if (!hc) { cld::set_error("decompose: pinned host buffer allocation failed"); return CLDIAM_EHIP; }
+  struct Readback {
+    char zero[kReadback];
+  };
+  cld::Pinned<Readback> pinned;   // back to the pool when the call returns
+  if (!pinned.p) { cld::set_error("decompose: pinned host buffer allocation failed"); return CLDIAM_EHIP; }
+  const Ctl *hc = (const Ctl *)(pinned.p->zero + ((char *)L.ctl - L.zero));   // one graph: where ctl is read back
   // the last line of the same buffer: the control step's mirror for the host loop
-  volatile uint32_t *hm = (volatile uint32_t *)((char *)hc + kMirrorOffset);
+  volatile uint32_t *hm = (volatile uint32_t *)((char *)pinned.p + kMirrorOffset);
   hipEvent_t ev0 = nullptr, ev1 = nullptr;
   CLD_HIP(hipEventCreate(&ev0));
   CLD_HIP(hipEventCreate(&ev1));
@@ -1994,16 +2089,11 @@ extern "C" int cldiam_decompose_batch(int32_t G, const cldiam_graph *gs, cldiam_
     void *args[] = {&job};
     CLD_HIP(hipLaunchCooperativeKernel((const void *)k_persistent, dim3(blocks), dim3(kSweepThreads), args, 0,
                                        stream));
-    CLD_HIP(hipEventRecord(ev1, stream));
-    CLD_HIP(hipMemcpyAsync(hc, L.ctl, sizeof(Ctl), hipMemcpyDeviceToHost, stream));
-    CLD_HIP(hipStreamSynchronize(stream));
-    if (hc->timeout) { cld::set_error("decompose: grid barrier timed out"); return CLDIAM_ETIMEOUT; }
-    if (!hc->done && !hc->error) { cld::set_error("decompose: persistent kernel ended early"); return CLDIAM_EHIP; }
   } else {
-    // The host queues control + sweep steps at most kLeadSteps ahead of the
-    // control steps the device has finished (read from the mapped mirror, no
-    // stream synchronisation), and stops queueing once the device reports the
-    // job done: only the steps already queued then run, and they return at once.
+    // The host queues steps at most kLeadSteps ahead of the control steps the
+    // device has finished (read from the mapped mirror, no stream
+    // synchronisation), and stops queueing once the device reports the job
+    // done: only the steps already queued then run, and they return at once.
     hm[0] = 0;
     hm[1] = 0;
     uint32_t *dm = nullptr;
@@ -2014,9 +2104,7 @@ extern "C" int cldiam_decompose_batch(int32_t G, const cldiam_graph *gs, cldiam_
     for (;;) {
       if (hm[1]) break;
       if (queued < hm[0] + kLeadSteps) {
-        launch_control(job, stream);
-        k_sweep<<<blocks, kSweepThreads, 0, stream>>>(job);
-        ++queued;
+        launch_step(job, one, ++queued, stream);
         if ((queued & 15u) == 0) CLD_LAUNCH_CHECK("k_sweep");
         continue;
       }
@@ -2028,30 +2116,33 @@ extern "C" int cldiam_decompose_batch(int32_t G, const cldiam_graph *gs, cldiam_
       std::this_thread::yield();
     }
     CLD_LAUNCH_CHECK("k_sweep");
-    CLD_HIP(hipEventRecord(ev1, stream));
-    CLD_HIP(hipMemcpyAsync(hc, L.ctl, sizeof(Ctl), hipMemcpyDeviceToHost, stream));
-    CLD_HIP(hipStreamSynchronize(stream));
-    if (!hc->done) { cld::set_error("decompose: host-driven job ended without its done flag"); return CLDIAM_EHIP; }
-    blocks = 0;
   }
-  std::vector<GState> st(G);
-  std::vector<GCount> cn(G);
-  std::vector<int32_t> lg((size_t)G * CLDIAM_STAGE_LOG * 4);
-  CLD_HIP(hipMemcpyAsync(st.data(), L.st, sizeof(GState) * G, hipMemcpyDeviceToHost, stream));
-  CLD_HIP(hipMemcpyAsync(cn.data(), L.cn, sizeof(GCount) * G, hipMemcpyDeviceToHost, stream));
-  CLD_HIP(hipMemcpyAsync(lg.data(), L.log, sizeof(int32_t) * lg.size(), hipMemcpyDeviceToHost, stream));
+  CLD_HIP(hipEventRecord(ev1, stream));
+  std::vector<char> many(one ? 0 : L.zero_bytes);
+  char *back = one ? pinned.p->zero : many.data();
+  CLD_HIP(hipMemcpyAsync(back, L.zero, L.zero_bytes, hipMemcpyDeviceToHost, stream));
   CLD_HIP(hipStreamSynchronize(stream));
+  if (!one) hc = (const Ctl *)(back + ((char *)L.ctl - L.zero));
+  if (persistent && hc->timeout) { cld::set_error("decompose: grid barrier timed out"); return CLDIAM_ETIMEOUT; }
+  if (!hc->done && !(persistent && hc->error)) {
+    cld::set_error("decompose: %s", persistent ? "persistent kernel ended early"
+                                               : "host-driven job ended without its done flag");
+    return CLDIAM_EHIP;
+  }
+  if (!persistent) blocks = 0;
+  const GState *st = (const GState *)back;
+  const int32_t *lg = (const int32_t *)(back + ((char *)L.log - L.zero));
   float kernel_ms = 0.f;
   CLD_HIP(hipEventElapsedTime(&kernel_ms, ev0, ev1));
-  int rc = CLDIAM_OK;
+  rc = CLDIAM_OK;
   for (int g = 0; g < G; ++g) {
     if (st[g].status != CLDIAM_OK && rc == CLDIAM_OK) {
       rc = st[g].status;
       cld::set_error("decompose: graph %d failed: %s", g, cldiam_strerror(rc));
     }
     if (!stats) continue;
-    fill_stats(desc[g], st[g], cn[g], &lg[(size_t)g * CLDIAM_STAGE_LOG * 4], &stats[g]);
-    stats[g].arcs_scanned = (G == 1) ? hc->arcs.v : 0;
+    fill_stats(desc[g], st[g], lg + (size_t)g * CLDIAM_STAGE_LOG * 4, &stats[g]);
+    stats[g].arcs_scanned = one ? st[g].arcs : 0;
     stats[g].grid_blocks = blocks;
     stats[g].kernel_ms = kernel_ms;
     stats[g].iterations = (int32_t)hc->iterations;
@@ -2147,7 +2238,9 @@ extern "C" int cldiam_server_create(cldiam_server **out, int64_t node_capacity, 
   *out = nullptr;
   cldiam_server *s = new cldiam_server();
   PtrArena pa(ws, ws_bytes);
-  if (!carve(pa, node_capacity, max_graphs, &s->L) || pa.a.used > ws_bytes) {
+  // room for every set of graphs of node_capacity nodes in all, each aligned
+  const int64_t slots = aligned_nodes(node_capacity + (int64_t)(max_graphs - 1) * (kNodeAlign - 1));
+  if (!carve(pa, slots, max_graphs, &s->L) || pa.a.used > ws_bytes) {
     delete s;
     cld::set_error("server: workspace of %zu bytes, %zu needed", ws_bytes,
                    cldiam_decompose_workspace_size(node_capacity, max_graphs));
@@ -2157,13 +2250,9 @@ extern "C" int cldiam_server_create(cldiam_server **out, int64_t node_capacity, 
   s->gcap = max_graphs;
   s->tuning = tuning ? *tuning : cldiam_tuning{-1, 0, 0.f, 0, 0, 0, 0, 0, 0, 0};
   s->stream = (hipStream_t)stream;
-  Job &job = s->job;
   const Layout &L = s->L;
-  job.desc = L.desc; job.st = L.st; job.cn = L.cn; job.ctl = L.ctl; job.seg = L.seg; job.log = L.log;
-  job.key = L.key; job.keyn = L.keyn; job.R = L.R; job.slim = L.slim; job.fstamp = L.fstamp;
-  job.bstamp = L.bstamp;
-  for (int i = 0; i < 3; ++i) job.pool[i] = L.pool[i];
-  job.U[0] = L.U[0]; job.U[1] = L.U[1]; job.C = L.C; job.G = max_graphs;
+  s->job = make_job(L, max_graphs);
+  Job &job = s->job;
   int rc = grid_blocks(CLDIAM_DRIVER_HOST, tuning ? tuning->grid_blocks : 0, &s->blocks);
   if (rc) { delete s; return rc; }
   if (s->blocks <= 0) s->blocks = 256;
@@ -2172,7 +2261,7 @@ extern "C" int cldiam_server_create(cldiam_server **out, int64_t node_capacity, 
   s->desc.assign(max_graphs, GDesc{});
   s->tag.assign(max_graphs, 0);
   s->active.assign(max_graphs, 0);
-  s->free_ranges.push_back({0, node_capacity});
+  s->free_ranges.push_back({0, slots});
   s->st_host.assign(max_graphs, GState{});
   for (auto &g : s->st_host) g.phase = PH_IDLE;
   void *p = nullptr;
@@ -2186,10 +2275,9 @@ extern "C" int cldiam_server_create(cldiam_server **out, int64_t node_capacity, 
   rc = read_wall_limit(&limit);
   if (rc) { cldiam_server_destroy(s); return rc; }
   hipStream_t st = s->stream;
-  if (hipMemcpyAsync(L.desc, s->desc.data(), sizeof(GDesc) * max_graphs, hipMemcpyHostToDevice, st) != hipSuccess ||
+  if (hipMemsetAsync(L.zero, 0, L.zero_bytes, st) != hipSuccess ||
+      hipMemcpyAsync(L.desc, s->desc.data(), sizeof(GDesc) * max_graphs, hipMemcpyHostToDevice, st) != hipSuccess ||
       hipMemcpyAsync(L.st, s->st_host.data(), sizeof(GState) * max_graphs, hipMemcpyHostToDevice, st) != hipSuccess ||
-      hipMemsetAsync(L.cn, 0, sizeof(GCount) * max_graphs, st) != hipSuccess ||
-      hipMemsetAsync(L.ctl, 0, sizeof(Ctl), st) != hipSuccess ||
       hipMemcpyAsync(&L.ctl->t_limit, &limit, sizeof limit, hipMemcpyHostToDevice, st) != hipSuccess ||
       hipStreamSynchronize(st) != hipSuccess) {
     cldiam_server_destroy(s);
@@ -2229,7 +2317,7 @@ extern "C" int cldiam_server_step(cldiam_server *s, int32_t max_sweeps, int32_t 
     if (slot < 0) break;
     cldiam_server::Pending &p = s->queue[s->qhead];
     int64_t off = 0;
-    if (!take_range(s, p.d.n, &off)) break;
+    if (!take_range(s, aligned_nodes(p.d.n), &off)) break;
     p.d.off = off;
     s->desc[slot] = p.d;
     s->tag[slot] = p.tag;
@@ -2238,11 +2326,10 @@ extern "C" int cldiam_server_step(cldiam_server *s, int32_t max_sweeps, int32_t 
     fresh.phase = PH_START;
     CLD_HIP(hipMemcpyAsync(&s->L.desc[slot], &s->desc[slot], sizeof(GDesc), hipMemcpyHostToDevice, stream));
     CLD_HIP(hipMemcpyAsync(&job.st[slot], &fresh, sizeof(GState), hipMemcpyHostToDevice, stream));
-    CLD_HIP(hipMemsetAsync(&job.cn[slot], 0, sizeof(GCount), stream));
     CLD_HIP(hipMemsetAsync(job.log + (size_t)slot * CLDIAM_STAGE_LOG * 4, 0, sizeof(int32_t) * CLDIAM_STAGE_LOG * 4,
                            stream));
-    k_init_range<<<cld::blocks_for(p.d.n, 256, 4096), 256, 0, stream>>>(job, off, p.d.n);
-    CLD_LAUNCH_CHECK("k_init_range");
+    k_init<<<init_grid(p.d.n, 1), 256, 0, stream>>>(job, slot);
+    CLD_LAUNCH_CHECK("k_init");
     // the host copies above read s->desc / fresh before the next host write
     CLD_HIP(hipStreamSynchronize(stream));
     s->qhead++;
@@ -2256,8 +2343,7 @@ extern "C" int cldiam_server_step(cldiam_server *s, int32_t max_sweeps, int32_t 
   if (nactive > 0 && max_sweeps > 0) {
     CLD_HIP(hipMemsetAsync(&job.ctl->iterations, 0, sizeof(uint32_t), stream));
     for (int i = 0; i < max_sweeps; ++i) {
-      launch_control(job, stream);
-      k_sweep<<<s->blocks, kSweepThreads, 0, stream>>>(job);
+      launch_step(job, false, 0, stream);
     }
     CLD_LAUNCH_CHECK("k_sweep");
     CLD_HIP(hipMemcpyAsync(s->st_host.data(), job.st, sizeof(GState) * s->gcap, hipMemcpyDeviceToHost, stream));
@@ -2269,9 +2355,7 @@ extern "C" int cldiam_server_step(cldiam_server *s, int32_t max_sweeps, int32_t 
     }
     for (int g = 0; g < s->gcap; ++g) {
       if (!s->active[g] || s->st_host[g].phase != PH_DONE) continue;
-      GCount cn;
       std::vector<int32_t> lg(CLDIAM_STAGE_LOG * 4);
-      CLD_HIP(hipMemcpyAsync(&cn, &job.cn[g], sizeof cn, hipMemcpyDeviceToHost, stream));
       CLD_HIP(hipMemcpyAsync(lg.data(), job.log + (size_t)g * CLDIAM_STAGE_LOG * 4, sizeof(int32_t) * lg.size(),
                              hipMemcpyDeviceToHost, stream));
       const GState idle = [] { GState x{}; x.phase = PH_IDLE; return x; }();
@@ -2279,10 +2363,10 @@ extern "C" int cldiam_server_step(cldiam_server *s, int32_t max_sweeps, int32_t 
       CLD_HIP(hipStreamSynchronize(stream));
       cldiam_server::Done dn;
       dn.tag = s->tag[g];
-      fill_stats(s->desc[g], s->st_host[g], cn, lg.data(), &dn.st);
+      fill_stats(s->desc[g], s->st_host[g], lg.data(), &dn.st);
       s->done.push_back(dn);
       s->active[g] = 0;
-      give_range(s, s->desc[g].off, s->desc[g].n);
+      give_range(s, s->desc[g].off, aligned_nodes(s->desc[g].n));
       --nactive;
     }
   }
