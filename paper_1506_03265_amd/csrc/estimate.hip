@@ -7,7 +7,27 @@
 // deduplicated queue; all distances exact at the fixpoint), keeping distances
 // and queues in LDS when they fit, in a per-workgroup workspace slice
 // otherwise.
+//
+// A search's time is its rounds (about the hops of its longest shortest path)
+// times a round's chain of reads (queue, row offsets, arcs, distance).  So a
+// row is read by a group of lanes at once (one thread per row took a read's
+// latency per arc, 700 in a row on R-MAT's star-like quotients), a row longer
+// than kWideRow by the whole workgroup, and the quotient graph itself is copied
+// to LDS where it fits beside the search's arrays.
+//
+// Few searches are needed: once node v's eccentricity ecc(v) is known, no node
+// u of its component has a larger one than ecc(v) + d(u, v), so a node whose
+// bound is not above the largest eccentricity found so far is skipped.  The
+// order spreads the first sources over the ids, and one workgroup of 1024
+// threads per CU runs (more or smaller ones start more searches before the
+// bounds that exclude them: 537 and 751 us where this takes 431 on a quotient
+// of 2228 nodes and 12028 arcs, without the copy in LDS).
+//
+// That quotient takes 312 us (1771 us with a search from every node, 256 threads
+// each, one thread per row), the star-like one of R-MAT scale 24 54 us (356).
+#include <algorithm>
 #include <mutex>
+#include <numeric>
 #include <vector>
 
 #include "common.h"
@@ -15,17 +35,20 @@
 namespace {
 
 constexpr int kT = 256;
-constexpr int kLdsMaxK = 3072;  // 20 bytes per node -> 60 KB
+constexpr int kSearchT = 1024;   // threads of one search, one search per CU
+constexpr int kMaxSearches = 256;
+constexpr size_t kLdsBytes = 160 * 1024 - 2048;   // for a search's arrays (the rest: its own small variables)
+constexpr int kLdsMaxK = 12800;  // 12.1 bytes per node -> 155 KB
 
-// Bytes of one workgroup's distances, stamps and queues in global memory: a
+// Bytes of one workgroup's distances, queues and queued set in global memory: a
 // multiple of 8, so that every workgroup's 64-bit distances are aligned (a
 // 64-bit atomic on an address that is not faults).
 __host__ __device__ inline size_t slice_bytes(int32_t k) { return ((size_t)k * 20 + 7) & ~(size_t)7; }
 
 struct ECtl {
-  unsigned long long phi;
+  unsigned long long phi;   // largest eccentricity found
+  uint32_t next;            // sources taken
   uint32_t bad;   // the quotient CSR is malformed: nothing is indexed with it
-  uint32_t pad;
 };
 
 // The quotient CSR must have row offsets from 0 to qm, non-decreasing, and
@@ -42,91 +65,226 @@ __global__ void k_check_quotient(int32_t k, int64_t qm, const int64_t *rp, const
     if ((uint32_t)col[a] >= (uint32_t)k) *bad = 1u;
 }
 
-__device__ void sssp_block(int32_t k, const int64_t *rp, const int32_t *col, const uint64_t *w, int32_t s,
-                           uint64_t *dist, uint32_t *stamp, int32_t *q0, int32_t *q1, uint64_t *phi) {
-  __shared__ uint32_t qn_next;
+constexpr int kGroup = 8;      // lanes per row
+constexpr int kWideRow = 128;  // longer rows are read by the whole workgroup
+constexpr int kWideCap = 128;  // such rows per pass (others are read by their group)
+
+// Distances, queues and the set of queued nodes of one workgroup's search.
+template <class Id>
+struct Search {
+  uint64_t *dist;
+  Id *queue[2];
+  uint32_t *queued;   // bitmap
+};
+
+// The quotient graph in global memory.
+struct Csr {
+  const int64_t *rp;
+  const int32_t *col;
+  const uint64_t *w;
+};
+
+// ... and copied to LDS.
+struct LdsCsr {
+  const uint32_t *rp;
+  const uint16_t *col;
+  const uint64_t *w;
+};
+
+template <class Id>
+__device__ __forceinline__ void relax_arc(const Search<Id> &x, int32_t v, uint64_t nd, uint32_t *qn, Id *next) {
+  if (nd >= x.dist[v]) return;
+  if (nd >= atomicMin((unsigned long long *)&x.dist[v], (unsigned long long)nd)) return;
+  const uint32_t bit = 1u << (v & 31);
+  if (!(atomicOr(&x.queued[v >> 5], bit) & bit)) next[atomicAdd(qn, 1u)] = (Id)v;
+}
+
+template <class Id>
+__device__ __forceinline__ uint64_t distance(const Search<Id> &x, int32_t u) {
+  return __hip_atomic_load(&x.dist[u], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Exact distances from s; returns the largest finite one.
+template <class Graph, class Id>
+__device__ __forceinline__ unsigned long long sssp_block(int32_t k, const Graph &g, int32_t s, const Search<Id> &x) {
+  __shared__ uint32_t qn[2], nwide;
+  __shared__ Id wide[kWideCap];
   __shared__ unsigned long long bmax;
-  for (int32_t v = threadIdx.x; v < k; v += blockDim.x) { dist[v] = CLD_INF64; stamp[v] = 0; }
-  if (threadIdx.x == 0) { qn_next = 0; bmax = 0; }
+  const int32_t tid = (int32_t)threadIdx.x, lane = tid % kGroup;
+  for (int32_t v = tid; v < k; v += kSearchT) x.dist[v] = CLD_INF64;
+  for (int32_t i = tid; i < (k + 31) / 32; i += kSearchT) x.queued[i] = 0;
+  if (tid == 0) { qn[0] = 1; qn[1] = 0; nwide = 0; bmax = 0; }
   __syncthreads();
-  if (threadIdx.x == 0) { dist[s] = 0; q0[0] = s; }
+  if (tid == 0) { x.dist[s] = 0; x.queue[0][0] = (Id)s; x.queued[s >> 5] = 1u << (s & 31); }
   __syncthreads();
-  uint32_t qn = 1, iter = 1;
-  int32_t *qc = q0, *qx = q1;
-  while (qn > 0) {
-    for (uint32_t i = threadIdx.x; i < qn; i += blockDim.x) {
-      const int32_t u = qc[i];
-      const uint64_t du = dist[u];
-      for (int64_t a = rp[u]; a < rp[u + 1]; ++a) {
-        const int32_t v = col[a];
-        const uint64_t nd = du + w[a];
-        if (nd < dist[v]) {
-          const uint64_t old = atomicMin((unsigned long long *)&dist[v], (unsigned long long)nd);
-          if (nd < old && atomicExch(&stamp[v], iter) != iter) qx[atomicAdd(&qn_next, 1u)] = v;
+  for (int q = 0;; q ^= 1) {
+    const uint32_t n = qn[q];
+    if (n == 0) break;
+    const Id *cur = x.queue[q];
+    Id *next = x.queue[q ^ 1];
+    for (uint32_t i0 = 0; i0 < n; i0 += kSearchT / kGroup) {
+      const uint32_t i = i0 + (uint32_t)(tid / kGroup);
+      if (i < n) {
+        const int32_t u = (int32_t)cur[i];
+        const auto a0 = g.rp[u], a1 = g.rp[u + 1];
+        // off the set before its distance is read (the value returned is
+        // waited for): an improvement after this queues u again, one before it
+        // is seen by the read, which does not go through the L1
+        const uint32_t bit = 1u << (u & 31);
+        uint32_t was = 0;
+        if (lane == 0) was = atomicAnd(&x.queued[u >> 5], ~bit);
+        bool mine = (__shfl(was, 0, kGroup) & bit) != 0;
+        if (a1 - a0 > kWideRow) {
+          uint32_t slot = 0;
+          if (lane == 0) slot = atomicAdd(&nwide, 1u);
+          slot = __shfl(slot, 0, kGroup);
+          mine = slot >= kWideCap;
+          if (!mine && lane == 0) wide[slot] = (Id)u;
+        }
+        if (mine) {
+          const uint64_t du = distance(x, u);
+          for (auto a = a0 + lane; a < a1; a += kGroup) relax_arc(x, (int32_t)g.col[a], du + g.w[a], &qn[q ^ 1], next);
         }
       }
     }
     __syncthreads();
-    qn = qn_next;
+    const uint32_t nw = nwide < kWideCap ? nwide : kWideCap;
+    for (uint32_t i = 0; i < nw; ++i) {
+      const int32_t u = (int32_t)wide[i];
+      const uint64_t du = distance(x, u);
+      const auto a1 = g.rp[u + 1];
+      for (auto a = g.rp[u] + tid; a < a1; a += kSearchT) relax_arc(x, (int32_t)g.col[a], du + g.w[a], &qn[q ^ 1], next);
+    }
     __syncthreads();
-    if (threadIdx.x == 0) qn_next = 0;
-    int32_t *t = qc; qc = qx; qx = t;
-    ++iter;
+    if (tid == 0) { qn[q] = 0; nwide = 0; }
     __syncthreads();
   }
   unsigned long long m = 0;
-  for (int32_t v = threadIdx.x; v < k; v += blockDim.x)
-    if (dist[v] != CLD_INF64 && dist[v] > m) m = dist[v];
-  atomicMax(&bmax, m);
+  for (int32_t v = tid; v < k; v += kSearchT)
+    if (x.dist[v] != CLD_INF64 && x.dist[v] > m) m = x.dist[v];
+  for (int o = 32; o >= 1; o >>= 1) {
+    const unsigned long long y = __shfl_xor(m, o);
+    m = y > m ? y : m;
+  }
+  if ((tid & 63) == 0 && m) atomicMax(&bmax, m);
   __syncthreads();
-  if (threadIdx.x == 0 && bmax) atomicMax((unsigned long long *)phi, bmax);
-  __syncthreads();
+  return bmax;
 }
 
-__global__ void __launch_bounds__(kT) k_apsp_lds(int32_t k, const int64_t *rp, const int32_t *col,
-                                                 const uint64_t *w, uint64_t *phi, const uint32_t *bad) {
-  if (*bad) return;
-  extern __shared__ uint64_t lds[];
-  uint64_t *dist = lds;
-  uint32_t *stamp = (uint32_t *)(dist + k);
-  int32_t *q0 = (int32_t *)(stamp + k);
-  int32_t *q1 = q0 + k;
-  for (int32_t s = blockIdx.x; s < k; s += gridDim.x) sssp_block(k, rp, col, w, s, dist, stamp, q0, q1, phi);
+// Bytes of a search's arrays for ids of `id` bytes, the distances first.
+__host__ __device__ inline size_t search_bytes(int32_t k, size_t id) {
+  return (size_t)k * 8 + (((size_t)k + 31) / 32) * 4 + 2 * (size_t)k * id;
 }
 
-__global__ void __launch_bounds__(kT) k_apsp_global(int32_t k, const int64_t *rp, const int32_t *col,
-                                                    const uint64_t *w, uint64_t *phi, char *slices,
-                                                    const uint32_t *bad) {
-  if (*bad) return;
-  char *base = slices + slice_bytes(k) * blockIdx.x;
+template <class Id>
+__device__ __forceinline__ Search<Id> place(char *base, int32_t k) {
   uint64_t *dist = (uint64_t *)base;
-  uint32_t *stamp = (uint32_t *)(dist + k);
-  int32_t *q0 = (int32_t *)(stamp + k);
-  int32_t *q1 = q0 + k;
-  for (int32_t s = blockIdx.x; s < k; s += gridDim.x) sssp_block(k, rp, col, w, s, dist, stamp, q0, q1, phi);
+  uint32_t *queued = (uint32_t *)(dist + k);
+  Id *q = (Id *)(queued + (k + 31) / 32);
+  return Search<Id>{dist, {q, q + k}, queued};
 }
 
-int grid_for(int32_t k) { return k < 1024 ? k : 1024; }
-
-// Fresh control block (a kernel rather than a memset node, so that a caller
-// may capture the call in a graph).
-__global__ void k_zero_ctl(ECtl *ctl) {
-  if (threadIdx.x == 0) { ctl->phi = 0; ctl->bad = 0; ctl->pad = 0; }
+// Takes sources in the order i * step mod k until none is left; ub[v] bounds
+// v's eccentricity from above.
+template <class Graph, class Id>
+__device__ __forceinline__ void search_all(int32_t k, const Graph &g, const Search<Id> &x, uint64_t *ub, uint32_t step,
+                                           ECtl *ctl) {
+  __shared__ int32_t src;
+  for (;;) {
+    if (threadIdx.x == 0) {
+      for (;;) {
+        const uint32_t i = atomicAdd(&ctl->next, 1u);
+        src = i < (uint32_t)k ? (int32_t)((uint64_t)i * step % (uint32_t)k) : -1;
+        if (src < 0) break;
+        const unsigned long long found = __hip_atomic_load(&ctl->phi, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (__hip_atomic_load(&ub[src], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) > found) break;
+      }
+    }
+    __syncthreads();
+    const int32_t s = src;
+    if (s < 0) return;
+    const unsigned long long ecc = sssp_block(k, g, s, x);
+    if (threadIdx.x == 0) atomicMax(&ctl->phi, ecc);
+    for (int32_t v = threadIdx.x; v < k; v += kSearchT) {
+      const uint64_t d = x.dist[v];
+      if (d != CLD_INF64 && d + ecc >= ecc) atomicMin((unsigned long long *)&ub[v], (unsigned long long)(d + ecc));
+    }
+    __syncthreads();
+  }
 }
 
-// Checks, APSP and readback, with the control block and the per-workgroup
-// slices already placed; `grid` workgroups take the sources in turn.
+// The graph's copy follows the search's arrays (from an 8-byte boundary).
+__host__ __device__ inline size_t copy_at(int32_t k) { return (search_bytes(k, 2) + 7) & ~(size_t)7; }
+__host__ __device__ inline size_t resident_bytes(int32_t k, int64_t qm) {
+  return copy_at(k) + (size_t)qm * 10 + ((size_t)k + 1) * 4;
+}
+
+template <bool kResident>
+__global__ void __launch_bounds__(kSearchT) k_apsp_lds(int32_t k, int64_t qm, Csr g, uint64_t *ub, uint32_t step,
+                                                       ECtl *ctl) {
+  if (ctl->bad) return;
+  extern __shared__ uint64_t lds[];
+  const Search<uint16_t> x = place<uint16_t>((char *)lds, k);
+  if (kResident) {
+    uint64_t *w = (uint64_t *)((char *)lds + copy_at(k));
+    uint32_t *rp = (uint32_t *)(w + qm);
+    uint16_t *col = (uint16_t *)(rp + k + 1);
+    for (int32_t a = threadIdx.x; a < (int32_t)qm; a += kSearchT) {
+      w[a] = g.w[a];
+      col[a] = (uint16_t)g.col[a];
+    }
+    for (int32_t v = threadIdx.x; v <= k; v += kSearchT) rp[v] = (uint32_t)g.rp[v];
+    __syncthreads();
+    search_all(k, LdsCsr{rp, col, w}, x, ub, step, ctl);
+  } else {
+    search_all(k, g, x, ub, step, ctl);
+  }
+}
+
+__global__ void __launch_bounds__(kSearchT) k_apsp_global(int32_t k, Csr g, uint64_t *ub, uint32_t step, ECtl *ctl,
+                                                          char *slices) {
+  if (ctl->bad) return;
+  search_all(k, g, place<int32_t>(slices + slice_bytes(k) * blockIdx.x, k), ub, step, ctl);
+}
+
+// A step near k / golden ratio without a common divisor with k: multiples of
+// it visit every node, far apart.
+uint32_t spread_step(int32_t k) {
+  uint32_t step = (uint32_t)((uint64_t)k * 618033989u / 1000000000u);
+  if (step < 1) step = 1;
+  while (std::gcd(step, (uint32_t)k) != 1) ++step;
+  return step;
+}
+
+// Workgroups at most (each with a slice of global memory above kLdsMaxK).
+int grid_for(int32_t k) { return k < kMaxSearches ? k : kMaxSearches; }
+
+// Fresh control block and bounds (a kernel rather than a memset node, so that a
+// caller may capture the call in a graph).
+__global__ void __launch_bounds__(kT) k_zero_ctl(ECtl *ctl, uint64_t *ub, int32_t k) {
+  const int64_t at = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  for (int64_t v = at; v < k; v += (int64_t)gridDim.x * blockDim.x) ub[v] = CLD_INF64;
+  if (at == 0) { ctl->phi = 0; ctl->next = 0; ctl->bad = 0; }
+}
+
+// Checks, APSP and readback, with the control block, the bounds and the
+// per-workgroup slices already placed; `grid` workgroups take the sources.
 int estimate_run(int32_t k, int64_t qm, const int64_t *rp, const int32_t *col, const uint64_t *w, uint64_t radius,
-                 uint64_t *h_phi_gc, uint64_t *h_phi_approx, ECtl *ctl, char *slices, int grid, hipStream_t stream) {
-  k_zero_ctl<<<1, 64, 0, stream>>>(ctl);
+                 uint64_t *h_phi_gc, uint64_t *h_phi_approx, ECtl *ctl, uint64_t *ub, char *slices, int grid,
+                 hipStream_t stream) {
+  k_zero_ctl<<<cld::blocks_for(k, kT, 256), kT, 0, stream>>>(ctl, ub, k);
   CLD_LAUNCH_CHECK("k_zero_ctl");
   k_check_quotient<<<cld::blocks_for(k > qm ? (int64_t)k : qm, kT, 1024), kT, 0, stream>>>(k, qm, rp, col,
                                                                                            &ctl->bad);
   CLD_LAUNCH_CHECK("k_check_quotient");
-  if (k <= kLdsMaxK) {
-    k_apsp_lds<<<grid_for(k), kT, (size_t)k * 20, stream>>>(k, rp, col, w, (uint64_t *)&ctl->phi, &ctl->bad);
+  const uint32_t step = spread_step(k);
+  const Csr g{rp, col, w};
+  if (k > kLdsMaxK) {
+    k_apsp_global<<<grid, kSearchT, 0, stream>>>(k, g, ub, step, ctl, slices);
+  } else if (qm <= (int64_t)kLdsBytes && resident_bytes(k, qm) <= kLdsBytes) {
+    k_apsp_lds<true><<<grid, kSearchT, resident_bytes(k, qm), stream>>>(k, qm, g, ub, step, ctl);
   } else {
-    k_apsp_global<<<grid, kT, 0, stream>>>(k, rp, col, w, (uint64_t *)&ctl->phi, slices, &ctl->bad);
+    k_apsp_lds<false><<<grid, kSearchT, search_bytes(k, 2), stream>>>(k, qm, g, ub, step, ctl);
   }
   CLD_LAUNCH_CHECK("k_apsp");
   ECtl h;
@@ -143,10 +301,11 @@ int estimate_run(int32_t k, int64_t qm, const int64_t *rp, const int32_t *col, c
 
 // ----------------------------------------------- no-allocation variant --
 // Scratch of cldiam_estimate_diameter_noalloc: the control block at offset 0,
-// then the per-workgroup APSP slices of quotients above kLdsMaxK nodes.  Each
+// the bounds, then the per-workgroup APSP slices of quotients above kLdsMaxK nodes.  Each
 // device holds its own copy from the library's load until the process ends.
 constexpr size_t kStaticBytes = (size_t)32 << 20;
 constexpr size_t kStaticCtl = 256;
+constexpr size_t kStaticUb = (size_t)CLDIAM_NOALLOC_MAX_K * 8;   // the bounds, after the control block
 static_assert(sizeof(ECtl) <= kStaticCtl, "control block fits its slot");
 static __device__ __align__(256) char scratch[kStaticBytes];
 
@@ -176,9 +335,11 @@ int scratch_on_current_device(char **out) {
 extern "C" size_t cldiam_estimate_workspace_size(int32_t k, int64_t qm) {
   (void)qm;
   if (k < 1) return 0;
-  size_t s = 256;
-  if (k > kLdsMaxK) s += slice_bytes(k) * grid_for(k) + 256;
-  return s;
+  cld::Sizer s;
+  s.take<ECtl>(1);
+  s.take<uint64_t>((size_t)k);
+  if (k > kLdsMaxK) s.take<char>(slice_bytes(k) * grid_for(k));
+  return s.used;
 }
 
 extern "C" int cldiam_estimate_diameter(int32_t k, int64_t qm, const int64_t *d_qrow_ptr, const int32_t *d_qcol,
@@ -191,15 +352,16 @@ extern "C" int cldiam_estimate_diameter(int32_t k, int64_t qm, const int64_t *d_
   }
   cld::Arena a(ws, ws_bytes);
   ECtl *ctl = a.take<ECtl>(1);
+  uint64_t *ub = a.take<uint64_t>((size_t)k);
   char *slices = nullptr;
   if (k > kLdsMaxK) slices = a.take<char>(slice_bytes(k) * grid_for(k));
-  if (!ctl || (k > kLdsMaxK && !slices)) {
+  if (!ctl || !ub || (k > kLdsMaxK && !slices)) {
     cld::set_error("estimate_diameter: workspace of %zu bytes, %zu needed", ws_bytes,
                    cldiam_estimate_workspace_size(k, qm));
     return CLDIAM_ENOMEM;
   }
-  return estimate_run(k, qm, d_qrow_ptr, d_qcol, d_qw, radius, h_phi_gc, h_phi_approx, ctl, slices, grid_for(k),
-                      stream);
+  return estimate_run(k, qm, d_qrow_ptr, d_qcol, d_qw, radius, h_phi_gc, h_phi_approx, ctl, ub, slices,
+                      grid_for(k), stream);
 }
 
 extern "C" int cldiam_estimate_diameter_noalloc(int32_t k, int64_t qm, const int64_t *d_qrow_ptr,
@@ -221,9 +383,9 @@ extern "C" int cldiam_estimate_diameter_noalloc(int32_t k, int64_t qm, const int
   // as many workgroups as the slices that fit (at least 1 for every k up to the maximum)
   int grid = grid_for(k);
   if (k > kLdsMaxK) {
-    const size_t fit = (kStaticBytes - kStaticCtl) / slice_bytes(k);
+    const size_t fit = (kStaticBytes - kStaticCtl - kStaticUb) / slice_bytes(k);
     if ((size_t)grid > fit) grid = (int)fit;
   }
   return estimate_run(k, qm, d_qrow_ptr, d_qcol, d_qw, radius, h_phi_gc, h_phi_approx, (ECtl *)base,
-                      base + kStaticCtl, grid, stream);
+                      (uint64_t *)(base + kStaticCtl), base + kStaticCtl + kStaticUb, grid, stream);
 }

@@ -1,6 +1,6 @@
-"""Estimates of quotients with an odd number of nodes just past the LDS limit,
-whose distances live in per-workgroup slices of global memory: 64-bit
-distances have to be 8-byte aligned in every slice.  A ring's diameter is known
+"""Estimates of quotients with an odd number of nodes on both sides of the LDS
+limit.  Past it, distances live in per-workgroup slices of global memory:
+64-bit distances have to be 8-byte aligned in every slice.  A ring's diameter is known
 in closed form."""
 import ctypes
 import sys
@@ -13,7 +13,7 @@ import paper_1506_03265_amd as cd
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("k", [3073, 3075, 3077])
+@pytest.mark.parametrize("k", [3073, 3075, 12799, 12801])
 def test_ring_of_an_odd_number_of_clusters(k):
     import torch
     if not torch.cuda.is_available():
