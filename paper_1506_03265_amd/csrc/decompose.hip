@@ -146,7 +146,7 @@ struct GState {
   uint32_t pull_base;   // distance at which the current pulled level starts (its first bucket)
   uint32_t src_blk;     // the next stage's sources are the blocked set (no NEXT has filtered it)
   uint32_t records;     // some long row has a scan record
-  uint32_t pad;
+  uint32_t closed;      // one graph: done, and the books are closed (later sweeps return at once)
 };
 static_assert(sizeof(GState) % 4 == 0, "copied word by word");
 
@@ -202,7 +202,8 @@ struct Job {
   uint32_t *slim;    // with keyn: the light limit (Delta - d) of that scan; arcs up to it have been offered
   uint64_t *R;       // by center: largest D of its cluster after the last stage; CLUSTER2: birth iteration
   uint64_t *U;       // bitmap: uncovered nodes
-  uint64_t *F[4];    // bitmaps in the roles of GState
+  uint64_t *F;       // four bitmaps, one after the other, in the roles of GState
+  int64_t fwords;    // words of one
   int32_t G;
   int32_t nblocks;        // workgroups of a sweep launch
   uint32_t *hmirror = nullptr;   // host-driven job: mapped pinned words {control steps done, done flag} that
@@ -247,14 +248,14 @@ constexpr int64_t kHubShare = 8;    // ... holding more than 1/kHubShare of the 
 // ------------------------------------------------------------- control --
 
 // A failing graph stops alone; the other graphs of the job go on.
-__device__ void fail(GState &s, int status) {
+__device__ __forceinline__ void fail(GState &s, int status) {
   s.status = status;
   s.phase = PH_DONE;
 }
 
-__device__ void finish(const GDesc &d, GState &s);
+__device__ __forceinline__ void finish(const GDesc &d, GState &s);
 
-__device__ void begin_stage(const GDesc &d, GState &s) {
+__device__ __forceinline__ void begin_stage(const GDesc &d, GState &s) {
   s.centers = 0;
   s.cov = 0;
   if (s.nU == 0 || s.nU < d.stop || d.n < 2) {
@@ -303,7 +304,7 @@ __device__ __forceinline__ void begin_growth(const GDesc &d, GState &s, uint32_t
 }
 
 // CLUSTER2: iteration s.stage + 1 draws centers with probability 2^i / n.
-__device__ void c2_begin_iteration(const GDesc &d, GState &s) {
+__device__ __forceinline__ void c2_begin_iteration(const GDesc &d, GState &s) {
   const int i = (int)s.stage + 1;
   const double p = ldexp(1.0, i) / (double)d.n;
   s.T = p >= 1.0 ? ((uint64_t)1 << 32) : (uint64_t)floor(p * 4294967296.0);
@@ -362,7 +363,7 @@ __device__ __forceinline__ void log_stage(const GState &s, int32_t *log) {
 }
 
 // CLUSTER is complete (singletons included): the end, or CLUSTER2's start.
-__device__ void finish(const GDesc &d, GState &s) {
+__device__ __forceinline__ void finish(const GDesc &d, GState &s) {
   s.singletons = s.nU;
   s.phase = PH_DONE;
   if (d.variant != CLDIAM_VARIANT_CLUSTER2) return;
@@ -382,7 +383,7 @@ __device__ void finish(const GDesc &d, GState &s) {
 }
 
 // The stage's covered nodes are assigned and off the uncovered set.
-__device__ void end_stage(const GDesc &d, GState &s, int32_t *log) {
+__device__ __forceinline__ void end_stage(const GDesc &d, GState &s, int32_t *log) {
   log_stage(s, log);
   s.nU -= s.cov;
   s.stage++;
@@ -416,7 +417,7 @@ __device__ void end_stage(const GDesc &d, GState &s, int32_t *log) {
 
 // Transition of one graph after a sweep of its current phase, whose counters
 // are c.  log: its stage log (nullptr: another workgroup writes it).
-__device__ void control_graph(const GDesc &d, GState &s, const GCount &c, int32_t *log) {
+__device__ __forceinline__ void control_graph(const GDesc &d, GState &s, const GCount &c, int32_t *log) {
   s.arcs += c.arcs;
   s.records |= c.records;
   switch (s.phase) {
@@ -687,14 +688,14 @@ struct Stage {
       unsigned long long mx[kRmaxSlots];
     } rmax;
   };
-  uint32_t qn[2];
+  uint32_t qn[3];              // queued nodes, by round modulo 3
   uint32_t mid_cnt[2], big_cnt[2];   // of the even and the odd passes (see coop_rows)
   unsigned long long blk_min;  // workgroup minimum over a big row (NEXT, PULL)
   unsigned long long row_key;  // key of the big row being scanned
   int32_t row_lo;              // end of its light prefix (index within the row)
   int32_t row_start;           // first arc of its scan (index within the row)
   uint32_t blk_hit;
-  uint32_t wsum[kWaves];
+  uint32_t wsum[2][kWaves];
   uint32_t chunk;              // next chunk of this workgroup
   uint32_t stop;               // local rounds end early: most of the grid has finished the sweep
   GCount sum;                  // this workgroup's part of the sweep's counters
@@ -716,6 +717,7 @@ struct Run {
   uint32_t delta, theta, theta_row;
   bool resume;           // long rows resume their last scan
   uint32_t pass = 0;     // list passes so far
+  uint32_t q = 0, qslot = 0;   // queue and counter that improvements go to
   // per-thread sums
   uint32_t scanned = 0, heavy = 0;
   unsigned long long acc = 0;   // NEXT: min; ASSIGN: max; SELECT: hub arcs
@@ -742,9 +744,9 @@ __device__ __forceinline__ void mark_blocked(Run &r, int32_t u, uint64_t word, i
 __device__ __forceinline__ uint64_t marks_of(const Run &r, int32_t u) { return r.mark ? r.mark[u >> 6] : ~0ull; }
 
 // Applies a thread's K offers cand[i] to v[i] that beat the keys read
-// (better[i]) and queues them in queue q: one reservation per wave.
+// (better[i]) and queues them: one reservation per wave.
 template <int K>
-__device__ __forceinline__ void improve(Run &r, int q, const bool (&better)[K], const int32_t (&v)[K],
+__device__ __forceinline__ void improve(Run &r, const bool (&better)[K], const int32_t (&v)[K],
                                         const uint64_t (&cand)[K]) {
   const uint64_t below = (1ull << (threadIdx.x & 63)) - 1ull;
   uint32_t at[K], total = 0;
@@ -760,15 +762,15 @@ __device__ __forceinline__ void improve(Run &r, int q, const bool (&better)[K], 
   if (total) {
     uint32_t base = 0;
     const int first = __ffsll((long long)__ballot(true)) - 1;
-    if ((int)(threadIdx.x & 63) == first) base = atomicAdd(&r.S.qn[q], total);
+    if ((int)(threadIdx.x & 63) == first) base = atomicAdd(&r.S.qn[r.qslot], total);
     base = __shfl(base, first);
 #pragma unroll
     for (int i = 0; i < K; ++i) {
       if (!near[i]) continue;
       const uint32_t slot = base + at[i];
       if (slot < r.d.lq_cap) {
-        r.S.qv[q][slot] = v[i];
-        r.S.qk[q][slot] = cand[i];
+        r.S.qv[r.q][slot] = v[i];
+        r.S.qk[r.q][slot] = cand[i];
       } else {
         leave(r, v[i], (uint32_t)(cand[i] >> 32));
       }
@@ -799,7 +801,7 @@ __device__ __forceinline__ void improve_sync(Run &r, const bool (&better)[K], co
 // (w <= lim) are offered, the first heavy one ends the scan.  Returns the
 // number of light arcs; *blocked is set if a heavy one is among them.
 template <bool kSync, int K>
-__device__ __forceinline__ uint32_t offer(Run &r, int q, uint64_t ku, uint32_t lim, const bool (&in)[K],
+__device__ __forceinline__ uint32_t offer(Run &r, uint64_t ku, uint32_t lim, const bool (&in)[K],
                                           const uint64_t (&arc)[K], bool *blocked) {
   bool better[K];
   int32_t v[K];
@@ -820,7 +822,7 @@ __device__ __forceinline__ uint32_t offer(Run &r, int q, uint64_t ku, uint32_t l
     better[i] = kSync ? (cand[i] >> 32) < (k >> 32) && better[i] : cand[i] < k;   // no offer is below 0
   }
   if (kSync) improve_sync<K>(r, better, v, cand);
-  else improve<K>(r, q, better, v, cand);
+  else improve<K>(r, better, v, cand);
   return light;
 }
 
@@ -840,7 +842,7 @@ __device__ __forceinline__ bool defer_row(Run &r, int32_t u, int32_t deg) {
 // Relaxes u with key ku, four arcs of its row at a time so that their loads
 // overlap; long rows are deferred.
 template <bool kSync>
-__device__ __forceinline__ void relax_row(Run &r, int q, int32_t u, uint64_t ku, int64_t a0, int32_t deg) {
+__device__ __forceinline__ void relax_row(Run &r, int32_t u, uint64_t ku, int64_t a0, int32_t deg) {
   if (deg > r.d.mid_deg && defer_row(r, u, deg)) return;
   const uint64_t word = marks_of(r, u);
   const uint64_t *row = r.d.arcs + a0;
@@ -855,7 +857,7 @@ __device__ __forceinline__ void relax_row(Run &r, int q, int32_t u, uint64_t ku,
       in[i] = base + i < deg;
       arc[i] = in[i] ? row[base + i] : ~0ull;
     }
-    light += offer<kSync, kArcBatch>(r, q, ku, lim, in, arc, &blocked);
+    light += offer<kSync, kArcBatch>(r, ku, lim, in, arc, &blocked);
   }
   r.scanned += light;
   if (blocked) mark_blocked(r, u, word, deg - (int32_t)light);
@@ -870,18 +872,18 @@ __device__ __forceinline__ void relax_item(Run &r, int32_t u) {
   const uint32_t dist = (uint32_t)(ku >> 32);
   // beyond the current distance bucket: stays for a later sweep
   if (!kSync && (dist >= r.theta || (deg > r.d.mid_deg && dist >= r.theta_row))) leave(r, u, dist);
-  else relax_row<kSync>(r, 0, u, ku, a0, deg);
+  else relax_row<kSync>(r, u, ku, a0, deg);
 }
 
 // A queued improvement.
-__device__ __forceinline__ void relax_queued(Run &r, int q, int32_t u, uint64_t ku) {
+__device__ __forceinline__ void relax_queued(Run &r, int32_t u, uint64_t ku) {
   const uint64_t now = r.key[u];
   const int64_t a0 = r.d.row_ptr[u];
   const int32_t deg = (int32_t)(r.d.row_ptr[u + 1] - a0);
   if (now < ku) return;   // improved again since: another entry's business
   const uint32_t dist = (uint32_t)(ku >> 32);
   if (deg > r.d.mid_deg && dist >= r.theta_row) leave(r, u, dist);
-  else relax_row<false>(r, q, u, ku, a0, deg);
+  else relax_row<false>(r, u, ku, a0, deg);
 }
 
 // NEXT for a short row: smallest d_u + w over its heavy arcs (w > Delta - d_u)
@@ -986,7 +988,7 @@ __device__ __forceinline__ void coop_rows(Run &r, Mid mid, Big big) {
 }
 
 template <bool kSync>
-__device__ __forceinline__ void relax_long(Run &r, int q) {
+__device__ __forceinline__ void relax_long(Run &r) {
   const int32_t lane = (int32_t)(threadIdx.x & 63), tid = (int32_t)threadIdx.x;
   auto mid = [&](int32_t u, const uint64_t *row, int32_t deg) {
     const uint64_t word = marks_of(r, u), ku = r.key[u];
@@ -1003,7 +1005,7 @@ __device__ __forceinline__ void relax_long(Run &r, int q) {
         in[i] = a < deg;
         arc[i] = in[i] ? row[a] : ~0ull;
       }
-      uint32_t light = offer<kSync, kArcBatch>(r, q, ku, lim, in, arc, &blocked);
+      uint32_t light = offer<kSync, kArcBatch>(r, ku, lim, in, arc, &blocked);
       r.scanned += light;
       any = __any(blocked);
       for (int o = 32; o >= 1; o >>= 1) light += __shfl_xor(light, o);
@@ -1041,7 +1043,7 @@ __device__ __forceinline__ void relax_long(Run &r, int q) {
         in[i] = a < lo;
         arc[i] = in[i] ? row[a] : ~0ull;
       }
-      r.scanned += offer<kSync, kArcBatch>(r, q, ku, lim, in, arc, &blocked);
+      r.scanned += offer<kSync, kArcBatch>(r, ku, lim, in, arc, &blocked);
     }
     if (threadIdx.x == 0 && lo < deg) mark_blocked(r, u, marks_of(r, u), deg - lo);
     __syncthreads();
@@ -1257,24 +1259,19 @@ __device__ __forceinline__ void list_pass(Run &r, uint32_t lo, uint32_t hi, Word
   Stage &S = r.S;
   const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   uint64_t ahead = lo + tid < hi ? word(lo + tid) : 0ull;
+  uint32_t window = 0;
   for (uint32_t w0 = lo; w0 < hi; w0 += kSweepThreads) {
     const uint64_t mine = ahead;
     const uint32_t w = w0 + tid;
     ahead = w + kSweepThreads < hi ? word(w + kSweepThreads) : 0ull;
     const uint32_t count = (uint32_t)__popcll(mine);
-    uint32_t incl = count;
-    for (int o = 1; o < 64; o <<= 1) {
-      const uint32_t y = __shfl_up(incl, o);
-      if (lane >= (uint32_t)o) incl += y;
-    }
+    const uint32_t incl = cld_wave_scan_u32(count);
+    uint32_t *wsum = S.wsum[window++ & 1];   // the window before may still be read
+    if (lane == 63) wsum[wave] = incl;
     __syncthreads();
-    if (lane == 63) S.wsum[wave] = incl;
-    __syncthreads();
-    uint32_t at = incl - count, total = 0;
-    for (uint32_t k = 0; k < (uint32_t)kWaves; ++k) {
-      if (k < wave) at += S.wsum[k];
-      total += S.wsum[k];
-    }
+    const uint32_t ws = lane < (uint32_t)kWaves ? wsum[lane] : 0u, wincl = cld_wave_scan_u32(ws);
+    const uint32_t total = cld_last_lane(wincl);
+    const uint32_t at = incl - count + (uint32_t)__shfl(wincl - ws, (int)wave);
     const bool dense = __any(count > 8);
     for (uint32_t r0 = 0; r0 < total; r0 += kList) {
       if (dense) {
@@ -1350,14 +1347,14 @@ __device__ __forceinline__ void process_run(const Job &job, const GDesc &d, cons
   const uint32_t woff = (uint32_t)(d.off >> 6);
   const bool steps = d.variant == CLDIAM_VARIANT_STEPS;
   uint64_t *U = job.U + woff, *R = job.R + d.off;
-  uint64_t *blk = job.F[s.blk] + woff, *alt = job.F[s.alt] + woff;
+  uint64_t *F = job.F + woff, *blk = F + s.blk * job.fwords, *alt = F + s.alt * job.fwords;
   const uint32_t row_lim = row_limit(d, s.delta, s.row_base);
-  Run r{job, d, s, S, job.key + d.off, job.keyn + d.off, job.slim + d.off, job.F[s.cur] + woff, job.F[s.nxt] + woff,
-        s.pull ? nullptr : (s.merge ? alt : blk), s.delta, s.theta, row_lim < s.theta ? row_lim : s.theta,
+  Run r{job, d, s, S, job.key + d.off, job.keyn + d.off, job.slim + d.off, F + s.cur * job.fwords,
+        F + s.nxt * job.fwords, s.pull ? nullptr : (s.merge ? alt : blk), s.delta, s.theta, row_lim < s.theta ? row_lim : s.theta,
         !steps && !s.c2};
   if (threadIdx.x == 0) {
     clear_count(S.sum);
-    S.qn[0] = S.qn[1] = 0;
+    S.qn[0] = S.qn[1] = S.qn[2] = 0;
     S.mid_cnt[0] = S.mid_cnt[1] = S.big_cnt[0] = S.big_cnt[1] = 0;
     S.stop = 0;
   }
@@ -1419,10 +1416,10 @@ __device__ __forceinline__ void process_run(const Job &job, const GDesc &d, cons
                     }
                     return x;
                   },
-                  [&](int32_t u) { relax_item<true>(r, u); }, [&] { relax_long<true>(r, 0); });
+                  [&](int32_t u) { relax_item<true>(r, u); }, [&] { relax_long<true>(r); });
       } else {
         list_pass(r, lo, hi, [&](uint32_t w) { const uint64_t x = r.cur[w]; if (x) r.cur[w] = 0; return x; },
-                  [&](int32_t u) { relax_item<false>(r, u); }, [&] { relax_long<false>(r, 0); });
+                  [&](int32_t u) { relax_item<false>(r, u); }, [&] { relax_long<false>(r); });
       }
       break;
     case PH_COMMIT: {
@@ -1516,7 +1513,7 @@ __device__ __forceinline__ void process_run(const Job &job, const GDesc &d, cons
       for (uint32_t w = lo + threadIdx.x; w < hi; w += kSweepThreads) {
         const int64_t left = (int64_t)d.n - ((int64_t)w << 6);
         U[w] = left >= 64 ? ~0ull : (1ull << left) - 1ull;
-        for (int i = 0; i < 4; ++i) job.F[i][woff + w] = 0;
+        for (int i = 0; i < 4; ++i) F[i * job.fwords + w] = 0;
       }
       for (int64_t v = ((int64_t)lo << 6) + threadIdx.x; v < ((int64_t)hi << 6) && v < d.n; v += kSweepThreads)
         r.key[v] = CLD_INF64;
@@ -1544,43 +1541,57 @@ __device__ __forceinline__ void process_run(const Job &job, const GDesc &d, cons
   }
   if (phase == PH_RELAX && !steps) {
     // Local rounds: relax the nodes that this workgroup improved.  What is
-    // left when they end stays for the next sweep.
+    // left when they end stays for the next sweep.  Round i reads queue i & 1
+    // and counter i % 3 and fills the other queue and the next counter; the
+    // third counter is cleared meanwhile, so the barrier that ends a round's
+    // last pass is the only one.
+    uint32_t n = 0, slot = 0;
     int q = 0;
-    uint32_t n = 0;
+    __syncthreads();
     for (int round = 0;; ++round) {
-      __syncthreads();
-      n = S.qn[q] < d.lq_cap ? S.qn[q] : d.lq_cap;
-      if (n == 0 || S.stop || round >= d.local_rounds) break;
-      __syncthreads();
-      if (threadIdx.x == 0) {
-        S.qn[q ^ 1] = 0;
-        S.stop = job.cutoff < (uint32_t)job.nblocks &&
-                 __hip_atomic_load(idle, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= job.cutoff;
+      n = S.qn[slot] < d.lq_cap ? S.qn[slot] : d.lq_cap;
+      if (n == 0 || round >= d.local_rounds) break;
+      if (job.cutoff < (uint32_t)job.nblocks) {
+        if (threadIdx.x == 0)
+          S.stop = __hip_atomic_load(idle, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= job.cutoff;
+        __syncthreads();
+        const uint32_t stop = S.stop;
+        __syncthreads();
+        if (stop) break;
       }
-      __syncthreads();
+      r.q = q ^ 1;
+      r.qslot = slot == 2 ? 0 : slot + 1;
+      if (threadIdx.x == 0) S.qn[slot == 0 ? 2 : slot - 1] = 0;
       for (uint32_t i = threadIdx.x; i - threadIdx.x < n; i += kSweepThreads) {
-        if (i < n) relax_queued(r, q ^ 1, S.qv[q][i], S.qk[q][i]);
-        relax_long<false>(r, q ^ 1);
+        if (i < n) relax_queued(r, S.qv[q][i], S.qk[q][i]);
+        relax_long<false>(r);
       }
       q ^= 1;
+      slot = r.qslot;
     }
     for (uint32_t i = threadIdx.x; i < n; i += kSweepThreads) leave(r, S.qv[q][i], (uint32_t)(S.qk[q][i] >> 32));
   }
   // fold the threads' and waves' sums
   const bool is_min = phase == PH_NEXT || phase == PH_NEXT_PULL;
-  for (int o = 32; o >= 1; o >>= 1) {
-    r.scanned += __shfl_xor(r.scanned, o);
-    r.heavy += __shfl_xor(r.heavy, o);
-    const unsigned long long y = __shfl_xor(r.acc, o);
-    r.acc = is_min ? (y < r.acc ? y : r.acc) : (phase == PH_SELECT ? r.acc + y : (y > r.acc ? y : r.acc));
+  if (is_growth(phase) || phase == PH_C2_SELECT) {
+    r.scanned = cld_last_lane(cld_wave_scan_u32(r.scanned));
+    r.heavy = cld_last_lane(cld_wave_scan_u32(r.heavy));
   }
+  if (phase != PH_RELAX && __any(r.acc != (is_min ? CLD_INF64 : 0ull)))
+    for (int o = 32; o >= 1; o >>= 1) {
+      const unsigned long long y = __shfl_xor(r.acc, o);
+      r.acc = is_min ? (y < r.acc ? y : r.acc) : (phase == PH_SELECT ? r.acc + y : (y > r.acc ? y : r.acc));
+    }
   if (lane == 0) {
     if (r.scanned) atomicAdd(&S.sum.arcs, (unsigned long long)r.scanned);
     if (r.heavy) atomicAdd(&S.sum.blk_arcs, (unsigned long long)r.heavy);
     if (cov) atomicAdd(&S.sum.cov, cov);
-    if (is_min) atomicMin(&S.sum.next, r.acc);
-    else if (phase == PH_SELECT) atomicAdd(&S.sum.hub_arcs, r.acc);
-    else if (r.acc) atomicMax(&S.sum.radius, r.acc);
+    if (is_min) {
+      if (r.acc != CLD_INF64) atomicMin(&S.sum.next, r.acc);
+    } else if (r.acc) {
+      if (phase == PH_SELECT) atomicAdd(&S.sum.hub_arcs, r.acc);
+      else atomicMax(&S.sum.radius, r.acc);
+    }
   }
   __syncthreads();
   if (table) {
@@ -1658,18 +1669,21 @@ __device__ __forceinline__ void sweep_many(const Job &job, uint32_t block, uint3
 
 // Sweep t (from 1) of a job of one graph, its control step included; false
 // when the graph is done.
-__device__ __forceinline__ bool sweep_one(const Job &job, uint32_t t, uint32_t block, uint32_t nblocks, Stage &S) {
+__device__ __forceinline__ bool sweep_one(const Job &job, const GDesc &d, uint32_t t, uint32_t block,
+                                          uint32_t nblocks, Stage &S) {
   Ctl *ctl = job.ctl;
-  const GDesc &d = job.desc[0];
   const uint32_t tid = threadIdx.x;
   const uint32_t *st = (const uint32_t *)&job.ring[(t - 1) & 1], *cn = (const uint32_t *)&job.cn[(t + 2) % 3];
   for (uint32_t i = tid; i < sizeof(GState) / 4; i += kSweepThreads) ((uint32_t *)&S.st)[i] = st[i];
   for (uint32_t i = tid; i < sizeof(GCount) / 4; i += kSweepThreads) ((uint32_t *)&S.last)[i] = cn[i];
   __syncthreads();
-  if (tid == 0) control_graph(d, S.st, S.last, block == 0 ? job.log : nullptr);
+  if (S.st.closed) return false;
+  // the last workgroup, which has no chunk in a small graph, keeps the books
+  const bool books = block == nblocks - 1;
+  if (tid == 0) control_graph(d, S.st, S.last, books ? job.log : nullptr);
   __syncthreads();
   const bool done = S.st.phase == PH_DONE;
-  if (block == 0) {
+  if (books) {
     uint32_t *to = (uint32_t *)&job.ring[t & 1], *fin = (uint32_t *)&job.st[0];
     for (uint32_t i = tid; i < sizeof(GState) / 4; i += kSweepThreads) {
       const uint32_t x = ((const uint32_t *)&S.st)[i];
@@ -1686,7 +1700,10 @@ __device__ __forceinline__ bool sweep_one(const Job &job, uint32_t t, uint32_t b
       ctl->sc[(t + 1) % 3].cursor = 0;
       ctl->sc[(t + 1) % 3].idle = 0;
       ctl->iterations = t;
-      if (done) ctl->done = 1;
+      if (done) {
+        ctl->done = 1;
+        job.ring[0].closed = job.ring[1].closed = 1;   // whichever the next sweep reads
+      }
       report(job, t, done ? 1u : 0u);
     }
   }
@@ -1725,7 +1742,7 @@ __global__ void __launch_bounds__(256) k_init(Job job, int32_t first) {
   for (int64_t w = at; w < d.words; w += stride) {
     const int64_t left = (int64_t)d.n - (w << 6);
     job.U[woff + w] = left >= 64 ? ~0ull : (1ull << left) - 1ull;
-    for (int i = 0; i < 4; ++i) job.F[i][woff + w] = 0;
+    for (int i = 0; i < 4; ++i) job.F[i * job.fwords + woff + w] = 0;
   }
 }
 
@@ -1743,15 +1760,16 @@ __global__ void __launch_bounds__(kSweepThreads, kCuThreads / kSweepThreads) k_s
   sweep_many(job, blockIdx.x, gridDim.x, S);
 }
 
-__global__ void __launch_bounds__(kSweepThreads, kCuThreads / kSweepThreads) k_sweep(Job job, uint32_t t) {
+// The descriptor comes as an argument: reading it from memory field by field
+// delayed every sweep by 1 to 2 us.
+__global__ void __launch_bounds__(kSweepThreads, kCuThreads / kSweepThreads) k_sweep(Job job, GDesc d, uint32_t t) {
   __shared__ Stage S;
-  if (job.ctl->done) return;
-  sweep_one(job, t, blockIdx.x, gridDim.x, S);
+  sweep_one(job, d, t, blockIdx.x, gridDim.x, S);
 }
 
-void launch_step(const Job &job, bool one, uint32_t t, hipStream_t stream) {
+void launch_step(const Job &job, const GDesc *one, uint32_t t, hipStream_t stream) {
   if (one) {
-    k_sweep<<<job.nblocks, kSweepThreads, 0, stream>>>(job, t);
+    k_sweep<<<job.nblocks, kSweepThreads, 0, stream>>>(job, *one, t);
     return;
   }
   if (job.G <= kSmallControl) k_control<kSmallControl><<<1, kSmallControl, 0, stream>>>(job);
@@ -1763,7 +1781,7 @@ __global__ void __launch_bounds__(kSweepThreads, kCuThreads / kSweepThreads) k_p
   __shared__ Stage S;
   const uint32_t nb = gridDim.x;
   if (job.G == 1) {
-    for (uint32_t t = 1; sweep_one(job, t, blockIdx.x, nb, S); ++t)
+    for (uint32_t t = 1; sweep_one(job, job.desc[0], t, blockIdx.x, nb, S); ++t)
       if (!cld_grid_barrier(&job.ctl->bar, &job.ctl->timeout, nb)) return;
     return;
   }
@@ -1789,7 +1807,8 @@ struct Layout {
   int32_t *log;
   uint64_t *key, *keyn, *R;
   uint32_t *slim;
-  uint64_t *U, *F[4];
+  uint64_t *U, *F;
+  int64_t fwords;
 };
 
 // Every graph's nodes start at a multiple of 64, so that its bitmap words are
@@ -1811,14 +1830,14 @@ bool carve(A &a, int64_t N, int32_t G, Layout *L) {
   auto p_keyn = a.template take<uint64_t>(N);
   auto p_R = a.template take<uint64_t>(N);
   auto p_slim = a.template take<uint32_t>(N);
-  void *b[5];
-  for (auto &x : b) x = a.template take<uint64_t>(N / 64);
+  auto p_U = a.template take<uint64_t>(N / 64);
+  auto p_F = a.template take<uint64_t>(4 * (N / 64));
   if (L) {
     *L = Layout{(GDesc *)p_desc, (char *)p_st, (size_t)((char *)p_cn - (char *)p_st), (GState *)p_st,
                 (GState *)p_ring, (GCount *)p_cn, (Ctl *)p_ctl, (uint32_t *)p_seg, (int32_t *)p_log,
-                (uint64_t *)p_key, (uint64_t *)p_keyn, (uint64_t *)p_R, (uint32_t *)p_slim, (uint64_t *)b[0],
-                {(uint64_t *)b[1], (uint64_t *)b[2], (uint64_t *)b[3], (uint64_t *)b[4]}};
-    return p_desc && b[4];
+                (uint64_t *)p_key, (uint64_t *)p_keyn, (uint64_t *)p_R, (uint32_t *)p_slim, (uint64_t *)p_U,
+                (uint64_t *)p_F, N / 64};
+    return p_desc && p_F;
   }
   return true;
 }
@@ -1827,7 +1846,7 @@ Job make_job(const Layout &L, int32_t G) {
   Job job{};
   job.desc = L.desc; job.st = L.st; job.ring = L.ring; job.cn = L.cn; job.ctl = L.ctl; job.seg = L.seg;
   job.log = L.log; job.key = L.key; job.keyn = L.keyn; job.R = L.R; job.slim = L.slim; job.U = L.U;
-  for (int i = 0; i < 4; ++i) job.F[i] = L.F[i];
+  job.F = L.F; job.fwords = L.fwords;
   job.G = G;
   return job;
 }
@@ -2104,7 +2123,7 @@ extern "C" int cldiam_decompose_batch(int32_t G, const cldiam_graph *gs, cldiam_
     for (;;) {
       if (hm[1]) break;
       if (queued < hm[0] + kLeadSteps) {
-        launch_step(job, one, ++queued, stream);
+        launch_step(job, one ? &desc[0] : nullptr, ++queued, stream);
         if ((queued & 15u) == 0) CLD_LAUNCH_CHECK("k_sweep");
         continue;
       }
@@ -2343,7 +2362,7 @@ extern "C" int cldiam_server_step(cldiam_server *s, int32_t max_sweeps, int32_t 
   if (nactive > 0 && max_sweeps > 0) {
     CLD_HIP(hipMemsetAsync(&job.ctl->iterations, 0, sizeof(uint32_t), stream));
     for (int i = 0; i < max_sweeps; ++i) {
-      launch_step(job, false, 0, stream);
+      launch_step(job, nullptr, 0, stream);
     }
     CLD_LAUNCH_CHECK("k_sweep");
     CLD_HIP(hipMemcpyAsync(s->st_host.data(), job.st, sizeof(GState) * s->gcap, hipMemcpyDeviceToHost, stream));
