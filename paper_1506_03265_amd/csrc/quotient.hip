@@ -1,14 +1,15 @@
 // Weighted quotient graph G_C (Section 4 of arXiv:1506.03265).
 //
-// Clusters are numbered densely by ascending center id (a scan over the
-// center flags).  Every arc u->v of G whose endpoints lie in different
-// clusters emits the pair key (a, b) = (cluster index of u, of v), packed as
-// a << kb | b with kb = bits of k-1, and the weight w(u,v) + D_u + D_v.  A
-// radix sort over the 2*kb key bits groups equal pairs; the first element of
-// each run marks a quotient arc and an atomic minimum over the run keeps the
-// lightest parallel edge.  Because both arcs of every edge are emitted, the
-// sorted unique pairs are directly the symmetric CSR of G_C with rows sorted
-// by column.
+// Clusters are numbered densely by ascending center id (ranks in a bitmap of
+// the centers).  Every edge {u, v} of G whose endpoints lie in different
+// clusters a < b gives the pair key a << kb | b (kb = bits of k-1) and the
+// value w(u,v) + D_u + D_v.  Pairs are folded to their minimum in an LDS table
+// of each workgroup and then in one table in global memory.  When that table
+// holds them all (up to kTableMost pairs, a clustering of thousands of
+// clusters), one kernel ranks the keys of both directions and writes the CSR.
+// Pairs that find the table full go to a list instead; then the list and the
+// table's pairs are radix sorted, the first element of each run marks a
+// quotient arc and an atomic minimum over the run keeps the lightest.
 #include <vector>
 
 #include "common.h"
@@ -27,73 +28,201 @@ namespace {
 constexpr int kT = 256;
 
 struct QCtl {
-  unsigned long long pairs;   // emitted arcs
+  unsigned long long pairs;   // directed pairs on the list
   uint32_t k;
-  uint32_t uniq;    // quotient arcs
-  uint32_t wide;    // some D does not fit the packed node word
+  uint32_t uniq;    // pairs in the table (each stands for both directions); later: quotient arcs
   uint32_t bad;     // some label is out of range or not a center
+  uint32_t pad;
 };
 
-// Center flags; a label that is out of range or names a node that is not its
+// ------------------------------------------------------------ numbering --
+
+constexpr int kNumThreads = 1024;
+constexpr int kNumWaves = kNumThreads / 64;
+constexpr int kNumBlocks = 4096;    // wanted workgroups at most; a wave takes 4 to 64 bitmap words
+constexpr int kPackBlocks = 512;
+
+// Bitmap of the centers and ranks in it: words[w] holds nodes 64 w .. 64 w + 63,
+// before[w] counts the centers of the workgroup's earlier words, total[] those
+// of each workgroup.
+struct Ranks {
+  uint64_t *words;
+  uint32_t *before;
+  uint32_t *total;
+  uint32_t per;      // words per workgroup
+  uint32_t blocks;
+};
+
+// Center bits; a label that is out of range or names a node that is not its
 // own center is reported (the caller then gets CLDIAM_EINVAL, no kernel
 // indexes with it).
-__global__ void k_center_flags(const int32_t *cluster, int32_t n, uint32_t *flag, QCtl *ctl) {
-  for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < n; v += (int64_t)gridDim.x * blockDim.x) {
-    const int32_t c = cluster[v];
-    flag[v] = c == (int32_t)v ? 1u : 0u;
-    if ((uint32_t)c >= (uint32_t)n || cluster[c] != c) ctl->bad = 1u;
+__global__ void __launch_bounds__(kNumThreads) k_centers(const int32_t *cluster, int32_t n, Ranks r, QCtl *ctl) {
+  __shared__ uint32_t wsum[kNumWaves];
+  const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const uint32_t nwords = (uint32_t)(((int64_t)n + 63) >> 6), wpw = r.per / kNumWaves;
+  const uint32_t w0 = blockIdx.x * r.per + wave * wpw;
+  uint64_t mine = 0;   // lane l keeps word w0 + l
+  bool bad = false;
+  for (uint32_t j = 0; j < wpw; j += 4) {
+    int32_t c[4];
+#pragma unroll
+    for (uint32_t i = 0; i < 4; ++i) {
+      const int64_t v = ((int64_t)(w0 + j + i) << 6) + lane;
+      c[i] = v < n ? cluster[v] : -1;
+    }
+#pragma unroll
+    for (uint32_t i = 0; i < 4; ++i) {
+      const int64_t v = ((int64_t)(w0 + j + i) << 6) + lane;
+      const bool center = v < n && c[i] == (int32_t)v;
+      if (v < n && !center) {
+        if ((uint32_t)c[i] >= (uint32_t)n) bad = true;
+        else if (cluster[c[i]] != c[i]) bad = true;
+      }
+      const uint64_t x = __ballot(center);
+      if (lane == j + i) mine = x;
+    }
   }
+  if (bad) ctl->bad = 1u;
+  const uint32_t count = (uint32_t)__popcll(mine), incl = cld_wave_scan_u32(count);
+  if (lane == 63) wsum[wave] = incl;
+  __syncthreads();
+  uint32_t at = incl - count, all = 0;
+  for (uint32_t i = 0; i < (uint32_t)kNumWaves; ++i) {
+    if (i < wave) at += wsum[i];
+    all += wsum[i];
+  }
+  if (lane < wpw && w0 + lane < nwords) {
+    r.words[w0 + lane] = mine;
+    r.before[w0 + lane] = at;
+  }
+  if (threadIdx.x == 0) r.total[blockIdx.x] = all;
 }
 
 __device__ __forceinline__ int bits_for_dev(uint32_t x) {  // bits needed for values 0..x, at least 1
   return x ? 32 - __clz(x) : 1;
 }
 
-// Node word of the packed emission: the dense cluster index in the top kb
-// bits (kb = bits of k-1, k counted by the scan), D in the low 64 - kb bits,
-// so that an arc's far end costs one 8-byte gather instead of three.  A D
-// that does not fit sets ctl->wide, and the emission then reads the plain
-// arrays instead.
-__global__ void k_pack_nodes(const int32_t *cluster, const uint64_t *D, const uint32_t *dense, int32_t n,
-                             QCtl *ctl, uint64_t *pk) {
-  const uint32_t k = ctl->k;
-  const int lb = 64 - bits_for_dev(k > 0 ? k - 1 : 0u);
-  for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < n; v += (int64_t)gridDim.x * blockDim.x) {
-    const uint64_t d = D[v];
-    const int32_t c = cluster[v];
-    if (d >> lb) ctl->wide = 1u;
-    pk[v] = (uint32_t)c < (uint32_t)n ? ((uint64_t)dense[c] << lb) | d : 0ull;   // bad labels fail the call
+// Dense cluster index of every node, 16 bits each while they suffice (an arc's
+// far end then costs a 2-byte gather), and the list of centers.
+__global__ void __launch_bounds__(kNumThreads) k_number(const int32_t *cluster, int32_t n, Ranks r, QCtl *ctl,
+                                                        void *cid, int32_t *qcenter) {
+  extern __shared__ uint32_t base[];   // centers before each workgroup of k_centers
+  __shared__ uint32_t wsum[kNumWaves];
+  if (ctl->bad) return;
+  const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const uint32_t each = (r.blocks + kNumThreads - 1) / kNumThreads;
+  uint32_t sum = 0;
+  for (uint32_t i = 0; i < each; ++i)
+    if (tid * each + i < r.blocks) sum += r.total[tid * each + i];
+  const uint32_t incl = cld_wave_scan_u32(sum);
+  if (lane == 63) wsum[wave] = incl;
+  __syncthreads();
+  uint32_t at = incl - sum, k = 0;
+  for (uint32_t i = 0; i < (uint32_t)kNumWaves; ++i) {
+    if (i < wave) at += wsum[i];
+    k += wsum[i];
+  }
+  for (uint32_t i = 0; i < each; ++i)
+    if (tid * each + i < r.blocks) {
+      base[tid * each + i] = at;
+      at += r.total[tid * each + i];
+    }
+  __syncthreads();
+  if (blockIdx.x == 0 && tid == 0) ctl->k = k;
+  const bool narrow = k <= 65536;
+  for (int64_t v = (int64_t)blockIdx.x * kNumThreads + tid; v < n; v += (int64_t)gridDim.x * kNumThreads) {
+    const uint32_t c = (uint32_t)cluster[v], w = c >> 6;
+    const uint32_t id = base[w / r.per] + r.before[w] + (uint32_t)__popcll(r.words[w] & ((1ull << (c & 63)) - 1ull));
+    if (narrow) ((uint16_t *)cid)[v] = (uint16_t)id;
+    else ((uint32_t *)cid)[v] = id;
+    if (c == (uint32_t)v) qcenter[id] = (int32_t)v;
   }
 }
 
-__global__ void k_center_list(const int32_t *cluster, int32_t n, const uint32_t *dense, int32_t *qcenter) {
-  for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < n; v += (int64_t)gridDim.x * blockDim.x)
-    if (cluster[v] == (int32_t)v) qcenter[dense[v]] = (int32_t)v;
+// ------------------------------------------------------------- emission --
+
+// The table of all pairs in global memory.
+constexpr uint32_t kTableSlots = 32768;
+constexpr uint32_t kTableMost = 8192;   // pairs the table is meant for (a few more may slip in)
+constexpr int kTableProbes = 32;
+
+struct Table {
+  unsigned long long *key, *val;
+  uint32_t *slot;              // slots in the order they were taken
+  uint64_t *keys, *vals;       // the list: directed pairs
+  QCtl *ctl;
+  int kb;
+};
+
+__global__ void __launch_bounds__(kT) k_clear(Table t) {
+  const uint32_t at = blockIdx.x * blockDim.x + threadIdx.x;
+  for (uint32_t i = at; i < kTableSlots; i += gridDim.x * blockDim.x) {
+    t.key[i] = ~0ull;
+    t.val[i] = ~0ull;
+  }
+  if (at == 0) *t.ctl = QCtl{};
 }
 
-// Emission of inter-cluster arcs.  Each workgroup takes a contiguous range of
-// rows; rows of up to kEmitThreadDeg arcs are walked by one thread, longer rows
-// are deferred to LDS and walked by one wave (64 arcs per step) or, above
-// kEmitBlockDeg, by the whole workgroup.  Every pair (key, weight) first goes
-// into an LDS hash table of the workgroup that keeps the minimum weight per key
-// (the same minimum the quotient keeps), so only distinct pairs reach global
-// memory: the table is written out, with one global reservation, whenever it
-// is half full after a round and at the end.  A pair that finds no slot after
-// a few probes goes straight to global memory.
+__device__ __forceinline__ uint64_t reversed(uint64_t key, int kb) {
+  return (key & ((1ull << kb) - 1ull)) << kb | key >> kb;
+}
+
+__device__ void put_pair(const Table &t, uint64_t key, uint64_t val) {
+  uint32_t h = (uint32_t)((key * 0xD6E8FEB86659FD93ull) >> 44) & (kTableSlots - 1);
+  for (int p = 0; p < kTableProbes; ++p) {
+    unsigned long long at = t.key[h];
+    if (at == ~0ull) {
+      if (__hip_atomic_load(&t.ctl->uniq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= kTableMost) break;
+      at = atomicCAS(&t.key[h], ~0ull, (unsigned long long)key);
+      if (at == ~0ull) {
+        t.slot[atomicAdd(&t.ctl->uniq, 1u)] = h;
+        at = key;
+      }
+    }
+    if (at == key) {
+      if (val < t.val[h]) atomicMin(&t.val[h], (unsigned long long)val);
+      return;
+    }
+    h = (h + 1) & (kTableSlots - 1);
+  }
+  const unsigned long long at = atomicAdd(&t.ctl->pairs, 2ull);
+  t.keys[at] = key;
+  t.vals[at] = val;
+  t.keys[at + 1] = reversed(key, t.kb);
+  t.vals[at + 1] = val;
+}
+
+// Each workgroup takes a contiguous range of rows; rows of up to
+// kEmitThreadDeg arcs are walked by one thread, longer rows are deferred to LDS
+// and walked by one wave (64 lanes) or, above kEmitBlockDeg, by the whole
+// workgroup.  Every pair first goes into an LDS hash table of the workgroup
+// that keeps the minimum per key, and from there, whenever it is half full
+// after a round and at the end, to the table of all pairs.  A pair that finds
+// no slot after a few probes goes straight there.
+//
+// Bound by the gathers of the arcs' far ends (260 million on R-MAT scale 24).
+// So a far end's 2-byte cluster index is read first; most arcs end there: both
+// ends in one cluster, or the arc's weight plus the near end's D already no
+// better than the pair's value in the LDS table (R-MAT's few large clusters:
+// 61% of the arcs join two, and their values fall early), and D is read for
+// the rest only.  R-MAT scale 24: 3.55 ms (6.65 with an 8-byte word of index and
+// D gathered for every arc, both directions folded apart), scale 18: 0.11
+// (0.24), the road-like 4096 x 4096 mesh: 0.30 (0.32).
 constexpr int kEmitThreads = 1024;
 constexpr int kEmitThreadDeg = 16;
 constexpr int kEmitBlockDeg = 4096;
 constexpr int kEmitDefer = 512;     // deferred rows per round
 constexpr int kHashCap = 4096;      // LDS hash slots (power of two)
 constexpr int kHashProbes = 16;
+constexpr int kEmitBatch = 4;       // arcs of a row in flight per thread
 
 struct EmitState {
   unsigned long long hkey[kHashCap];
   unsigned long long hval[kHashCap];
   int32_t mid[kEmitDefer];
   int32_t big[kEmitDefer];
-  unsigned long long base;
-  uint32_t nmid, nbig, used, cursor;
+  uint32_t nmid, nbig, used;
+  Table table;
 };
 
 __device__ __forceinline__ uint32_t hash_slot(uint64_t key) {
@@ -101,35 +230,43 @@ __device__ __forceinline__ uint32_t hash_slot(uint64_t key) {
   return (uint32_t)(x >> 40) & (kHashCap - 1);
 }
 
-__device__ __forceinline__ void emit_pair(EmitState &E, uint64_t key, uint64_t val, uint64_t *keys, uint64_t *vals,
-                                          QCtl *ctl) {
+// Whether the LDS table holds a value for key that is no larger than x.
+__device__ __forceinline__ bool no_better(const EmitState &E, uint64_t key, uint64_t x) {
   uint32_t h = hash_slot(key);
   for (int p = 0; p < kHashProbes; ++p) {
-    const unsigned long long k = atomicCAS(&E.hkey[h], ~0ull, (unsigned long long)key);
-    if (k == ~0ull) atomicAdd(&E.used, 1u);
-    if (k == ~0ull || k == key) {
+    const unsigned long long at = E.hkey[h];
+    if (at == key) return E.hval[h] <= x;
+    if (at == ~0ull) return false;
+    h = (h + 1) & (kHashCap - 1);
+  }
+  return false;
+}
+
+__device__ __forceinline__ void emit_pair(EmitState &E, uint64_t key, uint64_t val) {
+  uint32_t h = hash_slot(key);
+  for (int p = 0; p < kHashProbes; ++p) {
+    unsigned long long at = E.hkey[h];
+    if (at == ~0ull) {
+      at = atomicCAS(&E.hkey[h], ~0ull, (unsigned long long)key);
+      if (at == ~0ull) {
+        atomicAdd(&E.used, 1u);
+        at = key;
+      }
+    }
+    if (at == key) {
       atomicMin(&E.hval[h], (unsigned long long)val);
       return;
     }
     h = (h + 1) & (kHashCap - 1);
   }
-  const unsigned long long at = atomicAdd(&ctl->pairs, 1ull);
-  keys[at] = key;
-  vals[at] = val;
+  put_pair(E.table, key, val);
 }
 
-__device__ void hash_flush(EmitState &E, uint64_t *keys, uint64_t *vals, QCtl *ctl) {
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    E.base = E.used ? atomicAdd(&ctl->pairs, (unsigned long long)E.used) : 0ull;
-    E.cursor = 0;
-  }
+__device__ void hash_flush(EmitState &E) {
   __syncthreads();
   for (uint32_t i = threadIdx.x; i < kHashCap; i += blockDim.x) {
     if (E.hkey[i] != ~0ull) {
-      const unsigned long long at = E.base + atomicAdd(&E.cursor, 1u);
-      keys[at] = E.hkey[i];
-      vals[at] = E.hval[i];
+      put_pair(E.table, E.hkey[i], E.hval[i]);
       E.hkey[i] = ~0ull;
       E.hval[i] = ~0ull;
     }
@@ -147,84 +284,53 @@ struct PairCache {
   uint64_t key = ~0ull, val = ~0ull;
 };
 
-__device__ __forceinline__ void cache_pair(PairCache &pc, uint64_t key, uint64_t val, EmitState &E, uint64_t *keys,
-                                           uint64_t *vals, QCtl *ctl) {
-  if (key == pc.key) {
-    if (val < pc.val) pc.val = val;
-    return;
-  }
-  if (pc.key != ~0ull) emit_pair(E, pc.key, pc.val, keys, vals, ctl);
-  pc.key = key;
-  pc.val = val;
-}
-
-__device__ __forceinline__ void cache_flush(PairCache &pc, EmitState &E, uint64_t *keys, uint64_t *vals, QCtl *ctl) {
-  if (pc.key != ~0ull) emit_pair(E, pc.key, pc.val, keys, vals, ctl);
+__device__ __forceinline__ void cache_flush(PairCache &pc, EmitState &E) {
+  if (pc.key != ~0ull) emit_pair(E, pc.key, pc.val);
   pc.key = ~0ull;
 }
 
-// Node-side inputs of the emission: either cluster ids, D and the dense
-// numbering, or the packed words of k_pack_nodes.
-struct NodeIn {
-  const int32_t *cluster;
-  const uint64_t *D;
-  const uint32_t *dense;
-  const uint64_t *pk;
-  int lb;
-};
-
-// Cluster tag (cluster id, or dense index when packed), D and the key's
-// high part of node u.
-template <bool kPacked>
-__device__ __forceinline__ void node_of(const NodeIn &in, int32_t u, int kb, uint32_t *cu, uint64_t *du,
-                                        uint64_t *ka) {
-  if (kPacked) {
-    const uint64_t x = in.pk[u];
-    *cu = (uint32_t)(x >> in.lb);
-    *du = x & ((1ull << in.lb) - 1ull);
-    *ka = (uint64_t)*cu << kb;
-  } else {
-    *cu = (uint32_t)in.cluster[u];
-    *du = in.D[u];
-    *ka = (uint64_t)in.dense[*cu] << kb;
+// Arcs first, first + stride, ... of u's row.  The graph is symmetric with
+// equal weights both ways and w + D_u + D_v is symmetric, so each edge is taken
+// once, from its smaller end (u < v).
+template <class Id>
+__device__ __forceinline__ void emit_row(int32_t u, const uint64_t *row, int32_t deg, int32_t first, int32_t stride,
+                                         const Id *cid, const uint64_t *D, EmitState &E, int kb) {
+  const uint32_t cu = cid[u];
+  const uint64_t du = D[u];
+  PairCache pc;
+  for (int32_t a = first; a < deg; a += stride * kEmitBatch) {
+    uint64_t arc[kEmitBatch];
+    uint32_t cv[kEmitBatch];
+#pragma unroll
+    for (int i = 0; i < kEmitBatch; ++i) arc[i] = a + i * stride < deg ? row[a + i * stride] : 0ull;
+#pragma unroll
+    for (int i = 0; i < kEmitBatch; ++i) cv[i] = (int32_t)(uint32_t)arc[i] > u ? cid[(uint32_t)arc[i]] : cu;
+#pragma unroll
+    for (int i = 0; i < kEmitBatch; ++i) {
+      if (cv[i] == cu) continue;
+      const uint64_t key = cu < cv[i] ? (uint64_t)cu << kb | cv[i] : (uint64_t)cv[i] << kb | cu;
+      const uint64_t least = (arc[i] >> 32) + du;
+      if (key == pc.key) {
+        if (least >= pc.val) continue;
+      } else if (no_better(E, key, least)) {
+        continue;
+      }
+      const uint64_t val = least + D[(uint32_t)arc[i]];
+      if (key != pc.key) {
+        cache_flush(pc, E);
+        pc.key = key;
+        pc.val = val;
+      } else if (val < pc.val) {
+        pc.val = val;
+      }
+    }
   }
+  cache_flush(pc, E);
 }
 
-// The graph is symmetric with equal weights both ways and w + D_u + D_v is
-// symmetric, so each edge is taken once, from its smaller end (u < v), and
-// gives both directed pairs: half the far-end gathers of walking every arc.
-// pc folds the pairs out of u's cluster, rc those into it.
-template <bool kPacked>
-__device__ __forceinline__ void emit_arc(uint64_t arc, int32_t u, uint32_t cu, uint64_t du, uint64_t ka, int kb,
-                                         const NodeIn &in, PairCache &pc, PairCache &rc, EmitState &E,
-                                         uint64_t *keys, uint64_t *vals, QCtl *ctl) {
-  const int32_t v = (int32_t)(uint32_t)arc;
-  if (v < u) return;
-  const uint64_t da = ka >> kb;   // dense index of u's cluster
-  uint64_t db, val;
-  if (kPacked) {
-    const uint64_t x = in.pk[v];
-    const uint32_t cv = (uint32_t)(x >> in.lb);
-    if (cv == cu) return;
-    db = cv;
-    val = (arc >> 32) + du + (x & ((1ull << in.lb) - 1ull));
-  } else {
-    const int32_t cv = in.cluster[v];
-    if ((uint32_t)cv == cu) return;
-    db = in.dense[cv];
-    val = (arc >> 32) + du + in.D[v];
-  }
-  cache_pair(pc, ka | db, val, E, keys, vals, ctl);
-  cache_pair(rc, (db << kb) | da, val, E, keys, vals, ctl);
-}
-
-template <bool kPacked>
-__global__ void __launch_bounds__(kEmitThreads) k_emit(const int64_t *rp, const uint64_t *arcs, int32_t n, NodeIn in,
-                                                       int kb, uint64_t *keys, uint64_t *vals, QCtl *ctl) {
-  __shared__ EmitState E;
-  for (uint32_t i = threadIdx.x; i < kHashCap; i += blockDim.x) { E.hkey[i] = ~0ull; E.hval[i] = ~0ull; }
-  if (threadIdx.x == 0) { E.nmid = 0; E.nbig = 0; E.used = 0; }
-  __syncthreads();
+template <class Id>
+__device__ __forceinline__ void emit_rows(const int64_t *rp, const uint64_t *arcs, int32_t n, const Id *cid,
+                                          const uint64_t *D, EmitState &E, int kb) {
   const int64_t per = ((int64_t)n + gridDim.x - 1) / gridDim.x;
   const int64_t lo = (int64_t)blockIdx.x * per;
   const int64_t hi = lo + per < n ? lo + per : n;
@@ -241,57 +347,103 @@ __global__ void __launch_bounds__(kEmitThreads) k_emit(const int64_t *rp, const 
         const uint32_t slot = atomicAdd(cnt, 1u);
         if (slot < kEmitDefer) { lst[slot] = (int32_t)u; done = true; }
       }
-      if (!done) {
-        uint32_t cu;
-        uint64_t du, ka;
-        node_of<kPacked>(in, (int32_t)u, kb, &cu, &du, &ka);
-        const uint64_t *row = arcs + a0;
-        PairCache pc, rc;
-        for (int32_t a = 0; a < deg; ++a)
-          emit_arc<kPacked>(row[a], (int32_t)u, cu, du, ka, kb, in, pc, rc, E, keys, vals, ctl);
-        cache_flush(pc, E, keys, vals, ctl);
-        cache_flush(rc, E, keys, vals, ctl);
-      }
+      if (!done) emit_row((int32_t)u, arcs + a0, deg, 0, 1, cid, D, E, kb);
     }
     __syncthreads();
     const uint32_t nm = E.nmid < kEmitDefer ? E.nmid : kEmitDefer;
     for (uint32_t i = wave; i < nm; i += nwaves) {
-      const int32_t u = E.mid[i];
-      const int64_t a0 = rp[u];
-      const int32_t deg = (int32_t)(rp[u + 1] - a0);
-      const uint64_t *row = arcs + a0;
-      uint32_t cu;
-      uint64_t du, ka;
-      node_of<kPacked>(in, u, kb, &cu, &du, &ka);
-      PairCache pc, rc;
-      for (int32_t a = (int32_t)lane; a < deg; a += 64)
-        emit_arc<kPacked>(row[a], u, cu, du, ka, kb, in, pc, rc, E, keys, vals, ctl);
-      cache_flush(pc, E, keys, vals, ctl);
-      cache_flush(rc, E, keys, vals, ctl);
+      const int32_t x = E.mid[i];
+      const int64_t a0 = rp[x];
+      emit_row(x, arcs + a0, (int32_t)(rp[x + 1] - a0), (int32_t)lane, 64, cid, D, E, kb);
     }
     const uint32_t nbg = E.nbig < kEmitDefer ? E.nbig : kEmitDefer;
     for (uint32_t i = 0; i < nbg; ++i) {
-      const int32_t u = E.big[i];
-      const int64_t a0 = rp[u];
-      const int32_t deg = (int32_t)(rp[u + 1] - a0);
-      const uint64_t *row = arcs + a0;
-      uint32_t cu;
-      uint64_t du, ka;
-      node_of<kPacked>(in, u, kb, &cu, &du, &ka);
-      PairCache pc, rc;
-      for (int32_t a = (int32_t)threadIdx.x; a < deg; a += (int32_t)blockDim.x)
-        emit_arc<kPacked>(row[a], u, cu, du, ka, kb, in, pc, rc, E, keys, vals, ctl);
-      cache_flush(pc, E, keys, vals, ctl);
-      cache_flush(rc, E, keys, vals, ctl);
+      const int32_t x = E.big[i];
+      const int64_t a0 = rp[x];
+      emit_row(x, arcs + a0, (int32_t)(rp[x + 1] - a0), (int32_t)threadIdx.x, kEmitThreads, cid, D, E, kb);
       __syncthreads();
-      if (E.used > kHashCap / 2) hash_flush(E, keys, vals, ctl);
+      const bool full = E.used > kHashCap / 2;
+      __syncthreads();
+      if (full) hash_flush(E);
     }
     __syncthreads();
+    const bool full = E.used > kHashCap / 2;
     if (threadIdx.x == 0) { E.nmid = 0; E.nbig = 0; }
     __syncthreads();
-    if (E.used > kHashCap / 2) hash_flush(E, keys, vals, ctl);
+    if (full) hash_flush(E);
   }
-  hash_flush(E, keys, vals, ctl);
+  hash_flush(E);
+}
+
+__global__ void __launch_bounds__(kEmitThreads, 8) k_emit(const int64_t *rp, const uint64_t *arcs, int32_t n,
+                                                       const void *cid, const uint64_t *D, Table t) {
+  __shared__ EmitState E;
+  if (t.ctl->bad) return;
+  const uint32_t k = t.ctl->k;
+  const int kb = bits_for_dev(k > 0 ? k - 1 : 0u);
+  for (uint32_t i = threadIdx.x; i < kHashCap; i += blockDim.x) { E.hkey[i] = ~0ull; E.hval[i] = ~0ull; }
+  if (threadIdx.x == 0) {
+    E.nmid = 0; E.nbig = 0; E.used = 0;
+    E.table = t;
+    E.table.kb = kb;
+  }
+  __syncthreads();
+  if (k <= 65536) emit_rows(rp, arcs, n, (const uint16_t *)cid, D, E, kb);
+  else emit_rows(rp, arcs, n, (const uint32_t *)cid, D, E, kb);
+}
+
+// -------------------------------------------------------------- ranking --
+
+// With all pairs in the table: every workgroup holds the keys of both
+// directions in LDS, and each wave counts, for its keys and row starts, the
+// keys below: a key's rank is its place in the CSR, a row's its offset.
+// 4 to 11 us for 300 to 12,000 arcs, where sorting, marking and reducing runs of
+// the unfolded pairs took 15 launches, two host synchronisations and 150 to 250.
+constexpr int kRankThreads = 1024;
+constexpr int kRankBlocks = 128;
+constexpr uint32_t kRankMostK = 16384;
+
+__device__ __host__ inline bool table_holds_all(const QCtl &c) {
+  return !c.bad && c.pairs == 0 && c.uniq <= kTableMost && c.k <= kRankMostK;
+}
+
+__global__ void __launch_bounds__(kRankThreads) k_rank(Table t, int32_t *qcol, uint64_t *qw, int64_t *qrp) {
+  extern __shared__ uint64_t keys[];
+  const QCtl c = *t.ctl;
+  if (!table_holds_all(c)) return;
+  const int kb = bits_for_dev(c.k > 0 ? c.k - 1 : 0u);
+  const uint32_t lane = threadIdx.x & 63, n = 2 * c.uniq;
+  for (uint32_t i = threadIdx.x; i < c.uniq; i += kRankThreads) {
+    const uint64_t key = t.key[t.slot[i]];
+    keys[2 * i] = key;
+    keys[2 * i + 1] = reversed(key, kb);
+  }
+  __syncthreads();
+  const uint32_t waves = gridDim.x * (kRankThreads / 64);
+  for (uint32_t e = blockIdx.x * (kRankThreads / 64) + (threadIdx.x >> 6); e < n + c.k + 1; e += waves) {
+    const uint64_t x = e < n ? keys[e] : (uint64_t)(e - n) << kb;
+    uint32_t below = 0;
+    for (uint32_t i = lane; i < n; i += 64) below += keys[i] < x;
+    below = cld_last_lane(cld_wave_scan_u32(below));
+    if (lane != 0) continue;
+    if (e < n) {
+      qcol[below] = (int32_t)(x & ((1ull << kb) - 1ull));
+      qw[below] = t.val[t.slot[e >> 1]];
+    } else {
+      qrp[e - n] = below;
+    }
+  }
+}
+
+// The table's pairs join the list.
+__global__ void __launch_bounds__(kT) k_table_to_list(Table t, uint32_t uniq, uint64_t pairs) {
+  for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < uniq; i += gridDim.x * blockDim.x) {
+    const uint64_t key = t.key[t.slot[i]], val = t.val[t.slot[i]];
+    t.keys[pairs + 2 * i] = key;
+    t.vals[pairs + 2 * i] = val;
+    t.keys[pairs + 2 * i + 1] = reversed(key, t.kb);
+    t.vals[pairs + 2 * i + 1] = val;
+  }
 }
 
 __global__ void k_heads(const uint64_t *keys, int64_t P, uint32_t *head) {
@@ -349,19 +501,45 @@ int bits_for(uint32_t x) {  // bits needed for values 0..x
 
 constexpr int kEmitBlocks = 2048;
 
+struct Buffers {
+  Ranks ranks;
+  Table table;
+  void *cid;
+  uint64_t *ktmp, *vtmp;
+  uint32_t *head, *idx;
+  bool fits;
+};
+
+// Words per workgroup of k_centers: 4 to 64 per wave.
+uint32_t words_per_block(int32_t n) {
+  const int64_t words = ((int64_t)n + 63) >> 6;
+  int64_t wpw = (words + (int64_t)kNumBlocks * kNumWaves - 1) / ((int64_t)kNumBlocks * kNumWaves);
+  wpw = wpw < 4 ? 4 : (wpw > 64 ? 64 : (wpw + 3) / 4 * 4);
+  return (uint32_t)(wpw * kNumWaves);
+}
+
 template <class A>
-void carve(A &a, int32_t n, int64_t m, uint32_t **flag, uint32_t **dense, QCtl **ctl, uint64_t **keys,
-           uint64_t **vals, uint64_t **ktmp, uint64_t **vtmp, uint32_t **head, uint32_t **idx, uint64_t **pk) {
-  *ctl = a.template take<QCtl>(1);
-  *pk = a.template take<uint64_t>((size_t)n);
-  *flag = a.template take<uint32_t>((size_t)n);
-  *dense = a.template take<uint32_t>((size_t)n);
-  *keys = a.template take<uint64_t>((size_t)m + 1);
-  *vals = a.template take<uint64_t>((size_t)m + 1);
-  *ktmp = a.template take<uint64_t>((size_t)m + 1);
-  *vtmp = a.template take<uint64_t>((size_t)m + 1);
-  *head = a.template take<uint32_t>((size_t)m + 1);
-  *idx = a.template take<uint32_t>((size_t)m + 1);
+Buffers carve(A &a, int32_t n, int64_t m) {
+  Buffers b{};
+  const size_t words = ((size_t)n + 63) / 64;
+  b.ranks.per = words_per_block(n);
+  b.ranks.blocks = (uint32_t)((words + b.ranks.per - 1) / b.ranks.per);
+  b.table.ctl = a.template take<QCtl>(1);
+  b.ranks.words = a.template take<uint64_t>(words);
+  b.ranks.before = a.template take<uint32_t>(words);
+  b.ranks.total = a.template take<uint32_t>(b.ranks.blocks);
+  b.cid = a.template take<uint32_t>((size_t)n);
+  b.table.key = a.template take<unsigned long long>(kTableSlots);
+  b.table.val = a.template take<unsigned long long>(kTableSlots);
+  b.table.slot = a.template take<uint32_t>(kTableSlots);
+  b.table.keys = a.template take<uint64_t>((size_t)m + 1);
+  b.table.vals = a.template take<uint64_t>((size_t)m + 1);
+  b.ktmp = a.template take<uint64_t>((size_t)m + 1);
+  b.vtmp = a.template take<uint64_t>((size_t)m + 1);
+  b.head = a.template take<uint32_t>((size_t)m + 1);
+  b.idx = a.template take<uint32_t>((size_t)m + 1);
+  b.fits = b.idx != nullptr;
+  return b;
 }
 
 struct SizeA {
@@ -375,13 +553,9 @@ struct SizeA {
 extern "C" size_t cldiam_quotient_workspace_size(int32_t n, int64_t m) {
   if (n < 1 || m < 0) return 0;
   SizeA s;
-  uint32_t *f, *d, *h, *x;
-  QCtl *c;
-  uint64_t *k, *v, *kt, *vt;
-  uint64_t *pk;
-  carve(s, n, m, &f, &d, &c, &k, &v, &kt, &vt, &h, &x, &pk);
+  carve(s, n, m);
   size_t extra = cld::radix_ws_bytes(m + 1);
-  size_t sc = cld::scan_ws_bytes((int64_t)n > m + 1 ? (int64_t)n : m + 1);
+  size_t sc = cld::scan_ws_bytes(m + 1);
   return s.s.used + (extra > sc ? extra : sc);
 }
 
@@ -396,57 +570,59 @@ extern "C" int cldiam_build_quotient(int32_t n, int64_t m, const int64_t *d_row_
     return CLDIAM_EINVAL;
   }
   cld::Arena a(ws, ws_bytes);
-  uint32_t *flag, *dense, *head, *idx;
-  QCtl *ctl;
-  uint64_t *keys, *vals, *ktmp, *vtmp;
-  uint64_t *pk;
-  carve(a, n, m, &flag, &dense, &ctl, &keys, &vals, &ktmp, &vtmp, &head, &idx, &pk);
-  if (!idx || a.used > ws_bytes) {
+  Buffers b = carve(a, n, m);
+  if (!b.fits || a.used > ws_bytes) {
     cld::set_error("build_quotient: workspace of %zu bytes, %zu needed", ws_bytes, cldiam_quotient_workspace_size(n, m));
     return CLDIAM_ENOMEM;
   }
   void *rest = a.base + a.used;
   const size_t rest_bytes = a.cap - a.used;
-  CLD_HIP(hipMemsetAsync(ctl, 0, sizeof(QCtl), stream));
-  k_center_flags<<<cld::blocks_for(n, kT, 8192), kT, 0, stream>>>(d_cluster, n, flag, ctl);
-  CLD_LAUNCH_CHECK("k_center_flags");
-  int rc = cld::scan_exclusive_u32(flag, dense, n, &ctl->k, rest, rest_bytes, stream);
-  if (rc) return rc;
-  k_center_list<<<cld::blocks_for(n, kT, 8192), kT, 0, stream>>>(d_cluster, n, dense, d_qcenter);
-  CLD_LAUNCH_CHECK("k_center_list");
+  QCtl *ctl = b.table.ctl;
+  k_clear<<<32, kT, 0, stream>>>(b.table);
+  CLD_LAUNCH_CHECK("k_clear");
+  k_centers<<<b.ranks.blocks, kNumThreads, 0, stream>>>(d_cluster, n, b.ranks, ctl);
+  CLD_LAUNCH_CHECK("k_centers");
+  k_number<<<cld::blocks_for(n, kNumThreads, kPackBlocks), kNumThreads, (size_t)b.ranks.blocks * 4, stream>>>(
+      d_cluster, n, b.ranks, ctl, b.cid, d_qcenter);
+  CLD_LAUNCH_CHECK("k_number");
   if (m > 0) {
-    k_pack_nodes<<<cld::blocks_for(n, kT, 8192), kT, 0, stream>>>(d_cluster, d_D, dense, n, ctl, pk);
-    CLD_LAUNCH_CHECK("k_pack_nodes");
+    const unsigned eb = (unsigned)(n < kEmitBlocks * 64 ? (n + 63) / 64 : kEmitBlocks);
+    k_emit<<<eb, kEmitThreads, 0, stream>>>(d_row_ptr, d_arcs, n, b.cid, d_D, b.table);
+    CLD_LAUNCH_CHECK("k_emit");
   }
-  QCtl h;
-  CLD_HIP(hipMemcpyAsync(&h, ctl, sizeof h, hipMemcpyDeviceToHost, stream));
+  k_rank<<<kRankBlocks, kRankThreads, (size_t)2 * kTableMost * 8, stream>>>(b.table, d_qcol, d_qw, d_qrow_ptr);
+  CLD_LAUNCH_CHECK("k_rank");
+  cld::Pinned<QCtl> pinned;
+  if (!pinned.p) { cld::set_error("build_quotient: pinned host buffer allocation failed"); return CLDIAM_EHIP; }
+  CLD_HIP(hipMemcpyAsync(pinned.p, ctl, sizeof(QCtl), hipMemcpyDeviceToHost, stream));
   CLD_HIP(hipStreamSynchronize(stream));
+  const QCtl h = *pinned.p;
   if (h.bad) {
     cld::set_error("build_quotient: a cluster label is out of range or not a center (cluster[c] != c)");
     return CLDIAM_EINVAL;
   }
   const int32_t k = (int32_t)h.k;
-  const int kb = bits_for(k > 0 ? (uint32_t)(k - 1) : 0u);
-  if (m > 0) {
-    const unsigned eb = (unsigned)(n < kEmitBlocks * 64 ? (n + 63) / 64 : kEmitBlocks);
-    NodeIn in{d_cluster, d_D, dense, pk, 64 - kb};
-    if (!h.wide) {   // every D fits beside the cluster index
-      k_emit<true><<<eb, kEmitThreads, 0, stream>>>(d_row_ptr, d_arcs, n, in, kb, keys, vals, ctl);
-    } else {
-      k_emit<false><<<eb, kEmitThreads, 0, stream>>>(d_row_ptr, d_arcs, n, in, kb, keys, vals, ctl);
-    }
-    CLD_LAUNCH_CHECK("k_emit");
+  if (table_holds_all(h)) {
+    *h_k = k;
+    *h_qm = 2 * (int64_t)h.uniq;
+    return CLDIAM_OK;
   }
-  CLD_HIP(hipMemcpyAsync(&h, ctl, sizeof h, hipMemcpyDeviceToHost, stream));
-  CLD_HIP(hipStreamSynchronize(stream));
-  const int64_t P = (int64_t)h.pairs;
+  const int kb = bits_for(k > 0 ? (uint32_t)(k - 1) : 0u);
+  b.table.kb = kb;
+  if (h.uniq) {
+    k_table_to_list<<<cld::blocks_for(h.uniq, kT, 256), kT, 0, stream>>>(b.table, h.uniq, h.pairs);
+    CLD_LAUNCH_CHECK("k_table_to_list");
+  }
+  const int64_t P = (int64_t)h.pairs + 2 * (int64_t)h.uniq;
   if (P >= (int64_t)0xffffffff) {
     cld::set_error("build_quotient: %lld distinct cluster pairs exceed the 2^32 - 1 the run numbering holds",
                    (long long)P);
     return CLDIAM_EOVERFLOW;
   }
+  uint64_t *keys = b.table.keys, *vals = b.table.vals, *ktmp = b.ktmp, *vtmp = b.vtmp;
+  uint32_t *head = b.head, *idx = b.idx;
   bool in_tmp = false;
-  rc = cld::radix_sort_u64(keys, vals, P, 0, 2 * kb, ktmp, vtmp, &in_tmp, rest, rest_bytes, stream);
+  int rc = cld::radix_sort_u64(keys, vals, P, 0, 2 * kb, ktmp, vtmp, &in_tmp, rest, rest_bytes, stream);
   if (rc) return rc;
   const uint64_t *sk = in_tmp ? ktmp : keys;
   const uint64_t *sv = in_tmp ? vtmp : vals;
@@ -456,9 +632,9 @@ extern "C" int cldiam_build_quotient(int32_t n, int64_t m, const int64_t *d_row_
     CLD_LAUNCH_CHECK("k_heads");
     rc = cld::scan_exclusive_u32(head, idx, P, &ctl->uniq, rest, rest_bytes, stream);
     if (rc) return rc;
-    CLD_HIP(hipMemcpyAsync(&h, ctl, sizeof h, hipMemcpyDeviceToHost, stream));
+    CLD_HIP(hipMemcpyAsync(pinned.p, ctl, sizeof(QCtl), hipMemcpyDeviceToHost, stream));
     CLD_HIP(hipStreamSynchronize(stream));
-    uniq = h.uniq;
+    uniq = pinned.p->uniq;
     k_fill_inf<<<cld::blocks_for(uniq, kT, 8192), kT, 0, stream>>>(d_qw, uniq);
     CLD_LAUNCH_CHECK("k_fill_inf");
     k_reduce_runs<<<cld::blocks_for((P + kRunChunk - 1) / kRunChunk, kT, 8192), kT, 0, stream>>>(sk, sv, P, head, idx, kb, d_qcol, d_qw,
