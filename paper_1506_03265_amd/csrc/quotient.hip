@@ -32,7 +32,7 @@ struct QCtl {
   uint32_t k;
   uint32_t uniq;    // pairs in the table (each stands for both directions); later: quotient arcs
   uint32_t bad;     // some label is out of range or not a center
-  uint32_t pad;
+  uint32_t chunk;   // chunks of rows taken beyond each workgroup's first
 };
 
 // ------------------------------------------------------------ numbering --
@@ -167,20 +167,25 @@ __device__ __forceinline__ uint64_t reversed(uint64_t key, int kb) {
   return (key & ((1ull << kb) - 1ull)) << kb | key >> kb;
 }
 
-__device__ void put_pair(const Table &t, uint64_t key, uint64_t val) {
+// Lowers key's value in the table; a new key's slot is noted in claims[] (up to
+// claim_cap, counted in *claimed) for one reservation later, or at once.
+__device__ void put_pair(const Table &t, bool full, uint64_t key, uint64_t val, int32_t *claims, uint32_t claim_cap,
+                         uint32_t *claimed) {
   uint32_t h = (uint32_t)((key * 0xD6E8FEB86659FD93ull) >> 44) & (kTableSlots - 1);
   for (int p = 0; p < kTableProbes; ++p) {
-    unsigned long long at = t.key[h];
+    unsigned long long at = __hip_atomic_load(&t.key[h], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (at == ~0ull) {
-      if (__hip_atomic_load(&t.ctl->uniq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= kTableMost) break;
+      if (full) break;
       at = atomicCAS(&t.key[h], ~0ull, (unsigned long long)key);
       if (at == ~0ull) {
-        t.slot[atomicAdd(&t.ctl->uniq, 1u)] = h;
+        const uint32_t i = claim_cap ? atomicAdd(claimed, 1u) : 0u;
+        if (i < claim_cap) claims[i] = (int32_t)h;
+        else t.slot[atomicAdd(&t.ctl->uniq, 1u)] = h;
         at = key;
       }
     }
     if (at == key) {
-      if (val < t.val[h]) atomicMin(&t.val[h], (unsigned long long)val);
+      if (val < __hip_atomic_load(&t.val[h], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMin(&t.val[h], (unsigned long long)val);
       return;
     }
     h = (h + 1) & (kTableSlots - 1);
@@ -192,7 +197,8 @@ __device__ void put_pair(const Table &t, uint64_t key, uint64_t val) {
   t.vals[at + 1] = val;
 }
 
-// Each workgroup takes a contiguous range of rows; rows of up to
+// The rows are cut into up to kEmitChunks chunks, the first of each workgroup
+// fixed, the others for whichever is free (hubs make them unequal); rows of up to
 // kEmitThreadDeg arcs are walked by one thread, longer rows are deferred to LDS
 // and walked by one wave (64 lanes) or, above kEmitBlockDeg, by the whole
 // workgroup.  Every pair first goes into an LDS hash table of the workgroup
@@ -222,6 +228,8 @@ struct EmitState {
   int32_t mid[kEmitDefer];
   int32_t big[kEmitDefer];
   uint32_t nmid, nbig, used;
+  uint32_t chunk, base;
+  uint32_t full;   // the table of all pairs takes no new keys (as read at the last flush)
   Table table;
 };
 
@@ -259,20 +267,35 @@ __device__ __forceinline__ void emit_pair(EmitState &E, uint64_t key, uint64_t v
     }
     h = (h + 1) & (kHashCap - 1);
   }
-  put_pair(E.table, key, val);
+  put_pair(E.table, E.full != 0, key, val, nullptr, 0, nullptr);
 }
 
 __device__ void hash_flush(EmitState &E) {
+  // One look at the count and one reservation per flush: with one of each per
+  // new key, the count's line took 200 of the arc pass's 300 us on a road-like
+  // 2048 x 2048 mesh of 2228 clusters.
+  if (threadIdx.x == 0) {
+    E.nmid = 0;   // E.mid holds the slots of new keys meanwhile: their count is reserved once
+    E.full = __hip_atomic_load(&E.table.ctl->uniq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= kTableMost;
+  }
   __syncthreads();
   for (uint32_t i = threadIdx.x; i < kHashCap; i += blockDim.x) {
     if (E.hkey[i] != ~0ull) {
-      put_pair(E.table, E.hkey[i], E.hval[i]);
+      put_pair(E.table, E.full != 0, E.hkey[i], E.hval[i], E.mid, kEmitDefer, &E.nmid);
       E.hkey[i] = ~0ull;
       E.hval[i] = ~0ull;
     }
   }
   __syncthreads();
-  if (threadIdx.x == 0) E.used = 0;
+  const uint32_t n = E.nmid < kEmitDefer ? E.nmid : kEmitDefer;
+  if (threadIdx.x == 0) {
+    E.used = 0;
+    E.base = n ? atomicAdd(&E.table.ctl->uniq, n) : 0u;
+  }
+  __syncthreads();
+  for (uint32_t i = threadIdx.x; i < n; i += blockDim.x) E.table.slot[E.base + i] = (uint32_t)E.mid[i];
+  __syncthreads();
+  if (threadIdx.x == 0) E.nmid = 0;
   __syncthreads();
 }
 
@@ -330,11 +353,10 @@ __device__ __forceinline__ void emit_row(int32_t u, const uint64_t *row, int32_t
 
 template <class Id>
 __device__ __forceinline__ void emit_rows(const int64_t *rp, const uint64_t *arcs, int32_t n, const Id *cid,
-                                          const uint64_t *D, EmitState &E, int kb) {
-  const int64_t per = ((int64_t)n + gridDim.x - 1) / gridDim.x;
-  const int64_t lo = (int64_t)blockIdx.x * per;
-  const int64_t hi = lo + per < n ? lo + per : n;
+                                          const uint64_t *D, EmitState &E, int kb, uint32_t chunk, int64_t per) {
   const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nwaves = blockDim.x >> 6;
+  const int64_t lo = (int64_t)chunk * per;
+  const int64_t hi = lo + per < n ? lo + per : n;
   for (int64_t r = lo; r < hi; r += blockDim.x) {
     const int64_t u = r + threadIdx.x;
     if (u < hi) {
@@ -372,24 +394,31 @@ __device__ __forceinline__ void emit_rows(const int64_t *rp, const uint64_t *arc
     __syncthreads();
     if (full) hash_flush(E);
   }
-  hash_flush(E);
 }
 
 __global__ void __launch_bounds__(kEmitThreads, 8) k_emit(const int64_t *rp, const uint64_t *arcs, int32_t n,
-                                                       const void *cid, const uint64_t *D, Table t) {
+                                                       const void *cid, const uint64_t *D, int64_t per, Table t) {
   __shared__ EmitState E;
   if (t.ctl->bad) return;
   const uint32_t k = t.ctl->k;
   const int kb = bits_for_dev(k > 0 ? k - 1 : 0u);
   for (uint32_t i = threadIdx.x; i < kHashCap; i += blockDim.x) { E.hkey[i] = ~0ull; E.hval[i] = ~0ull; }
   if (threadIdx.x == 0) {
-    E.nmid = 0; E.nbig = 0; E.used = 0;
+    E.nmid = 0; E.nbig = 0; E.used = 0; E.full = 0;
     E.table = t;
     E.table.kb = kb;
   }
   __syncthreads();
-  if (k <= 65536) emit_rows(rp, arcs, n, (const uint16_t *)cid, D, E, kb);
-  else emit_rows(rp, arcs, n, (const uint32_t *)cid, D, E, kb);
+  const uint32_t chunks = (uint32_t)(((int64_t)n + per - 1) / per);
+  for (uint32_t chunk = blockIdx.x; chunk < chunks;) {
+    if (k <= 65536) emit_rows(rp, arcs, n, (const uint16_t *)cid, D, E, kb, chunk, per);
+    else emit_rows(rp, arcs, n, (const uint32_t *)cid, D, E, kb, chunk, per);
+    if (threadIdx.x == 0) E.chunk = gridDim.x + atomicAdd(&t.ctl->chunk, 1u);
+    __syncthreads();
+    chunk = E.chunk;
+    __syncthreads();
+  }
+  hash_flush(E);
 }
 
 // -------------------------------------------------------------- ranking --
@@ -397,40 +426,52 @@ __global__ void __launch_bounds__(kEmitThreads, 8) k_emit(const int64_t *rp, con
 // With all pairs in the table: every workgroup holds the keys of both
 // directions in LDS, and each wave counts, for its keys and row starts, the
 // keys below: a key's rank is its place in the CSR, a row's its offset.
-// 4 to 11 us for 300 to 12,000 arcs, where sorting, marking and reducing runs of
+// 8 to 35 us for 300 to 12,000 arcs, where sorting, marking and reducing runs of
 // the unfolded pairs took 15 launches, two host synchronisations and 150 to 250.
 constexpr int kRankThreads = 1024;
-constexpr int kRankBlocks = 128;
-constexpr uint32_t kRankMostK = 16384;
+constexpr int kRankBlocks = 256;
+constexpr int kRankBatch = 8;             // keys ranked by a wave in one walk
+constexpr uint32_t kRankMostK = 16384;    // 14-bit indices: keys of 28 bits
 
 __device__ __host__ inline bool table_holds_all(const QCtl &c) {
   return !c.bad && c.pairs == 0 && c.uniq <= kTableMost && c.k <= kRankMostK;
 }
 
 __global__ void __launch_bounds__(kRankThreads) k_rank(Table t, int32_t *qcol, uint64_t *qw, int64_t *qrp) {
-  extern __shared__ uint64_t keys[];
+  extern __shared__ uint4 keys4[];   // both directions' keys, filled up with ~0 to whole steps of a wave
+  uint32_t *keys = (uint32_t *)keys4;
   const QCtl c = *t.ctl;
   if (!table_holds_all(c)) return;
   const int kb = bits_for_dev(c.k > 0 ? c.k - 1 : 0u);
-  const uint32_t lane = threadIdx.x & 63, n = 2 * c.uniq;
-  for (uint32_t i = threadIdx.x; i < c.uniq; i += kRankThreads) {
-    const uint64_t key = t.key[t.slot[i]];
-    keys[2 * i] = key;
-    keys[2 * i + 1] = reversed(key, kb);
+  const uint32_t lane = threadIdx.x & 63, n = 2 * c.uniq, steps = (n + 255) / 256, all = n + c.k + 1;
+  for (uint32_t i = threadIdx.x; i < 128 * steps; i += kRankThreads) {
+    const uint64_t key = i < c.uniq ? t.key[t.slot[i]] : 0ull;
+    keys[2 * i] = i < c.uniq ? (uint32_t)key : ~0u;
+    keys[2 * i + 1] = i < c.uniq ? (uint32_t)reversed(key, kb) : ~0u;
   }
   __syncthreads();
+  const uint32_t wave = blockIdx.x * (kRankThreads / 64) + (threadIdx.x >> 6);
   const uint32_t waves = gridDim.x * (kRankThreads / 64);
-  for (uint32_t e = blockIdx.x * (kRankThreads / 64) + (threadIdx.x >> 6); e < n + c.k + 1; e += waves) {
-    const uint64_t x = e < n ? keys[e] : (uint64_t)(e - n) << kb;
-    uint32_t below = 0;
-    for (uint32_t i = lane; i < n; i += 64) below += keys[i] < x;
-    below = cld_last_lane(cld_wave_scan_u32(below));
-    if (lane != 0) continue;
-    if (e < n) {
-      qcol[below] = (int32_t)(x & ((1ull << kb) - 1ull));
-      qw[below] = t.val[t.slot[e >> 1]];
-    } else {
-      qrp[e - n] = below;
+  for (uint32_t e0 = wave * kRankBatch; e0 < all; e0 += waves * kRankBatch) {
+    uint32_t x[kRankBatch], below[kRankBatch] = {};
+#pragma unroll
+    for (int j = 0; j < kRankBatch; ++j) x[j] = e0 + j < n ? keys[e0 + j] : (e0 + j - n) << kb;
+    for (uint32_t i = 0; i < steps; ++i) {
+      const uint4 y = keys4[i * 64 + lane];
+#pragma unroll
+      for (int j = 0; j < kRankBatch; ++j)
+        below[j] += (uint32_t)(y.x < x[j]) + (uint32_t)(y.y < x[j]) + (uint32_t)(y.z < x[j]) + (uint32_t)(y.w < x[j]);
+    }
+#pragma unroll
+    for (int j = 0; j < kRankBatch; ++j) {
+      const uint32_t rank = cld_last_lane(cld_wave_scan_u32(below[j])), e = e0 + j;
+      if (lane != 0 || e >= all) continue;
+      if (e < n) {
+        qcol[rank] = (int32_t)(x[j] & ((1u << kb) - 1u));
+        qw[rank] = t.val[t.slot[e >> 1]];
+      } else {
+        qrp[e - n] = rank;
+      }
     }
   }
 }
@@ -499,7 +540,11 @@ int bits_for(uint32_t x) {  // bits needed for values 0..x
   return b;
 }
 
-constexpr int kEmitBlocks = 2048;
+// Two workgroups per CU, each with one table to fold its chunks in (2048
+// workgroups of one chunk brought several times the pairs to the table of all
+// pairs: 198 instead of 162 us on a road-like 2048 x 2048 mesh of 2228 clusters).
+constexpr int kEmitBlocks = 512;
+constexpr int kEmitChunks = 2048;
 
 struct Buffers {
   Ranks ranks;
@@ -586,11 +631,12 @@ extern "C" int cldiam_build_quotient(int32_t n, int64_t m, const int64_t *d_row_
       d_cluster, n, b.ranks, ctl, b.cid, d_qcenter);
   CLD_LAUNCH_CHECK("k_number");
   if (m > 0) {
-    const unsigned eb = (unsigned)(n < kEmitBlocks * 64 ? (n + 63) / 64 : kEmitBlocks);
-    k_emit<<<eb, kEmitThreads, 0, stream>>>(d_row_ptr, d_arcs, n, b.cid, d_D, b.table);
+    const int64_t chunks = n < kEmitChunks * 64 ? ((int64_t)n + 63) / 64 : kEmitChunks, per = (n + chunks - 1) / chunks;
+    k_emit<<<(unsigned)(chunks < kEmitBlocks ? chunks : kEmitBlocks), kEmitThreads, 0, stream>>>(
+        d_row_ptr, d_arcs, n, b.cid, d_D, per, b.table);
     CLD_LAUNCH_CHECK("k_emit");
   }
-  k_rank<<<kRankBlocks, kRankThreads, (size_t)2 * kTableMost * 8, stream>>>(b.table, d_qcol, d_qw, d_qrow_ptr);
+  k_rank<<<kRankBlocks, kRankThreads, (size_t)2 * kTableMost * 4, stream>>>(b.table, d_qcol, d_qw, d_qrow_ptr);
   CLD_LAUNCH_CHECK("k_rank");
   cld::Pinned<QCtl> pinned;
   if (!pinned.p) { cld::set_error("build_quotient: pinned host buffer allocation failed"); return CLDIAM_EHIP; }
