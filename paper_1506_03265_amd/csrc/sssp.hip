@@ -20,13 +20,19 @@
 // Distances are exact (u32, overflow checked); the schedule only changes the
 // work.
 //
+// A row is relaxed by four lanes together, one arc each at a time: a local
+// round of a few dozen nodes, the usual case, costs latency and a wave's
+// instructions, which this quarters (one lane per row with four arcs in flight:
+// 5.2 instead of 3.6 ms on a 700 x 900 grid, 3.0 instead of 2.0 on an R-GG of
+// 100,000 nodes).  No load is under a branch of its own, so they overlap.
+//
 // What bounds it: the number of hops (8,600 on the road-like 4096 x 4096 mesh)
 // times the chain of dependent accesses of one (queue, row offsets and
-// distance, arcs, far distances: 4.6 us where they miss the L2).  That mesh
-// takes 44 ms at the default width, R-MAT scale 20 4 ms; with node lists,
+// distance, arcs, far distances: 3.5 us where they miss the L2).  That mesh
+// takes 35 ms at the default width, R-MAT scale 20 4 ms; with node lists,
 // returning atomics and one hop per launch they took 255 and 237 ms.  Looking
 // up an improved node's row together with its distance, which makes the chain
-// one access shorter, gained nothing (47 ms: four times the offset loads).
+// one access shorter, gained nothing (four times the offset loads).
 #include <chrono>
 #include <thread>
 
@@ -35,20 +41,23 @@
 namespace {
 
 constexpr int kT = 256;
-// Four workgroups per CU, whose chains of accesses interleave: the road-like
-// 4096 x 4096 mesh takes 43 ms with 256 threads, 45 with 512, 50 with 1024.
+// Eight workgroups per CU, whose chains of accesses interleave: the road-like
+// 4096 x 4096 mesh takes 34.7 ms with 8 of 256 threads, 43 with 4, 36.7 with 16
+// (more than are resident), 43 with 4 of 512, 47 with 2 of 1024.  The list and
+// the queue are no longer than lets eight share a CU's LDS.
 constexpr int kStepThreads = 256;
-constexpr int kBlocksPerCu = 1024 / kStepThreads;
-constexpr int kList = 8 * kStepThreads;    // nodes of one expansion of a bitmap window
-constexpr int kQueue = 4 * kStepThreads;   // improved nodes of one local round
+constexpr int kBlocksPerCu = 2048 / kStepThreads;
+constexpr int kList = 4 * kStepThreads;    // nodes of one expansion of a bitmap window
+constexpr int kQueue = 2 * kStepThreads;   // improved nodes of one local round
+constexpr int kRowLanes = 4;      // lanes that relax a row together
 constexpr int kMidRow = 32;       // longer rows are relaxed by one wave ...
 constexpr int kBigRow = 4096;     // ... and these by the whole workgroup
-constexpr int kMidCap = 2 * kStepThreads;
+constexpr int kMidCap = kStepThreads;
 constexpr int kBigCap = 64;
 constexpr int kMinWords = 16;     // fewest bitmap words of a workgroup
 // Local rounds: on sparse graphs a round carries the search a hop further for
-// a third of a step's cost (road-like 4096 x 4096 mesh: 145 ms without, 45 with
-// 16, 44 with 32, 46 with 64).  On graphs of more than kDenseDegree arcs per
+// a quarter of a step's cost (road-like 4096 x 4096 mesh: 145 ms without, 37 with
+// 16 or 32, 39 with 64 and a longer queue).  On graphs of more than kDenseDegree arcs per
 // node a few hops reach everything and distances taken early are mostly
 // improved again (R-MAT scale 20: 4.0 ms without, 5.3 with one round, 20 with 32).
 constexpr uint32_t kRounds = 32;
@@ -88,112 +97,95 @@ struct SStep {
   uint2 queue[2][kQueue];   // (node, distance to relax it with)
   uint2 mid[kMidCap];       // rows for one wave each
   uint2 big[kBigCap];       // rows for the whole workgroup
-  uint32_t qn[2];
+  uint32_t qn[3];           // queued nodes, by round modulo 3
   uint32_t nmid[2], nbig[2];   // rows set aside by the even and the odd passes (see relax_long)
   uint32_t wsum[kStepThreads / 64];
   uint32_t fmin;
 };
 
-__device__ __forceinline__ void leave(const SJob &j, SStep &S, uint32_t *next, uint32_t v, uint32_t d) {
-  atomicOr(&next[v >> 5], 1u << (v & 31));
-  if (d < S.fmin) atomicMin(&S.fmin, d);
+// What a thread carries through a step.
+struct Walk {
+  const SJob &j;
+  SStep &S;
+  uint32_t *next;
+  uint32_t theta;
+  uint32_t q = 0, qslot = 0;   // queue and counter that improvements go to
+  uint32_t pass = 0;
+  uint32_t fmin = CLD_INF32;   // smallest distance that this thread has left for the next step
+};
+
+__device__ __forceinline__ void leave(Walk &k, uint32_t v, uint32_t d) {
+  atomicOr(&k.next[v >> 5], 1u << (v & 31));
+  if (d < k.fmin) k.fmin = d;
 }
 
-// Applies a thread's K offers nd[i] to v[i] that beat the distances read
-// (better[i]), and queues them: one reservation per wave.
-template <int K>
-__device__ __forceinline__ void improve(const SJob &j, SStep &S, uint32_t *next, int q, uint32_t theta,
-                                        const bool (&better)[K], const uint32_t (&v)[K], const uint32_t (&nd)[K]) {
-  const uint64_t below = (1ull << (threadIdx.x & 63)) - 1ull;
-  uint32_t at[K], total = 0;
-  bool near[K];
-#pragma unroll
-  for (int i = 0; i < K; ++i) {
-    if (better[i]) atomicMin(&j.dist[v[i]], nd[i]);
-    near[i] = better[i] && nd[i] < theta;
-    const uint64_t m = __ballot(near[i]);
-    at[i] = total + (uint32_t)__popcll(m & below);
-    total += (uint32_t)__popcll(m);
-  }
-  if (total) {
-    uint32_t base = 0;
-    const int first = __ffsll((long long)__ballot(true)) - 1;
-    if ((int)(threadIdx.x & 63) == first) base = atomicAdd(&S.qn[q], total);
-    base = __shfl(base, first);
-#pragma unroll
-    for (int i = 0; i < K; ++i) {
-      if (!near[i]) continue;
-      if (base + at[i] < kQueue) S.queue[q][base + at[i]] = make_uint2(v[i], nd[i]);
-      else leave(j, S, next, v[i], nd[i]);
-    }
-  }
-#pragma unroll
-  for (int i = 0; i < K; ++i)
-    if (better[i] && !near[i]) leave(j, S, next, v[i], nd[i]);
-}
-
-__device__ __forceinline__ void offer(const SJob &j, SStep &S, uint32_t *next, int q, uint32_t theta, uint32_t du,
-                                      uint64_t arc) {
+// Offers u's distance du over one arc per lane (in: the lane has one).  An
+// improvement is queued, one reservation per wave.  The load of the
+// neighbour's distance is not under a branch (a lane without an arc reads
+// node 0's): loads under branches do not overlap.
+__device__ __forceinline__ void offer(Walk &k, uint32_t du, bool in, uint64_t arc) {
   const uint64_t x = (uint64_t)du + (arc >> 32);
-  const uint32_t v[1] = {(uint32_t)arc}, nd[1] = {(uint32_t)x};
-  if (x >= CLD_INF32) j.ctl->maybe = 1u;
-  const bool better[1] = {x < CLD_INF32 && nd[0] < j.dist[v[0]]};
-  improve<1>(j, S, next, q, theta, better, v, nd);
+  const bool fits = x < CLD_INF32;
+  const uint32_t v = in && fits ? (uint32_t)arc : 0u, nd = (uint32_t)x, old = k.j.dist[v];
+  if (in && !fits) k.j.ctl->maybe = 1u;
+  const bool better = in && fits && nd < old, near = better && nd < k.theta;
+  if (better) atomicMin(&k.j.dist[v], nd);
+  const uint64_t m = __ballot(near);
+  if (m) {
+    const int first = __ffsll((long long)m) - 1;
+    uint32_t base = 0;
+    if ((int)(threadIdx.x & 63) == first) base = atomicAdd(&k.S.qn[k.qslot], (uint32_t)__popcll(m));
+    base = (uint32_t)__builtin_amdgcn_readlane((int)base, first);
+    const uint32_t slot = base + (uint32_t)__popcll(m & ((1ull << (threadIdx.x & 63)) - 1ull));
+    if (near && slot < kQueue) k.S.queue[k.q][slot] = make_uint2(v, nd);
+    else if (near) leave(k, v, nd);
+  }
+  if (better && !near) leave(k, v, nd);
 }
 
-// Relaxes u's row (degree deg, first arc a0) with distance du; improvements
-// go to queue q.  Arcs are taken four at a time so that their loads overlap.
-// Long rows are set aside for the relax_long that ends the pass.
-__device__ __forceinline__ void relax_row(const SJob &j, SStep &S, uint32_t *next, int q, uint32_t theta,
-                                          uint32_t pass, uint32_t u, uint32_t du, int64_t a0, int32_t deg) {
+__device__ __forceinline__ uint32_t row_lane() { return threadIdx.x & (kRowLanes - 1); }
+
+// Relaxes u's row (degree deg, first arc a0) with distance du by the kRowLanes
+// lanes of a group together, one arc each at a time.  Long rows are set aside
+// for the relax_long that ends the pass.
+__device__ __forceinline__ void relax_row(Walk &k, uint32_t u, uint32_t du, int64_t a0, int32_t deg) {
   if (deg > kMidRow) {
-    if (deg > kBigRow) {
-      const uint32_t slot = atomicAdd(&S.nbig[pass & 1], 1u);
-      if (slot < kBigCap) { S.big[slot] = make_uint2(u, du); return; }
-    } else {
-      const uint32_t slot = atomicAdd(&S.nmid[pass & 1], 1u);
-      if (slot < kMidCap) { S.mid[slot] = make_uint2(u, du); return; }
+    uint32_t aside = 0;
+    if (row_lane() == 0) {
+      const uint32_t p = k.pass & 1;
+      const uint32_t slot = atomicAdd(deg > kBigRow ? &k.S.nbig[p] : &k.S.nmid[p], 1u);
+      aside = slot < (uint32_t)(deg > kBigRow ? kBigCap : kMidCap);
+      if (aside) (deg > kBigRow ? k.S.big : k.S.mid)[slot] = make_uint2(u, du);
     }
+    if (__shfl((int)aside, (int)(threadIdx.x & 63 & ~(kRowLanes - 1)))) return;
   }
-  const uint64_t *row = j.arcs + a0;
-  for (int32_t base = 0; base < deg; base += 4) {
-    uint64_t arc[4];
-    uint32_t v[4], nd[4];
-    bool ok[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) arc[i] = base + i < deg ? row[base + i] : ~0ull;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const uint64_t x = (uint64_t)du + (arc[i] >> 32);
-      ok[i] = base + i < deg && x < CLD_INF32;
-      if (base + i < deg && !ok[i]) j.ctl->maybe = 1u;
-      nd[i] = (uint32_t)x;
-      v[i] = (uint32_t)arc[i];
-      ok[i] = ok[i] && nd[i] < j.dist[v[i]];
-    }
-    improve<4>(j, S, next, q, theta, ok, v, nd);
+  const uint64_t *row = k.j.arcs + a0;
+  for (int32_t base = 0; base < deg; base += kRowLanes) {
+    const int32_t a = base + (int32_t)row_lane();
+    offer(k, du, a < deg, row[a < deg ? a : base]);
   }
 }
 
 // Ends a pass: relaxes the long rows that it set aside.  The counters alternate
 // between passes: a wave that is late to read this pass's sees none of the next
 // pass's rows, so every wave takes the same branch after the one barrier.
-__device__ void relax_long(const SJob &j, SStep &S, uint32_t *next, int q, uint32_t theta, uint32_t &pass) {
+__device__ __forceinline__ void relax_long(Walk &k) {
+  SStep &S = k.S;
   __syncthreads();
-  const uint32_t p = pass++ & 1;
+  const uint32_t p = k.pass++ & 1;
   const uint32_t nm = S.nmid[p] < kMidCap ? S.nmid[p] : kMidCap, nb = S.nbig[p] < kBigCap ? S.nbig[p] : kBigCap;
   if (nm == 0 && nb == 0) return;
   for (uint32_t r = threadIdx.x >> 6; r < nm; r += kStepThreads / 64) {
     const uint2 x = S.mid[r];
-    const int64_t a0 = j.rp[x.x];
-    const int32_t deg = (int32_t)(j.rp[x.x + 1] - a0);
-    for (int32_t a = (int32_t)(threadIdx.x & 63); a < deg; a += 64) offer(j, S, next, q, theta, x.y, j.arcs[a0 + a]);
+    const int64_t a0 = k.j.rp[x.x];
+    const int32_t deg = (int32_t)(k.j.rp[x.x + 1] - a0);
+    for (int32_t a = (int32_t)(threadIdx.x & 63); a < deg; a += 64) offer(k, x.y, true, k.j.arcs[a0 + a]);
   }
   for (uint32_t r = 0; r < nb; ++r) {
     const uint2 x = S.big[r];
-    const int64_t a0 = j.rp[x.x];
-    const int32_t deg = (int32_t)(j.rp[x.x + 1] - a0);
-    for (int32_t a = (int32_t)threadIdx.x; a < deg; a += kStepThreads) offer(j, S, next, q, theta, x.y, j.arcs[a0 + a]);
+    const int64_t a0 = k.j.rp[x.x];
+    const int32_t deg = (int32_t)(k.j.rp[x.x + 1] - a0);
+    for (int32_t a = (int32_t)threadIdx.x; a < deg; a += kStepThreads) offer(k, x.y, true, k.j.arcs[a0 + a]);
   }
   __syncthreads();
   if (threadIdx.x == 0) { S.nmid[p] = 0; S.nbig[p] = 0; }
@@ -212,13 +204,13 @@ __global__ void __launch_bounds__(kStepThreads) k_sssp_step(SJob j, uint32_t t) 
   if (low == CLD_INF32) return;
   const uint32_t theta = low < CLD_INF32 - j.delta ? low + j.delta : CLD_INF32;
   uint32_t *cur = j.front[t & 1], *next = j.front[(t + 1) & 1];
-  if (tid == 0) { S.qn[0] = S.qn[1] = S.nmid[0] = S.nmid[1] = S.nbig[0] = S.nbig[1] = 0; S.fmin = CLD_INF32; }
+  if (tid == 0) { S.qn[0] = S.qn[1] = S.qn[2] = S.nmid[0] = S.nmid[1] = S.nbig[0] = S.nbig[1] = 0; S.fmin = CLD_INF32; }
   // Workgroups go to the XCDs in turn; each XCD takes one eighth of the words,
   // so that neighbouring ranges share an L2 (2 to 6% faster than in turn).
   const uint32_t range = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
   const uint32_t lo = range * j.chunk < j.words ? range * j.chunk : j.words;
   const uint32_t hi = lo + j.chunk < j.words ? lo + j.chunk : j.words;
-  uint32_t pass = 0;
+  Walk k{j, S, next, theta};
   uint32_t ahead = lo + tid < hi ? cur[lo + tid] : 0u;
   for (uint32_t w0 = lo; w0 < hi; w0 += kStepThreads) {
     const uint32_t word = ahead, w = w0 + tid;
@@ -234,9 +226,9 @@ __global__ void __launch_bounds__(kStepThreads) k_sssp_step(SJob j, uint32_t t) 
     if (lane == 63) S.wsum[wave] = incl;
     __syncthreads();
     uint32_t at = incl - __popc(word), total = 0;
-    for (uint32_t k = 0; k < kStepThreads / 64; ++k) {
-      if (k < wave) at += S.wsum[k];
-      total += S.wsum[k];
+    for (uint32_t i = 0; i < kStepThreads / 64; ++i) {
+      if (i < wave) at += S.wsum[i];
+      total += S.wsum[i];
     }
     for (uint32_t r0 = 0; r0 < total; r0 += kList) {
       uint32_t p = at;
@@ -245,41 +237,50 @@ __global__ void __launch_bounds__(kStepThreads) k_sssp_step(SJob j, uint32_t t) 
       __syncthreads();
       const uint32_t n = total - r0 < kList ? total - r0 : kList;
       for (uint32_t i0 = 0; i0 < n; i0 += kStepThreads) {
-        const uint32_t i = i0 + tid;
-        if (i < n) {
+        for (uint32_t i = i0 + tid / kRowLanes; i < n && i < i0 + kStepThreads; i += kStepThreads / kRowLanes) {
           const uint32_t u = (uint32_t)S.list[i], du = j.dist[u];
           const int64_t a0 = j.rp[u], a1 = j.rp[u + 1];
-          if (du >= theta) leave(j, S, next, u, du);
-          else relax_row(j, S, next, 0, theta, pass, u, du, a0, (int32_t)(a1 - a0));
+          if (du < theta) relax_row(k, u, du, a0, (int32_t)(a1 - a0));
+          else if (row_lane() == 0) leave(k, u, du);
         }
-        relax_long(j, S, next, 0, theta, pass);
+        relax_long(k);
       }
       __syncthreads();
     }
   }
-  int q = 0;
-  uint32_t n = 0;
+  // Round i reads queue i & 1 and counter i % 3 and fills the other queue and
+  // the next counter; the third counter is cleared meanwhile, so the barrier
+  // that ends a round's last pass is the only one.
+  uint32_t n = 0, q = 0, slot = 0;
+  __syncthreads();
   for (uint32_t round = 0;; ++round) {
-    __syncthreads();
-    n = S.qn[q] < kQueue ? S.qn[q] : kQueue;
+    n = S.qn[slot] < kQueue ? S.qn[slot] : kQueue;
     if (n == 0 || round >= j.rounds) break;
-    if (tid == 0) S.qn[q ^ 1] = 0;
-    __syncthreads();
+    k.q = q ^ 1;
+    k.qslot = slot == 2 ? 0 : slot + 1;
+    if (tid == 0) S.qn[slot == 0 ? 2 : slot - 1] = 0;
     for (uint32_t i0 = 0; i0 < n; i0 += kStepThreads) {
-      const uint32_t i = i0 + tid;
-      if (i < n) {
+      for (uint32_t i = i0 + tid / kRowLanes; i < n && i < i0 + kStepThreads; i += kStepThreads / kRowLanes) {
         const uint2 x = S.queue[q][i];
         const uint32_t d = j.dist[x.x];
         const int64_t a0 = j.rp[x.x], a1 = j.rp[x.x + 1];
-        if (d >= x.y) relax_row(j, S, next, q ^ 1, theta, pass, x.x, x.y, a0, (int32_t)(a1 - a0));
+        if (d >= x.y) relax_row(k, x.x, x.y, a0, (int32_t)(a1 - a0));
       }
-      relax_long(j, S, next, q ^ 1, theta, pass);
+      relax_long(k);
     }
-    q ^= 1;
+    q = k.q;
+    slot = k.qslot;
   }
   for (uint32_t i = tid; i < n; i += kStepThreads) {
     const uint2 x = S.queue[q][i];
-    leave(j, S, next, x.x, x.y);
+    leave(k, x.x, x.y);
+  }
+  if (__any(k.fmin != CLD_INF32)) {
+    for (int o = 32; o >= 1; o >>= 1) {
+      const uint32_t y = __shfl_xor(k.fmin, o);
+      k.fmin = y < k.fmin ? y : k.fmin;
+    }
+    if (lane == 0) atomicMin(&S.fmin, k.fmin);
   }
   __syncthreads();
   if (tid == 0 && S.fmin != CLD_INF32) atomicMin(&j.ctl->slot[t & 3].fmin, S.fmin);
