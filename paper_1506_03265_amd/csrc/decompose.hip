@@ -719,7 +719,7 @@ struct Run {
   uint32_t pass = 0;     // list passes so far
   uint32_t q = 0, qslot = 0;   // queue and counter that improvements go to
   // per-thread sums
-  uint32_t scanned = 0, heavy = 0;
+  uint32_t scanned = 0, heavy = 0, fmin = 0xffffffffu;
   unsigned long long acc = 0;   // NEXT: min; ASSIGN: max; SELECT: hub arcs
 };
 
@@ -730,7 +730,7 @@ __device__ __forceinline__ void set_bit(uint64_t *bits, int32_t v) {
 // v stays for the next sweep, at tentative distance dist.
 __device__ __forceinline__ void leave(Run &r, int32_t v, uint32_t dist) {
   set_bit(r.nxt, v);
-  if (dist < r.S.sum.fmin) atomicMin(&r.S.sum.fmin, dist);
+  if (dist < r.fmin) r.fmin = dist;
 }
 
 // u's scan stopped at a heavy arc; `heavy` arcs are left on its row.  word is
@@ -763,7 +763,7 @@ __device__ __forceinline__ void improve(Run &r, const bool (&better)[K], const i
     uint32_t base = 0;
     const int first = __ffsll((long long)__ballot(true)) - 1;
     if ((int)(threadIdx.x & 63) == first) base = atomicAdd(&r.S.qn[r.qslot], total);
-    base = __shfl(base, first);
+    base = (uint32_t)__builtin_amdgcn_readlane((int)base, first);
 #pragma unroll
     for (int i = 0; i < K; ++i) {
       if (!near[i]) continue;
@@ -781,7 +781,8 @@ __device__ __forceinline__ void improve(Run &r, const bool (&better)[K], const i
     if (better[i] && !near[i]) leave(r, v[i], (uint32_t)(cand[i] >> 32));
 }
 
-constexpr int kArcBatch = 4;   // arcs of a row in flight per thread
+constexpr int kArcBatch = 2;    // arcs of a long row in flight per thread (4 spill registers)
+constexpr int kScanBatch = 4;   // ... and of a row that one thread scans (NEXT, PULL)
 
 // The same for synchronous steps: offers were judged against the state before
 // the step (key) and go to the state after it (keyn), the lexicographic
@@ -812,15 +813,15 @@ __device__ __forceinline__ uint32_t offer(Run &r, uint64_t ku, uint32_t lim, con
     const bool ok = in[i] && (uint32_t)(arc[i] >> 32) <= lim;
     if (in[i] && !ok) *blocked = true;
     light += ok;
-    v[i] = (int32_t)(uint32_t)arc[i];
+    v[i] = ok ? (int32_t)(uint32_t)arc[i] : 0;
     cand[i] = ku + (arc[i] & 0xffffffff00000000ull);
     better[i] = ok;
   }
+  uint64_t k[K];
 #pragma unroll
-  for (int i = 0; i < K; ++i) {
-    const uint64_t k = better[i] ? r.key[v[i]] : 0ull;
-    better[i] = kSync ? (cand[i] >> 32) < (k >> 32) && better[i] : cand[i] < k;   // no offer is below 0
-  }
+  for (int i = 0; i < K; ++i) k[i] = r.key[v[i]];
+#pragma unroll
+  for (int i = 0; i < K; ++i) better[i] = better[i] && (kSync ? (cand[i] >> 32) < (k[i] >> 32) : cand[i] < k[i]);
   if (kSync) improve_sync<K>(r, better, v, cand);
   else improve<K>(r, better, v, cand);
   return light;
@@ -839,28 +840,50 @@ __device__ __forceinline__ bool defer_row(Run &r, int32_t u, int32_t deg) {
   return false;
 }
 
-// Relaxes u with key ku, four arcs of its row at a time so that their loads
-// overlap; long rows are deferred.
+// Rows are relaxed by kRowLanes lanes together, one arc each at a time.  A
+// local round of a few dozen nodes, the usual case on meshes, takes 2 to 3 us
+// of latency and of one wave's instructions, which this cuts to a quarter of
+// those of one lane per row with four arcs in flight (CLUSTER2 on the road-like
+// 2048 x 2048 mesh 9.4 instead of 13.0 ms, 1153 x 1021 mesh 1.40 instead of
+// 1.87, R-MAT scale 18 1.11 instead of 1.27).  Eight lanes leave half of them
+// idle on meshes (10.9 and 1.68 ms) and gain 5% on R-MAT scale 24.  All lanes of
+// a group have the same arguments.
+//
+// Loads in flight together are not under branches of their own (lanes without
+// an arc or a node read some other): the compiler waits for a load before it
+// leaves the branch, which had four far keys follow one another.
+constexpr int kRowLanes = 4;
+__device__ __forceinline__ uint32_t row_lane() { return threadIdx.x & (kRowLanes - 1); }
+__device__ __forceinline__ uint32_t group_sum(uint32_t x) {
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0xb1, 0xf, 0xf, true);   // lanes [1, 0, 3, 2]
+  return x + (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x4e, 0xf, 0xf, true);   // [2, 3, 0, 1]
+}
+
+// Relaxes u with key ku; long rows are deferred.
 template <bool kSync>
 __device__ __forceinline__ void relax_row(Run &r, int32_t u, uint64_t ku, int64_t a0, int32_t deg) {
-  if (deg > r.d.mid_deg && defer_row(r, u, deg)) return;
+  if (deg > r.d.mid_deg) {
+    uint32_t deferred = 0;
+    if (row_lane() == 0) deferred = defer_row(r, u, deg);
+    if (group_sum(deferred)) return;
+  }
   const uint64_t word = marks_of(r, u);
   const uint64_t *row = r.d.arcs + a0;
   const uint32_t lim = r.delta - (uint32_t)(ku >> 32);
-  bool blocked = false;
-  uint32_t light = 0;
-  for (int32_t base = 0; base < deg && !blocked; base += kArcBatch) {
-    uint64_t arc[kArcBatch];
-    bool in[kArcBatch];
-#pragma unroll
-    for (int i = 0; i < kArcBatch; ++i) {
-      in[i] = base + i < deg;
-      arc[i] = in[i] ? row[base + i] : ~0ull;
-    }
-    light += offer<kSync, kArcBatch>(r, ku, lim, in, arc, &blocked);
+  uint32_t light = 0, heavy = 0;
+  for (int32_t base = 0; base < deg && !heavy; base += kRowLanes) {
+    const int32_t a = base + (int32_t)row_lane();
+    const bool in[1] = {a < deg};
+    const uint64_t arc[1] = {row[in[0] ? a : base]};
+    bool blocked = false;
+    light += offer<kSync, 1>(r, ku, lim, in, arc, &blocked);
+    heavy = group_sum(blocked);
   }
   r.scanned += light;
-  if (blocked) mark_blocked(r, u, word, deg - (int32_t)light);
+  if (heavy) {
+    light = group_sum(light);
+    if (row_lane() == 0) mark_blocked(r, u, word, deg - (int32_t)light);
+  }
 }
 
 // A frontier node.
@@ -871,8 +894,11 @@ __device__ __forceinline__ void relax_item(Run &r, int32_t u) {
   const int32_t deg = (int32_t)(r.d.row_ptr[u + 1] - a0);   // indices within a row are 32-bit
   const uint32_t dist = (uint32_t)(ku >> 32);
   // beyond the current distance bucket: stays for a later sweep
-  if (!kSync && (dist >= r.theta || (deg > r.d.mid_deg && dist >= r.theta_row))) leave(r, u, dist);
-  else relax_row<kSync>(r, u, ku, a0, deg);
+  if (!kSync && (dist >= r.theta || (deg > r.d.mid_deg && dist >= r.theta_row))) {
+    if (row_lane() == 0) leave(r, u, dist);
+  } else {
+    relax_row<kSync>(r, u, ku, a0, deg);
+  }
 }
 
 // A queued improvement.
@@ -882,8 +908,11 @@ __device__ __forceinline__ void relax_queued(Run &r, int32_t u, uint64_t ku) {
   const int32_t deg = (int32_t)(r.d.row_ptr[u + 1] - a0);
   if (now < ku) return;   // improved again since: another entry's business
   const uint32_t dist = (uint32_t)(ku >> 32);
-  if (deg > r.d.mid_deg && dist >= r.theta_row) leave(r, u, dist);
-  else relax_row<false>(r, u, ku, a0, deg);
+  if (deg > r.d.mid_deg && dist >= r.theta_row) {
+    if (row_lane() == 0) leave(r, u, dist);
+  } else {
+    relax_row<false>(r, u, ku, a0, deg);
+  }
 }
 
 // NEXT for a short row: smallest d_u + w over its heavy arcs (w > Delta - d_u)
@@ -892,16 +921,20 @@ __device__ __forceinline__ void relax_queued(Run &r, int32_t u, uint64_t ku) {
 __device__ __forceinline__ uint64_t next_small(const Run &r, uint64_t ku, int64_t a0, int32_t deg) {
   const uint32_t du = (uint32_t)(ku >> 32), lim = r.delta - du;
   const uint64_t *row = r.d.arcs + a0;
-  for (int32_t base = 0; base < deg; base += kArcBatch) {
-    uint64_t arc[kArcBatch];
-    bool hit[kArcBatch];
+  for (int32_t base = 0; base < deg; base += kScanBatch) {
+    uint64_t arc[kScanBatch];
+    bool hit[kScanBatch];
 #pragma unroll
-    for (int i = 0; i < kArcBatch; ++i) arc[i] = base + i < deg ? row[base + i] : 0ull;   // 0: light
+    for (int i = 0; i < kScanBatch; ++i) arc[i] = row[base + i < deg ? base + i : base];
+    uint64_t k[kScanBatch];
 #pragma unroll
-    for (int i = 0; i < kArcBatch; ++i)
-      hit[i] = (uint32_t)(arc[i] >> 32) > lim && r.key[(int32_t)(uint32_t)arc[i]] == CLD_INF64;
+    for (int i = 0; i < kScanBatch; ++i) hit[i] = (uint32_t)(arc[i] >> 32) > lim;
 #pragma unroll
-    for (int i = 0; i < kArcBatch; ++i)
+    for (int i = 0; i < kScanBatch; ++i) k[i] = r.key[hit[i] ? (int32_t)(uint32_t)arc[i] : 0];
+#pragma unroll
+    for (int i = 0; i < kScanBatch; ++i) hit[i] = hit[i] && k[i] == CLD_INF64;
+#pragma unroll
+    for (int i = 0; i < kScanBatch; ++i)
       if (hit[i]) return (uint64_t)du + (arc[i] >> 32);
   }
   return CLD_INF64;
@@ -1003,7 +1036,7 @@ __device__ __forceinline__ void relax_long(Run &r) {
       for (int i = 0; i < kArcBatch; ++i) {
         const int32_t a = base + 64 * i + lane;
         in[i] = a < deg;
-        arc[i] = in[i] ? row[a] : ~0ull;
+        arc[i] = row[in[i] ? a : deg - 1];
       }
       uint32_t light = offer<kSync, kArcBatch>(r, ku, lim, in, arc, &blocked);
       r.scanned += light;
@@ -1041,7 +1074,7 @@ __device__ __forceinline__ void relax_long(Run &r) {
       for (int i = 0; i < kArcBatch; ++i) {
         const int32_t a = base + kSweepThreads * i + tid;
         in[i] = a < lo;
-        arc[i] = in[i] ? row[a] : ~0ull;
+        arc[i] = row[in[i] ? a : lo - 1];
       }
       r.scanned += offer<kSync, kArcBatch>(r, ku, lim, in, arc, &blocked);
     }
@@ -1122,11 +1155,11 @@ __device__ __forceinline__ bool pull_more(uint64_t w, uint64_t best, uint32_t de
   return next ? w < best : (w <= delta && w <= (best >> 32));
 }
 
-// Value of one arc (pull) or distance (next) offered to an unreached node.
-__device__ __forceinline__ uint64_t pull_offer(const Run &r, uint64_t arc, bool next) {
-  const uint64_t k = r.key[(int32_t)(uint32_t)arc];
+// Value (pull) or distance (next) that a neighbour with key k offers to an
+// unreached node over an arc of weight w.
+__device__ __forceinline__ uint64_t pull_offer(const Run &r, uint64_t w, uint64_t k, bool next) {
   if (k == CLD_INF64) return CLD_INF64;
-  const uint64_t du = k >> 32, w = arc >> 32;
+  const uint64_t du = k >> 32;
   if (next) return du + w;
   return du + w <= r.delta ? k + (w << 32) : CLD_INF64;
 }
@@ -1148,23 +1181,26 @@ __device__ __forceinline__ void pull_item(Run &r, int32_t v, bool next) {
   if (deg > r.d.mid_deg && defer_row(r, v, deg)) return;
   const uint64_t *row = r.d.arcs + a0;
   uint64_t best = CLD_INF64;
-  for (int32_t base = 0; base < deg; base += kArcBatch) {
-    uint64_t arc[kArcBatch];
-    bool ok[kArcBatch];
+  for (int32_t base = 0; base < deg; base += kScanBatch) {
+    uint64_t arc[kScanBatch];
+    bool ok[kScanBatch];
     bool stop = false;
 #pragma unroll
-    for (int j = 0; j < kArcBatch; ++j) arc[j] = base + j < deg ? row[base + j] : ~0ull;
+    for (int j = 0; j < kScanBatch; ++j) arc[j] = row[base + j < deg ? base + j : base];
 #pragma unroll
-    for (int j = 0; j < kArcBatch; ++j) {
+    for (int j = 0; j < kScanBatch; ++j) {
       const uint64_t w = arc[j] >> 32;
       ok[j] = base + j < deg && pull_more(w, best, r.delta, next);
       if (base + j < deg && !ok[j]) stop = true;
     }
-    uint64_t c[kArcBatch];
+    uint64_t k[kScanBatch];
 #pragma unroll
-    for (int j = 0; j < kArcBatch; ++j) c[j] = ok[j] ? pull_offer(r, arc[j], next) : CLD_INF64;
+    for (int j = 0; j < kScanBatch; ++j) k[j] = r.key[ok[j] ? (int32_t)(uint32_t)arc[j] : v];
 #pragma unroll
-    for (int j = 0; j < kArcBatch; ++j) best = c[j] < best ? c[j] : best;
+    for (int j = 0; j < kScanBatch; ++j) {
+      const uint64_t c = ok[j] ? pull_offer(r, arc[j] >> 32, k[j], next) : CLD_INF64;
+      best = c < best ? c : best;
+    }
     if (stop) break;
   }
   pull_apply(r, v, best, next);
@@ -1189,7 +1225,7 @@ __device__ __forceinline__ void pull_long(Run &r, bool next) {
       const uint64_t arc = a < deg ? row[a] : ~0ull;
       const bool in = a < deg && pull_more(arc >> 32, best, r.delta, next);
       if (!__any(in)) break;
-      const uint64_t m = wave_min_all(in ? pull_offer(r, arc, next) : CLD_INF64);
+      const uint64_t m = wave_min_all(in ? pull_offer(r, arc >> 32, r.key[(int32_t)(uint32_t)arc], next) : CLD_INF64);
       best = m < best ? m : best;
     }
     if (lane == 0) pull_apply(r, v, best, next);
@@ -1205,7 +1241,7 @@ __device__ __forceinline__ void pull_long(Run &r, bool next) {
       if (a < deg) {
         const uint64_t arc = row[a];
         if (pull_more(arc >> 32, cur, r.delta, next)) {
-          const uint64_t c = pull_offer(r, arc, next);
+          const uint64_t c = pull_offer(r, arc >> 32, r.key[(int32_t)(uint32_t)arc], next);
           if (c < cur) atomicMin(&S.blk_min, (unsigned long long)c);
         }
       }
@@ -1254,7 +1290,7 @@ __device__ __forceinline__ void c2_boundary(Run &r, int32_t u) {
 // per word, by the workgroup that owns it); item(v) handles a node and end()
 // the pass's end (every thread, with a barrier inside).  Dense words are
 // spread by their wave together, sparse ones each by its own thread.
-template <class Word, class Item, class End>
+template <int kLanes = 1, class Word, class Item, class End>
 __device__ __forceinline__ void list_pass(Run &r, uint32_t lo, uint32_t hi, Word word, Item item, End end) {
   Stage &S = r.S;
   const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -1288,8 +1324,8 @@ __device__ __forceinline__ void list_pass(Run &r, uint32_t lo, uint32_t hi, Word
       }
       __syncthreads();
       const uint32_t n = total - r0 < kList ? total - r0 : kList;
-      for (uint32_t i = tid; i - tid < n; i += kSweepThreads) {
-        if (i < n) item(S.list[i]);
+      for (uint32_t i0 = 0; i0 < n; i0 += kSweepThreads) {
+        for (uint32_t i = i0 + tid / kLanes; i < n && i < i0 + kSweepThreads; i += kSweepThreads / kLanes) item(S.list[i]);
         end();
       }
       __syncthreads();
@@ -1308,14 +1344,24 @@ __device__ __forceinline__ void node_pass(const uint64_t *bits, uint32_t lo, uin
   const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   for (uint32_t base = lo + wave * kNodeWords; base < hi; base += kWaves * kNodeWords) {
     const uint64_t mine = lane < (uint32_t)kNodeWords && base + lane < hi ? bits[base + lane] : 0ull;
-    if (__ballot(mine != 0) == 0) continue;
+    const uint64_t filled = __ballot(mine != 0);
+    if (filled == 0) continue;
+    const int at = __ffsll((long long)filled) - 1;   // a word with members, and its first
+    const int32_t some = (int32_t)(((base + at) << 6) + (uint32_t)__ffsll((long long)__shfl(mine, at)) - 1u);
     uint64_t word[kNodeWords], x[kNodeWords];
+    int32_t any[kNodeWords];
 #pragma unroll
     for (int j = 0; j < kNodeWords; ++j) {
       word[j] = __shfl(mine, j);
       const bool in = word[j] >> lane & 1;
-      x[j] = in ? load((int32_t)(((base + j) << 6) + lane)) : 0ull;
+      // one load whether in or not (a branch around it would wait for the
+      // load before): lanes outside the set read a member's
+      const uint32_t other = word[j] ? (uint32_t)__ffsll((long long)word[j]) - 1u : lane;
+      any[j] = (int32_t)(((base + j) << 6) + (in ? lane : other));
+      if (!word[j]) any[j] = some;
     }
+#pragma unroll
+    for (int j = 0; j < kNodeWords; ++j) x[j] = load(any[j]);
 #pragma unroll
     for (int j = 0; j < kNodeWords; ++j)
       if (word[j]) use(base + j, (int32_t)(((base + j) << 6) + lane), (bool)(word[j] >> lane & 1), x[j]);
@@ -1383,7 +1429,7 @@ __device__ __forceinline__ void process_run(const Job &job, const GDesc &d, cons
       node_pass(U, lo, hi,
                 [&](int32_t v) { return hubs ? (uint64_t)(d.row_ptr[v + 1] - d.row_ptr[v]) : 0ull; },
                 [&](uint32_t w, int32_t v, bool in, uint64_t deg) {
-        if (deg > d.hub_deg) r.acc += deg;
+        if (in && deg > d.hub_deg) r.acc += deg;
         const uint32_t x0 = cld_philox_word0((uint32_t)v, c2 ? stage + 1 : stage, 0u, c2 ? 1u : 0u, (uint32_t)d.seed,
                                              (uint32_t)(d.seed >> 32));
         const bool sel = in && (uint64_t)x0 < s.T;
@@ -1405,7 +1451,7 @@ __device__ __forceinline__ void process_run(const Job &job, const GDesc &d, cons
     case PH_RELAX:
       if (steps) {
         const bool merge = s.merge != 0;
-        list_pass(r, lo, hi,
+        list_pass<kRowLanes>(r, lo, hi,
                   [&](uint32_t w) {
                     uint64_t x = r.cur[w];
                     if (x) r.cur[w] = 0;
@@ -1418,7 +1464,7 @@ __device__ __forceinline__ void process_run(const Job &job, const GDesc &d, cons
                   },
                   [&](int32_t u) { relax_item<true>(r, u); }, [&] { relax_long<true>(r); });
       } else {
-        list_pass(r, lo, hi, [&](uint32_t w) { const uint64_t x = r.cur[w]; if (x) r.cur[w] = 0; return x; },
+        list_pass<kRowLanes>(r, lo, hi, [&](uint32_t w) { const uint64_t x = r.cur[w]; if (x) r.cur[w] = 0; return x; },
                   [&](int32_t u) { relax_item<false>(r, u); }, [&] { relax_long<false>(r); });
       }
       break;
@@ -1562,8 +1608,9 @@ __device__ __forceinline__ void process_run(const Job &job, const GDesc &d, cons
       r.q = q ^ 1;
       r.qslot = slot == 2 ? 0 : slot + 1;
       if (threadIdx.x == 0) S.qn[slot == 0 ? 2 : slot - 1] = 0;
-      for (uint32_t i = threadIdx.x; i - threadIdx.x < n; i += kSweepThreads) {
-        if (i < n) relax_queued(r, S.qv[q][i], S.qk[q][i]);
+      for (uint32_t i0 = 0; i0 < n; i0 += kSweepThreads) {
+        for (uint32_t i = i0 + threadIdx.x / kRowLanes; i < n && i < i0 + kSweepThreads; i += kSweepThreads / kRowLanes)
+          relax_queued(r, S.qv[q][i], S.qk[q][i]);
         relax_long<false>(r);
       }
       q ^= 1;
@@ -1582,6 +1629,13 @@ __device__ __forceinline__ void process_run(const Job &job, const GDesc &d, cons
       const unsigned long long y = __shfl_xor(r.acc, o);
       r.acc = is_min ? (y < r.acc ? y : r.acc) : (phase == PH_SELECT ? r.acc + y : (y > r.acc ? y : r.acc));
     }
+  if (phase == PH_RELAX && __any(r.fmin != 0xffffffffu)) {
+    for (int o = 32; o >= 1; o >>= 1) {
+      const uint32_t y = __shfl_xor(r.fmin, o);
+      r.fmin = y < r.fmin ? y : r.fmin;
+    }
+    if (lane == 0) atomicMin(&S.sum.fmin, r.fmin);
+  }
   if (lane == 0) {
     if (r.scanned) atomicAdd(&S.sum.arcs, (unsigned long long)r.scanned);
     if (r.heavy) atomicAdd(&S.sum.blk_arcs, (unsigned long long)r.heavy);
