@@ -85,7 +85,7 @@ enum Phase : uint32_t {
   PH_RMAX = 6,
   PH_SINGLE = 7,
   PH_DONE = 8,
-  PH_IDLE = 9,     // empty slot of a server job
+  PH_IDLE = 9,     // slot of a server job that no graph has used yet (a used one stays DONE)
   PH_COMMIT = 10,  // synchronous steps: publish the step's updates
   PH_C2_INIT = 11,      // CLUSTER2: fresh state for every node
   PH_C2_SELECT = 12,    // CLUSTER2: centers of iteration i with probability 2^i / n, and Contract2's
@@ -600,8 +600,9 @@ __device__ __forceinline__ void report(const Job &job, uint32_t iterations, uint
 
 // One workgroup of T threads: control of every graph of a job of several,
 // then the next sweep's chunks.
+// restart: the job's time limit counts from here.
 template <int T>
-__device__ void control_block(const Job &job) {
+__device__ void control_block(const Job &job, bool restart = false) {
   __shared__ uint32_t scan[T];
   __shared__ uint32_t carry, alldone;
   __shared__ unsigned long long work;
@@ -610,6 +611,7 @@ __device__ void control_block(const Job &job) {
     carry = 0;
     alldone = 1;
     work = 0;
+    if (restart) ctl->iterations = 0;
     check_time(ctl);
   }
   __syncthreads();
@@ -1780,11 +1782,9 @@ __global__ void k_describe(Job job, GDesc d, unsigned long long t_limit) {
   job.ctl->t_limit = t_limit;
 }
 
-// Fresh state of the nodes, sets and counters of graph first + blockIdx.y
-// (a job of one graph has three sets of counters).
-__global__ void __launch_bounds__(256) k_init(Job job, int32_t first) {
-  const int32_t g = first + (int32_t)blockIdx.y;
-  const GDesc &d = job.desc[g];
+// Fresh state of the nodes, sets and counters of graph g (a job of one graph
+// has three sets of counters).
+__device__ __forceinline__ void fresh_nodes(const Job &job, int32_t g, const GDesc &d) {
   if (blockIdx.x == 0 && threadIdx.x < (job.G == 1 ? 3u : 1u)) clear_count(job.cn[g + threadIdx.x]);
   const int64_t at = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, stride = (int64_t)gridDim.x * blockDim.x;
   for (int64_t i = at; i < d.n; i += stride) {
@@ -1800,10 +1800,31 @@ __global__ void __launch_bounds__(256) k_init(Job job, int32_t first) {
   }
 }
 
+// Every graph of a job: graph first + blockIdx.y.
+__global__ void __launch_bounds__(256) k_init(Job job, int32_t first) {
+  const int32_t g = first + (int32_t)blockIdx.y;
+  fresh_nodes(job, g, job.desc[g]);
+}
+
+// A server's graph enters slot g: descriptor, state, stage log and nodes.  One
+// launch, with the descriptor as an argument (two copies, a fill and a wait
+// for them took 80 us a graph).
+__global__ void __launch_bounds__(256) k_admit(Job job, int32_t g, GDesc d) {
+  if (blockIdx.x == 0) {
+    if (threadIdx.x == 0) {
+      const_cast<GDesc *>(job.desc)[g] = d;
+      job.st[g] = GState{};   // PH_START
+    }
+    int32_t *log = job.log + (size_t)g * CLDIAM_STAGE_LOG * 4;
+    for (int i = threadIdx.x; i < CLDIAM_STAGE_LOG * 4; i += 256) log[i] = 0;
+  }
+  fresh_nodes(job, g, d);
+}
+
 // A job of up to kSmallControl graphs takes a one-wave control step: no
 // cross-wave barriers, a 64-entry scan.
 template <int T>
-__global__ void __launch_bounds__(T) k_control(Job job) { control_block<T>(job); }
+__global__ void __launch_bounds__(T) k_control(Job job, bool restart) { control_block<T>(job, restart); }
 
 constexpr int kSmallControl = 64;
 
@@ -1821,13 +1842,13 @@ __global__ void __launch_bounds__(kSweepThreads, kCuThreads / kSweepThreads) k_s
   sweep_one(job, d, t, blockIdx.x, gridDim.x, S);
 }
 
-void launch_step(const Job &job, const GDesc *one, uint32_t t, hipStream_t stream) {
+void launch_step(const Job &job, const GDesc *one, uint32_t t, hipStream_t stream, bool restart = false) {
   if (one) {
     k_sweep<<<job.nblocks, kSweepThreads, 0, stream>>>(job, *one, t);
     return;
   }
-  if (job.G <= kSmallControl) k_control<kSmallControl><<<1, kSmallControl, 0, stream>>>(job);
-  else k_control<kThreads><<<1, kThreads, 0, stream>>>(job);
+  if (job.G <= kSmallControl) k_control<kSmallControl><<<1, kSmallControl, 0, stream>>>(job, restart);
+  else k_control<kThreads><<<1, kThreads, 0, stream>>>(job, restart);
   k_sweep_many<<<job.nblocks, kSweepThreads, 0, stream>>>(job);
 }
 
@@ -2261,8 +2282,11 @@ struct cldiam_server {
     cldiam_stats st;
   };
   std::vector<Done> done;
-  std::vector<GState> st_host;
-  Ctl *hc = nullptr;
+  // pinned copy of the device's states (all slots) and Ctl, as they lie in the workspace
+  char *back = nullptr;
+  size_t back_bytes = 0;
+  const GState *st_host() const { return (const GState *)back; }
+  const Ctl *hc() const { return (const Ctl *)(back + ((char *)L.ctl - L.zero)); }
 };
 
 namespace {
@@ -2335,22 +2359,23 @@ extern "C" int cldiam_server_create(cldiam_server **out, int64_t node_capacity, 
   s->tag.assign(max_graphs, 0);
   s->active.assign(max_graphs, 0);
   s->free_ranges.push_back({0, slots});
-  s->st_host.assign(max_graphs, GState{});
-  for (auto &g : s->st_host) g.phase = PH_IDLE;
+  s->back_bytes = (size_t)((char *)L.log - L.zero);
+  std::vector<GState> idle(max_graphs, GState{});
+  for (auto &g : idle) g.phase = PH_IDLE;
   void *p = nullptr;
-  if (hipHostMalloc(&p, sizeof(Ctl), hipHostMallocDefault) != hipSuccess) {
+  if (hipHostMalloc(&p, s->back_bytes, hipHostMallocDefault) != hipSuccess) {
     delete s;
     cld::set_error("server: pinned host buffer allocation failed");
     return CLDIAM_EHIP;
   }
-  s->hc = (Ctl *)p;
+  s->back = (char *)p;
   unsigned long long limit = 0;
   rc = read_wall_limit(&limit);
   if (rc) { cldiam_server_destroy(s); return rc; }
   hipStream_t st = s->stream;
   if (hipMemsetAsync(L.zero, 0, L.zero_bytes, st) != hipSuccess ||
       hipMemcpyAsync(L.desc, s->desc.data(), sizeof(GDesc) * max_graphs, hipMemcpyHostToDevice, st) != hipSuccess ||
-      hipMemcpyAsync(L.st, s->st_host.data(), sizeof(GState) * max_graphs, hipMemcpyHostToDevice, st) != hipSuccess ||
+      hipMemcpyAsync(L.st, idle.data(), sizeof(GState) * max_graphs, hipMemcpyHostToDevice, st) != hipSuccess ||
       hipMemcpyAsync(&L.ctl->t_limit, &limit, sizeof limit, hipMemcpyHostToDevice, st) != hipSuccess ||
       hipStreamSynchronize(st) != hipSuccess) {
     cldiam_server_destroy(s);
@@ -2363,7 +2388,7 @@ extern "C" int cldiam_server_create(cldiam_server **out, int64_t node_capacity, 
 
 extern "C" void cldiam_server_destroy(cldiam_server *s) {
   if (!s) return;
-  if (s->hc) (void)hipHostFree(s->hc);
+  if (s->back) (void)hipHostFree(s->back);
   delete s;
 }
 
@@ -2382,6 +2407,7 @@ extern "C" int cldiam_server_step(cldiam_server *s, int32_t max_sweeps, int32_t 
   if (!s || max_sweeps < 0) { cld::set_error("server: invalid step"); return CLDIAM_EINVAL; }
   hipStream_t stream = s->stream;
   Job &job = s->job;
+  bool admitted = false;
   // admit queued graphs in arrival order while a slot and a node range are free
   while (s->qhead < s->queue.size()) {
     int slot = -1;
@@ -2395,16 +2421,9 @@ extern "C" int cldiam_server_step(cldiam_server *s, int32_t max_sweeps, int32_t 
     s->desc[slot] = p.d;
     s->tag[slot] = p.tag;
     s->active[slot] = 1;
-    GState fresh{};
-    fresh.phase = PH_START;
-    CLD_HIP(hipMemcpyAsync(&s->L.desc[slot], &s->desc[slot], sizeof(GDesc), hipMemcpyHostToDevice, stream));
-    CLD_HIP(hipMemcpyAsync(&job.st[slot], &fresh, sizeof(GState), hipMemcpyHostToDevice, stream));
-    CLD_HIP(hipMemsetAsync(job.log + (size_t)slot * CLDIAM_STAGE_LOG * 4, 0, sizeof(int32_t) * CLDIAM_STAGE_LOG * 4,
-                           stream));
-    k_init<<<init_grid(p.d.n, 1), 256, 0, stream>>>(job, slot);
-    CLD_LAUNCH_CHECK("k_init");
-    // the host copies above read s->desc / fresh before the next host write
-    CLD_HIP(hipStreamSynchronize(stream));
+    k_admit<<<init_grid(p.d.n, 1), 256, 0, stream>>>(job, slot, p.d);
+    CLD_LAUNCH_CHECK("k_admit");
+    admitted = true;
     s->qhead++;
   }
   if (s->qhead > 1024 && s->qhead * 2 > s->queue.size()) {
@@ -2414,34 +2433,42 @@ extern "C" int cldiam_server_step(cldiam_server *s, int32_t max_sweeps, int32_t 
   int nactive = 0;
   for (int g = 0; g < s->gcap; ++g) nactive += s->active[g];
   if (nactive > 0 && max_sweeps > 0) {
-    CLD_HIP(hipMemsetAsync(&job.ctl->iterations, 0, sizeof(uint32_t), stream));
-    for (int i = 0; i < max_sweeps; ++i) {
-      launch_step(job, nullptr, 0, stream);
-    }
+    for (int i = 0; i < max_sweeps; ++i) launch_step(job, nullptr, 0, stream, i == 0);
     CLD_LAUNCH_CHECK("k_sweep");
-    CLD_HIP(hipMemcpyAsync(s->st_host.data(), job.st, sizeof(GState) * s->gcap, hipMemcpyDeviceToHost, stream));
-    CLD_HIP(hipMemcpyAsync(s->hc, job.ctl, sizeof(Ctl), hipMemcpyDeviceToHost, stream));
+    CLD_HIP(hipMemcpyAsync(s->back, s->L.zero, s->back_bytes, hipMemcpyDeviceToHost, stream));
     CLD_HIP(hipStreamSynchronize(stream));
-    if (s->hc->error) {
-      cld::set_error("server: device reported %s", cldiam_strerror(-(int)s->hc->error));
-      return -(int)s->hc->error;
+    const GState *st = s->st_host();
+    if (s->hc()->error) {
+      cld::set_error("server: device reported %s", cldiam_strerror(-(int)s->hc()->error));
+      return -(int)s->hc()->error;
     }
+    // the stage logs of the slots that are done, in one copy
+    int first = -1, last = -1;
     for (int g = 0; g < s->gcap; ++g) {
-      if (!s->active[g] || s->st_host[g].phase != PH_DONE) continue;
-      std::vector<int32_t> lg(CLDIAM_STAGE_LOG * 4);
-      CLD_HIP(hipMemcpyAsync(lg.data(), job.log + (size_t)g * CLDIAM_STAGE_LOG * 4, sizeof(int32_t) * lg.size(),
+      if (!s->active[g] || st[g].phase != PH_DONE) continue;
+      if (first < 0) first = g;
+      last = g;
+    }
+    std::vector<int32_t> lg;
+    constexpr size_t kLog = CLDIAM_STAGE_LOG * 4;
+    if (first >= 0) {
+      lg.resize((size_t)(last - first + 1) * kLog);
+      CLD_HIP(hipMemcpyAsync(lg.data(), job.log + (size_t)first * kLog, sizeof(int32_t) * lg.size(),
                              hipMemcpyDeviceToHost, stream));
-      const GState idle = [] { GState x{}; x.phase = PH_IDLE; return x; }();
-      CLD_HIP(hipMemcpyAsync(&job.st[g], &idle, sizeof(GState), hipMemcpyHostToDevice, stream));
       CLD_HIP(hipStreamSynchronize(stream));
+    }
+    for (int g = first; g >= 0 && g <= last; ++g) {
+      if (!s->active[g] || st[g].phase != PH_DONE) continue;
       cldiam_server::Done dn;
       dn.tag = s->tag[g];
-      fill_stats(s->desc[g], s->st_host[g], lg.data(), &dn.st);
+      fill_stats(s->desc[g], st[g], lg.data() + (size_t)(g - first) * kLog, &dn.st);
       s->done.push_back(dn);
       s->active[g] = 0;
       give_range(s, s->desc[g].off, aligned_nodes(s->desc[g].n));
       --nactive;
     }
+  } else if (admitted) {
+    CLD_HIP(hipStreamSynchronize(stream));
   }
   if (h_active) *h_active = nactive;
   if (h_queued) *h_queued = (int32_t)(s->queue.size() - s->qhead);
