@@ -86,7 +86,7 @@ enum Phase : uint32_t {
   PH_SINGLE = 7,
   PH_DONE = 8,
   PH_IDLE = 9,     // slot of a server job that no graph has used yet (a used one stays DONE)
-  PH_COMMIT = 10,  // synchronous steps: publish the step's updates
+  PH_COMMIT = 10,  // synchronous steps: the last step's updates go into the keys
   PH_C2_INIT = 11,      // CLUSTER2: fresh state for every node
   PH_C2_SELECT = 12,    // CLUSTER2: centers of iteration i with probability 2^i / n, and Contract2's
                         // rescaled edges out of last iteration's clusters
@@ -153,7 +153,7 @@ static_assert(sizeof(GState) % 4 == 0, "copied word by word");
 // What a sweep of one graph reports to its next control step.
 struct alignas(128) GCount {
   uint32_t fmin;        // RELAX: smallest tentative distance on the next frontier (~0: it is empty)
-  uint32_t cov;         // covered nodes (COUNT, NEXT, COMMIT: newly covered, C2_ASSIGN)
+  uint32_t cov;         // covered nodes (COUNT, NEXT, C2_ASSIGN; synchronous steps: newly covered)
   uint32_t centers;     // centers drawn
   uint32_t upd;         // synchronous steps: nodes updated
   uint32_t records;
@@ -196,11 +196,12 @@ struct Job {
   uint32_t *seg;     // [0, G]: exclusive prefix of per-graph chunks; [G+1, 2G]: words per chunk
   int32_t *log;      // G x CLDIAM_STAGE_LOG x 4
   uint64_t *key;
-  uint64_t *keyn;    // synchronous steps: state after the current step (key holds the state before it);
-                     // CLUSTER2's iterations: growth distance of the assigned nodes; otherwise, for long rows,
-                     // the key of the row's last scan
+  uint64_t *keyn;    // synchronous steps: updates of the odd steps (see step_state); CLUSTER2's iterations:
+                     // growth distance of the assigned nodes; otherwise, for long rows, the key of the
+                     // row's last scan
   uint32_t *slim;    // with keyn: the light limit (Delta - d) of that scan; arcs up to it have been offered
-  uint64_t *R;       // by center: largest D of its cluster after the last stage; CLUSTER2: birth iteration
+  uint64_t *R;       // by center: largest D of its cluster after the last stage; CLUSTER2: birth iteration;
+                     // synchronous steps: for nodes with a distance, updates of the even steps as well
   uint64_t *U;       // bitmap: uncovered nodes
   uint64_t *F;       // four bitmaps, one after the other, in the roles of GState
   int64_t fwords;    // words of one
@@ -466,7 +467,19 @@ __device__ __forceinline__ void control_graph(const GDesc &d, GState &s, const G
         s.steps_call++;
         s.msgs += c.msgs;
         if (s.merge) { swap_roles(s.blk, s.alt); s.merge = 0; }   // the old blocked set is used up
-        s.phase = PH_COMMIT;
+        s.updates += c.upd;
+        s.cov += c.cov;
+        swap_roles(s.cur, s.nxt);   // the updated nodes are the next active set
+        if (c.upd == 0) {
+          s.phase = PH_NEXT;      // fixpoint: is any uncovered node reachable?
+        } else if (2ull * s.cov >= (uint64_t)s.nU) {
+          s.merge = 1;
+          s.phase = PH_COMMIT;
+        } else if (d.step_cap && s.steps_call >= d.step_cap) {
+          if (!double_delta(s)) break;
+          s.merge = 1;
+          begin_call(s);
+        }
         break;
       }
       s.blk_arcs += c.blk_arcs;
@@ -495,25 +508,9 @@ __device__ __forceinline__ void control_graph(const GDesc &d, GState &s, const G
       if (!s.pull && pull_pays(s, s.nU - s.cov)) s.pull = 1;
       s.phase = s.pull ? PH_NEXT_PULL : PH_NEXT;
       break;
-    case PH_COMMIT: {
-      const uint32_t nn = c.upd;
-      s.updates += nn;
-      s.cov += c.cov;
-      swap_roles(s.cur, s.nxt);   // the updated nodes are the next active set
-      if (nn > 0 && 2ull * s.cov >= (uint64_t)s.nU) {
-        s.merge = 1;
-        s.phase = PH_ASSIGN;
-      } else if (nn > 0 && d.step_cap && s.steps_call >= d.step_cap) {
-        if (!double_delta(s)) break;
-        s.merge = 1;
-        begin_call(s);
-      } else if (nn > 0) {
-        s.phase = PH_RELAX;
-      } else {
-        s.phase = PH_NEXT;      // fixpoint: is any uncovered node reachable?
-      }
+    case PH_COMMIT:
+      s.phase = PH_ASSIGN;
       break;
-    }
     case PH_NEXT:
       if (d.variant == CLDIAM_VARIANT_STEPS) {
         s.merge = 1;
@@ -714,6 +711,7 @@ struct Run {
   uint64_t *key;         // this graph's part of the node arrays and bitmaps
   uint64_t *keyn;
   uint32_t *slim;
+  uint64_t *pend, *pnew;   // synchronous steps: updates of the last step and of this one
   uint64_t *cur, *nxt;
   uint64_t *mark;        // where blocked nodes are marked (nullptr: nowhere)
   uint32_t delta, theta, theta_row;
@@ -721,6 +719,7 @@ struct Run {
   uint32_t pass = 0;     // list passes so far
   uint32_t q = 0, qslot = 0;   // queue and counter that improvements go to
   // per-thread sums
+  uint32_t updated = 0, covered = 0;   // synchronous steps
   uint32_t scanned = 0, heavy = 0, fmin = 0xffffffffu;
   unsigned long long acc = 0;   // NEXT: min; ASSIGN: max; SELECT: hub arcs
 };
@@ -786,17 +785,42 @@ __device__ __forceinline__ void improve(Run &r, const bool (&better)[K], const i
 constexpr int kArcBatch = 2;    // arcs of a long row in flight per thread (4 spill registers)
 constexpr int kScanBatch = 4;   // ... and of a row that one thread scans (NEXT, PULL)
 
-// The same for synchronous steps: offers were judged against the state before
-// the step (key) and go to the state after it (keyn), the lexicographic
-// minimum over the step's offers wins.
+// Synchronous steps.  A step's offers are judged against the state before it,
+// and the lexicographic minimum over a node's offers is its state after it.  A
+// step's updates go to one of two arrays in turn (pnew; atomicMin over what an
+// earlier step left there, which is never below the node's state) and the nodes
+// that have one to the next frontier.  The next step's state of a node is the
+// smaller of its key and its entry in that array (then pend): nothing writes
+// either in that step but the owner of an updated node, who copies the update
+// into the key.  So a step is one sweep, bound by its launch and the chain of
+// dependent accesses of one hop (20 us): the road-like 2048 x 2048 mesh takes 8.6
+// ms for 371 steps, and took 11.8 with a second sweep that published the updates.
+// A node at distance 0 (a center, or assigned) takes no offer: its key alone
+// counts, and the arrays hold nothing for it (one is R, by center).
+__device__ __forceinline__ uint64_t step_state(uint64_t key, uint64_t pend) {
+  return key >> 32 && pend < key ? pend : key;
+}
+
+// Applies the offers of a step (state[i]: of v[i] before the step) and counts
+// the nodes that it updates and covers: the thread that puts a node on the
+// frontier counts it.
 template <int K>
 __device__ __forceinline__ void improve_sync(Run &r, const bool (&better)[K], const int32_t (&v)[K],
-                                             const uint64_t (&cand)[K]) {
+                                             const uint64_t (&cand)[K], const uint64_t (&state)[K]) {
+  uint64_t old[K];
 #pragma unroll
   for (int i = 0; i < K; ++i) {
-    if (!better[i]) continue;
-    atomicMin((unsigned long long *)&r.keyn[v[i]], (unsigned long long)cand[i]);
-    set_bit(r.nxt, v[i]);
+    old[i] = ~0ull;
+    if (better[i]) {
+      atomicMin((unsigned long long *)&r.pnew[v[i]], (unsigned long long)cand[i]);
+      old[i] = atomicOr((unsigned long long *)&r.nxt[v[i] >> 6], 1ull << (v[i] & 63));
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < K; ++i) {
+    const bool first = !(old[i] >> (v[i] & 63) & 1);
+    r.updated += first;
+    r.covered += first && state[i] == CLD_INF64;
   }
 }
 
@@ -822,9 +846,16 @@ __device__ __forceinline__ uint32_t offer(Run &r, uint64_t ku, uint32_t lim, con
   uint64_t k[K];
 #pragma unroll
   for (int i = 0; i < K; ++i) k[i] = r.key[v[i]];
+  if (kSync) {
+    uint64_t p[K];
+#pragma unroll
+    for (int i = 0; i < K; ++i) p[i] = r.pend[v[i]];
+#pragma unroll
+    for (int i = 0; i < K; ++i) k[i] = step_state(k[i], p[i]);
+  }
 #pragma unroll
   for (int i = 0; i < K; ++i) better[i] = better[i] && (kSync ? (cand[i] >> 32) < (k[i] >> 32) : cand[i] < k[i]);
-  if (kSync) improve_sync<K>(r, better, v, cand);
+  if (kSync) improve_sync<K>(r, better, v, cand, k);
   else improve<K>(r, better, v, cand);
   return light;
 }
@@ -891,9 +922,14 @@ __device__ __forceinline__ void relax_row(Run &r, int32_t u, uint64_t ku, int64_
 // A frontier node.
 template <bool kSync>
 __device__ __forceinline__ void relax_item(Run &r, int32_t u) {
-  const uint64_t ku = r.key[u];
+  uint64_t ku = r.key[u];
   const int64_t a0 = r.d.row_ptr[u];
   const int32_t deg = (int32_t)(r.d.row_ptr[u + 1] - a0);   // indices within a row are 32-bit
+  if (kSync) {
+    const uint64_t now = step_state(ku, r.pend[u]);
+    if (now != ku && row_lane() == 0) r.key[u] = now;
+    ku = now;
+  }
   const uint32_t dist = (uint32_t)(ku >> 32);
   // beyond the current distance bucket: stays for a later sweep
   if (!kSync && (dist >= r.theta || (deg > r.d.mid_deg && dist >= r.theta_row))) {
@@ -1026,7 +1062,7 @@ template <bool kSync>
 __device__ __forceinline__ void relax_long(Run &r) {
   const int32_t lane = (int32_t)(threadIdx.x & 63), tid = (int32_t)threadIdx.x;
   auto mid = [&](int32_t u, const uint64_t *row, int32_t deg) {
-    const uint64_t word = marks_of(r, u), ku = r.key[u];
+    const uint64_t word = marks_of(r, u), ku = kSync ? step_state(r.key[u], r.pend[u]) : r.key[u];
     const uint32_t lim = r.delta - (uint32_t)(ku >> 32);
     const int32_t start = r.resume ? resume_at_wave(r, u, ku, row, deg) : 0;
     int32_t end = start;   // of the light prefix
@@ -1056,7 +1092,7 @@ __device__ __forceinline__ void relax_long(Run &r) {
     // with the same key and the scan record describes all of them) and finds
     // the end of the light prefix and the resume point
     if (threadIdx.x < 64) {
-      const uint64_t k = r.key[u];
+      const uint64_t k = kSync ? step_state(r.key[u], r.pend[u]) : r.key[u];
       const int32_t light_end = wave_first_above(row, 0, deg, r.delta - (uint32_t)(k >> 32));
       const int32_t from = r.resume ? resume_at_wave(r, u, k, row, light_end) : 0;
       if (threadIdx.x == 0) {
@@ -1397,7 +1433,9 @@ __device__ __forceinline__ void process_run(const Job &job, const GDesc &d, cons
   uint64_t *U = job.U + woff, *R = job.R + d.off;
   uint64_t *F = job.F + woff, *blk = F + s.blk * job.fwords, *alt = F + s.alt * job.fwords;
   const uint32_t row_lim = row_limit(d, s.delta, s.row_base);
-  Run r{job, d, s, S, job.key + d.off, job.keyn + d.off, job.slim + d.off, F + s.cur * job.fwords,
+  const bool odd = s.rounds & 1;
+  Run r{job, d, s, S, job.key + d.off, job.keyn + d.off, job.slim + d.off,
+        odd ? R : job.keyn + d.off, odd ? job.keyn + d.off : R, F + s.cur * job.fwords,
         F + s.nxt * job.fwords, s.pull ? nullptr : (s.merge ? alt : blk), s.delta, s.theta, row_lim < s.theta ? row_lim : s.theta,
         !steps && !s.c2};
   if (threadIdx.x == 0) {
@@ -1438,7 +1476,6 @@ __device__ __forceinline__ void process_run(const Job &job, const GDesc &d, cons
         if (sel) {
           r.key[v] = (uint64_t)(uint32_t)v;
           R[v] = c2 ? stage + 1 : 0;
-          if (steps) r.keyn[v] = (uint64_t)(uint32_t)v;
         }
         const uint64_t m = __ballot(sel);
         if (m && lane == 0) atomicOr((unsigned long long *)&r.cur[w], (unsigned long long)m);
@@ -1470,16 +1507,11 @@ __device__ __forceinline__ void process_run(const Job &job, const GDesc &d, cons
                   [&](int32_t u) { relax_item<false>(r, u); }, [&] { relax_long<false>(r); });
       }
       break;
-    case PH_COMMIT: {
-      uint32_t upd = 0;
-      node_pass(r.nxt, lo, hi, key_of, [&](uint32_t, int32_t v, bool in, uint64_t old) {
-        if (in) r.key[v] = r.keyn[v];
-        upd += (uint32_t)__popcll(__ballot(in));
-        cov += (uint32_t)__popcll(__ballot(in && old == CLD_INF64));
+    case PH_COMMIT:
+      node_pass(r.cur, lo, hi, key_of, [&](uint32_t, int32_t v, bool in, uint64_t k) {
+        if (in) r.key[v] = step_state(k, r.pend[v]);
       });
-      if (lane == 0 && upd) atomicAdd(&S.sum.upd, upd);
       break;
-    }
     case PH_COUNT:
       node_pass(U, lo, hi, key_of, [&](uint32_t, int32_t, bool in, uint64_t k) {
         cov += (uint32_t)__popcll(__ballot(in && k != CLD_INF64));
@@ -1528,7 +1560,7 @@ __device__ __forceinline__ void process_run(const Job &job, const GDesc &d, cons
           if (stage == 0) {
             fold_rmax(r, R, c, Dv);
             r.key[v] = (uint64_t)c;
-            if (s.records || steps) r.keyn[v] = (uint64_t)c;
+            if (s.records) r.keyn[v] = (uint64_t)c;
           }
         }
         if (stage == 0) {
@@ -1544,7 +1576,7 @@ __device__ __forceinline__ void process_run(const Job &job, const GDesc &d, cons
           const uint32_t c = (uint32_t)k;
           fold_rmax(r, R, c, d.D[v]);
           r.key[v] = (uint64_t)c;
-          if (s.records || steps) r.keyn[v] = (uint64_t)c;
+          if (s.records) r.keyn[v] = (uint64_t)c;
         }
         const uint64_t m = __ballot(got);
         if (m && lane == 0) U[w] &= ~m;
@@ -1625,6 +1657,11 @@ __device__ __forceinline__ void process_run(const Job &job, const GDesc &d, cons
   if (is_growth(phase) || phase == PH_C2_SELECT) {
     r.scanned = cld_last_lane(cld_wave_scan_u32(r.scanned));
     r.heavy = cld_last_lane(cld_wave_scan_u32(r.heavy));
+  }
+  if (steps && phase == PH_RELAX) {
+    cov = cld_last_lane(cld_wave_scan_u32(r.covered));
+    const uint32_t upd = cld_last_lane(cld_wave_scan_u32(r.updated));
+    if (lane == 0 && upd) atomicAdd(&S.sum.upd, upd);
   }
   if (phase != PH_RELAX && __any(r.acc != (is_min ? CLD_INF64 : 0ull)))
     for (int o = 32; o >= 1; o >>= 1) {
@@ -1791,6 +1828,7 @@ __device__ __forceinline__ void fresh_nodes(const Job &job, int32_t g, const GDe
     job.key[d.off + i] = CLD_INF64;
     job.keyn[d.off + i] = CLD_INF64;
     job.slim[d.off + i] = 0;
+    if (d.variant == CLDIAM_VARIANT_STEPS) job.R[d.off + i] = CLD_INF64;   // see step_state
   }
   const int64_t woff = d.off >> 6;
   for (int64_t w = at; w < d.words; w += stride) {
