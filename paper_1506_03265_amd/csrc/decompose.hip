@@ -144,6 +144,7 @@ struct GState {
   uint32_t c2;          // 1 while in CLUSTER2's iterations
   uint32_t pull;        // 1 once the graph grows new levels and stages by pulling (see PH_PULL)
   uint32_t pull_base;   // distance at which the current pulled level starts (its first bucket)
+  uint32_t again;       // PULL passes of this level so far
   uint32_t src_blk;     // the next stage's sources are the blocked set (no NEXT has filtered it)
   uint32_t records;     // some long row has a scan record
   uint32_t closed;      // one graph: done, and the books are closed (later sweeps return at once)
@@ -243,6 +244,16 @@ constexpr uint32_t kRmaxSlots = 1024;   // RMAX: LDS table of cluster maxima (di
 constexpr uint32_t kRmaxFree = 0xffffffffu;
 static_assert(kRmaxSlots == 1024, "RMAX slots are the top 10 bits of a 32-bit hash");
 constexpr uint32_t kPullArcs = 8;   // pull-mode switch: heavy blocked arcs per unreached node
+// PULL is repeated, by then over all uncovered nodes, while a pass changes more
+// than one in 2^kPullAgainShift of them.  A repeated pass reads a row only up to
+// its node's distance (0.65 to 1.2 ms on R-MAT scale 24, where pushing from the
+// nodes of the first pass took 13 ms and some 380 million arcs), and each hop of
+// the last few nodes costs less pushed.  R-MAT scale 24, 18 and two dozen mixed
+// requests take 15.4, 1.15 and 11.6 ms with one pass, 10.9, 1.16 and 9.8 with a
+// quarter, 10.4, 1.17 and 9.4 with 1/16, 10.6, 0.76 and 9.4 with 1/32, 11.2, 0.74
+// and 9.6 with 1/256.  kPullMost bounds the passes where distances take many hops.
+constexpr uint32_t kPullAgainShift = 5;
+constexpr uint32_t kPullMost = 16;
 constexpr int64_t kHubDegree = 8;   // hub rows: more than kHubDegree x the average degree ...
 constexpr int64_t kHubShare = 8;    // ... holding more than 1/kHubShare of the arcs: pull from the first stage
 
@@ -451,14 +462,18 @@ __device__ __forceinline__ void control_graph(const GDesc &d, GState &s, const G
       if (s.pull) {
         // the uncovered nodes pull from the assigned nodes and the new centers
         s.pull_base = 0;
+        s.again = 0;
         s.phase = PH_PULL;
         break;
       }
       begin_growth(d, s, 0);
       break;
     case PH_PULL:
-      // the pulled nodes are the frontier of the level
-      begin_growth(d, s, s.pull_base);
+      // while a pass changes many nodes another costs less than pushing from
+      // them (see kPullAgainShift); then those that it changed are the frontier
+      s.again++;
+      if (c.upd > s.nU >> kPullAgainShift && s.again < kPullMost) break;
+      begin_growth(d, s, c.fmin != 0xffffffffu && c.fmin > s.pull_base ? c.fmin : s.pull_base);
       break;
     case PH_RELAX:
       s.sweeps++;
@@ -527,6 +542,7 @@ __device__ __forceinline__ void control_graph(const GDesc &d, GState &s, const G
         s.phase = PH_ASSIGN;
       } else if (raise_delta(s, c.next)) {
         s.pull_base = (uint32_t)c.next;
+        s.again = 0;
         s.phase = PH_PULL;
       }
       break;
@@ -1181,7 +1197,11 @@ __device__ __forceinline__ void next_long(Run &r) {
 // neighbours u with a key of (d_u + w, c_u), d_u + w <= Delta (only v's own
 // thread writes v's key, so no atomic is needed); NEXT_PULL folds the smallest
 // d_u + w over the same arcs.  Rows are sorted by weight, so both stop early
-// (pull_more).
+// (pull_more).  A pass that changed many nodes is followed by another, in which
+// the reached nodes look for smaller offers as well.  Every node then has the
+// minimum over what its neighbours had after the pass before, so only the nodes
+// changed by the last pass have offers left to make and are the frontier.
+// One thread per row: four lanes, as in relaxation, took 5% longer.
 // A key read while its node is being pulled in the same pass is a real path
 // too, so taking it only moves the fixpoint closer.
 
@@ -1202,23 +1222,27 @@ __device__ __forceinline__ uint64_t pull_offer(const Run &r, uint64_t w, uint64_
   return du + w <= r.delta ? k + (w << 32) : CLD_INF64;
 }
 
-__device__ __forceinline__ void pull_apply(Run &r, int32_t v, uint64_t best, bool next) {
+// now: v's key before.
+__device__ __forceinline__ void pull_apply(Run &r, int32_t v, uint64_t now, uint64_t best, bool next) {
   if (next) {
     if (best < r.acc) r.acc = best;
-  } else if (best != CLD_INF64) {
+  } else if (best < now) {
     r.key[v] = best;
     set_bit(r.cur, v);
+    ++r.updated;
+    if ((uint32_t)(best >> 32) < r.fmin) r.fmin = (uint32_t)(best >> 32);
   }
 }
 
-// One uncovered node, its row scanned by this thread (long rows are deferred).
+// One uncovered node (in a level's first pass an unreached one), its row scanned by this thread (long rows are deferred).
 __device__ __forceinline__ void pull_item(Run &r, int32_t v, bool next) {
-  if (r.key[v] != CLD_INF64) return;
+  const uint64_t now = r.key[v];
   const int64_t a0 = r.d.row_ptr[v];
   const int32_t deg = (int32_t)(r.d.row_ptr[v + 1] - a0);
+  if (now != CLD_INF64 && (next || r.s.again == 0)) return;
   if (deg > r.d.mid_deg && defer_row(r, v, deg)) return;
   const uint64_t *row = r.d.arcs + a0;
-  uint64_t best = CLD_INF64;
+  uint64_t best = now;
   for (int32_t base = 0; base < deg; base += kScanBatch) {
     uint64_t arc[kScanBatch];
     bool ok[kScanBatch];
@@ -1241,7 +1265,7 @@ __device__ __forceinline__ void pull_item(Run &r, int32_t v, bool next) {
     }
     if (stop) break;
   }
-  pull_apply(r, v, best, next);
+  pull_apply(r, v, now, best, next);
 }
 
 __device__ __forceinline__ uint64_t wave_min_all(uint64_t x) {
@@ -1257,7 +1281,8 @@ __device__ __forceinline__ uint64_t wave_min_all(uint64_t x) {
 __device__ __forceinline__ void pull_long(Run &r, bool next) {
   const int32_t lane = (int32_t)(threadIdx.x & 63);
   auto mid = [&](int32_t v, const uint64_t *row, int32_t deg) {
-    uint64_t best = CLD_INF64;
+    const uint64_t now = r.key[v];
+    uint64_t best = now;
     for (int32_t base = 0; base < deg; base += 64) {
       const int32_t a = base + lane;
       const uint64_t arc = a < deg ? row[a] : ~0ull;
@@ -1266,11 +1291,12 @@ __device__ __forceinline__ void pull_long(Run &r, bool next) {
       const uint64_t m = wave_min_all(in ? pull_offer(r, arc >> 32, r.key[(int32_t)(uint32_t)arc], next) : CLD_INF64);
       best = m < best ? m : best;
     }
-    if (lane == 0) pull_apply(r, v, best, next);
+    if (lane == 0) pull_apply(r, v, now, best, next);
   };
   auto big = [&](int32_t v, const uint64_t *row, int32_t deg) {
     Stage &S = r.S;
-    if (threadIdx.x == 0) S.blk_min = CLD_INF64;
+    const uint64_t now = r.key[v];   // read before thread 0 writes it: every thread passes the barriers below first
+    if (threadIdx.x == 0) S.blk_min = now;
     __syncthreads();
     for (int32_t base = 0; base < deg; base += kSweepThreads) {
       const uint64_t cur = S.blk_min;   // the same for every thread: nothing changes it between the barriers
@@ -1288,7 +1314,7 @@ __device__ __forceinline__ void pull_long(Run &r, bool next) {
       const bool stop = nxt >= deg || !pull_more(row[nxt] >> 32, S.blk_min, r.delta, next);
       if (stop) break;
     }
-    if (threadIdx.x == 0) pull_apply(r, v, S.blk_min, next);
+    if (threadIdx.x == 0) pull_apply(r, v, now, S.blk_min, next);
   };
   coop_rows(r, mid, big);
 }
@@ -1539,8 +1565,11 @@ __device__ __forceinline__ void process_run(const Job &job, const GDesc &d, cons
     case PH_NEXT_PULL: {
       const bool next = phase == PH_NEXT_PULL;
       if (next) r.acc = CLD_INF64;
-      for (uint32_t w = lo + threadIdx.x; w < hi; w += kSweepThreads)
+      for (uint32_t w = lo + threadIdx.x; w < hi; w += kSweepThreads) {
         if (blk[w]) blk[w] = 0;   // left from before the switch to pull mode
+        if (s.again && !next && r.cur[w]) r.cur[w] = 0;   // every node looks at the changes of the pass before
+      }
+      __syncthreads();
       list_pass(r, lo, hi, [&](uint32_t w) { return U[w]; }, [&](int32_t v) { pull_item(r, v, next); },
                 [&] { pull_long(r, next); });
       break;
@@ -1658,8 +1687,8 @@ __device__ __forceinline__ void process_run(const Job &job, const GDesc &d, cons
     r.scanned = cld_last_lane(cld_wave_scan_u32(r.scanned));
     r.heavy = cld_last_lane(cld_wave_scan_u32(r.heavy));
   }
-  if (steps && phase == PH_RELAX) {
-    cov = cld_last_lane(cld_wave_scan_u32(r.covered));
+  if (phase == PH_PULL || (steps && phase == PH_RELAX)) {
+    if (steps) cov = cld_last_lane(cld_wave_scan_u32(r.covered));
     const uint32_t upd = cld_last_lane(cld_wave_scan_u32(r.updated));
     if (lane == 0 && upd) atomicAdd(&S.sum.upd, upd);
   }
@@ -1668,7 +1697,7 @@ __device__ __forceinline__ void process_run(const Job &job, const GDesc &d, cons
       const unsigned long long y = __shfl_xor(r.acc, o);
       r.acc = is_min ? (y < r.acc ? y : r.acc) : (phase == PH_SELECT ? r.acc + y : (y > r.acc ? y : r.acc));
     }
-  if (phase == PH_RELAX && __any(r.fmin != 0xffffffffu)) {
+  if ((phase == PH_RELAX || phase == PH_PULL) && __any(r.fmin != 0xffffffffu)) {
     for (int o = 32; o >= 1; o >>= 1) {
       const uint32_t y = __shfl_xor(r.fmin, o);
       r.fmin = y < r.fmin ? y : r.fmin;
