@@ -233,7 +233,7 @@ def step_bench(args, name):
                    "driver": "host-driven" if st.grid_blocks == 0 else "persistent"},
         "roofline": {"bound": "hbm", "achieved": round(achieved, 2), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": round(achieved / HBM_PEAK_GBS, 5), "traffic": traffic,
-                     "kernel": ("k_sweep+k_control launch loop" if st.grid_blocks == 0 else "k_persistent")
+                     "kernel": ("k_sweep launch loop" if st.grid_blocks == 0 else "k_persistent")
                                + " (one decomposition)", "kernel_ms": round(kernel_ms, 4),
                      "algorithmic_bytes": counts["bytes_decompose"], "random_access": random_access},
         "cpu_baseline": cpu,
