@@ -34,7 +34,7 @@ def _hub_path(leaves):
 
 
 GRAPHS = {"path2": _path(2), "path65": _path(65), "path3000": _path(3000), "grid40x90": graphgen.grid(40, 90, 1000, 4),
-          "hub33": _hub_path(33), "hub1025": _hub_path(1025), "hub9000": _hub_path(9000),
+          "hub33": _hub_path(33), "hub1024": _hub_path(1024), "hub1025": _hub_path(1025), "hub9000": _hub_path(9000),
           "rmat9": graphgen.rmat(9, seed=3), "rmat13": graphgen.rmat(13, seed=4)}
 KNOBS = [{}, dict(wave_row_min=2, group_row_min=30), dict(grid_blocks=8, chunk_factor=3), dict(local_rounds=0)]
 
