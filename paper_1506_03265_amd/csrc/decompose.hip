@@ -246,10 +246,10 @@ static_assert(kRmaxSlots == 1024, "RMAX slots are the top 10 bits of a 32-bit ha
 constexpr uint32_t kPullArcs = 8;   // pull-mode switch: heavy blocked arcs per unreached node
 // PULL is repeated, by then over all uncovered nodes, while a pass changes more
 // than one in 2^kPullAgainShift of them.  A repeated pass reads a row only up to
-// its node's distance (0.65 to 1.2 ms on R-MAT scale 24, where pushing from the
-// nodes of the first pass took 13 ms and some 380 million arcs), and each hop of
-// the last few nodes costs less pushed.  R-MAT scale 24, 18 and two dozen mixed
-// requests take 15.4, 1.15 and 11.6 ms with one pass, 10.9, 1.16 and 9.8 with a
+// its node's distance (0.4 to 1 ms on R-MAT scale 24, where pushing from the nodes
+// of the first pass took 13 ms and some 380 million arcs), and each hop of the
+// last few nodes costs less pushed.  With a wave for every long row (see kPullRow)
+// R-MAT scale 24, 18 and two dozen mixed requests took 15.4, 1.15 and 11.6 ms with one pass, 10.9, 1.16 and 9.8 with a
 // quarter, 10.4, 1.17 and 9.4 with 1/16, 10.6, 0.76 and 9.4 with 1/32, 11.2, 0.74
 // and 9.6 with 1/256.  kPullMost bounds the passes where distances take many hops.
 constexpr uint32_t kPullAgainShift = 5;
