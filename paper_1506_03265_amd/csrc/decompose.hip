@@ -249,9 +249,10 @@ constexpr uint32_t kPullArcs = 8;   // pull-mode switch: heavy blocked arcs per 
 // its node's distance (0.4 to 1 ms on R-MAT scale 24, where pushing from the nodes
 // of the first pass took 13 ms and some 380 million arcs), and each hop of the
 // last few nodes costs less pushed.  With a wave for every long row (see kPullRow)
-// R-MAT scale 24, 18 and two dozen mixed requests took 15.4, 1.15 and 11.6 ms with one pass, 10.9, 1.16 and 9.8 with a
-// quarter, 10.4, 1.17 and 9.4 with 1/16, 10.6, 0.76 and 9.4 with 1/32, 11.2, 0.74
-// and 9.6 with 1/256.  kPullMost bounds the passes where distances take many hops.
+// R-MAT scale 24, 18 and two dozen mixed requests took 15.4, 1.15 and 11.6 ms with
+// one pass, 10.9, 1.16 and 9.8 with a quarter, 10.4, 1.17 and 9.4 with 1/16, 10.6,
+// 0.76 and 9.4 with 1/32, 11.2, 0.74 and 9.6 with 1/256.  kPullMost bounds the
+// passes where distances take many hops.
 constexpr uint32_t kPullAgainShift = 5;
 constexpr uint32_t kPullMost = 16;
 // A reached node's row is read up to its distance only, a few arcs even of a long
