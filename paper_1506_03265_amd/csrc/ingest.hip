@@ -47,26 +47,38 @@ struct IngestCtl {
   unsigned long long diff;   // arcs that look their reverse up minus arcs that are looked up (mod 2^64)
 };
 
-// Checks the row offsets and notes, for every tile of kTile arcs, the row that
-// its first arc lies in.  The offsets of a row that passes are in [0, m], so
-// the notes stay in range whatever the others are.
-__global__ void __launch_bounds__(kT) k_check_rows(const int64_t *rp, int32_t n, int64_t m, int32_t *tile_row,
-                                                   IngestCtl *ctl) {
+// Checks the row offsets: two reads a row, whatever they hold.
+__global__ void __launch_bounds__(kT) k_check_rows(const int64_t *rp, int32_t n, int64_t m, IngestCtl *ctl) {
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
     const int64_t a0 = rp[i], a1 = rp[i + 1];
     bool ok = a0 <= a1 && a0 >= 0 && a1 <= m;
-    if (ok)
-      for (int64_t t = (a0 + kTile - 1) / kTile; t * kTile < a1; ++t) tile_row[t] = (int32_t)i;
     if (i == 0) ok = ok && a0 == 0;
     if (i == n - 1) ok = ok && a1 == m;
     if (!ok) atomicOr(&ctl->bad, BAD_ROWPTR);
   }
 }
 
+// The row that arc a lies in: the last of the n rows to start at or before a
+// (rows without arcs that start there come before it).  The offsets have been
+// checked.  Every lane of the wave calls it with the same arguments; each step
+// samples 64 offsets, three to five dependent reads in all.
+__device__ __forceinline__ int32_t row_of_arc(const int64_t *rp, int32_t n, int64_t a) {
+  const int64_t lane = threadIdx.x & 63;
+  int64_t lo = 0, hi = n;   // rp[lo] <= a < rp[hi]
+  while (hi - lo > 1) {
+    const int64_t step = (hi - lo + 63) >> 6, p = lo + lane * step;
+    lo += (__popcll(__ballot(p < hi && rp[p < hi ? p : lo] <= a)) - 1) * step;
+    hi = lo + step < hi ? lo + step : hi;
+  }
+  return (int32_t)lo;
+}
+
 // Validates and packs tiles of kTile consecutive arcs, one arc per thread and
 // step, so that a hub's row is spread over many workgroups (one wave per row
 // left the longest row alone with 20 ms of R-MAT scale 21's ingest).  An arc's
-// row comes from a maximum scan over the row starts inside the tile.
+// row comes from a maximum scan over the row starts inside the tile; the tile's
+// first row is searched for (noted by the row check it took work in the product of
+// rows and arcs when the offsets were malformed).
 //
 // Bound by scattered reads: 3.5 ms for the 62M arcs of R-MAT scale 21 (far row
 // offsets of every arc, a search per edge), 1.0 ms for the road-like 4096 x
@@ -78,10 +90,10 @@ __global__ void __launch_bounds__(kT) k_check_rows(const int64_t *rp, int32_t n,
 // a column once), and all arcs are matched if no others are left: the two
 // kinds of arcs must be equally many.
 __global__ void __launch_bounds__(kT) k_validate_pack(const int64_t *rp, const int32_t *col, const uint32_t *w,
-                                                      int32_t n, int64_t m, const int32_t *tile_row, uint64_t *arcs,
-                                                      IngestCtl *ctl) {
+                                                      int32_t n, int64_t m, uint64_t *arcs, IngestCtl *ctl) {
   __shared__ int32_t row[kTile];
   __shared__ int32_t wmax[kT / 64];
+  __shared__ int32_t ends[2];   // rows of the tile's first and last arc
   if (ctl->bad & BAD_ROWPTR) return;   // nothing is indexed with malformed offsets
   constexpr int kPer = kTile / kT;
   const int tid = (int)threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -91,12 +103,15 @@ __global__ void __launch_bounds__(kT) k_validate_pack(const int64_t *rp, const i
   for (int64_t t = blockIdx.x; t < tiles; t += gridDim.x) {
     const int64_t a0 = t * kTile;
     const int len = (int)(m - a0 < kTile ? m - a0 : kTile);
-    const int32_t row0 = tile_row[t], row1 = t + 1 < tiles ? tile_row[t + 1] : n - 1;
+    if (wave < 2) {
+      const int32_t r = row_of_arc(rp, n, wave == 0 ? a0 : a0 + len - 1);
+      if (lane == 0) ends[wave] = r;
+    }
     for (int i = tid; i < kTile; i += kT) row[i] = 0;
     __syncthreads();
+    const int32_t row0 = ends[0], row1 = ends[1];
     for (int64_t r = (int64_t)row0 + 1 + tid; r <= row1; r += kT) {
-      const int64_t at = rp[r] - a0;
-      if (at < len) atomicMax(&row[at], (int32_t)(r - row0));
+      atomicMax(&row[rp[r] - a0], (int32_t)(r - row0));
     }
     __syncthreads();
     // inclusive maximum scan, kPer consecutive entries per thread
@@ -368,7 +383,6 @@ extern "C" size_t cldiam_load_csr_workspace_size(int32_t n, int64_t m) {
   cld::Sizer s;
   s.take<IngestCtl>(1);
   s.take<int32_t>((size_t)ROW_CLASSES * n);        // rows by size class
-  s.take<int32_t>((size_t)((m + kTile - 1) / kTile) + 1);   // first row of each tile
   const int64_t nb = big_rows_cap(m), B = batch_cap(n, m);
   s.take<int64_t>(2 * (size_t)nb);   // (offset, degree) of every big row
   s.take<BigRow>((size_t)nb);
@@ -389,25 +403,24 @@ extern "C" int cldiam_load_csr(const cldiam_csr *g, uint64_t *d_arcs, uint64_t *
   cld::Arena a(ws, ws_bytes);
   IngestCtl *ctl = a.take<IngestCtl>(1);
   int32_t *rows = a.take<int32_t>((size_t)ROW_CLASSES * n);
-  int32_t *tile_row = a.take<int32_t>((size_t)((m + kTile - 1) / kTile) + 1);
   const int64_t nbcap = big_rows_cap(m), B = batch_cap(n, m);
   int64_t *binfo = a.take<int64_t>(2 * (size_t)nbcap);
   BigRow *brows = a.take<BigRow>((size_t)nbcap);
   uint64_t *bk = a.take<uint64_t>((size_t)B), *bo = a.take<uint64_t>((size_t)B);
   uint64_t *bkt = a.take<uint64_t>((size_t)B), *bot = a.take<uint64_t>((size_t)B);
-  if (!ctl || !rows || !tile_row || !binfo || !brows || !bk || !bo || !bkt || !bot) {
+  if (!ctl || !rows || !binfo || !brows || !bk || !bo || !bkt || !bot) {
     cld::set_error("load_csr: workspace of %zu bytes, %zu needed", ws_bytes, cldiam_load_csr_workspace_size(n, m));
     return CLDIAM_ENOMEM;
   }
   CLD_HIP(hipMemsetAsync(ctl, 0, sizeof(IngestCtl), stream));
   const int32_t *list[ROW_CLASSES];
   for (int c = 0; c < ROW_CLASSES; ++c) list[c] = rows + (int64_t)c * n;
-  k_check_rows<<<cld::blocks_for(n, kT, 4096), kT, 0, stream>>>(g->d_row_ptr, n, m, tile_row, ctl);
+  k_check_rows<<<cld::blocks_for(n, kT, 4096), kT, 0, stream>>>(g->d_row_ptr, n, m, ctl);
   CLD_LAUNCH_CHECK("k_check_rows");
   if (m > 0) {
     // malformed row offsets end the next two kernels at once
-    k_validate_pack<<<cld::blocks_for(m, kTile, 4096), kT, 0, stream>>>(g->d_row_ptr, g->d_col, g->d_w, n, m, tile_row,
-                                                                       d_arcs, ctl);
+    k_validate_pack<<<cld::blocks_for(m, kTile, 4096), kT, 0, stream>>>(g->d_row_ptr, g->d_col, g->d_w, n, m, d_arcs,
+                                                                       ctl);
     CLD_LAUNCH_CHECK("k_validate_pack");
     k_small_sort<<<cld::blocks_for(n, kSmallThreads, 4096), kSmallThreads, 0, stream>>>(g->d_row_ptr, n, d_arcs, rows, ctl);
     CLD_LAUNCH_CHECK("k_small_sort");
