@@ -24,6 +24,10 @@ namespace {
 
 constexpr int kT = 256;
 constexpr int kTile = 2048;       // arcs of one validation tile
+// A tile that spans more rows searches for those of its arcs: some 100 dependent
+// reads a thread, where visiting 16 rows per arc of the tile is 128 that overlap
+// (324 and 328 us for a 512 x 512 mesh with 63 nodes without arcs after each).
+constexpr int kWalkRows = 8 * kTile;
 constexpr int kThreadRow = 16;    // rows of up to 8 or 16 arcs: sorting network of one thread
 constexpr int kWaveRow = 64;      // ... one arc per lane of a wave
 constexpr int kWaveRow4 = 256;    // ... four
@@ -73,12 +77,25 @@ __device__ __forceinline__ int32_t row_of_arc(const int64_t *rp, int32_t n, int6
   return (int32_t)lo;
 }
 
+// The same by one thread, among the rows lo .. hi, which hold a.
+__device__ __forceinline__ int32_t row_between(const int64_t *rp, int32_t lo, int32_t hi, int64_t a) {
+  while (lo < hi) {
+    const int32_t mid = lo + ((hi - lo + 1) >> 1);
+    if (rp[mid] <= a) lo = mid; else hi = mid - 1;
+  }
+  return lo;
+}
+
 // Validates and packs tiles of kTile consecutive arcs, one arc per thread and
 // step, so that a hub's row is spread over many workgroups (one wave per row
 // left the longest row alone with 20 ms of R-MAT scale 21's ingest).  An arc's
-// row comes from a maximum scan over the row starts inside the tile; the tile's
-// first row is searched for (noted by the row check it took work in the product of
-// rows and arcs when the offsets were malformed).
+// row comes from a maximum scan over the row starts inside the tile; the rows of
+// the tile's first and last arc are searched for (noted by the row check they took
+// work in the product of rows and arcs when the offsets were malformed).  A tile
+// whose arcs lie more than kWalkRows rows apart, with a long run of rows without
+// arcs between them, searches for each thread's rows instead of visiting them all
+// (16 million such rows, at the end of a 1000 x 1000 mesh or amid it: 0.35 ms,
+// 18.5 when one workgroup visited them).
 //
 // Bound by scattered reads: 3.5 ms for the 62M arcs of R-MAT scale 21 (far row
 // offsets of every arc, a search per edge), 1.0 ms for the road-like 4096 x
@@ -110,30 +127,36 @@ __global__ void __launch_bounds__(kT) k_validate_pack(const int64_t *rp, const i
     for (int i = tid; i < kTile; i += kT) row[i] = 0;
     __syncthreads();
     const int32_t row0 = ends[0], row1 = ends[1];
-    for (int64_t r = (int64_t)row0 + 1 + tid; r <= row1; r += kT) {
-      atomicMax(&row[rp[r] - a0], (int32_t)(r - row0));
-    }
-    __syncthreads();
-    // inclusive maximum scan, kPer consecutive entries per thread
-    int32_t mx[kPer], run = 0;
+    if (row1 - row0 > kWalkRows) {
+      int32_t r = row0;
+      for (int i = tid * kPer; i < (tid + 1) * kPer && i < len; ++i) {
+        if (i == tid * kPer || rp[r + 1] <= a0 + i) r = row_between(rp, r, row1, a0 + i);
+        row[i] = r - row0;
+      }
+    } else {
+      for (int64_t r = (int64_t)row0 + 1 + tid; r <= row1; r += kT) atomicMax(&row[rp[r] - a0], (int32_t)(r - row0));
+      __syncthreads();
+      // inclusive maximum scan, kPer consecutive entries per thread
+      int32_t mx[kPer], run = 0;
 #pragma unroll
-    for (int j = 0; j < kPer; ++j) {
-      const int32_t x = row[tid * kPer + j];
-      run = x > run ? x : run;
-      mx[j] = run;
-    }
-    int32_t incl = run;
-    for (int o = 1; o < 64; o <<= 1) {
-      const int32_t y = __shfl_up(incl, o);
-      if (lane >= o && y > incl) incl = y;
-    }
-    if (lane == 63) wmax[wave] = incl;
-    int32_t before = __shfl_up(incl, 1);
-    if (lane == 0) before = 0;
-    __syncthreads();
-    for (int k = 0; k < wave; ++k) before = wmax[k] > before ? wmax[k] : before;
+      for (int j = 0; j < kPer; ++j) {
+        const int32_t x = row[tid * kPer + j];
+        run = x > run ? x : run;
+        mx[j] = run;
+      }
+      int32_t incl = run;
+      for (int o = 1; o < 64; o <<= 1) {
+        const int32_t y = __shfl_up(incl, o);
+        if (lane >= o && y > incl) incl = y;
+      }
+      if (lane == 63) wmax[wave] = incl;
+      int32_t before = __shfl_up(incl, 1);
+      if (lane == 0) before = 0;
+      __syncthreads();
+      for (int k = 0; k < wave; ++k) before = wmax[k] > before ? wmax[k] : before;
 #pragma unroll
-    for (int j = 0; j < kPer; ++j) row[tid * kPer + j] = mx[j] > before ? mx[j] : before;
+      for (int j = 0; j < kPer; ++j) row[tid * kPer + j] = mx[j] > before ? mx[j] : before;
+    }
     __syncthreads();
 #pragma unroll 2
     for (int j = 0; j < kPer; ++j) {
