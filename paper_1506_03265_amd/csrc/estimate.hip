@@ -17,7 +17,8 @@
 //
 // Few searches are needed: once node v's eccentricity ecc(v) is known, no node
 // u of its component has a larger one than ecc(v) + d(u, v), so a node whose
-// bound is not above the largest eccentricity found so far is skipped.  The
+// bound is not above the largest eccentricity found so far is skipped (on a
+// symmetric quotient: see k_check_symmetry).  The
 // order spreads the first sources over the ids, and one workgroup of 1024
 // threads per CU runs (more or smaller ones start more searches before the
 // bounds that exclude them: 537 and 751 us where this takes 431 on a quotient
@@ -48,7 +49,15 @@ __host__ __device__ inline size_t slice_bytes(int32_t k) { return ((size_t)k * 2
 struct ECtl {
   unsigned long long phi;   // largest eccentricity found
   uint32_t next;            // sources taken
-  uint32_t bad;   // the quotient CSR is malformed: nothing is indexed with it
+  uint32_t bad;        // the quotient CSR is malformed: nothing is indexed with it
+  uint32_t directed;   // some arc has no reverse of its weight where its row's order has it: no bounds
+};
+
+// The quotient graph in global memory.
+struct Csr {
+  const int64_t *rp;
+  const int32_t *col;
+  const uint64_t *w;
 };
 
 // The quotient CSR must have row offsets from 0 to qm, non-decreasing, and
@@ -65,6 +74,32 @@ __global__ void k_check_quotient(int32_t k, int64_t qm, const int64_t *rp, const
     if ((uint32_t)col[a] >= (uint32_t)k) *bad = 1u;
 }
 
+// The bounds on eccentricities hold where distances are the same both ways, so
+// every arc's reverse is looked up, a wave per row and an arc per lane, by binary
+// search in the far row.  An arc whose reverse is not where a row in ascending order
+// has it makes the estimate search from every node.
+__global__ void __launch_bounds__(kT) k_check_symmetry(int32_t k, Csr g, ECtl *ctl) {
+  if (ctl->bad) return;   // nothing is indexed with malformed offsets
+  const int64_t at = (int64_t)blockIdx.x * kT + threadIdx.x;
+  bool directed = false;
+  for (int64_t u = at >> 6; u < k; u += (int64_t)gridDim.x * (kT / 64)) {
+    const int64_t a1 = g.rp[u + 1];
+    for (int64_t a = g.rp[u] + (at & 63); a < a1; a += 64) {
+      const int32_t v = g.col[a];
+      int64_t lo = g.rp[v], hi = g.rp[v + 1];
+      bool found = false;
+      while (lo < hi) {
+        const int64_t mid = lo + ((hi - lo) >> 1);
+        const int32_t c = g.col[mid];
+        if (c == u) { found = g.w[mid] == g.w[a]; break; }
+        if (c < u) lo = mid + 1; else hi = mid;
+      }
+      if (!found) directed = true;
+    }
+  }
+  if (directed) ctl->directed = 1u;
+}
+
 constexpr int kGroup = 8;      // lanes per row
 constexpr int kWideRow = 128;  // longer rows are read by the whole workgroup
 constexpr int kWideCap = 128;  // such rows per pass (others are read by their group)
@@ -77,14 +112,7 @@ struct Search {
   uint32_t *queued;   // bitmap
 };
 
-// The quotient graph in global memory.
-struct Csr {
-  const int64_t *rp;
-  const int32_t *col;
-  const uint64_t *w;
-};
-
-// ... and copied to LDS.
+// The quotient graph copied to LDS.
 struct LdsCsr {
   const uint32_t *rp;
   const uint16_t *col;
@@ -190,6 +218,7 @@ template <class Graph, class Id>
 __device__ __forceinline__ void search_all(int32_t k, const Graph &g, const Search<Id> &x, uint64_t *ub, uint32_t step,
                                            ECtl *ctl) {
   __shared__ int32_t src;
+  const bool bounds = !ctl->directed;
   for (;;) {
     if (threadIdx.x == 0) {
       for (;;) {
@@ -197,7 +226,7 @@ __device__ __forceinline__ void search_all(int32_t k, const Graph &g, const Sear
         src = i < (uint32_t)k ? (int32_t)((uint64_t)i * step % (uint32_t)k) : -1;
         if (src < 0) break;
         const unsigned long long found = __hip_atomic_load(&ctl->phi, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (__hip_atomic_load(&ub[src], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) > found) break;
+        if (!bounds || __hip_atomic_load(&ub[src], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) > found) break;
       }
     }
     __syncthreads();
@@ -264,7 +293,7 @@ int grid_for(int32_t k) { return k < kMaxSearches ? k : kMaxSearches; }
 __global__ void __launch_bounds__(kT) k_zero_ctl(ECtl *ctl, uint64_t *ub, int32_t k) {
   const int64_t at = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   for (int64_t v = at; v < k; v += (int64_t)gridDim.x * blockDim.x) ub[v] = CLD_INF64;
-  if (at == 0) { ctl->phi = 0; ctl->next = 0; ctl->bad = 0; }
+  if (at == 0) { ctl->phi = 0; ctl->next = 0; ctl->bad = 0; ctl->directed = 0; }
 }
 
 // Checks, APSP and readback, with the control block, the bounds and the
@@ -277,8 +306,10 @@ int estimate_run(int32_t k, int64_t qm, const int64_t *rp, const int32_t *col, c
   k_check_quotient<<<cld::blocks_for(k > qm ? (int64_t)k : qm, kT, 1024), kT, 0, stream>>>(k, qm, rp, col,
                                                                                            &ctl->bad);
   CLD_LAUNCH_CHECK("k_check_quotient");
-  const uint32_t step = spread_step(k);
   const Csr g{rp, col, w};
+  k_check_symmetry<<<cld::blocks_for((int64_t)k * 64, kT, 1024), kT, 0, stream>>>(k, g, ctl);
+  CLD_LAUNCH_CHECK("k_check_symmetry");
+  const uint32_t step = spread_step(k);
   if (k > kLdsMaxK) {
     k_apsp_global<<<grid, kSearchT, 0, stream>>>(k, g, ub, step, ctl, slices);
   } else if (qm <= (int64_t)kLdsBytes && resident_bytes(k, qm) <= kLdsBytes) {
