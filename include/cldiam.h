@@ -339,7 +339,9 @@ int cldiam_estimate_diameter_noalloc(int32_t k, int64_t qm, const int64_t *d_qro
  * bucket_delta = 0 picks the default width: 16 x floor(sum of arc weights /
  * m), at least 1 and at most 2^31 (1 on a graph without arcs), computed on
  * the device from d_arcs.  A finite distance >= 0xFFFFFFFF returns
- * CLDIAM_EOVERFLOW. */
+ * CLDIAM_EOVERFLOW.  A search that is not done 60 s after its first step on
+ * the device (earlier work of the stream does not count) returns
+ * CLDIAM_ETIMEOUT. */
 size_t cldiam_sssp_workspace_size(int32_t n, int64_t m);
 int cldiam_sssp_delta_stepping(int32_t n, int64_t m, const int64_t *d_row_ptr, const uint64_t *d_arcs,
                                int32_t source, uint32_t bucket_delta, uint32_t *d_dist, uint64_t *h_max_dist,

@@ -408,8 +408,10 @@ extern "C" int cldiam_sssp_delta_stepping(int32_t n, int64_t m, const int64_t *d
   k_sssp_init<<<cld::blocks_for(n, kT, 8192), kT, 0, stream>>>(j, source);
   CLD_LAUNCH_CHECK("k_sssp_init");
   // The host queues steps at most kLead ahead of the device and stops once a
-  // step reports that the step before it left nothing to relax.
-  const auto t0 = std::chrono::steady_clock::now();
+  // step reports that the step before it left nothing to relax.  The time limit
+  // counts from the first step: the stream may have other work before it.
+  std::chrono::steady_clock::time_point t0;
+  bool begun = false;
   uint32_t queued = 0;
   while (!hm[1]) {
     if (queued < hm[0] + kLead) {
@@ -422,7 +424,12 @@ extern "C" int cldiam_sssp_delta_stepping(int32_t n, int64_t m, const int64_t *d
       }
       continue;
     }
-    if (std::chrono::steady_clock::now() - t0 > std::chrono::seconds(kLimitSeconds)) {
+    const auto now = std::chrono::steady_clock::now();
+    if (!begun && hm[0]) {
+      begun = true;
+      t0 = now;
+    }
+    if (begun && now - t0 > std::chrono::seconds(kLimitSeconds)) {
       CLD_HIP(hipStreamSynchronize(stream));
       cld::set_error("sssp: search exceeded its time limit");
       return CLDIAM_ETIMEOUT;
