@@ -402,6 +402,13 @@ extern "C" int cldiam_sssp_delta_stepping(int32_t n, int64_t m, const int64_t *d
   cld::Pinned<SCtl> pinned;   // readback buffer; its first line mirrors the device's progress during the search
   if (!pinned.p) { cld::set_error("sssp: pinned host buffer allocation failed"); return CLDIAM_EHIP; }
   volatile uint32_t *hm = (volatile uint32_t *)pinned.p;
+  // queued steps write the mirror, so the buffer goes back to the pool after them
+  // on every way out
+  struct Drain {
+    hipStream_t stream;
+    bool armed;
+    ~Drain() { if (armed) (void)hipStreamSynchronize(stream); }
+  } drain{stream, true};
   hm[0] = 0;
   hm[1] = 0;
   CLD_HIP(hipHostGetDevicePointer((void **)&j.mirror, (void *)pinned.p, 0));
@@ -417,11 +424,7 @@ extern "C" int cldiam_sssp_delta_stepping(int32_t n, int64_t m, const int64_t *d
     if (queued < hm[0] + kLead) {
       ++queued;
       k_sssp_step<<<blocks, kStepThreads, 0, stream>>>(j, queued);
-      const hipError_t e = hipGetLastError();
-      if (e != hipSuccess) {
-        (void)hipStreamSynchronize(stream);   // queued steps still write the mirror
-        return cld::hip_fail(e, "k_sssp_step");
-      }
+      CLD_LAUNCH_CHECK("k_sssp_step");
       continue;
     }
     const auto now = std::chrono::steady_clock::now();
@@ -430,7 +433,6 @@ extern "C" int cldiam_sssp_delta_stepping(int32_t n, int64_t m, const int64_t *d
       t0 = now;
     }
     if (begun && now - t0 > std::chrono::seconds(kLimitSeconds)) {
-      CLD_HIP(hipStreamSynchronize(stream));
       cld::set_error("sssp: search exceeded its time limit");
       return CLDIAM_ETIMEOUT;
     }
@@ -440,6 +442,7 @@ extern "C" int cldiam_sssp_delta_stepping(int32_t n, int64_t m, const int64_t *d
   CLD_LAUNCH_CHECK("k_sssp_max");
   CLD_HIP(hipMemcpyAsync(pinned.p, j.ctl, sizeof(SCtl), hipMemcpyDeviceToHost, stream));
   CLD_HIP(hipStreamSynchronize(stream));
+  drain.armed = false;
   if (pinned.p->maybe) {
     k_sssp_overflow<<<cld::blocks_for(n, kT, 4096), kT, 0, stream>>>(j);
     CLD_LAUNCH_CHECK("k_sssp_overflow");

@@ -1,7 +1,8 @@
 """The host side of the SSSP search against a stand-in for the GPU, on the CPU:
 its host code is linked with a small runtime whose stream runs the launched
 steps one by one on a clock of its own.  The time limit counts from the search's
-first step, whatever the stream had to do before it."""
+first step, whatever the stream had to do before it, and the mapped buffer that
+queued steps write is not given back before they have run."""
 import os
 import re
 import shutil
@@ -130,3 +131,9 @@ def test_a_search_past_its_limit_ends(search):
         out = search(begins, begins + 10**6, 0)
         assert f"status {cd.CLDIAM_ETIMEOUT} " in out
         assert begins + 59 < float(out.split()[-2]) < begins + 63
+
+
+def test_the_mirror_is_given_back_after_the_last_step(search):
+    for out in (search(0, 3, 0), search(0, 3, 1), search(0, 10**6, 0)):
+        assert "released with 0 steps queued" in out
+    assert f"status {cd.CLDIAM_EHIP} " in search(0, 3, 1)       # a launch after the search fails
