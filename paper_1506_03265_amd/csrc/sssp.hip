@@ -54,7 +54,14 @@ constexpr int kMidRow = 32;       // longer rows are relaxed by one wave ...
 constexpr int kBigRow = 4096;     // ... and these by the whole workgroup
 constexpr int kMidCap = kStepThreads;
 constexpr int kBigCap = 64;
-constexpr int kMinWords = 16;     // fewest bitmap words of a workgroup
+// Fewest bitmap words of a workgroup: as many as hold kMinArcs arcs on average, but
+// no more than kMinWords (a launch of more workgroups costs more: R-MAT scale 18 at
+// width 5000 takes 5.9 ms with 16 words, 6.5 with 9, 8.7 with 4).  A frontier of
+// neighbouring nodes with long rows otherwise falls to one or two workgroups: a
+// band of 200,000 nodes joined to the 80 nearest takes 742 ms with 6 words, 1110
+// with 16, the complete graph of 3000 nodes 1.7 with one word, 14.1 with 16.
+constexpr int kMinWords = 16;
+constexpr int64_t kMinArcs = 16384;
 // Local rounds: on sparse graphs a round carries the search a hop further for
 // a quarter of a step's cost (road-like 4096 x 4096 mesh: 145 ms without, 37 with
 // 16 or 32, 39 with 64 and a longer queue).  On graphs of more than kDenseDegree arcs per
@@ -396,7 +403,9 @@ extern "C" int cldiam_sssp_delta_stepping(int32_t n, int64_t m, const int64_t *d
   j.words = bitmap_words(n);
   const uint32_t most = (uint32_t)(cus * kBlocksPerCu);
   j.chunk = (j.words + most - 1) / most;
-  if (j.chunk < kMinWords) j.chunk = kMinWords;
+  const int64_t fit = m > 0 ? kMinArcs * n / (32 * m) : kMinWords;
+  const uint32_t least = fit < 1 ? 1u : (fit < kMinWords ? (uint32_t)fit : (uint32_t)kMinWords);
+  if (j.chunk < least) j.chunk = least;
   const int blocks = (int)(((j.words + j.chunk - 1) / j.chunk + 7) / 8 * 8);   // a multiple of the XCDs
   j.rounds = m > kDenseDegree * n ? 0 : kRounds;
   cld::Pinned<SCtl> pinned;   // readback buffer; its first line mirrors the device's progress during the search
