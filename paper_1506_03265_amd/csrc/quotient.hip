@@ -167,30 +167,53 @@ __device__ __forceinline__ uint64_t reversed(uint64_t key, int kb) {
   return (key & ((1ull << kb) - 1ull)) << kb | key >> kb;
 }
 
+// Room for `each` entries of every active lane of a wave, one addition in all:
+// the first entry of this lane's.  Out of line: inlined wherever a pair is
+// emitted it cost the arc pass 4% (R-MAT scale 20, 2 clusters: 2.16, now 2.06 ms).
+template <class T>
+__device__ __attribute__((noinline)) T reserve(T *counter, uint32_t each) {
+  const uint64_t m = __ballot(true);
+  const int lane = (int)(threadIdx.x & 63), first = __ffsll((long long)m) - 1;
+  T base = 0;
+  if (lane == first) base = atomicAdd(counter, (T)(each * (uint32_t)__popcll(m)));
+  return __shfl(base, first) + (T)(each * (uint32_t)__popcll(m & ((1ull << lane) - 1ull)));
+}
+
 // Lowers key's value in the table; a new key's slot is noted in claims[] (up to
-// claim_cap, counted in *claimed) for one reservation later, or at once.
-__device__ void put_pair(const Table &t, bool full, uint64_t key, uint64_t val, int32_t *claims, uint32_t claim_cap,
-                         uint32_t *claimed) {
+// claim_cap, counted in *claimed) for one reservation later, or at once.  False:
+// the table has no room for the key.  *full: the table takes no new keys.
+__device__ __forceinline__ bool put_pair(const Table &t, uint32_t *full, uint64_t key, uint64_t val, int32_t *claims,
+                                         uint32_t claim_cap, uint32_t *claimed) {
   uint32_t h = (uint32_t)((key * 0xD6E8FEB86659FD93ull) >> 44) & (kTableSlots - 1);
   for (int p = 0; p < kTableProbes; ++p) {
     unsigned long long at = __hip_atomic_load(&t.key[h], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (at == ~0ull) {
-      if (full) break;
+      if (*full) return false;
       at = atomicCAS(&t.key[h], ~0ull, (unsigned long long)key);
       if (at == ~0ull) {
         const uint32_t i = claim_cap ? atomicAdd(claimed, 1u) : 0u;
-        if (i < claim_cap) claims[i] = (int32_t)h;
-        else t.slot[atomicAdd(&t.ctl->uniq, 1u)] = h;
+        if (i < claim_cap) {
+          claims[i] = (int32_t)h;
+        } else {
+          const uint32_t c = reserve(&t.ctl->uniq, 1u);
+          t.slot[c] = h;
+          if (c >= kTableMost) *full = 1;
+        }
         at = key;
       }
     }
     if (at == key) {
       if (val < __hip_atomic_load(&t.val[h], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMin(&t.val[h], (unsigned long long)val);
-      return;
+      return true;
     }
     h = (h + 1) & (kTableSlots - 1);
   }
-  const unsigned long long at = atomicAdd(&t.ctl->pairs, 2ull);
+  *full = 1;
+  return false;
+}
+
+// Both directions of a pair at `at` on the list.
+__device__ __forceinline__ void list_pair(const Table &t, uint64_t at, uint64_t key, uint64_t val) {
   t.keys[at] = key;
   t.vals[at] = val;
   t.keys[at + 1] = reversed(key, t.kb);
@@ -229,7 +252,10 @@ struct EmitState {
   int32_t big[kEmitDefer];
   uint32_t nmid, nbig, used;
   uint32_t chunk, base;
-  uint32_t full;   // the table of all pairs takes no new keys (as read at the last flush)
+  uint32_t listed;            // of a flush: pairs for the list ...
+  unsigned long long list;    // ... and their place
+  uint32_t full;   // the table of all pairs takes no new keys (from the last flush on, or met since)
+  uint32_t blind;  // ... and holds so few of this workgroup's that they go to the list unseen
   Table table;
 };
 
@@ -267,33 +293,59 @@ __device__ __forceinline__ void emit_pair(EmitState &E, uint64_t key, uint64_t v
     }
     h = (h + 1) & (kHashCap - 1);
   }
-  put_pair(E.table, E.full != 0, key, val, nullptr, 0, nullptr);
+  if (E.blind || !put_pair(E.table, &E.full, key, val, nullptr, 0, nullptr))
+    list_pair(E.table, reserve(&E.table.ctl->pairs, 2u), key, val);
 }
 
 __device__ void hash_flush(EmitState &E) {
-  // One look at the count and one reservation per flush: with one of each per
-  // new key, the count's line took 200 of the arc pass's 300 us on a road-like
-  // 2048 x 2048 mesh of 2228 clusters.
+  // One look at the count and one reservation per flush, of new keys as of pairs
+  // for the list: with one of each per new key, the count's line took 200 of the
+  // arc pass's 300 us on a road-like 2048 x 2048 mesh of 2228 clusters, and with
+  // one per listed pair a 2048 x 2048 mesh of 5000 scattered clusters, 4 million
+  // such pairs, took 104 ms (4.3 now).  A workgroup whose pairs are hardly ever in
+  // the full table stops looking there (blind).
   if (threadIdx.x == 0) {
     E.nmid = 0;   // E.mid holds the slots of new keys meanwhile: their count is reserved once
+    E.listed = 0;
     E.full = __hip_atomic_load(&E.table.ctl->uniq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= kTableMost;
   }
   __syncthreads();
-  for (uint32_t i = threadIdx.x; i < kHashCap; i += blockDim.x) {
-    if (E.hkey[i] != ~0ull) {
-      put_pair(E.table, E.full != 0, E.hkey[i], E.hval[i], E.mid, kEmitDefer, &E.nmid);
+  uint32_t mine = 0;
+  for (uint32_t i = threadIdx.x; i < kHashCap; i += kEmitThreads) {
+    const uint64_t key = E.hkey[i];
+    if (key == ~0ull) continue;
+    if (!E.blind && put_pair(E.table, &E.full, key, E.hval[i], E.mid, kEmitDefer, &E.nmid)) {
       E.hkey[i] = ~0ull;
       E.hval[i] = ~0ull;
+    } else {
+      ++mine;
     }
+  }
+  const uint32_t incl = cld_wave_scan_u32(mine), all = cld_last_lane(incl);
+  uint32_t at = 0;
+  if (all) {
+    if ((threadIdx.x & 63) == 0) at = atomicAdd(&E.listed, all);
+    at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at) + incl - mine;
   }
   __syncthreads();
   const uint32_t n = E.nmid < kEmitDefer ? E.nmid : kEmitDefer;
   if (threadIdx.x == 0) {
+    E.blind = E.listed > E.used / 8 * 7;
     E.used = 0;
     E.base = n ? atomicAdd(&E.table.ctl->uniq, n) : 0u;
+    E.list = E.listed ? atomicAdd(&E.table.ctl->pairs, 2ull * E.listed) : 0ull;
   }
   __syncthreads();
-  for (uint32_t i = threadIdx.x; i < n; i += blockDim.x) E.table.slot[E.base + i] = (uint32_t)E.mid[i];
+  for (uint32_t i = threadIdx.x; i < n; i += kEmitThreads) E.table.slot[E.base + i] = (uint32_t)E.mid[i];
+  if (mine) {
+    for (uint32_t i = threadIdx.x; i < kHashCap; i += kEmitThreads) {
+      const uint64_t key = E.hkey[i];
+      if (key == ~0ull) continue;
+      list_pair(E.table, E.list + 2ull * at++, key, E.hval[i]);
+      E.hkey[i] = ~0ull;
+      E.hval[i] = ~0ull;
+    }
+  }
   __syncthreads();
   if (threadIdx.x == 0) E.nmid = 0;
   __syncthreads();
@@ -404,7 +456,7 @@ __global__ void __launch_bounds__(kEmitThreads, 8) k_emit(const int64_t *rp, con
   const int kb = bits_for_dev(k > 0 ? k - 1 : 0u);
   for (uint32_t i = threadIdx.x; i < kHashCap; i += blockDim.x) { E.hkey[i] = ~0ull; E.hval[i] = ~0ull; }
   if (threadIdx.x == 0) {
-    E.nmid = 0; E.nbig = 0; E.used = 0; E.full = 0;
+    E.nmid = 0; E.nbig = 0; E.used = 0; E.full = 0; E.blind = 0;
     E.table = t;
     E.table.kb = kb;
   }
