@@ -18,14 +18,24 @@
 // Few searches are needed: once node v's eccentricity ecc(v) is known, no node
 // u of its component has a larger one than ecc(v) + d(u, v), so a node whose
 // bound is not above the largest eccentricity found so far is skipped (on a
-// symmetric quotient: see k_check_symmetry).  The
-// order spreads the first sources over the ids, and one workgroup of 1024
-// threads per CU runs (more or smaller ones start more searches before the
-// bounds that exclude them: 537 and 751 us where this takes 431 on a quotient
-// of 2228 nodes and 12028 arcs, without the copy in LDS).
+// symmetric quotient: see k_check_symmetry).  The order spreads the first sources
+// over the ids.  How the searches are launched:
+//   - kPilots first, one workgroup of 1024 threads per CU.  Their bounds exclude
+//     nearly all others on quotients of meshes and social graphs, and on a ring or
+//     a torus, whose eccentricities are all alike, none;
+//   - then wide searches again if at most kFewLeft sources are left, else as many
+//     of 256 threads as the card holds, which a few nodes' frontier leaves free;
+//   - a quotient of short rows (fewer than kThinRow arcs a node) that the card holds
+//     a search for every node of has them all at once, of 128 threads: bounds would
+//     come no sooner than the results;
+//   - in global memory, with longer rows, wide searches alone take sources from a
+//     counter (waiting for the pilots cost 40% on 32,000 nodes of 25 arcs).
 //
-// That quotient takes 312 us (1771 us with a search from every node, 256 threads
-// each, one thread per row), the star-like one of R-MAT scale 24 54 us (356).
+// A quotient of 2228 nodes and 12028 arcs takes 312 us (1771 us with a search
+// from every node, 256 threads each, one thread per row), the star-like one of R-MAT
+// scale 24 54 us (356).  A ring of 1000 nodes takes 0.47 ms (1.68 with one search per
+// CU throughout), of 3000 5.8 (14.4), of 13,000 192 (592), a torus of 50 x 60 0.48
+// (0.93), a mesh of 55 x 55 0.39 (0.45).
 #include <algorithm>
 #include <mutex>
 #include <numeric>
@@ -36,9 +46,17 @@
 namespace {
 
 constexpr int kT = 256;
-constexpr int kSearchT = 1024;   // threads of one search, one search per CU
-constexpr int kMaxSearches = 256;
-constexpr size_t kLdsBytes = 160 * 1024 - 2048;   // for a search's arrays (the rest: its own small variables)
+constexpr int kWideT = 1024;   // threads of a search ...
+constexpr int kThinT = 256;    // ... where many are left
+constexpr int kSmallT = 128;   // ... in a quotient of short rows that the card holds a search for every node of
+constexpr int64_t kThinRow = 3;
+constexpr int kCus = 256;
+constexpr int kCuThreads = 2048;
+constexpr int kPilots = kCus;        // searches that run first, for their bounds
+constexpr uint32_t kFewLeft = 4 * kCus;   // wide searches follow for no more than these
+constexpr int kMaxSlices = 1024;     // searches in global memory at most
+constexpr size_t kLdsTotal = 160 * 1024, kLdsOwn = 2048;   // a CU's, and of a search for its own small variables
+constexpr size_t kLdsBytes = kLdsTotal - kLdsOwn;          // for a search's arrays
 constexpr int kLdsMaxK = 12800;  // 12.1 bytes per node -> 155 KB
 
 // Bytes of one workgroup's distances, queues and queued set in global memory: a
@@ -48,7 +66,7 @@ __host__ __device__ inline size_t slice_bytes(int32_t k) { return ((size_t)k * 2
 
 struct ECtl {
   unsigned long long phi;   // largest eccentricity found
-  uint32_t next;            // sources taken
+  uint32_t next;            // sources that the shared counter has handed out
   uint32_t bad;        // the quotient CSR is malformed: nothing is indexed with it
   uint32_t directed;   // some arc has no reverse of its weight where its row's order has it: no bounds
 };
@@ -133,14 +151,14 @@ __device__ __forceinline__ uint64_t distance(const Search<Id> &x, int32_t u) {
 }
 
 // Exact distances from s; returns the largest finite one.
-template <class Graph, class Id>
+template <int T, class Graph, class Id>
 __device__ __forceinline__ unsigned long long sssp_block(int32_t k, const Graph &g, int32_t s, const Search<Id> &x) {
   __shared__ uint32_t qn[2], nwide;
   __shared__ Id wide[kWideCap];
   __shared__ unsigned long long bmax;
   const int32_t tid = (int32_t)threadIdx.x, lane = tid % kGroup;
-  for (int32_t v = tid; v < k; v += kSearchT) x.dist[v] = CLD_INF64;
-  for (int32_t i = tid; i < (k + 31) / 32; i += kSearchT) x.queued[i] = 0;
+  for (int32_t v = tid; v < k; v += T) x.dist[v] = CLD_INF64;
+  for (int32_t i = tid; i < (k + 31) / 32; i += T) x.queued[i] = 0;
   if (tid == 0) { qn[0] = 1; qn[1] = 0; nwide = 0; bmax = 0; }
   __syncthreads();
   if (tid == 0) { x.dist[s] = 0; x.queue[0][0] = (Id)s; x.queued[s >> 5] = 1u << (s & 31); }
@@ -150,7 +168,7 @@ __device__ __forceinline__ unsigned long long sssp_block(int32_t k, const Graph 
     if (n == 0) break;
     const Id *cur = x.queue[q];
     Id *next = x.queue[q ^ 1];
-    for (uint32_t i0 = 0; i0 < n; i0 += kSearchT / kGroup) {
+    for (uint32_t i0 = 0; i0 < n; i0 += T / kGroup) {
       const uint32_t i = i0 + (uint32_t)(tid / kGroup);
       if (i < n) {
         const int32_t u = (int32_t)cur[i];
@@ -181,14 +199,14 @@ __device__ __forceinline__ unsigned long long sssp_block(int32_t k, const Graph 
       const int32_t u = (int32_t)wide[i];
       const uint64_t du = distance(x, u);
       const auto a1 = g.rp[u + 1];
-      for (auto a = g.rp[u] + tid; a < a1; a += kSearchT) relax_arc(x, (int32_t)g.col[a], du + g.w[a], &qn[q ^ 1], next);
+      for (auto a = g.rp[u] + tid; a < a1; a += T) relax_arc(x, (int32_t)g.col[a], du + g.w[a], &qn[q ^ 1], next);
     }
     __syncthreads();
     if (tid == 0) { qn[q] = 0; nwide = 0; }
     __syncthreads();
   }
   unsigned long long m = 0;
-  for (int32_t v = tid; v < k; v += kSearchT)
+  for (int32_t v = tid; v < k; v += T)
     if (x.dist[v] != CLD_INF64 && x.dist[v] > m) m = x.dist[v];
   for (int o = 32; o >= 1; o >>= 1) {
     const unsigned long long y = __shfl_xor(m, o);
@@ -212,31 +230,65 @@ __device__ __forceinline__ Search<Id> place(char *base, int32_t k) {
   return Search<Id>{dist, {q, q + k}, queued};
 }
 
-// Takes sources in the order i * step mod k until none is left; ub[v] bounds
-// v's eccentricity from above.
-template <class Graph, class Id>
-__device__ __forceinline__ void search_all(int32_t k, const Graph &g, const Search<Id> &x, uint64_t *ub, uint32_t step,
-                                           ECtl *ctl) {
+// Sources of a launch: those at places first .. end - 1 in the order
+// i * step mod k; workgroup b's at first + b, first + b + blocks, ..., or whichever
+// is next (`shared`: a counter, 25 ns a source).  ub[v] bounds v's eccentricity from
+// above.
+struct Sources {
+  uint32_t k, step, first, end;
+  bool shared;
+  uint32_t most;   // the launch makes no search where more are left
+  uint64_t *ub;
+  ECtl *ctl;
+  __device__ __forceinline__ int32_t at(uint32_t i) const { return (int32_t)((uint64_t)i * step % k); }
+  // whether no node beats the largest eccentricity found when its own is that of source i
+  __device__ __forceinline__ bool excluded(uint32_t i) const {
+    return !ctl->directed && __hip_atomic_load(&ub[at(i)], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) <=
+                                 __hip_atomic_load(&ctl->phi, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+};
+
+// Whether the workgroup has any search to make: some source of its own is not
+// excluded, and no more than q.most of all are.
+__device__ __forceinline__ bool some_left(const Sources &q) {
+  if (q.ctl->bad) return false;
+  const uint32_t tid = threadIdx.x, threads = blockDim.x;
+  bool some = false;
+  for (uint64_t i = q.first + blockIdx.x + (uint64_t)tid * gridDim.x; i < q.end; i += (uint64_t)threads * gridDim.x)
+    some = some || !q.excluded((uint32_t)i);
+  if (!__syncthreads_or(some)) return false;
+  if (q.most >= q.k) return true;
+  if (q.ctl->directed) return false;   // nothing is ever excluded
+  uint32_t left = 0;
+  for (uint32_t i = q.first; i < q.end && left <= q.most; i += threads)
+    left += (uint32_t)__syncthreads_count(i + tid < q.end && !q.excluded(i + tid));
+  return left <= q.most;
+}
+
+template <int T, class Graph, class Id>
+__device__ __forceinline__ void search_all(const Graph &g, const Search<Id> &x, const Sources &q) {
   __shared__ int32_t src;
-  const bool bounds = !ctl->directed;
+  const int32_t k = (int32_t)q.k;
+  uint64_t i = q.first + blockIdx.x;   // thread 0's place
   for (;;) {
     if (threadIdx.x == 0) {
       for (;;) {
-        const uint32_t i = atomicAdd(&ctl->next, 1u);
-        src = i < (uint32_t)k ? (int32_t)((uint64_t)i * step % (uint32_t)k) : -1;
-        if (src < 0) break;
-        const unsigned long long found = __hip_atomic_load(&ctl->phi, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (!bounds || __hip_atomic_load(&ub[src], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) > found) break;
+        if (q.shared) i = q.first + (uint64_t)atomicAdd(&q.ctl->next, 1u);
+        src = i < q.end ? q.at((uint32_t)i) : -1;
+        if (src < 0 || !q.excluded((uint32_t)i)) break;
+        i += gridDim.x;
       }
+      i += gridDim.x;
     }
     __syncthreads();
     const int32_t s = src;
     if (s < 0) return;
-    const unsigned long long ecc = sssp_block(k, g, s, x);
-    if (threadIdx.x == 0) atomicMax(&ctl->phi, ecc);
-    for (int32_t v = threadIdx.x; v < k; v += kSearchT) {
+    const unsigned long long ecc = sssp_block<T>(k, g, s, x);
+    if (threadIdx.x == 0 && ecc > __hip_atomic_load(&q.ctl->phi, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+      atomicMax(&q.ctl->phi, ecc);
+    for (int32_t v = threadIdx.x; v < k; v += T) {
       const uint64_t d = x.dist[v];
-      if (d != CLD_INF64 && d + ecc >= ecc) atomicMin((unsigned long long *)&ub[v], (unsigned long long)(d + ecc));
+      if (d != CLD_INF64 && d + ecc >= ecc) atomicMin((unsigned long long *)&q.ub[v], (unsigned long long)(d + ecc));
     }
     __syncthreads();
   }
@@ -248,32 +300,32 @@ __host__ __device__ inline size_t resident_bytes(int32_t k, int64_t qm) {
   return copy_at(k) + (size_t)qm * 10 + ((size_t)k + 1) * 4;
 }
 
-template <bool kResident>
-__global__ void __launch_bounds__(kSearchT) k_apsp_lds(int32_t k, int64_t qm, Csr g, uint64_t *ub, uint32_t step,
-                                                       ECtl *ctl) {
-  if (ctl->bad) return;
+template <int T, bool kResident>
+__global__ void __launch_bounds__(T) k_apsp_lds(int64_t qm, Csr g, Sources q) {
+  if (!some_left(q)) return;
   extern __shared__ uint64_t lds[];
+  const int32_t k = (int32_t)q.k;
   const Search<uint16_t> x = place<uint16_t>((char *)lds, k);
   if (kResident) {
     uint64_t *w = (uint64_t *)((char *)lds + copy_at(k));
     uint32_t *rp = (uint32_t *)(w + qm);
     uint16_t *col = (uint16_t *)(rp + k + 1);
-    for (int32_t a = threadIdx.x; a < (int32_t)qm; a += kSearchT) {
+    for (int32_t a = threadIdx.x; a < (int32_t)qm; a += T) {
       w[a] = g.w[a];
       col[a] = (uint16_t)g.col[a];
     }
-    for (int32_t v = threadIdx.x; v <= k; v += kSearchT) rp[v] = (uint32_t)g.rp[v];
+    for (int32_t v = threadIdx.x; v <= k; v += T) rp[v] = (uint32_t)g.rp[v];
     __syncthreads();
-    search_all(k, LdsCsr{rp, col, w}, x, ub, step, ctl);
+    search_all<T>(LdsCsr{rp, col, w}, x, q);
   } else {
-    search_all(k, g, x, ub, step, ctl);
+    search_all<T>(g, x, q);
   }
 }
 
-__global__ void __launch_bounds__(kSearchT) k_apsp_global(int32_t k, Csr g, uint64_t *ub, uint32_t step, ECtl *ctl,
-                                                          char *slices) {
-  if (ctl->bad) return;
-  search_all(k, g, place<int32_t>(slices + slice_bytes(k) * blockIdx.x, k), ub, step, ctl);
+template <int T>
+__global__ void __launch_bounds__(T) k_apsp_global(Csr g, Sources q, char *slices) {
+  if (!some_left(q)) return;
+  search_all<T>(g, place<int32_t>(slices + slice_bytes((int32_t)q.k) * blockIdx.x, (int32_t)q.k), q);
 }
 
 // A step near k / golden ratio without a common divisor with k: multiples of
@@ -285,8 +337,41 @@ uint32_t spread_step(int32_t k) {
   return step;
 }
 
-// Workgroups at most (each with a slice of global memory above kLdsMaxK).
-int grid_for(int32_t k) { return k < kMaxSearches ? k : kMaxSearches; }
+// Slices of global memory for quotients above kLdsMaxK nodes, one per workgroup.
+int slices_for(int32_t k) { return k < kMaxSlices ? k : kMaxSlices; }
+
+// Searches of T threads that the card holds with `bytes` of LDS each for arrays.
+template <int T>
+int resident_searches(size_t bytes) {
+  const int by_lds = (int)(kLdsTotal / (bytes + kLdsOwn)), by_threads = kCuThreads / T;
+  return kCus * (by_lds < by_threads ? by_lds : by_threads);
+}
+
+// The searches of q by at most `most` workgroups of T threads.  nslices: slices of
+// global memory that there are for quotients above kLdsMaxK nodes.
+template <int T>
+int search(int64_t qm, const Csr &g, const Sources &q, char *slices, int nslices, int most, hipStream_t stream) {
+  if (q.first >= q.end) return CLDIAM_OK;
+  const int32_t k = (int32_t)q.k;
+  int grid = (int)(q.end - q.first);
+  if (grid > most) grid = most;
+  if (k > kLdsMaxK) {
+    if (grid > nslices) grid = nslices;   // workgroup b works in slice b
+    k_apsp_global<T><<<grid, T, 0, stream>>>(g, q, slices);
+    CLD_LAUNCH_CHECK("k_apsp_global");
+    return CLDIAM_OK;
+  }
+  // wide searches take the copy of the graph where it fits at all, the others where
+  // it does not cost them places
+  const size_t bare = search_bytes(k, 2), with = qm <= (int64_t)kLdsBytes ? resident_bytes(k, qm) : kLdsTotal;
+  const bool copy = with <= kLdsBytes && (T == kWideT || resident_searches<T>(with) == resident_searches<T>(bare));
+  const int fit = resident_searches<T>(copy ? with : bare);
+  if (grid > fit) grid = fit;
+  if (copy) k_apsp_lds<T, true><<<grid, T, with, stream>>>(qm, g, q);
+  else k_apsp_lds<T, false><<<grid, T, bare, stream>>>(qm, g, q);
+  CLD_LAUNCH_CHECK("k_apsp_lds");
+  return CLDIAM_OK;
+}
 
 // Fresh control block and bounds (a kernel rather than a memset node, so that a
 // caller may capture the call in a graph).
@@ -297,9 +382,9 @@ __global__ void __launch_bounds__(kT) k_zero_ctl(ECtl *ctl, uint64_t *ub, int32_
 }
 
 // Checks, APSP and readback, with the control block, the bounds and the
-// per-workgroup slices already placed; `grid` workgroups take the sources.
+// `nslices` per-workgroup slices already placed.
 int estimate_run(int32_t k, int64_t qm, const int64_t *rp, const int32_t *col, const uint64_t *w, uint64_t radius,
-                 uint64_t *h_phi_gc, uint64_t *h_phi_approx, ECtl *ctl, uint64_t *ub, char *slices, int grid,
+                 uint64_t *h_phi_gc, uint64_t *h_phi_approx, ECtl *ctl, uint64_t *ub, char *slices, int nslices,
                  hipStream_t stream) {
   k_zero_ctl<<<cld::blocks_for(k, kT, 256), kT, 0, stream>>>(ctl, ub, k);
   CLD_LAUNCH_CHECK("k_zero_ctl");
@@ -309,15 +394,27 @@ int estimate_run(int32_t k, int64_t qm, const int64_t *rp, const int32_t *col, c
   const Csr g{rp, col, w};
   k_check_symmetry<<<cld::blocks_for((int64_t)k * 64, kT, 1024), kT, 0, stream>>>(k, g, ctl);
   CLD_LAUNCH_CHECK("k_check_symmetry");
-  const uint32_t step = spread_step(k);
-  if (k > kLdsMaxK) {
-    k_apsp_global<<<grid, kSearchT, 0, stream>>>(k, g, ub, step, ctl, slices);
-  } else if (qm <= (int64_t)kLdsBytes && resident_bytes(k, qm) <= kLdsBytes) {
-    k_apsp_lds<true><<<grid, kSearchT, resident_bytes(k, qm), stream>>>(k, qm, g, ub, step, ctl);
+  Sources q{(uint32_t)k, spread_step(k), 0, (uint32_t)k, false, (uint32_t)k, ub, ctl};
+  const bool thin = qm < kThinRow * (int64_t)k, in_lds = k <= kLdsMaxK;
+  int rc = CLDIAM_OK;
+  if (thin && in_lds && k <= resident_searches<kSmallT>(search_bytes(k, 2))) {
+    rc = search<kSmallT>(qm, g, q, slices, nslices, k, stream);
+  } else if (!thin && !in_lds) {
+    q.shared = true;
+    rc = search<kWideT>(qm, g, q, slices, nslices, kPilots, stream);
   } else {
-    k_apsp_lds<false><<<grid, kSearchT, search_bytes(k, 2), stream>>>(k, qm, g, ub, step, ctl);
+    q.end = (uint32_t)(k < kPilots ? k : kPilots);
+    rc = search<kWideT>(qm, g, q, slices, nslices, kPilots, stream);
+    q.first = q.end;
+    q.end = (uint32_t)k;
+    if (!rc && !thin) {
+      q.most = kFewLeft;
+      rc = search<kWideT>(qm, g, q, slices, nslices, kCus, stream);
+      q.most = (uint32_t)k;
+    }
+    if (!rc) rc = search<kThinT>(qm, g, q, slices, nslices, k, stream);
   }
-  CLD_LAUNCH_CHECK("k_apsp");
+  if (rc) return rc;
   ECtl h;
   CLD_HIP(hipMemcpyAsync(&h, ctl, sizeof h, hipMemcpyDeviceToHost, stream));
   CLD_HIP(hipStreamSynchronize(stream));
@@ -369,7 +466,7 @@ extern "C" size_t cldiam_estimate_workspace_size(int32_t k, int64_t qm) {
   cld::Sizer s;
   s.take<ECtl>(1);
   s.take<uint64_t>((size_t)k);
-  if (k > kLdsMaxK) s.take<char>(slice_bytes(k) * grid_for(k));
+  if (k > kLdsMaxK) s.take<char>(slice_bytes(k) * slices_for(k));
   return s.used;
 }
 
@@ -385,14 +482,14 @@ extern "C" int cldiam_estimate_diameter(int32_t k, int64_t qm, const int64_t *d_
   ECtl *ctl = a.take<ECtl>(1);
   uint64_t *ub = a.take<uint64_t>((size_t)k);
   char *slices = nullptr;
-  if (k > kLdsMaxK) slices = a.take<char>(slice_bytes(k) * grid_for(k));
+  if (k > kLdsMaxK) slices = a.take<char>(slice_bytes(k) * slices_for(k));
   if (!ctl || !ub || (k > kLdsMaxK && !slices)) {
     cld::set_error("estimate_diameter: workspace of %zu bytes, %zu needed", ws_bytes,
                    cldiam_estimate_workspace_size(k, qm));
     return CLDIAM_ENOMEM;
   }
   return estimate_run(k, qm, d_qrow_ptr, d_qcol, d_qw, radius, h_phi_gc, h_phi_approx, ctl, ub, slices,
-                      grid_for(k), stream);
+                      slices_for(k), stream);
 }
 
 extern "C" int cldiam_estimate_diameter_noalloc(int32_t k, int64_t qm, const int64_t *d_qrow_ptr,
@@ -412,7 +509,7 @@ extern "C" int cldiam_estimate_diameter_noalloc(int32_t k, int64_t qm, const int
   int rc = scratch_on_current_device(&base);
   if (rc) return rc;
   // as many workgroups as the slices that fit (at least 1 for every k up to the maximum)
-  int grid = grid_for(k);
+  int grid = slices_for(k);
   if (k > kLdsMaxK) {
     const size_t fit = (kStaticBytes - kStaticCtl - kStaticUb) / slice_bytes(k);
     if ((size_t)grid > fit) grid = (int)fit;
