@@ -307,7 +307,8 @@ int cldiam_build_quotient(int32_t n, int64_t m, const int64_t *d_row_ptr, const 
  * Phi(G_C) = exact largest finite shortest-path distance between two nodes of
  * the quotient graph (k nodes, symmetric CSR from cldiam_build_quotient), and
  * Phi_approx = Phi(G_C) + 2 radius, the conservative estimate of Section 4
- * (radius = max D of the decomposition).  Results on the host.  Row offsets
+ * (radius = max D of the decomposition).  A CSR that is not symmetric gives the
+ * largest finite distance of an ordered pair.  Results on the host.  Row offsets
  * that do not run from 0 to qm without decreasing, or a column outside
  * [0, k), return CLDIAM_EINVAL before the CSR is traversed. */
 size_t cldiam_estimate_workspace_size(int32_t k, int64_t qm);
@@ -317,11 +318,12 @@ int cldiam_estimate_diameter(int32_t k, int64_t qm, const int64_t *d_qrow_ptr, c
 
 /* For callers that cannot allocate device memory (code under graph capture,
  * tight serving loops, harnesses that forbid hipMalloc): the same estimate
- * with no workspace argument.  Its scratch (control words and, above 3072
- * quotient nodes, per-workgroup distance and queue slices) is a static 32 MiB
- * device array of the library; each GPU holds its own copy from the first
- * call on that device until the process ends.  The call allocates nothing
- * (no device or pinned memory; results are read back into host stack memory).
+ * with no workspace argument.  Its scratch (control words, a bound of 8 bytes
+ * per quotient node and, above 12800 nodes, per-workgroup distance and queue
+ * slices) is a static 32 MiB device array of the library; each GPU holds its own
+ * copy from the first call on that device until the process ends.  The call
+ * allocates nothing (no device or pinned memory; results are read back into host
+ * stack memory).
  * k above CLDIAM_NOALLOC_MAX_K returns CLDIAM_EINVAL before any device work.
  * Every call on one GPU uses that GPU's array: calls that overlap in time on
  * the same GPU (from several threads or streams) race and must not be made.

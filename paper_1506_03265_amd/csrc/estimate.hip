@@ -62,7 +62,7 @@ constexpr int kLdsMaxK = 12800;  // 12.1 bytes per node -> 155 KB
 // Bytes of one workgroup's distances, queues and queued set in global memory: a
 // multiple of 8, so that every workgroup's 64-bit distances are aligned (a
 // 64-bit atomic on an address that is not faults).
-__host__ __device__ inline size_t slice_bytes(int32_t k) { return ((size_t)k * 20 + 7) & ~(size_t)7; }
+__host__ __device__ constexpr size_t slice_bytes(int32_t k) { return ((size_t)k * 20 + 7) & ~(size_t)7; }
 
 struct ECtl {
   unsigned long long phi;   // largest eccentricity found
@@ -435,6 +435,7 @@ constexpr size_t kStaticBytes = (size_t)32 << 20;
 constexpr size_t kStaticCtl = 256;
 constexpr size_t kStaticUb = (size_t)CLDIAM_NOALLOC_MAX_K * 8;   // the bounds, after the control block
 static_assert(sizeof(ECtl) <= kStaticCtl, "control block fits its slot");
+static_assert(kStaticCtl + kStaticUb + slice_bytes(CLDIAM_NOALLOC_MAX_K) <= kStaticBytes, "a slice for every k");
 static __device__ __align__(256) char scratch[kStaticBytes];
 
 // Device address of `scratch` on each device, resolved once per device with
@@ -508,12 +509,12 @@ extern "C" int cldiam_estimate_diameter_noalloc(int32_t k, int64_t qm, const int
   char *base = nullptr;
   int rc = scratch_on_current_device(&base);
   if (rc) return rc;
-  // as many workgroups as the slices that fit (at least 1 for every k up to the maximum)
-  int grid = slices_for(k);
+  // the slices that fit (at least 1 for every k up to the maximum)
+  int nslices = slices_for(k);
   if (k > kLdsMaxK) {
     const size_t fit = (kStaticBytes - kStaticCtl - kStaticUb) / slice_bytes(k);
-    if ((size_t)grid > fit) grid = (int)fit;
+    if ((size_t)nslices > fit) nslices = (int)fit;
   }
   return estimate_run(k, qm, d_qrow_ptr, d_qcol, d_qw, radius, h_phi_gc, h_phi_approx, (ECtl *)base,
-                      (uint64_t *)(base + kStaticCtl), base + kStaticCtl + kStaticUb, grid, stream);
+                      (uint64_t *)(base + kStaticCtl), base + kStaticCtl + kStaticUb, nslices, stream);
 }
