@@ -92,24 +92,6 @@ __device__ __forceinline__ uint32_t cld_philox_word0(uint32_t c0, uint32_t c1, u
   return c0;
 }
 
-__device__ __forceinline__ int cld_lane() { return (int)(threadIdx.x & 63); }
-
-// Wave-aggregated reservation of `pred ? 1 : 0` slots on a counter.  Works
-// with any subset of active lanes; returns the slot of a predicated lane.
-__device__ __forceinline__ uint32_t cld_wave_reserve(bool pred, uint32_t *counter) {
-  unsigned long long mask = __ballot(pred);
-  uint32_t slot = 0;
-  if (mask) {
-    int leader = __ffsll((long long)mask) - 1;
-    int lane = cld_lane();
-    uint32_t base = 0;
-    if (lane == leader) base = atomicAdd(counter, (uint32_t)__popcll(mask));
-    base = __shfl(base, leader);
-    slot = base + (uint32_t)__popcll(mask & ((1ull << lane) - 1ull));
-  }
-  return slot;
-}
-
 // Inclusive sum over the lanes of a whole wave (every lane active): shifts by
 // 1, 2, 4 and 8 within rows of 16 lanes, then the rows' last lanes passed on.
 // Register moves (DPP) instead of the LDS permutes behind __shfl_up: 0.1
@@ -127,18 +109,6 @@ __device__ __forceinline__ uint32_t cld_wave_scan_u32(uint32_t x) {
 // The last lane's value, for every lane (a scan's total).
 __device__ __forceinline__ uint32_t cld_last_lane(uint32_t x) {
   return (uint32_t)__builtin_amdgcn_readlane((int)x, 63);
-}
-
-// Min / max / sum over the lanes that are active, result broadcast to them.
-__device__ __forceinline__ uint64_t cld_wave_min_u64(uint64_t v) {
-  unsigned long long mask = __ballot(true);
-  while (mask) {
-    int src = __ffsll((long long)mask) - 1;
-    mask &= mask - 1;
-    uint64_t o = __shfl(v, src);
-    v = o < v ? o : v;
-  }
-  return v;
 }
 
 // ------------------------------------------------------------ grid barrier --

@@ -722,7 +722,6 @@ struct Stage {
   unsigned long long row_key;  // key of the big row being scanned
   int32_t row_lo;              // end of its light prefix (index within the row)
   int32_t row_start;           // first arc of its scan (index within the row)
-  uint32_t blk_hit;
   uint32_t wsum[2][kWaves];
   uint32_t chunk;              // next chunk of this workgroup
   uint32_t stop;               // local rounds end early: most of the grid has finished the sweep
