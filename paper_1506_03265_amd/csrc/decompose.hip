@@ -16,10 +16,11 @@
 // and the blocked nodes, one 64-bit word per 64 nodes.  Each graph's words are
 // cut into chunks (one per workgroup, or a few per workgroup on large dense
 // graphs); workgroup b takes chunk b and further chunks go to whichever
-// workgroup asks next.  A workgroup owns the words of its chunk, so it walks its
-// nodes in ascending order (neighbouring nodes share cache lines: frontiers
-// kept as unordered lists moved several times the lines) and changes the sets
-// that it walks without atomics.
+// workgroup asks next.  (Growth chunks of a graph whose arcs lie in a small part of
+// the id range are cut at nodes of equal arcs, see kSkew.)  A workgroup owns
+// the words of its chunk, so it walks its nodes in ascending order (neighbouring
+// nodes share cache lines: frontiers kept as unordered lists moved several times the
+// lines) and changes the sets that it walks without atomics.
 //
 // Node state is one u64 key per node: (growth distance << 32) | center id,
 // ~0 when unset.  An offer (d_u + w, c_u) is applied with a 64-bit atomicMin,
@@ -148,6 +149,7 @@ struct GState {
   uint32_t again;       // PULL passes of this level so far
   uint32_t src_blk;     // the next stage's sources are the blocked set (no NEXT has filtered it)
   uint32_t records;     // some long row has a scan record
+  uint32_t cuts;        // growth chunks cut at nodes of equal arcs (0: chunks of equal ids)
   uint32_t closed;      // one graph: done, and the books are closed (later sweeps return at once)
 };
 static_assert(sizeof(GState) % 4 == 0, "copied word by word");
@@ -195,7 +197,7 @@ struct Job {
   GState *ring;      // one graph: the state after the last sweep and the current one
   GCount *cn;        // one per graph (one graph: a ring of three)
   Ctl *ctl;
-  uint32_t *seg;     // [0, G]: exclusive prefix of per-graph chunks; [G+1, 2G]: words per chunk
+  uint32_t *seg;     // [0, G]: exclusive prefix of per-graph chunks; [G+1, 2G]: words per chunk (0: cut)
   int32_t *log;      // G x CLDIAM_STAGE_LOG x 4
   uint64_t *key;
   uint64_t *keyn;    // synchronous steps: updates of the odd steps (see step_state); CLUSTER2's iterations:
@@ -206,6 +208,7 @@ struct Job {
                      // synchronous steps: for nodes with a distance, updates of the even steps as well
   uint64_t *U;       // bitmap: uncovered nodes
   uint64_t *F;       // four bitmaps, one after the other, in the roles of GState
+  int32_t *cut;      // graph at node slot off: first node of each of its cuts, from 2 (off / 64) on, and the end
   int64_t fwords;    // words of one
   int32_t G;
   int32_t nblocks;        // workgroups of a sweep launch
@@ -246,6 +249,22 @@ constexpr int kJobSeconds = 60;   // device-side limit of one decomposition job
 constexpr uint32_t kGrowWords = 8;
 constexpr int64_t kGrowArcs = 16384;
 constexpr uint32_t kPassWords = 16;
+// Chunks of equal ids leave most of the card idle where the arcs lie in few of
+// them, as in graphs numbered by degree.  So when the fullest of kRanges equal id
+// ranges holds more than kSkew times the average, growth chunks are cut at nodes
+// where arcs, and kNodeCost for every node, are equal (at least kCutArcs of them):
+// R-MAT scale 21 numbered by degree takes 5.1 ms in steps, 10.7 in CLUSTER2 and 5.2
+// pushed; in chunks of equal ids 240, 240 and 100.  A relaxation takes kCutChunks per
+// workgroup, since a frontier of neighbouring nodes lies in few of them, and passes
+// over those without one (a band of 60 arcs a node beside a mesh of a million nodes
+// in CLUSTER2: 44 ms with one chunk, 27 with 4, 26 with 8).  Graphs of many nearly
+// empty sweeps lose by it (R-MAT scale 17 with its isolated nodes 54 to 74 ms).
+// Meshes and R-MAT graphs of random numbers stay below a skew of 2.
+constexpr int kRanges = 64;
+constexpr uint64_t kSkew = 4;
+constexpr uint64_t kNodeCost = 4;
+constexpr uint64_t kCutArcs = 4096;
+constexpr uint64_t kCutChunks = 4;
 constexpr uint32_t kRmaxSlots = 1024;   // RMAX: LDS table of cluster maxima (direct-mapped by center id)
 constexpr uint32_t kRmaxFree = 0xffffffffu;
 static_assert(kRmaxSlots == 1024, "RMAX slots are the top 10 bits of a 32-bit hash");
@@ -611,6 +630,51 @@ __device__ __forceinline__ uint32_t chunk_words(const GDesc &d, uint32_t phase, 
   return per > least ? per : least;
 }
 
+// Where the i-th of kRanges equal id ranges begins in the arcs.
+__device__ __forceinline__ uint64_t range_start(const GDesc &d, int i) {
+  const int64_t at = i * (((int64_t)d.n + kRanges - 1) / kRanges);
+  return (uint64_t)d.row_ptr[at < d.n ? at : d.n];
+}
+
+// Whether a graph is too small to be cut by arcs.
+__device__ __forceinline__ bool below_cuts(const GDesc &d) {
+  return (uint64_t)d.row_ptr[d.n] + kNodeCost * (uint64_t)d.n < 2 * kCutArcs;
+}
+
+// Growth chunks cut by arcs for a graph whose fullest id range holds `fullest`
+// (0: chunks of equal ids will do).
+__device__ __forceinline__ uint32_t cuts_for(const GDesc &d, uint64_t fullest, int32_t nblocks) {
+  const uint64_t m = (uint64_t)d.row_ptr[d.n];
+  if (fullest * kRanges <= kSkew * m) return 0;
+  const uint64_t most = kCutChunks * (uint64_t)nblocks * (uint32_t)d.chunk_factor, fit = (m + kNodeCost * (uint64_t)d.n) / kCutArcs;
+  uint64_t k = fit < most ? fit : most;
+  if (k > d.words) k = d.words;
+  return k > 1 ? (uint32_t)k : 0u;
+}
+
+// The phases whose chunks are cut so.
+__device__ __forceinline__ bool by_arcs(const GState &s) {
+  return s.cuts != 0 && (is_growth(s.phase) || s.phase == PH_C2_SELECT);
+}
+
+// Chunks of such a phase.  Only a relaxation, whose frontier may lie in a few
+// neighbouring ones, takes kCutChunks per workgroup.
+__device__ __forceinline__ uint32_t cuts_per_chunk(const GState &s) { return s.phase == PH_RELAX ? 1u : (uint32_t)kCutChunks; }
+__device__ __forceinline__ uint32_t cut_chunks(const GState &s) {
+  return (s.cuts + cuts_per_chunk(s) - 1) / cuts_per_chunk(s);
+}
+
+// The first node of cut i of k: where arcs and nodes before it cost i / k.
+__device__ __forceinline__ int32_t cut_at(const GDesc &d, uint32_t i, uint32_t k) {
+  const uint64_t m = (uint64_t)d.row_ptr[d.n], want = (m + kNodeCost * (uint64_t)d.n) * i / k;
+  int32_t lo = 0, hi = d.n;
+  while (lo < hi) {
+    const int32_t mid = lo + ((hi - lo) >> 1);
+    if ((uint64_t)d.row_ptr[mid] + kNodeCost * (uint64_t)mid < want) lo = mid + 1; else hi = mid;
+  }
+  return lo;
+}
+
 // Device time limit of a job, checked once per control step.
 __device__ __forceinline__ void check_time(Ctl *ctl) {
   const unsigned long long now = wall_clock64();
@@ -646,6 +710,16 @@ __device__ void control_block(const Job &job, bool restart = false) {
     if (g < job.G) {
       GState &s = job.st[g];
       if (s.phase != PH_DONE && s.phase != PH_IDLE) {
+        if (s.phase == PH_START && !below_cuts(job.desc[g])) {
+          uint64_t fullest = 0, last = 0;
+#pragma unroll 16
+          for (int i = 1; i <= kRanges; ++i) {
+            const uint64_t x = range_start(job.desc[g], i);
+            fullest = x - last > fullest ? x - last : fullest;
+            last = x;
+          }
+          s.cuts = cuts_for(job.desc[g], fullest, job.nblocks);
+        }
         if (ctl->error == 0) control_graph(job.desc[g], s, job.cn[g], job.log + (size_t)g * CLDIAM_STAGE_LOG * 4);
         else s.phase = PH_DONE;
         clear_count(job.cn[g]);
@@ -667,7 +741,9 @@ __device__ void control_block(const Job &job, bool restart = false) {
     if (g < job.G) {
       const uint32_t phase = job.st[g].phase;
       uint32_t per = 0;
-      if (phase != PH_DONE && phase != PH_IDLE) {
+      if (by_arcs(job.st[g])) {
+        chunks = cut_chunks(job.st[g]);
+      } else if (phase != PH_DONE && phase != PH_IDLE) {
         per = chunk_words(job.desc[g], phase, job.nblocks);
         if (per < avg) per = (uint32_t)avg;
         chunks = (job.desc[g].words + per - 1) / per;
@@ -744,6 +820,7 @@ struct Run {
   uint64_t *mark;        // where blocked nodes are marked (nullptr: nowhere)
   uint32_t delta, theta, theta_row;
   bool resume;           // long rows resume their last scan
+  uint32_t na, nb;       // nodes of a chunk cut by arcs, which may share its first and last word (nb = 0: whole words)
   uint32_t pass = 0;     // list passes so far
   uint32_t q = 0, qslot = 0;   // queue and counter that improvements go to
   // per-thread sums
@@ -754,6 +831,28 @@ struct Run {
 
 __device__ __forceinline__ void set_bit(uint64_t *bits, int32_t v) {
   atomicOr((unsigned long long *)&bits[v >> 6], 1ull << (v & 63));
+}
+
+// The workgroup's nodes of word w.
+__device__ __forceinline__ uint64_t own_bits(const Run &r, uint32_t w) {
+  if (r.nb == 0) return ~0ull;
+  uint64_t x = ~0ull;
+  if (w == r.na >> 6) x <<= r.na & 63;
+  if (w == (r.nb - 1) >> 6) x &= ~0ull >> (63 - ((r.nb - 1) & 63));
+  return x;
+}
+
+// Takes them out of word w of a set that no other workgroup adds to.
+__device__ __forceinline__ void drop_bits(const Run &r, uint64_t *bits, uint32_t w) {
+  const uint64_t own = own_bits(r, w);
+  if (own == ~0ull) bits[w] = 0;
+  else atomicAnd((unsigned long long *)&bits[w], (unsigned long long)~own);
+}
+
+__device__ __forceinline__ uint64_t take_bits(const Run &r, uint64_t *bits, uint32_t w) {
+  const uint64_t x = bits[w] & own_bits(r, w);
+  if (x) drop_bits(r, bits, w);
+  return x;
 }
 
 // v stays for the next sweep, at tentative distance dist.
@@ -1416,10 +1515,10 @@ __device__ __forceinline__ void list_pass(Run &r, uint32_t lo, uint32_t hi, Word
 constexpr int kNodeWords = 8;
 
 template <class Load, class Use>
-__device__ __forceinline__ void node_pass(const uint64_t *bits, uint32_t lo, uint32_t hi, Load load, Use use) {
+__device__ __forceinline__ void node_pass(const Run &r, const uint64_t *bits, uint32_t lo, uint32_t hi, Load load, Use use) {
   const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   for (uint32_t base = lo + wave * kNodeWords; base < hi; base += kWaves * kNodeWords) {
-    const uint64_t mine = lane < (uint32_t)kNodeWords && base + lane < hi ? bits[base + lane] : 0ull;
+    const uint64_t mine = lane < (uint32_t)kNodeWords && base + lane < hi ? bits[base + lane] & own_bits(r, base + lane) : 0ull;
     const uint64_t filled = __ballot(mine != 0);
     if (filled == 0) continue;
     const int at = __ffsll((long long)filled) - 1;   // a word with members, and its first
@@ -1462,9 +1561,9 @@ __device__ __forceinline__ void fold_rmax(Run &r, uint64_t *R, uint32_t c, uint6
   }
 }
 
-// Bitmap words [lo, hi) of graph g.
+// Bitmap words [lo, hi) of graph g, or its nodes [na, nb) there.
 __device__ __forceinline__ void process_run(const Job &job, const GDesc &d, const GState &s, GCount &cn, uint32_t *idle, uint32_t lo,
-                            uint32_t hi, Stage &S) {
+                            uint32_t hi, uint32_t na, uint32_t nb, Stage &S) {
   const uint32_t phase = s.phase, stage = s.stage, lane = threadIdx.x & 63;
   const uint32_t woff = (uint32_t)(d.off >> 6);
   const bool steps = d.variant == CLDIAM_VARIANT_STEPS;
@@ -1475,7 +1574,7 @@ __device__ __forceinline__ void process_run(const Job &job, const GDesc &d, cons
   Run r{job, d, s, S, job.key + d.off, job.keyn + d.off, job.slim + d.off,
         odd ? R : job.keyn + d.off, odd ? job.keyn + d.off : R, F + s.cur * job.fwords,
         F + s.nxt * job.fwords, s.pull ? nullptr : (s.merge ? alt : blk), s.delta, s.theta, row_lim < s.theta ? row_lim : s.theta,
-        !steps && !s.c2};
+        !steps && !s.c2, na, nb};
   if (threadIdx.x == 0) {
     clear_count(S.sum);
     S.qn[0] = S.qn[1] = S.qn[2] = 0;
@@ -1503,8 +1602,10 @@ __device__ __forceinline__ void process_run(const Job &job, const GDesc &d, cons
           if (r.cur[w]) r.cur[w] = 0;
         __syncthreads();
       }
+      if (!c2 && stage == 0 && lo == 0 && s.cuts != 0)
+        for (uint32_t i = threadIdx.x; i <= s.cuts; i += kSweepThreads) job.cut[2 * (d.off >> 6) + i] = cut_at(d, i, s.cuts);
       const bool hubs = !c2 && stage == 0 && d.pull_mode == CLDIAM_PULL_AUTO;
-      node_pass(U, lo, hi,
+      node_pass(r, U, lo, hi,
                 [&](int32_t v) { return hubs ? (uint64_t)(d.row_ptr[v + 1] - d.row_ptr[v]) : 0ull; },
                 [&](uint32_t w, int32_t v, bool in, uint64_t deg) {
         if (in && deg > d.hub_deg) r.acc += deg;
@@ -1521,7 +1622,7 @@ __device__ __forceinline__ void process_run(const Job &job, const GDesc &d, cons
       });
       if (c2)
         list_pass(r, lo, hi,
-                  [&](uint32_t w) { const uint64_t x = blk[w]; if (x) blk[w] = 0; return x; },
+                  [&](uint32_t w) { return take_bits(r, blk, w); },
                   [&](int32_t u) { c2_boundary(r, u); }, no_end);
       break;
     }
@@ -1530,39 +1631,34 @@ __device__ __forceinline__ void process_run(const Job &job, const GDesc &d, cons
         const bool merge = s.merge != 0;
         list_pass<kRowLanes>(r, lo, hi,
                   [&](uint32_t w) {
-                    uint64_t x = r.cur[w];
-                    if (x) r.cur[w] = 0;
-                    if (merge) {
-                      const uint64_t y = blk[w];
-                      if (y) blk[w] = 0;
-                      x |= y;
-                    }
+                    uint64_t x = take_bits(r, r.cur, w);
+                    if (merge) x |= take_bits(r, blk, w);
                     return x;
                   },
                   [&](int32_t u) { relax_item<true>(r, u); }, [&] { relax_long<true>(r); });
       } else {
-        list_pass<kRowLanes>(r, lo, hi, [&](uint32_t w) { const uint64_t x = r.cur[w]; if (x) r.cur[w] = 0; return x; },
+        list_pass<kRowLanes>(r, lo, hi, [&](uint32_t w) { return take_bits(r, r.cur, w); },
                   [&](int32_t u) { relax_item<false>(r, u); }, [&] { relax_long<false>(r); });
       }
       break;
     case PH_COMMIT:
-      node_pass(r.cur, lo, hi, key_of, [&](uint32_t, int32_t v, bool in, uint64_t k) {
+      node_pass(r, r.cur, lo, hi, key_of, [&](uint32_t, int32_t v, bool in, uint64_t k) {
         if (in) r.key[v] = step_state(k, r.pend[v]);
       });
       break;
     case PH_COUNT:
-      node_pass(U, lo, hi, key_of, [&](uint32_t, int32_t, bool in, uint64_t k) {
+      node_pass(r, U, lo, hi, key_of, [&](uint32_t, int32_t, bool in, uint64_t k) {
         cov += (uint32_t)__popcll(__ballot(in && k != CLD_INF64));
       });
       break;
     case PH_NEXT:
       r.acc = CLD_INF64;
       if (!steps)
-        node_pass(U, lo, hi, key_of, [&](uint32_t, int32_t, bool in, uint64_t k) {
+        node_pass(r, U, lo, hi, key_of, [&](uint32_t, int32_t, bool in, uint64_t k) {
           cov += (uint32_t)__popcll(__ballot(in && k != CLD_INF64));
         });
       list_pass(r, lo, hi,
-                [&](uint32_t w) { const uint64_t x = blk[w]; if (x && !steps) blk[w] = 0; return x; },
+                [&](uint32_t w) { return steps ? blk[w] & own_bits(r, w) : take_bits(r, blk, w); },
                 [&](int32_t u) {
                   const uint64_t ku = r.key[u];
                   const int64_t a0 = d.row_ptr[u];
@@ -1578,11 +1674,11 @@ __device__ __forceinline__ void process_run(const Job &job, const GDesc &d, cons
       const bool next = phase == PH_NEXT_PULL;
       if (next) r.acc = CLD_INF64;
       for (uint32_t w = lo + threadIdx.x; w < hi; w += kSweepThreads) {
-        if (blk[w]) blk[w] = 0;   // left from before the switch to pull mode
-        if (s.again && !next && r.cur[w]) r.cur[w] = 0;   // every node looks at the changes of the pass before
+        if (blk[w]) drop_bits(r, blk, w);   // left from before the switch to pull mode
+        if (s.again && !next && r.cur[w]) drop_bits(r, r.cur, w);   // every node looks at the changes of the pass before
       }
       __syncthreads();
-      list_pass(r, lo, hi, [&](uint32_t w) { return U[w]; }, [&](int32_t v) { pull_item(r, v, next); },
+      list_pass(r, lo, hi, [&](uint32_t w) { return U[w] & own_bits(r, w); }, [&](int32_t v) { pull_item(r, v, next); },
                 [&] { pull_long(r, next); });
       break;
     }
@@ -1590,7 +1686,7 @@ __device__ __forceinline__ void process_run(const Job &job, const GDesc &d, cons
       // D = growth distance + the cluster's radius before this stage (0 in the
       // first, whose pass therefore folds the new radii and takes the covered
       // nodes off the uncovered set as well)
-      node_pass(U, lo, hi, key_of, [&](uint32_t w, int32_t v, bool in, uint64_t k) {
+      node_pass(r, U, lo, hi, key_of, [&](uint32_t w, int32_t v, bool in, uint64_t k) {
         const bool got = in && k != CLD_INF64;
         if (got) {
           const uint32_t c = (uint32_t)k;
@@ -1611,7 +1707,7 @@ __device__ __forceinline__ void process_run(const Job &job, const GDesc &d, cons
       });
       break;
     case PH_RMAX:
-      node_pass(U, lo, hi, key_of, [&](uint32_t w, int32_t v, bool in, uint64_t k) {
+      node_pass(r, U, lo, hi, key_of, [&](uint32_t w, int32_t v, bool in, uint64_t k) {
         const bool got = in && k != CLD_INF64;
         if (got) {
           const uint32_t c = (uint32_t)k;
@@ -1624,7 +1720,7 @@ __device__ __forceinline__ void process_run(const Job &job, const GDesc &d, cons
       });
       break;
     case PH_SINGLE:
-      node_pass(U, lo, hi, no_load, [&](uint32_t, int32_t v, bool in, uint64_t) {
+      node_pass(r, U, lo, hi, no_load, [&](uint32_t, int32_t v, bool in, uint64_t) {
         if (!in) return;
         d.cluster[v] = v;
         d.D[v] = 0;
@@ -1640,7 +1736,7 @@ __device__ __forceinline__ void process_run(const Job &job, const GDesc &d, cons
         r.key[v] = CLD_INF64;
       break;
     case PH_C2_ASSIGN:
-      node_pass(U, lo, hi, key_of, [&](uint32_t w, int32_t v, bool in, uint64_t k) {
+      node_pass(r, U, lo, hi, key_of, [&](uint32_t w, int32_t v, bool in, uint64_t k) {
         const bool got = in && k != CLD_INF64;
         if (got) {
           const uint32_t c = (uint32_t)k;
@@ -1787,6 +1883,31 @@ __device__ __forceinline__ void take_chunks(const Job &job, SweepCount &sc, uint
   if (threadIdx.x == 0 && job.cutoff < (uint32_t)job.nblocks) atomicAdd(&sc.idle, 1u);
 }
 
+// Chunk c of a graph's sweep: `per` words, or cut by arcs (per = 0).
+__device__ __forceinline__ void run_chunk(const Job &job, const GDesc &d, const GState &s, GCount &cn, uint32_t *idle, uint32_t per,
+                          uint32_t c, Stage &S) {
+  uint32_t lo = c * per, hi = lo + per < d.words ? lo + per : d.words, na = 0, nb = 0;
+  if (per == 0) {
+    const int32_t *cut = job.cut + 2 * (d.off >> 6);
+    const uint32_t f = cuts_per_chunk(s), first = c * f, end = first + f < s.cuts ? first + f : s.cuts;
+    na = (uint32_t)__builtin_amdgcn_readfirstlane(cut[first]);
+    nb = (uint32_t)__builtin_amdgcn_readfirstlane(cut[end]);
+    if (na >= nb) return;   // a row that costs more than a chunk
+    lo = na >> 6;
+    hi = (nb + 63) >> 6;
+    if (s.phase == PH_RELAX) {
+      // several chunks per workgroup, most of them without a frontier: not worth
+      // a pass's fixed part
+      const uint64_t *F = job.F + (d.off >> 6);
+      bool any = false;
+      for (uint32_t w = lo + threadIdx.x; w < hi; w += kSweepThreads)
+        any = any || F[s.cur * job.fwords + w] != 0 || (s.merge && F[s.blk * job.fwords + w] != 0);
+      if (!__syncthreads_or(any)) return;
+    }
+  }
+  process_run(job, d, s, cn, idle, lo, hi, na, nb, S);
+}
+
 // A sweep of a job of several graphs, after its control launch.
 __device__ __forceinline__ void sweep_many(const Job &job, uint32_t block, uint32_t nblocks, Stage &S) {
   const uint32_t total = job.ctl->total;
@@ -1794,10 +1915,7 @@ __device__ __forceinline__ void sweep_many(const Job &job, uint32_t block, uint3
   take_chunks(job, sc, total, block, nblocks, S, [&](uint32_t v) {
     const int g = graph_of(job, v);
     const GDesc &d = job.desc[g];
-    const uint32_t per = job.seg[job.G + 1 + g];
-    const uint32_t lo = (v - job.seg[g]) * per;
-    const uint32_t hi = lo + per < d.words ? lo + per : d.words;
-    process_run(job, d, job.st[g], job.cn[g], &sc.idle, lo, hi, S);
+    run_chunk(job, d, job.st[g], job.cn[g], &sc.idle, job.seg[job.G + 1 + g], v - job.seg[g], S);
   });
 }
 
@@ -1814,6 +1932,14 @@ __device__ __forceinline__ bool sweep_one(const Job &job, const GDesc &d, uint32
   if (S.st.closed) return false;
   // the last workgroup, which has no chunk in a small graph, keeps the books
   const bool books = block == nblocks - 1;
+  if (t == 1 && tid < kRanges) {
+    uint64_t x = range_start(d, (int)tid + 1) - range_start(d, (int)tid);
+    for (int o = 32; o >= 1; o >>= 1) {
+      const uint64_t y = __shfl_xor(x, o);
+      x = y > x ? y : x;
+    }
+    if (tid == 0) S.st.cuts = cuts_for(d, x, (int32_t)nblocks);
+  }
   if (tid == 0) control_graph(d, S.st, S.last, books ? job.log : nullptr);
   __syncthreads();
   const bool done = S.st.phase == PH_DONE;
@@ -1843,12 +1969,13 @@ __device__ __forceinline__ bool sweep_one(const Job &job, const GDesc &d, uint32
   }
   if (done) return false;
   SweepCount &sc = ctl->sc[t % 3];
-  const uint32_t per = chunk_words(d, S.st.phase, (int32_t)nblocks);
-  const uint32_t total = (d.words + per - 1) / per;
-  take_chunks(job, sc, total, block, nblocks, S, [&](uint32_t v) {
-    const uint32_t lo = v * per, hi = lo + per < d.words ? lo + per : d.words;
-    process_run(job, d, S.st, job.cn[t % 3], &sc.idle, lo, hi, S);
-  });
+  uint32_t per = chunk_words(d, S.st.phase, (int32_t)nblocks), total = (d.words + per - 1) / per;
+  if (by_arcs(S.st)) {
+    per = 0;
+    total = cut_chunks(S.st);
+  }
+  take_chunks(job, sc, total, block, nblocks, S,
+              [&](uint32_t v) { run_chunk(job, d, S.st, job.cn[t % 3], &sc.idle, per, v, S); });
   return true;
 }
 
@@ -1962,6 +2089,7 @@ struct Layout {
   uint64_t *key, *keyn, *R;
   uint32_t *slim;
   uint64_t *U, *F;
+  int32_t *cut;
   int64_t fwords;
 };
 
@@ -1986,12 +2114,13 @@ bool carve(A &a, int64_t N, int32_t G, Layout *L) {
   auto p_slim = a.template take<uint32_t>(N);
   auto p_U = a.template take<uint64_t>(N / 64);
   auto p_F = a.template take<uint64_t>(4 * (N / 64));
+  auto p_cut = a.template take<int32_t>(2 * (N / 64));   // at most a chunk for every word, and the end
   if (L) {
     *L = Layout{(GDesc *)p_desc, (char *)p_st, (size_t)((char *)p_cn - (char *)p_st), (GState *)p_st,
                 (GState *)p_ring, (GCount *)p_cn, (Ctl *)p_ctl, (uint32_t *)p_seg, (int32_t *)p_log,
                 (uint64_t *)p_key, (uint64_t *)p_keyn, (uint64_t *)p_R, (uint32_t *)p_slim, (uint64_t *)p_U,
-                (uint64_t *)p_F, N / 64};
-    return p_desc && p_F;
+                (uint64_t *)p_F, (int32_t *)p_cut, N / 64};
+    return p_desc && p_cut;
   }
   return true;
 }
@@ -2000,7 +2129,7 @@ Job make_job(const Layout &L, int32_t G) {
   Job job{};
   job.desc = L.desc; job.st = L.st; job.ring = L.ring; job.cn = L.cn; job.ctl = L.ctl; job.seg = L.seg;
   job.log = L.log; job.key = L.key; job.keyn = L.keyn; job.R = L.R; job.slim = L.slim; job.U = L.U;
-  job.F = L.F; job.fwords = L.fwords;
+  job.F = L.F; job.cut = L.cut; job.fwords = L.fwords;
   job.G = G;
   return job;
 }
