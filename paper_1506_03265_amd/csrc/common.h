@@ -66,6 +66,15 @@ struct Pinned {
   Pinned &operator=(const Pinned &) = delete;
 };
 
+// Waits for a stream on every way out of a scope that declares it after a pooled
+// buffer: steps queued on the stream write that buffer, so it goes back to the
+// pool after they have run.
+struct Drain {
+  hipStream_t stream;
+  bool armed;
+  ~Drain() { if (armed) (void)hipStreamSynchronize(stream); }
+};
+
 inline int blocks_for(int64_t items, int threads, int cap = 1 << 20) {
   int64_t b = (items + threads - 1) / threads;
   if (b < 1) b = 1;

@@ -2378,6 +2378,7 @@ extern "C" int cldiam_decompose_batch(int32_t G, const cldiam_graph *gs, cldiam_
   };
   cld::Pinned<Readback> pinned;   // back to the pool when the call returns
   if (!pinned.p) { cld::set_error("decompose: pinned host buffer allocation failed"); return CLDIAM_EHIP; }
+  cld::Drain drain{stream, true};   // queued steps write the mirror
   const Ctl *hc = (const Ctl *)(pinned.p->zero + ((char *)L.ctl - L.zero));   // one graph: where ctl is read back
   // the last line of the same buffer: the control step's mirror for the host loop
   volatile uint32_t *hm = (volatile uint32_t *)((char *)pinned.p + kMirrorOffset);
@@ -2413,7 +2414,6 @@ extern "C" int cldiam_decompose_batch(int32_t G, const cldiam_graph *gs, cldiam_
         continue;
       }
       if (std::chrono::steady_clock::now() - t0 > std::chrono::seconds(kJobSeconds + 30)) {
-        CLD_HIP(hipStreamSynchronize(stream));
         cld::set_error("decompose: host-driven job exceeded its time limit");
         return CLDIAM_ETIMEOUT;
       }
@@ -2426,6 +2426,7 @@ extern "C" int cldiam_decompose_batch(int32_t G, const cldiam_graph *gs, cldiam_
   char *back = one ? pinned.p->zero : many.data();
   CLD_HIP(hipMemcpyAsync(back, L.zero, L.zero_bytes, hipMemcpyDeviceToHost, stream));
   CLD_HIP(hipStreamSynchronize(stream));
+  drain.armed = false;
   if (!one) hc = (const Ctl *)(back + ((char *)L.ctl - L.zero));
   if (persistent && hc->timeout) { cld::set_error("decompose: grid barrier timed out"); return CLDIAM_ETIMEOUT; }
   if (!hc->done && !(persistent && hc->error)) {

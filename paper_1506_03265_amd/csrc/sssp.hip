@@ -411,13 +411,7 @@ extern "C" int cldiam_sssp_delta_stepping(int32_t n, int64_t m, const int64_t *d
   cld::Pinned<SCtl> pinned;   // readback buffer; its first line mirrors the device's progress during the search
   if (!pinned.p) { cld::set_error("sssp: pinned host buffer allocation failed"); return CLDIAM_EHIP; }
   volatile uint32_t *hm = (volatile uint32_t *)pinned.p;
-  // queued steps write the mirror, so the buffer goes back to the pool after them
-  // on every way out
-  struct Drain {
-    hipStream_t stream;
-    bool armed;
-    ~Drain() { if (armed) (void)hipStreamSynchronize(stream); }
-  } drain{stream, true};
+  cld::Drain drain{stream, true};   // queued steps write the mirror
   hm[0] = 0;
   hm[1] = 0;
   CLD_HIP(hipHostGetDevicePointer((void **)&j.mirror, (void *)pinned.p, 0));
