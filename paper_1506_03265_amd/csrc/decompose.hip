@@ -232,7 +232,9 @@ constexpr int kLocalRounds = 16;  // default local relaxation rounds per RELAX r
 // Default: local rounds do not wait for the other workgroups.  Ended once 75%
 // of the workgroups have finished the sweep, the rest of the growth waits for
 // the next launch (64 x 64 mesh 0.69 instead of 0.43 ms, 1153 x 1021 mesh 3.05
-// instead of 2.36, road-like 4096 x 4096 mesh 9.5 instead of 8.7).
+// instead of 2.36, road-like 4096 x 4096 mesh 9.5 instead of 8.7; 600 meshes of some
+// 150 nodes in one job 1.83 instead of 1.66, but 64 geometric graphs of up to a
+// million nodes 7.5 instead of 8.7).
 constexpr int kLocalCutoffPct = 100;
 constexpr int kDenseWaveRow = 128;     // default wave_row_min on graphs of more than kDenseDegree arcs per node
 constexpr int kLocalRoundsDense = 2;   // ... on graphs with more than kDenseDegree arcs per node and
@@ -274,7 +276,8 @@ constexpr uint32_t kPullArcs = 8;   // pull-mode switch: heavy blocked arcs per 
 // its node's distance (0.4 to 1 ms on R-MAT scale 24, where pushing from the nodes
 // of the first pass took 13 ms and some 380 million arcs), and each hop of the
 // last few nodes costs less pushed.  With a wave for every long row (see kPullRow)
-// R-MAT scale 24, 18 and two dozen mixed requests took 15.4, 1.15 and 11.6 ms with
+// R-MAT scale 24 and 18 (graphs of perf/cases.py, decomposition alone) and two dozen
+// mixed requests took 15.4, 1.15 and 11.6 ms with
 // one pass, 10.9, 1.16 and 9.8 with a quarter, 10.4, 1.17 and 9.4 with 1/16, 10.6,
 // 0.76 and 9.4 with 1/32, 11.2, 0.74 and 9.6 with 1/256.  kPullMost bounds the
 // passes where distances take many hops.
@@ -282,8 +285,8 @@ constexpr uint32_t kPullAgainShift = 5;
 constexpr uint32_t kPullMost = 16;
 // A reached node's row is read up to its distance only, a few arcs even of a long
 // one, so in pull passes rows of up to kPullRow arcs stay with one thread, 64 rows
-// in flight per wave: R-MAT scale 24, 18 and two dozen mixed requests take 8.7,
-// 0.71 and 8.6 ms; 10.5, 0.75 and 9.1 with a wave for every row above 128 arcs;
+// in flight per wave: the same take 8.7, 0.71 and 8.6 ms (10.1 on the benchmark's
+// R-MAT scale 24); 10.5, 0.75 and 9.1 with a wave for every row above 128 arcs;
 // 9.7, 1.06 and 9.4 with a thread for every row.
 constexpr int32_t kPullRow = 1024;
 constexpr int64_t kHubDegree = 8;   // hub rows: more than kHubDegree x the average degree ...

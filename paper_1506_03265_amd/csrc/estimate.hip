@@ -31,9 +31,9 @@
 //   - in global memory, with longer rows, wide searches alone take sources from a
 //     counter (waiting for the pilots cost 40% on 32,000 nodes of 25 arcs).
 //
-// A quotient of 2228 nodes and 12028 arcs takes 312 us (1771 us with a search
+// A quotient of 2228 nodes and 12028 arcs takes some 320 us (1771 us with a search
 // from every node, 256 threads each, one thread per row), the star-like one of R-MAT
-// scale 24 54 us (356).  A ring of 1000 nodes takes 0.47 ms (1.68 with one search per
+// scale 24 60 us (356).  A ring of 1000 nodes takes 0.47 ms (1.68 with one search per
 // CU throughout), of 3000 5.8 (14.4), of 13,000 192 (592), a torus of 50 x 60 0.48
 // (0.93), a mesh of 55 x 55 0.39 (0.45).
 #include <algorithm>

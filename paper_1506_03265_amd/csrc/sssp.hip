@@ -29,10 +29,10 @@
 // What bounds it: the number of hops (8,600 on the road-like 4096 x 4096 mesh)
 // times the chain of dependent accesses of one (queue, row offsets and
 // distance, arcs, far distances: 3.5 us where they miss the L2).  That mesh
-// takes 35 ms at the default width, R-MAT scale 20 4 ms; with node lists,
-// returning atomics and one hop per launch they took 255 and 237 ms.  Looking
-// up an improved node's row together with its distance, which makes the chain
-// one access shorter, gained nothing (four times the offset loads).
+// takes 28 to 33 ms at the default width, depending on the GPU; with node lists,
+// returning atomics and one hop per launch it took 190 to 205.  Looking up an
+// improved node's row together with its distance, which makes the chain one
+// access shorter, gained nothing (four times the offset loads).
 #include <chrono>
 #include <thread>
 
@@ -42,7 +42,7 @@ namespace {
 
 constexpr int kT = 256;
 // Eight workgroups per CU, whose chains of accesses interleave: the road-like
-// 4096 x 4096 mesh takes 34.7 ms with 8 of 256 threads, 43 with 4, 36.7 with 16
+// 4096 x 4096 mesh takes 34.7 ms, on one GPU, with 8 of 256 threads, 43 with 4, 36.7 with 16
 // (more than are resident), 43 with 4 of 512, 47 with 2 of 1024.  The list and
 // the queue are no longer than lets eight share a CU's LDS.
 constexpr int kStepThreads = 256;
